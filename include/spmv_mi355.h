@@ -321,7 +321,9 @@ spmv_status_t spmv_csr_create(spmv_handle_t* out, int64_t m, int64_t n, int64_t 
  *     (column - p) mod 4: the entries are dealt out by column residue, turned by the row's position, so that the 16 rows
  *     a wavefront reads at once ask for different quarters of the LDS banks.  It is built when it has at most 2 * nnz slots and 2^22 blocks (spmm_prepared = 2);
  *     otherwise only spmm_rows is (spmm_prepared = 1) and spmm_csr_run() reads CSR.  The copy
- *     holds the values as they were at analyze time, as binary32 (bf16 values widened).
+ *     holds the values as they were at analyze time, as binary32 (bf16 values widened).  While n <= 2048 and the rows of
+ *     like length suffice for groups of 32, spmm_csr_run() works from another form of the same copy (32-row groups, two
+ *     lanes per row, entries ordered against LDS bank conflicts) and the packed copy is made when it is read back.
  * params == NULL means all defaults.  May be called again to re-plan (old metadata is freed).
  * Synchronises the device.  Errors: INVALID_ARG, BAD_STRUCTURE, ALLOC, HIP. */
 spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* params);

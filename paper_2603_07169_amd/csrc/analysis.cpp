@@ -468,4 +468,39 @@ bool spmm_packed_layout(int64_t m, int64_t nnz, const int32_t* rowptr, const int
     return nnz > 0 && blocks * 256 <= 2 * nnz && blocks <= kSpmmMaxBlocks;
 }
 
+bool spmm_pair_layout(int64_t m, const int32_t* rowptr, const std::vector<int32_t>& packed_desc, std::vector<int32_t>* rows,
+                      std::vector<int32_t>* desc, int64_t* num_blocks) {
+    auto len_of = [&](int64_t i) { return static_cast<int64_t>(rowptr[i + 1]) - rowptr[i]; };
+    auto key_of = [&](int64_t i) { return static_cast<int>(std::min<int64_t>(len_of(i), kSpmmPairMaxKey)); };
+    rows->resize(static_cast<size_t>(m));
+    std::vector<int64_t> cursor(kSpmmPairMaxKey + 1);
+    for (int64_t w0 = 0; w0 < m; w0 += SPMV_SPMM_WINDOW) {
+        const int64_t w1 = std::min<int64_t>(w0 + SPMV_SPMM_WINDOW, m);
+        std::fill(cursor.begin(), cursor.end(), 0);
+        for (int64_t i = w0; i < w1; ++i) cursor[static_cast<size_t>(key_of(i))] += 1;
+        int64_t run = w0;
+        for (int k = kSpmmPairMaxKey; k >= 0; --k) {  // the longest rows come first
+            const int64_t count = cursor[static_cast<size_t>(k)];
+            cursor[static_cast<size_t>(k)] = run;
+            run += count;
+        }
+        for (int64_t i = w0; i < w1; ++i) (*rows)[static_cast<size_t>(cursor[static_cast<size_t>(key_of(i))]++)] = static_cast<int32_t>(i);
+    }
+    const int64_t groups = (m + 31) / 32;
+    desc->assign(static_cast<size_t>(2 * groups + 2), 0);
+    int64_t blocks = 0, packed_slots = 0;
+    for (int64_t g = 0; g < groups; ++g) {
+        int64_t longest = 0;
+        for (int64_t p = 32 * g; p < 32 * g + 32 && p < m; ++p) longest = std::max(longest, len_of((*rows)[static_cast<size_t>(p)]));
+        (*desc)[static_cast<size_t>(2 * g)] = static_cast<int32_t>(std::min<int64_t>(blocks, INT32_MAX));
+        (*desc)[static_cast<size_t>(2 * g + 1)] = static_cast<int32_t>(std::max<int64_t>(1, (longest + 1) / 2));
+        blocks += std::max<int64_t>(1, (longest + 3) / 4);
+    }
+    (*desc)[static_cast<size_t>(2 * groups)] = static_cast<int32_t>(std::min<int64_t>(blocks, INT32_MAX));
+    (*desc)[static_cast<size_t>(2 * groups + 1)] = 1;
+    *num_blocks = blocks;
+    for (size_t g = 0; 2 * g + 2 < packed_desc.size(); ++g) packed_slots += 64 * static_cast<int64_t>(packed_desc[2 * g + 1]);
+    return blocks <= kSpmmMaxBlocks && 4 * 128 * blocks <= 5 * packed_slots;
+}
+
 }  // namespace spmv

@@ -89,6 +89,24 @@ hipError_t launch_spmm_pack(const MatrixView& A, const int32_t* rows, const int3
 hipError_t launch_spmm_packed(const MatrixView& A, const PackedRows& P, const void* B, int64_t ldb, float* C, int64_t ldc,
                               int32_t K, Scalars s, hipStream_t st);
 const char* spmm_packed_kernel_name();
+// The pairs form of A that the product runs from while B's slice fits one LDS block (n <= kSpmmPairMaxN; device pointers):
+// groups of 32 rows of the order rows[], blocks of 32 rows x 4 entries, two lanes per row.  Position t of the group's row i
+// belongs to lane q = ((first + t / 4) * 64 + 2 i + t mod 2), element (t mod 4) / 2: ent[4 q + element] is the LDS offset of
+// the entry's row of B, ent[4 q + 2 + element] its value, src[2 q + element] its place in colidx / vals, -1 in padding.
+constexpr int kSpmmPairMaxN = 2048;
+struct PairRows {
+    const int32_t* rows;  // [m] row order: decreasing length inside windows of SPMV_SPMM_WINDOW rows
+    const int32_t* desc;  // [2 * (num_groups + 1)] pairs (first block, steps of two entries: at least 1)
+    uint32_t* ent;        // [(num_blocks + 1) * 256]
+    int32_t* src;         // [num_blocks * 128]
+    int32_t num_groups;
+    int64_t num_blocks;
+};
+hipError_t launch_spmm_pair_pack(const MatrixView& A, const PairRows& P, hipStream_t st);    // off, src and val from the CSR arrays
+hipError_t launch_spmm_pair_values(const MatrixView& A, const PairRows& P, hipStream_t st);  // val from the CSR values
+hipError_t launch_spmm_pair_unpack(const PairRows& P, float* vals, hipStream_t st);          // vals[nnz] as val holds them
+hipError_t launch_spmm_pair(const MatrixView& A, const PairRows& P, const void* B, int64_t ldb, float* C, int64_t ldc, int32_t K,
+                            Scalars s, hipStream_t st);
 // Whole aligned groups of eight entries (groups = nnz / 8): lidx8[g] = lidx[8g]; *flag (device int32, 0 on entry) is set to 1
 // if some group's eight positions are not consecutive numbers.
 hipError_t launch_lidx_groups(const uint16_t* lidx, int32_t groups, uint16_t* lidx8, int32_t* flag, hipStream_t st);
