@@ -173,6 +173,38 @@ bool merge_path_splits_snapped(int64_t m, int64_t nnz, const int32_t* rowptr, in
     return cuts;
 }
 
+void merge_chunk_desc(int64_t m, const int32_t* rowptr, const std::vector<int32_t>& mp_row, const std::vector<int32_t>& mp_nz,
+                      int64_t snap, std::vector<int32_t>* desc) {
+    desc->resize(2 * mp_row.size());
+    for (size_t p = 0; p < mp_row.size(); ++p) {
+        const int64_t i = mp_row[p];
+        int32_t taken = mp_nz[p];
+        if (i < m && rowptr[i] < taken && static_cast<int64_t>(rowptr[i + 1]) - rowptr[i] <= snap) taken = rowptr[i];
+        (*desc)[2 * p] = static_cast<int32_t>(i);
+        (*desc)[2 * p + 1] = taken;
+    }
+}
+
+void cut_ranges(int64_t m, const int32_t* rowptr, const std::vector<int32_t>& rows, const std::vector<int32_t>& entries,
+                std::vector<int32_t>* ranges) {
+    const size_t n = rows.size();
+    ranges->assign(2 * n, -1);
+    for (size_t q = 0; q < n;) {
+        const int64_t i = rows[q];
+        if (!(i < m && rowptr[i] < entries[q])) {
+            ++q;
+            continue;
+        }
+        size_t last = q;  // the splits inside row i follow one another
+        while (last + 1 < n && rows[last + 1] == i) ++last;
+        for (size_t u = q; u <= last; ++u) {
+            (*ranges)[2 * u] = static_cast<int32_t>(q) - 1;
+            (*ranges)[2 * u + 1] = static_cast<int32_t>(last);
+        }
+        q = last + 1;
+    }
+}
+
 void bin_rows_of(int64_t m, const int32_t* rowptr, std::vector<int32_t>* rows) {
     // a stable counting sort, in one thread: the lengths are counted per bin, then every row goes behind the rows
     // before it in its bin

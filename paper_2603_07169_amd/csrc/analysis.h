@@ -106,6 +106,15 @@ int32_t two_phase_piece_groups(int64_t C, const int32_t* block_first, int32_t re
 // (one slot per block and possible vector) no longer than a quarter of the entries.
 bool window_choice(const int32_t* nv, int64_t nb, int64_t nnz, int64_t* total, int32_t* largest);
 
+// The chunks as the merge-path kernels take them: pairs (mp_row[p], mp_nz[p]) with every split that falls inside a row of at most
+// `snap` entries moved back to the row's first entry.  May throw std::bad_alloc.
+void merge_chunk_desc(int64_t m, const int32_t* rowptr, const std::vector<int32_t>& mp_row, const std::vector<int32_t>& mp_nz,
+                      int64_t snap, std::vector<int32_t>* desc);
+// Per split of the two-pass plan: the first and the last chunk of the row it cuts, or -1, -1.  rowptr as the splits were made
+// with.  May throw std::bad_alloc.
+void cut_ranges(int64_t m, const int32_t* rowptr, const std::vector<int32_t>& rows, const std::vector<int32_t>& entries,
+                std::vector<int32_t>* ranges);
+
 // Row order of the sparse-times-dense kernel: inside every window of SPMV_SPMM_WINDOW consecutive
 // rows, the row ids by decreasing min(ceil(len / 4), 64), rows of equal key ascending.  rowptr is
 // a HOST array of m+1 checked entries.  May throw std::bad_alloc.

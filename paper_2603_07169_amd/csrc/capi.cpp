@@ -56,7 +56,7 @@ struct spmv_csr_s {
     void* d_cb_vals = nullptr;
     std::vector<int32_t> cb_ptr;   // host: [C+1]
     int32_t max_block_entries = 0;  // most entries of any row block that is not a single over-long row
-    int32_t* d_carry_row = nullptr;
+    unsigned* d_arrivals = nullptr;  // merge path: see finish_cut
     float* d_carry_val = nullptr;
     int32_t* d_xv_ptr = nullptr;  // x windows (WINDOWED plan)
     int32_t* d_xv_start = nullptr;
@@ -76,11 +76,11 @@ struct spmv_csr_s {
     int32_t* d_tp_from = nullptr;
     uint16_t* d_tp_pos = nullptr;
     float* d_tp_prod = nullptr;
-    int32_t* d_tp_carry_row = nullptr;
+    int32_t* d_tp_cuts = nullptr;      // [2*(P+1)] first and last chunk of the row each split cuts
+    unsigned* d_tp_arrivals = nullptr;
     float* d_tp_carry_val = nullptr;
     size_t tp_reduce_lds = 0;
     std::vector<int32_t> tp_row, tp_nz;  // host copies for the read-back
-    bool tp_carries = true;              // some chunk of the two-pass plan cuts a row
     // The MERGE and TWOPHASE plans keep scratch in the handle (carries, products): a run on another stream while one is
     // still in flight would share it.  An event recorded behind every such run tells.
     hipEvent_t scratch_free = nullptr;
@@ -102,24 +102,26 @@ namespace {
 
 void free_metadata(spmv_csr_s* h) {
     void* ptrs[] = {h->d_bin_rows, h->d_block_nz,
-                    h->d_carry_row, h->d_carry_val, h->d_xv_ptr,   h->d_xv_start, h->d_lidx,
+                    h->d_arrivals, h->d_carry_val, h->d_xv_ptr,   h->d_xv_start, h->d_lidx,
                     h->d_xv_pad,    h->d_block_desc, h->d_chunk_desc, h->d_cb_row, h->d_cb_col,
                     h->d_cb_src,    h->d_cb_vals,   h->d_spmm_rows, h->d_spmm_desc, h->d_spmm_col,
                     h->d_spmm_val,  h->d_tp_desc,   h->d_tp_piece_c, h->d_tp_piece_g, h->d_tp_chunk_g,
                     h->d_tp_col,    h->d_tp_val,    h->d_tp_src,    h->d_tp_from,    h->d_tp_pos,
-                    h->d_tp_prod,   h->d_tp_carry_row, h->d_tp_carry_val, h->d_lidx8, h->d_run_desc, h->d_pat_pad,
+                    h->d_tp_prod,   h->d_tp_cuts, h->d_tp_arrivals, h->d_tp_carry_val, h->d_lidx8, h->d_run_desc, h->d_pat_pad,
                     h->d_sell_ptr,  h->d_sell_col,  h->d_sell_src,  h->d_sell_val,
                     const_cast<int32_t*>(h->pairs.rows), const_cast<int32_t*>(h->pairs.desc), h->pairs.ent, h->pairs.src};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     h->d_tp_desc = h->d_tp_piece_c = h->d_tp_piece_g = h->d_tp_chunk_g = h->d_tp_src = h->d_tp_from = nullptr;
-    h->d_tp_carry_row = nullptr;
+    h->d_tp_cuts = nullptr;
+    h->d_tp_arrivals = nullptr;
     h->d_tp_col = h->d_tp_pos = nullptr;
     h->d_tp_val = nullptr;
     h->d_tp_prod = h->d_tp_carry_val = nullptr;
     h->tp_row.clear();
     h->tp_nz.clear();
-    h->d_bin_rows = h->d_block_nz = h->d_carry_row = nullptr;
+    h->d_bin_rows = h->d_block_nz = nullptr;
+    h->d_arrivals = nullptr;
     h->bin_rows.clear();
     h->row_blocks.clear();
     h->mp_row.clear();
@@ -492,7 +494,7 @@ spmv_status_t build_two_phase(spmv_csr_s* h, const HostRowptr& rowptr_host, spmv
         for (size_t i = 0; i < rowptr_host.size(); ++i) rowptr_groups[i] = rowptr_host[i] / group;
     }
     const int32_t* const rowptr_used = d_gcol ? rowptr_groups.data() : rowptr_host.data();
-    h->tp_carries = spmv::merge_path_splits_snapped(h->m, nent, rowptr_used, spmv::kTwoPhaseItems, spmv::kTwoPhaseSnap, &h->tp_row, &h->tp_nz);
+    spmv::merge_path_splits_snapped(h->m, nent, rowptr_used, spmv::kTwoPhaseItems, spmv::kTwoPhaseSnap, &h->tp_row, &h->tp_nz);
     const int64_t P = static_cast<int64_t>(h->tp_row.size()) - 1;
     if (C > 65535 || C * P > spmv::kTwoPhaseMaxTiles) return SPMV_ERR_UNSUPPORTED;
     spmv::MatrixView A = view_of(h);
@@ -513,6 +515,10 @@ spmv_status_t build_two_phase(spmv_csr_s* h, const HostRowptr& rowptr_host, spmv
     }
     h->tp_reduce_lds = lds;
     spmv_status_t st = upload(desc, &h->d_tp_desc);
+    if (st != SPMV_OK) return st;
+    std::vector<int32_t> cuts;
+    spmv::cut_ranges(h->m, rowptr_used, h->tp_row, h->tp_nz, &cuts);
+    st = upload(cuts, &h->d_tp_cuts);
     if (st != SPMV_OK) return st;
 
     // 32-bit prefix sums on the device: every tile adds at most three slots of padding
@@ -569,7 +575,8 @@ spmv_status_t build_two_phase(spmv_csr_s* h, const HostRowptr& rowptr_host, spmv
          hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_from), S)) ||
          hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_pos), 2 * S)) ||
          hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_prod), 4 * S)) ||
-         hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_carry_row), 4 * static_cast<size_t>(P))) ||
+         hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_arrivals), 4 * static_cast<size_t>(P))) ||
+         hip_failed(hipMemset(h->d_tp_arrivals, 0, 4 * static_cast<size_t>(P))) ||
          hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_carry_val), 4 * static_cast<size_t>(P)))))
         st = SPMV_ERR_ALLOC;
     if (st == SPMV_OK &&
@@ -641,7 +648,6 @@ spmv::TwoPhase two_phase_of(const spmv_csr_s* h) {
     t.group = h->info.tp_group > 1 ? h->info.tp_group : 1;
     t.num_pieces = h->info.tp_num_pieces;
     t.num_chunks = h->info.tp_num_chunks;
-    t.carries = h->tp_carries;
     t.reduce_lds = h->tp_reduce_lds;
     t.piece_c = h->d_tp_piece_c;
     t.piece_g = h->d_tp_piece_g;
@@ -652,7 +658,8 @@ spmv::TwoPhase two_phase_of(const spmv_csr_s* h) {
     t.chunk_desc = h->d_tp_desc;
     t.chunk_g = h->d_tp_chunk_g;
     t.prod = h->d_tp_prod;
-    t.carry_row = h->d_tp_carry_row;
+    t.cut_range = h->d_tp_cuts;
+    t.arrivals = h->d_tp_arrivals;
     t.carry_val = h->d_tp_carry_val;
     return t;
 }
@@ -820,11 +827,7 @@ spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* par
                 desc[2 * b + 1] = block_nz[b];
             }
             if (st == SPMV_OK) st = upload(desc, &h->d_block_desc);
-            desc.resize(2 * a.mp_row.size());
-            for (size_t q = 0; q < a.mp_row.size(); ++q) {
-                desc[2 * q] = a.mp_row[q];
-                desc[2 * q + 1] = a.mp_nz[q];
-            }
+            spmv::merge_chunk_desc(h->m, rowptr_host.data(), a.mp_row, a.mp_nz, spmv::merge_snap(a.info.items_per_chunk), &desc);
             if (st == SPMV_OK) st = upload(desc, &h->d_chunk_desc);
         } catch (const std::bad_alloc&) {
             st = SPMV_ERR_ALLOC;
@@ -865,12 +868,14 @@ spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* par
     if (st == SPMV_OK && p.prepare_spmm) st = build_spmm_order(h, rowptr_host, &a);
     if (st == SPMV_OK) {
         const size_t P = static_cast<size_t>(a.info.num_chunks > 0 ? a.info.num_chunks : 1);
-        if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_carry_row), sizeof(int32_t) * P)) ||
+        if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_arrivals), sizeof(unsigned) * P)) ||
+            hip_failed(hipMemset(h->d_arrivals, 0, sizeof(unsigned) * P)) ||
             hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_carry_val), sizeof(float) * P)))
             st = SPMV_ERR_ALLOC;
     }
     if (st == SPMV_OK && plan_has_scratch(a.info.plan) &&
-        hip_failed(hipEventCreateWithFlags(&h->scratch_free, hipEventDisableTiming)))
+        // nothing on the host reads what the runs wrote on this event's account: no system-scope fence with it
+        hip_failed(hipEventCreateWithFlags(&h->scratch_free, hipEventDisableTiming | hipEventDisableSystemFence)))
         st = SPMV_ERR_HIP;
     if (st == SPMV_OK && hip_failed(hipDeviceSynchronize())) st = SPMV_ERR_HIP;
     if (st != SPMV_OK) {
@@ -955,20 +960,20 @@ spmv_status_t spmv_csr_run(spmv_handle_t h, const void* x, float* y, float alpha
             break;
         }
         case SPMV_PLAN_TWOPHASE:
-            e = spmv::launch_two_phase(two_phase_of(h), A, x, y, s, st);
+            e = spmv::launch_two_phase(two_phase_of(h), A, x, y, s, st, tracked ? h->scratch_free : nullptr);
             break;
         case SPMV_PLAN_SELL:
             e = spmv::launch_sell(A, h->d_sell_ptr, h->info.sell_num_slices, h->d_sell_col, h->d_sell_val, x, y, s, st);
             break;
         case SPMV_PLAN_MERGE:
             e = spmv::launch_merge(A, h->d_chunk_desc, static_cast<int32_t>(h->info.num_chunks),
-                                   h->info.items_per_chunk, h->d_carry_row, h->d_carry_val, x, y, s, st);
+                                   h->info.items_per_chunk, h->d_arrivals, h->d_carry_val, x, y, s, st,
+                                   tracked ? h->scratch_free : nullptr);
             break;
         default:
             return SPMV_ERR_INVALID_ARG;
     }
-    if (tracked && e == hipSuccess) {
-        e = hipEventRecord(h->scratch_free, st);
+    if (tracked && e == hipSuccess) {  // the launch has recorded the event
         h->scratch_stream = st;
         h->scratch_used = true;
     }

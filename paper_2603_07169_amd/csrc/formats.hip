@@ -263,8 +263,8 @@ __global__ __launch_bounds__(kWG, 8) void spmv_ell_tile_kernel(const int32_t* __
         for (int i = tid + kWG; i < nr; i += kWG) y0_l[i] = y[r0 + i];
     __syncthreads();
 
-    const RowOut o{y, y0_l, nullptr, nullptr, alpha, beta};
-    tile_rows<false, kWG>(cols_l, vals_l, x, seg, nr, r0, 0, span, o, deferred, &n_deferred, tid);
+    const RowOut o{y, y0_l, alpha, beta, nullptr, false};
+    tile_rows<false, kWG>(cols_l, vals_l, x, seg, nr, r0, span, o, deferred, &n_deferred, tid);
 }
 
 }  // namespace

@@ -64,10 +64,15 @@ hipError_t launch_windowed(const MatrixView& A, const int32_t* block_desc, int32
 hipError_t launch_window_build(const MatrixView& A, const int32_t* block_nz, int32_t nb, int32_t block_nnz, bool fill,
                                int32_t* nv, const int32_t* xv_ptr, int32_t* xv_start, int32_t* xv_pad, int32_t x_cap,
                                uint16_t* lidx, hipStream_t st);
-// chunk_desc: device [2*(P+1)], pairs (mp_row[p], mp_nz[p]); carry_row/carry_val: device [P] scratch owned by the handle.
-hipError_t launch_merge(const MatrixView& A, const int32_t* chunk_desc, int32_t P,
-                        int32_t items_per_chunk, int32_t* carry_row, float* carry_val, const void* x, float* y,
-                        Scalars s, hipStream_t st);
+// Merge-path cuts that fall inside a row of at most this many entries are moved back to the row's first entry, so that only
+// longer rows leave carries: no chunk then grows by more than these entries.  Not with short chunks, which would grow by a
+// large part of their own size.
+constexpr int32_t kMergeSnap = 256;
+inline __host__ __device__ int32_t merge_snap(int32_t items_per_chunk) { return items_per_chunk >= 4 * kMergeSnap ? kMergeSnap : 0; }
+// chunk_desc: device [2*(P+1)], pairs (mp_row[p], mp_nz[p]) moved back as said above; arrivals (zero before the first run) and
+// carry_val: device [P] scratch of the caller's (see finish_cut).  done: null, or an event that the launch records at its end.
+hipError_t launch_merge(const MatrixView& A, const int32_t* chunk_desc, int32_t P, int32_t items_per_chunk, unsigned* arrivals,
+                        float* carry_val, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done);
 // C <- alpha*A*B + beta*C; A CSR, B device [n x ldb] in A's storage type, C device float[m x ldc], row-major, K columns used.
 // rows: device int32[m], the order in which the rows are handed to the wavefronts (a permutation
 // of 0..m-1), or NULL for the natural order.
@@ -146,17 +151,12 @@ hipError_t launch_column_block_scatter(const MatrixView& A, int shift, int C, co
 // cb_vals[k] = vals[cb_src[k]] for the nnz regrouped entries (the caller's values may have changed).
 hipError_t launch_column_block_values(const MatrixView& A, const int32_t* cb_src, void* cb_vals, hipStream_t st);
 
-// The carry fix-up of the merge-path kernels: y[carry_row[p]] += alpha * carry_val[p], runs of equal rows summed in chunk order.
-hipError_t launch_merge_fixup(const int32_t* carry_row, const float* carry_val, int32_t P, float* y, float alpha,
-                              hipStream_t st);
-
 // The two-pass plan (device arrays owned by the handle).
 struct TwoPhase {
     int32_t shift;              // column blocks of 2^shift columns (of 2^shift groups' columns when group == 8)
     int32_t group;              // 1, or 8: a slot stands for a group of eight entries (group-aligned matrix)
     int32_t num_pieces;         // multiply pass: workgroups
     int32_t num_chunks;         // reduce pass: merge-path chunks
-    bool carries;               // some chunk cuts a row: the fix-up kernel has to run
     size_t reduce_lds;          // two_phase_reduce_lds() of the largest chunk
     const int32_t* piece_c;     // [num_pieces]   column block of each piece
     const int32_t* piece_g;     // [num_pieces+1] first group of each piece (pieces are contiguous)
@@ -167,12 +167,13 @@ struct TwoPhase {
     const int32_t* chunk_desc;  // [2*(num_chunks+1)] pairs (rows finished, entries taken)
     const int32_t* chunk_g;     // [num_chunks+1] first group of each chunk in the reduce order
     float* prod;                // [slots] scratch: the products between the two passes, in the multiply order
-    int32_t* carry_row;         // [num_chunks] scratch
+    const int32_t* cut_range;   // [2*(num_chunks+1)] per cut that falls inside a row: first and last chunk of that row (else -1)
+    unsigned* arrivals;         // [num_chunks] scratch, zero before the first run
     float* carry_val;           // [num_chunks] scratch
 };
 constexpr int kTpMaxShift = 15;  // column blocks of at most 32768 columns (16-bit columns, one more value for padding)
 size_t two_phase_reduce_lds(int32_t entries, int32_t rows);
-hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st);
+hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done);
 // Analysis time.  Scratch of the regrouping (device, T = C*P tiles): all of it is temporary.
 struct TwoPhaseTables {
     int32_t* padded;       // [T]    slots of tile t = c*P + p (entries rounded up to whole groups of four)

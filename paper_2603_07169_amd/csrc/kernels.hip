@@ -10,7 +10,6 @@
 //                       lets teams of lanes take one row each, gathering x through the caches
 //   spmv_window_kernel  the same with the block's window of x in LDS and 16-bit window positions
 //                       in place of the column indices (built by window_build_kernel at analysis)
-//   merge_fixup_kernel  adds the carries of cut rows to y, in chunk order, without atomics
 // No matrix cores: nothing here is a dense contraction.
 #include <hip/hip_runtime.h>
 
@@ -165,7 +164,7 @@ __global__ __launch_bounds__(kWG) void spmv_vector_kernel(const int32_t* __restr
 // ------------------------------------------------------------------------------------------
 struct TileArgs {
     // what a workgroup needs before its first vector load comes first, in one stretch
-    int32_t nparts, x_cap, tile_cap, nnz;
+    int32_t nparts, x_cap, tile_cap, nnz;  // tile_cap: most entries of a staged row block; merge path: steps between cuts
     const int32_t* xv_pad;     // window kernel: [nparts * x_cap] first element of each 16-byte x vector of a block, -1 padded
     const uint16_t* lidx8;     // window kernel, grouped positions: [nnz/8] lidx[8g], the first of every aligned group of eight
     const uint16_t* lidx;      // window kernel: [nnz, padded to a multiple of 8] position of each entry's x value in the block's window
@@ -183,7 +182,7 @@ struct TileArgs {
     int32_t vec_ok;            // colidx and vals are 16-byte aligned
     int32_t x_vec_ok;          // x is 16-byte aligned
     const int32_t* colidx;
-    int32_t* carry_row;        // merge path only, [nparts]
+    unsigned* arrivals;        // merge path only, [nparts] (see finish_cut)
     float* carry_val;          // merge path only, [nparts]
 };
 
@@ -345,8 +344,15 @@ __global__ __launch_bounds__(WG, 8) void spmv_tile_kernel(const TileArgs a) {
     __syncthreads();
 
     // ---- 2. rows
-    const RowOut o{a.y, y0_l, a.carry_row, a.carry_val, a.alpha, a.beta};
-    tile_rows<MERGE, WG>(cols_l, vals_l, x, seg, nr, r0, part, k1 - k0, o, deferred, &n_deferred, tid);
+    if constexpr (MERGE) {
+        __shared__ float cut_sums[2];
+        const RowOut o{a.y, y0_l, a.alpha, a.beta, cut_sums, nr > 0 && a.rowptr[r0] < k0};
+        tile_rows<MERGE, WG>(cols_l, vals_l, x, seg, nr, r0, k1 - k0, o, deferred, &n_deferred, tid);
+        finish_cuts(o, CutOut{a.carry_val, a.arrivals, nullptr, a.rowptr, a.tile_cap}, seg, nr, r0, part, tid);
+    } else {
+        const RowOut o{a.y, y0_l, a.alpha, a.beta, nullptr, false};
+        tile_rows<MERGE, WG>(cols_l, vals_l, x, seg, nr, r0, k1 - k0, o, deferred, &n_deferred, tid);
+    }
 }
 
 // First elements of the x vectors a lane fetches for block `part` (-1: none; lanes from x_cap on read the start of lidx
@@ -514,8 +520,8 @@ __device__ __forceinline__ void window_block(const TileArgs& a, int part, int (&
         long_row<T, WG>(a, r0, k0, k1, wave_part, tid);
         return;
     }
-    const RowOut o{a.y, y0_l, a.carry_row, a.carry_val, a.alpha, a.beta};
-    tile_rows<false, WG>(lidx_l, vals_l, xbuf, seg, nr, r0, part, k1 - k0, o, deferred, &n_deferred, tid);
+    const RowOut o{a.y, y0_l, a.alpha, a.beta, nullptr, false};
+    tile_rows<false, WG>(lidx_l, vals_l, xbuf, seg, nr, r0, k1 - k0, o, deferred, &n_deferred, tid);
 }
 
 template <typename T, int WG, int XPL, int NG, bool GROUPED>
@@ -1122,21 +1128,6 @@ __global__ __launch_bounds__(256) void pattern_totals_kernel(const int32_t* __re
     }
 }
 
-// Adds the carries of rows that were cut by chunk boundaries.  Chunks that cut the same row
-// are consecutive; the thread of the first of them sums the run in chunk order.
-__global__ __launch_bounds__(kWG) void merge_fixup_kernel(const int32_t* __restrict__ carry_row,
-                                                          const float* __restrict__ carry_val, int P, float* y,
-                                                          float alpha) {
-    const int p = blockIdx.x * kWG + threadIdx.x;
-    if (p >= P) return;
-    const int r = carry_row[p];
-    if (r < 0) return;
-    if (p > 0 && carry_row[p - 1] == r) return;
-    float s = 0.f;
-    for (int q = p; q < P && carry_row[q] == r; ++q) s += carry_val[q];
-    y[r] += alpha * s;
-}
-
 // lidx8[g] = lidx[8g] for every whole aligned group of eight entries; *flag = 1 if some group's positions are not
 // eight consecutive numbers (then lidx8 is of no use).
 __global__ __launch_bounds__(kWG) void lidx_groups_kernel(const uint16_t* __restrict__ lidx, int groups, uint16_t* __restrict__ lidx8,
@@ -1260,7 +1251,7 @@ size_t merge_lds_bytes(int items) {
 }
 
 template <typename T, bool MERGE, int WG>
-hipError_t launch_tiles_wg(const TileArgs& a, size_t lds, hipStream_t st) {
+hipError_t launch_tiles_wg(const TileArgs& a, size_t lds, hipStream_t st, hipEvent_t done) {
     auto kernel = spmv_tile_kernel<T, MERGE, WG>;
     if (lds > 64 * 1024) {
         // beyond the default limit the kernel has to be told once (per process) how much it may get
@@ -1272,13 +1263,12 @@ hipError_t launch_tiles_wg(const TileArgs& a, size_t lds, hipStream_t st) {
             allowed = lds;
         }
     }
-    hipLaunchKernelGGL(kernel, dim3(a.nparts), dim3(WG), lds, st, a);
-    return hipGetLastError();
+    return launch_with_event(kernel, dim3(a.nparts), dim3(WG), lds, st, done, a);
 }
 
 template <typename T, bool MERGE>
-hipError_t launch_tiles(const TileArgs& a, size_t lds, hipStream_t st) {
-    return launch_tiles_wg<T, MERGE, 256>(a, lds, st);
+hipError_t launch_tiles(const TileArgs& a, size_t lds, hipStream_t st, hipEvent_t done = nullptr) {
+    return launch_tiles_wg<T, MERGE, 256>(a, lds, st, done);
 }
 
 template <typename T, int XPL, int NG, bool GROUPED>
@@ -1395,33 +1385,20 @@ hipError_t launch_pattern_build(const int32_t* block_desc, int32_t nb, const int
     return hipGetLastError();
 }
 
-hipError_t launch_merge(const MatrixView& A, const int32_t* chunk_desc, int32_t P,
-                        int32_t items_per_chunk, int32_t* carry_row, float* carry_val, const void* x, float* y,
-                        Scalars s, hipStream_t st) {
+hipError_t launch_merge(const MatrixView& A, const int32_t* chunk_desc, int32_t P, int32_t items_per_chunk, unsigned* arrivals,
+                        float* carry_val, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done) {
     if (P <= 0) return hipSuccess;
     TileArgs a = tile_args(A, x, y, s);
     a.part_desc = chunk_desc;
-    a.carry_row = carry_row;
+    a.arrivals = arrivals;
     a.carry_val = carry_val;
     a.nparts = P;
     a.tile_cap = items_per_chunk;
-    // entries + finished rows of a chunk add up to at most items_per_chunk; size for whichever of
-    // the two needs more LDS per item (an entry: colidx + value; a row: bound + old y)
-    hipError_t e;
-    if (A.bf16)
-        e = launch_tiles<BF16, true>(a, merge_lds_bytes<BF16>(items_per_chunk), st);
-    else
-        e = launch_tiles<F32, true>(a, merge_lds_bytes<F32>(items_per_chunk), st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(merge_fixup_kernel, dim3(ceil_div(P, kWG)), dim3(kWG), 0, st, carry_row, carry_val, P, y, s.alpha);
-    return hipGetLastError();
-}
-
-hipError_t launch_merge_fixup(const int32_t* carry_row, const float* carry_val, int32_t P, float* y, float alpha,
-                              hipStream_t st) {
-    if (P <= 0) return hipSuccess;
-    hipLaunchKernelGGL(merge_fixup_kernel, dim3(ceil_div(P, kWG)), dim3(kWG), 0, st, carry_row, carry_val, P, y, alpha);
-    return hipGetLastError();
+    // entries + finished rows of a chunk add up to at most items_per_chunk, and what its end was moved back over is the next
+    // chunk's; size for whichever of the two needs more LDS per item (an entry: colidx + value; a row: bound + old y)
+    const int32_t most = items_per_chunk + merge_snap(items_per_chunk);
+    return A.bf16 ? launch_tiles<BF16, true>(a, merge_lds_bytes<BF16>(most), st, done)
+                  : launch_tiles<F32, true>(a, merge_lds_bytes<F32>(most), st, done);
 }
 
 hipError_t launch_lidx_groups(const uint16_t* lidx, int32_t groups, uint16_t* lidx8, int32_t* flag, hipStream_t st) {

@@ -73,33 +73,78 @@ __device__ __forceinline__ float segment_dot(const I* cols, const E* vals, const
 struct RowOut {
     float* y;
     const float* y0;  // LDS: y0[i] = old y of row r0+i when beta != 0 (fetched while the tile was loading)
-    int32_t* carry_row;
-    float* carry_val;
     float alpha, beta;
+    float* cut_sums;  // merge path only, LDS: [0] the finished part of a first row that began in an earlier chunk, [1] the sum of the cut-off piece
+    bool head_cut;    // merge path only: the chunk's first row began in an earlier chunk
 };
+
+// Where the parts of rows that are cut by chunk boundaries are put together (finish_cut).
+struct CutOut {
+    float* carry_val;          // [chunks] the sum of the piece a chunk cuts off at its end
+    unsigned* arrivals;        // [chunks] 0 between runs
+    const int32_t* cut_range;  // [2*(chunks+1)] per cut: first and last chunk of the row it cuts; null: they follow from rowptr and items
+    const int32_t* rowptr;
+    int items;                 // merge-path steps between cuts
+};
+
+// A row in pieces: the chunks p0 .. p1 - 1 cut it at their ends and chunk p1 finishes it.  Every one of them leaves its part
+// in memory - p0 .. p1 - 1 their sums in carry_val, p1 the finished part in y - and counts itself in arrivals[p0]; whoever
+// comes last adds the carries to y in chunk order, so the result does not depend on who that is.  The counter wraps to 0 with the
+// last arrival, so nothing has to be cleared between runs.  What one die writes another reads: the accesses are agent-scope
+// atomics, which go past the dies' own L2s, and the part is in place (vmcnt 0) before its arrival is counted.
+// This was a kernel of its own behind the tiles (merge_fixup_kernel): 4.8 us a run for a few dozen rows.
+__device__ __forceinline__ void finish_cut(const RowOut& o, const CutOut& c, int r, int part, bool head, float value) {
+    int p0, p1;
+    if (c.cut_range) {
+        const int cut = head ? part : part + 1;
+        p0 = c.cut_range[2 * cut];
+        p1 = c.cut_range[2 * cut + 1];
+    } else {  // step r + rowptr[r] takes the row's first entry, step r + rowptr[r+1] finishes it
+        p0 = static_cast<int>((static_cast<int64_t>(r) + c.rowptr[r]) / c.items);
+        p1 = static_cast<int>((static_cast<int64_t>(r) + c.rowptr[r + 1]) / c.items);
+    }
+    __hip_atomic_store(head ? o.y + r : c.carry_val + part, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const unsigned last = static_cast<unsigned>(p1 - p0);
+    if (atomicInc(c.arrivals + p0, last) != last) return;
+    asm volatile("" ::: "memory");
+    float s = 0.f;
+    for (int q = p0; q < p1; q += 8) {
+        float part_sum[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            part_sum[u] = __hip_atomic_load(c.carry_val + (q + u < p1 ? q + u : q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q + u < p1) s += part_sum[u];
+    }
+    const float y = __hip_atomic_load(o.y + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + o.alpha * s;
+    __hip_atomic_store(o.y + r, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Row phase of a tile whose entries sit in LDS (cols[], vals[]); seg[i] .. seg[i+1] bounds the
 // slots of segment i.  cols[] indexes x[]: global column numbers into the x vector in memory,
 // or 16-bit positions into the tile's x window in LDS.  Segments 0 .. nr-1 are the rows r0 .. r0+nr-1 and go to y.  With MERGE
 // there is one more segment, the piece of row r0+nr that the chunk cuts off: its sum is the
-// chunk's carry (no carry when it is empty).  Teams of G lanes take one segment each;
+// chunk's carry (left in cut_sums for finish_cuts).  Teams of G lanes take one segment each;
 // segments longer than defer_len are set aside and taken by whole wavefronts afterwards.
 // Entered by the whole workgroup with *n_deferred == 0; contains one barrier.
 template <bool MERGE, int WG, int G, typename I, typename E>
 __device__ __forceinline__ void tile_rows_g(const I* cols, const E* vals, const E* x, const int* seg, int nr, int r0,
-                                            int part, const RowOut& o, int* deferred, int* n_deferred, int tid) {
+                                            const RowOut& o, int* deferred, int* n_deferred, int tid) {
     const int nseg = nr + (MERGE ? 1 : 0);
     constexpr int defer_len = 32 * G > 64 ? 32 * G : 64;
     constexpr int teams = WG / G;
     const int team = tid / G;
     const int tl = tid % G;
 
-    auto emit = [&](int i, float s, int len) {
+    auto emit = [&](int i, float s) {
         if (i < nr) {
-            o.y[r0 + i] = epilogue(s, o.alpha, o.beta, o.y0, i);
+            const float v = epilogue(s, o.alpha, o.beta, o.y0, i);
+            if (!(MERGE && i == 0 && o.head_cut)) o.y[r0 + i] = v;
+            else o.cut_sums[0] = v;
         } else {
-            o.carry_row[part] = len > 0 ? r0 + nr : -1;
-            o.carry_val[part] = s;
+            o.cut_sums[1] = s;
         }
     };
 
@@ -107,11 +152,9 @@ __device__ __forceinline__ void tile_rows_g(const I* cols, const E* vals, const 
         const int i = base + team;
         float acc = 0.f;
         bool mine = false;
-        int len = 0;
         if (i < nseg) {
             const int b = seg[i], e = seg[i + 1];
-            len = e - b;
-            if (len <= defer_len) {
+            if (e - b <= defer_len) {
                 mine = true;
                 acc = segment_dot<G>(cols, vals, x, b, e, tl);
             } else if (tl == 0) {
@@ -119,7 +162,7 @@ __device__ __forceinline__ void tile_rows_g(const I* cols, const E* vals, const 
             }
         }
         acc = group_sum<G>(acc);  // every lane takes part
-        if (mine && tl == 0) emit(i, acc, len);
+        if (mine && tl == 0) emit(i, acc);
     }
     __syncthreads();
 
@@ -130,7 +173,7 @@ __device__ __forceinline__ void tile_rows_g(const I* cols, const E* vals, const 
         const int b = seg[i], e = seg[i + 1];
         float acc = segment_dot<64>(cols, vals, x, b, e, lane);
         acc = group_sum<64>(acc);
-        if (lane == 0) emit(i, acc, e - b);
+        if (lane == 0) emit(i, acc);
     }
 }
 
@@ -139,7 +182,7 @@ __device__ __forceinline__ void tile_rows_g(const I* cols, const E* vals, const 
 // neighbouring rows, which is what makes the gathers of banded matrices coalesce.
 template <bool MERGE, int WG, typename I, typename E>
 __device__ __forceinline__ void tile_rows(const I* cols, const E* vals, const E* x, const int* seg, int nr, int r0,
-                                          int part, int tile_nnz, const RowOut& o, int* deferred, int* n_deferred,
+                                          int tile_nnz, const RowOut& o, int* deferred, int* n_deferred,
                                           int tid) {
     const int nseg = nr + (MERGE ? 1 : 0);
     // With mean = floor(tile_nnz / nseg):  k < mean  <=>  (k + 1) * nseg <= tile_nnz  and
@@ -154,14 +197,24 @@ __device__ __forceinline__ void tile_rows(const I* cols, const E* vals, const E*
         while (4 * G * nseg > tile_nnz) G >>= 1;
     }
     switch (G) {
-        case 1: tile_rows_g<MERGE, WG, 1>(cols, vals, x, seg, nr, r0, part, o, deferred, n_deferred, tid); break;
-        case 2: tile_rows_g<MERGE, WG, 2>(cols, vals, x, seg, nr, r0, part, o, deferred, n_deferred, tid); break;
-        case 4: tile_rows_g<MERGE, WG, 4>(cols, vals, x, seg, nr, r0, part, o, deferred, n_deferred, tid); break;
-        case 8: tile_rows_g<MERGE, WG, 8>(cols, vals, x, seg, nr, r0, part, o, deferred, n_deferred, tid); break;
-        case 16: tile_rows_g<MERGE, WG, 16>(cols, vals, x, seg, nr, r0, part, o, deferred, n_deferred, tid); break;
-        case 32: tile_rows_g<MERGE, WG, 32>(cols, vals, x, seg, nr, r0, part, o, deferred, n_deferred, tid); break;
-        default: tile_rows_g<MERGE, WG, 64>(cols, vals, x, seg, nr, r0, part, o, deferred, n_deferred, tid); break;
+        case 1: tile_rows_g<MERGE, WG, 1>(cols, vals, x, seg, nr, r0, o, deferred, n_deferred, tid); break;
+        case 2: tile_rows_g<MERGE, WG, 2>(cols, vals, x, seg, nr, r0, o, deferred, n_deferred, tid); break;
+        case 4: tile_rows_g<MERGE, WG, 4>(cols, vals, x, seg, nr, r0, o, deferred, n_deferred, tid); break;
+        case 8: tile_rows_g<MERGE, WG, 8>(cols, vals, x, seg, nr, r0, o, deferred, n_deferred, tid); break;
+        case 16: tile_rows_g<MERGE, WG, 16>(cols, vals, x, seg, nr, r0, o, deferred, n_deferred, tid); break;
+        case 32: tile_rows_g<MERGE, WG, 32>(cols, vals, x, seg, nr, r0, o, deferred, n_deferred, tid); break;
+        default: tile_rows_g<MERGE, WG, 64>(cols, vals, x, seg, nr, r0, o, deferred, n_deferred, tid); break;
     }
+}
+
+// After the row phase of a merge-path chunk (entered by the whole workgroup): hands over its first row's part, if that began
+// in an earlier chunk, and the piece cut off at its end, if there is one.  One lane each, in different wavefronts.
+__device__ __forceinline__ void finish_cuts(const RowOut& o, const CutOut& c, const int* seg, int nr, int r0, int part, int tid) {
+    const bool tail_cut = seg[nr + 1] > seg[nr];
+    if (!o.head_cut && !tail_cut) return;
+    __syncthreads();
+    if (tid == 0 && o.head_cut) finish_cut(o, c, r0, part, true, o.cut_sums[0]);
+    if (tid == 64 && tail_cut) finish_cut(o, c, r0 + nr, part, false, o.cut_sums[1]);
 }
 
 }  // namespace

@@ -15,7 +15,7 @@ namespace {
 
 // Layout of the array for P chunks (P <= kStaticMaxChunks):
 //   int32 desc[2 * (kStaticMaxChunks + 1)]   pairs (rows finished, entries taken) at every split
-//   int32 carry_row[kStaticMaxChunks]
+//   uint32 arrivals[kStaticMaxChunks]
 //   float carry_val[kStaticMaxChunks]
 constexpr int64_t kStaticMaxChunks = SPMV_STATIC_MAX_ITEMS / spmv::kDefaultItemsPerChunk;
 constexpr size_t kScratchBytes = 4 * (2 * (kStaticMaxChunks + 1) + 2 * kStaticMaxChunks);
@@ -47,9 +47,10 @@ hipError_t scratch_of_current_device(void** out) {
 }
 
 // Merge-path split p (p = 0..P): after d = min(p * ipc, m + nnz) steps of the path over (row ends, entry positions)
-// i rows are finished, i being the first row count in the feasible window with rowptr[i+1] + i > d - 1.
+// i rows are finished, i being the first row count in the feasible window with rowptr[i+1] + i > d - 1.  A split inside a row of
+// at most merge_snap(ipc) entries is moved back to the row's first entry (merge_chunk_desc does the same on the host).
 __global__ __launch_bounds__(256) void static_splits_kernel(const int32_t* __restrict__ rowptr, int m, int nnz, int ipc, int P,
-                                                            int32_t* __restrict__ desc) {
+                                                            int32_t* __restrict__ desc, unsigned* __restrict__ arrivals) {
     const int p = blockIdx.x * 256 + threadIdx.x;
     if (p > P) return;
     const int64_t T = static_cast<int64_t>(m) + nnz;
@@ -63,8 +64,11 @@ __global__ __launch_bounds__(256) void static_splits_kernel(const int32_t* __res
         else
             lo = mid + 1;
     }
+    int64_t taken = d - lo;
+    if (lo < m && rowptr[lo] < taken && rowptr[lo + 1] - rowptr[lo] <= spmv::merge_snap(ipc)) taken = rowptr[lo];
     desc[2 * p] = static_cast<int32_t>(lo);
-    desc[2 * p + 1] = static_cast<int32_t>(d - lo);
+    desc[2 * p + 1] = static_cast<int32_t>(taken);
+    if (p < P) arrivals[p] = 0;  // a call that overlapped another may have left something
 }
 
 }  // namespace
@@ -86,8 +90,8 @@ extern "C" spmv_status_t spmv_csr_run_static(int64_t m, int64_t n, int64_t nnz, 
     void* base = nullptr;
     if (spmv::note_hip_error(scratch_of_current_device(&base))) return SPMV_ERR_HIP;
     int32_t* desc = static_cast<int32_t*>(base);
-    int32_t* carry_row = desc + 2 * (kStaticMaxChunks + 1);
-    float* carry_val = reinterpret_cast<float*>(carry_row + kStaticMaxChunks);
+    unsigned* arrivals = reinterpret_cast<unsigned*>(desc + 2 * (kStaticMaxChunks + 1));
+    float* carry_val = reinterpret_cast<float*>(arrivals + kStaticMaxChunks);
 
     spmv::MatrixView A{};
     A.m = static_cast<int32_t>(m);
@@ -102,10 +106,9 @@ extern "C" spmv_status_t spmv_csr_run_static(int64_t m, int64_t n, int64_t nnz, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int ipc = spmv::kDefaultItemsPerChunk;
     const int P = static_cast<int>((m + nnz + ipc - 1) / ipc);  // >= 1 and <= kStaticMaxChunks
-    hipLaunchKernelGGL(static_splits_kernel, dim3((P + 1 + 255) / 256), dim3(256), 0, st, rowptr, A.m, A.nnz, ipc, P, desc);
+    hipLaunchKernelGGL(static_splits_kernel, dim3((P + 1 + 255) / 256), dim3(256), 0, st, rowptr, A.m, A.nnz, ipc, P, desc, arrivals);
     if (spmv::note_hip_error(hipGetLastError())) return SPMV_ERR_HIP;
-    // every chunk writes its carry (row -1 when it cuts no row), so nothing in the array has to start at zero
-    if (spmv::note_hip_error(spmv::launch_merge(A, desc, P, ipc, carry_row, carry_val, x, y, spmv::Scalars{alpha, beta}, st)))
+    if (spmv::note_hip_error(spmv::launch_merge(A, desc, P, ipc, arrivals, carry_val, x, y, spmv::Scalars{alpha, beta}, st, nullptr)))
         return SPMV_ERR_HIP;
     return SPMV_OK;
 }

@@ -12,8 +12,7 @@
 //             their cache lines), drops each into LDS at its CSR position within the chunk
 //             (16-bit), and then runs the row phase of the tile kernels over them: teams of lanes
 //             add up one row each, the piece of a row that the chunk cuts off leaves as a carry
-//             (chunks cut only rows of more than SPMV_TP_SNAP entries; where no row is cut the
-//             fix-up kernel that adds the carries is not launched).
+//             (chunks cut only rows of more than SPMV_TP_SNAP entries; finish_cut adds the carries).
 //
 // A tile is the set of entries that share a column block and a chunk.  Its entries keep their CSR
 // order, and every tile is padded to a multiple of four entries (value 0, column = the zero slot
@@ -210,7 +209,8 @@ struct TpReduceArgs {
     const float* prod;
     const int32_t* rowptr;
     float* y;
-    int32_t* carry_row;
+    const int32_t* cut_range;  // [2*(P+1)] (see finish_cut)
+    unsigned* arrivals;
     float* carry_val;
     int32_t nparts;
     int32_t row_shift;  // 0, or 3 when a slot stands for a group of eight entries: rowptr is then counted in groups
@@ -269,9 +269,12 @@ __global__ __launch_bounds__(WG) void tp_reduce_kernel(const TpReduceArgs a) {
             }
     }
     __syncthreads();
-    const RowOut o{a.y, y0_l, a.carry_row, a.carry_val, a.alpha, a.beta};
-    tile_rows<true, WG>(static_cast<const NoGather*>(nullptr), vals_l, static_cast<const float*>(nullptr), seg, nr, r0, part,
+    const bool head_cut = nr > 0 && (a.rowptr[r0] >> a.row_shift) < k0;
+    __shared__ float cut_sums[2];
+    const RowOut o{a.y, y0_l, a.alpha, a.beta, cut_sums, head_cut};
+    tile_rows<true, WG>(static_cast<const NoGather*>(nullptr), vals_l, static_cast<const float*>(nullptr), seg, nr, r0,
                         ent, o, deferred, &n_deferred, tid);
+    finish_cuts(o, CutOut{a.carry_val, a.arrivals, a.cut_range, nullptr, 0}, seg, nr, r0, part, tid);
 }
 
 // ---------------------------------------------------------------------------- analysis time
@@ -630,7 +633,7 @@ size_t two_phase_reduce_lds(int32_t entries, int32_t rows) {
     return sizeof(float) * static_cast<size_t>((entries + 3) & ~3) + (sizeof(int) + sizeof(float)) * static_cast<size_t>(rows + 2);
 }
 
-hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st) {
+hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done) {
     hipError_t e;
     if (t.num_pieces > 0 && t.group == 8) {
         // a slot is a group of eight entries: the block of x as 2^shift aligned runs of eight, and one run of zeros
@@ -668,16 +671,12 @@ hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* 
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const TpReduceArgs a{t.chunk_desc, t.chunk_g, t.tp_from, t.tp_pos, t.prod, A.rowptr, y, t.carry_row, t.carry_val, t.num_chunks,
+    const TpReduceArgs a{t.chunk_desc, t.chunk_g, t.tp_from, t.tp_pos, t.prod, A.rowptr, y, t.cut_range, t.arrivals, t.carry_val, t.num_chunks,
                          t.group == 8 ? 3 : 0, s.alpha, s.beta};
     auto k = tp_reduce_kernel<kTpRedWG, kTpRedGroups>;
     static thread_local size_t allowed = 0;
     if ((e = allow_lds(k, t.reduce_lds, &allowed)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3(t.num_chunks), dim3(kTpRedWG), t.reduce_lds, st, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // no chunk cuts a row (rows of up to kTwoPhaseSnap entries are kept whole): every carry is empty
-    if (!t.carries) return hipSuccess;
-    return launch_merge_fixup(t.carry_row, t.carry_val, t.num_chunks, y, s.alpha, st);
+    return launch_with_event(k, dim3(t.num_chunks), dim3(kTpRedWG), t.reduce_lds, st, done, a);
 }
 
 hipError_t launch_two_phase_groups(const int32_t* colidx, int32_t ngroups, int32_t* gcol, int32_t* flag, hipStream_t st) {

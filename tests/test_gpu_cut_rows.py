@@ -1,0 +1,68 @@
+"""GPU: rows that chunk boundaries cut into pieces (merge-path and two-pass plans, and the product without a handle).  Inputs
+are small integers, so every order of summation gives the same numbers: the results equal the oracle's bit for bit, run after
+run (the arrival counters wrap by themselves)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2603_07169_amd as s
+import workloads as w
+from gpu_util import DTYPE_CODE, DeviceProblem
+
+pytestmark = pytest.mark.gpu
+
+SNAP = 256        # merge-path cuts inside rows of at most this many entries are moved to the row's first entry
+LENGTHS = {
+    "around_the_snap": [255, 256, 257, 3, 0, 512, 513] * 40,
+    "one_row_over_many_chunks": [5] * 700 + [60000] + [1] * 300,
+    "long_rows_side_by_side": [3000, 2500, 0, 0, 4097, 2048, 2047, 1, 8193, 512],
+    "ends_on_a_cut": [2047, 2047, 4095, 1, 2046, 10000],     # row ends on steps that are multiples of 2048
+    "starts_and_ends_long": [9000] + [2] * 5000 + [9000],
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("name", LENGTHS)
+def test_cut_rows_bit_for_bit_run_after_run(name, dtype):
+    lens = LENGTHS[name]
+    p = w.exact_integer(lens, 70000, seed=11, dtype=dtype, alpha=2.0, beta=-1.0)
+    y_ref, _ = oracle.spmv_problem(p)
+    d = DeviceProblem(p)
+    cases = [dict(plan=s.SPMV_PLAN_MERGE, items_per_chunk=i) for i in (0, 7, 1023, 1024, 8192)] + [dict(plan=s.SPMV_PLAN_TWOPHASE)]
+    for params in cases:
+        A = d.matrix(params)
+        for _ in range(4):
+            y = d.run(A)
+            assert np.array_equal(y.astype(np.float64), y_ref), (name, params)
+        A.close()
+    for _ in range(3):
+        y = d.y0.clone()
+        s.check(s.spmv_csr_run_static(p.m, p.n, p.nnz, d.rowptr.data_ptr(), d.colidx.data_ptr(), d.vals.data_ptr(), DTYPE_CODE[dtype],
+                                      d.x.data_ptr(), y.data_ptr(), p.alpha, p.beta))
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref), name
+
+
+def test_cut_rows_replayed_from_a_graph():
+    p = w.exact_integer([4] * 3000 + [20000, 600, 9000], 30000, seed=12)
+    y_ref, _ = oracle.spmv_problem(p)
+    d = DeviceProblem(p)
+    for plan in (s.SPMV_PLAN_MERGE, s.SPMV_PLAN_TWOPHASE):
+        A = d.matrix(dict(plan=plan))
+        y = torch.zeros(p.m, device="cuda")
+        A.run(d.x, y)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+            for _ in range(3):
+                A.run(d.x, y, 1.0, 0.0, torch.cuda.current_stream().cuda_stream)
+        for _ in range(3):
+            y.fill_(7.0)
+            g.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref)
+            A.run(d.x, y)
+            torch.cuda.synchronize()
+            assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref)
+        A.close()
