@@ -276,6 +276,7 @@ class CsrMatrix:
                                           vals_t.data_ptr() if nnz else None, dtype)
         check(st, "spmv_csr_create")
         self.m, self.n, self.nnz, self.dtype = m, n, nnz, dtype
+        self._run = _load().spmv_csr_run  # looked up once: a small product is over in about the time the lookups took
         self.analyze(params)
 
     def analyze(self, params=None):
@@ -286,8 +287,9 @@ class CsrMatrix:
         return info
 
     def run(self, x_t, y_t, alpha=1.0, beta=0.0, stream=None):
-        check(spmv_csr_run(self.handle, x_t.data_ptr() if x_t is not None else None, y_t.data_ptr(), alpha, beta,
-                           stream), "spmv_csr_run")
+        status = self._run(self.handle, None if x_t is None else x_t.data_ptr(), y_t.data_ptr(), alpha, beta, stream)
+        if status != SPMV_OK:
+            raise SpmvError(status, "spmv_csr_run")
 
     def refresh_values(self, stream=None):
         check(spmv_csr_refresh_values(self.handle, stream), "spmv_csr_refresh_values")
