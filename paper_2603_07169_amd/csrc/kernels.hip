@@ -543,7 +543,8 @@ __global__ __launch_bounds__(WG, (XPL == 4 && NG == 2) ? 4 : 8) void spmv_window
 template <int G, typename E>
 __device__ __forceinline__ float pattern_dot(const E* vals, const E* xbuf, const uint16_t* pat, int slot, int pos0, int len,
                                              int tl) {
-    // the lane's entries j = tl, tl + G, ..: four at a time, then two, then one
+    // the lane's entries j = tl, tl + G, ..: eight at a time (27-point stencil, 14 or 13 a lane: 31.0 us against 31.4 with
+    // four), then four, two, one
     float acc = 0.f;
     int cnt = (len - tl + G - 1) / G;
     vals += slot + tl;
@@ -564,7 +565,8 @@ __device__ __forceinline__ float pattern_dot(const E* vals, const E* xbuf, const
         pat += B * G;
         cnt -= B;
     };
-    while (cnt >= 4) batch(std::integral_constant<int, 4>{});
+    while (cnt >= 8) batch(std::integral_constant<int, 8>{});
+    if (cnt >= 4) batch(std::integral_constant<int, 4>{});
     if (cnt >= 2) batch(std::integral_constant<int, 2>{});
     if (cnt >= 1) batch(std::integral_constant<int, 1>{});
     return acc;
