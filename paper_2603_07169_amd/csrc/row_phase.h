@@ -1,6 +1,8 @@
 // The row phase of the tile kernels: the entries of a tile sit in LDS and teams of lanes take one
 // row (segment) each.  Shared by the CSR tile kernels and the ELL kernel.  Internal linkage.
 #pragma once
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace spmv {
@@ -195,6 +197,17 @@ __device__ __forceinline__ void tile_rows(const I* cols, const E* vals, const E*
         // of the 128-byte bank cycle would otherwise have all their teams on the same LDS banks.
         G = 64;
         while (4 * G * nseg > tile_nnz) G >>= 1;
+    }
+    if constexpr (std::is_same_v<I, NoGather>) {
+        // Rows of one length that is a multiple of four put the lanes of G = 1 on a few LDS banks (16 entries: four of 64): about
+        // four entries per lane instead.  16 M groups in rows of 16: the reduce pass 27 -> 22 us; with rows of mixed lengths, whose
+        // starts spread over the banks by themselves, more lanes per row cost 2 us on the 4 M-row power law.
+        const int len = __builtin_amdgcn_readfirstlane(nr > 0 ? seg[1] - seg[0] : 0);
+        const int half = __builtin_amdgcn_readfirstlane(seg[nr >> 1] - seg[0]), all = __builtin_amdgcn_readfirstlane(seg[nr] - seg[0]);
+        if (len >= 8 && (len & 3) == 0 && all == nr * len && half == (nr >> 1) * len) {
+            G = 64;
+            while (4 * G > len) G >>= 1;
+        }
     }
     switch (G) {
         case 1: tile_rows_g<MERGE, WG, 1>(cols, vals, x, seg, nr, r0, o, deferred, n_deferred, tid); break;

@@ -66,3 +66,15 @@ def test_cut_rows_replayed_from_a_graph():
             torch.cuda.synchronize()
             assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref)
         A.close()
+
+
+@pytest.mark.parametrize("length", [1, 4, 7, 8, 12, 16, 20, 64, 100, 256, 512])
+def test_two_pass_rows_of_one_length(length):
+    """Chunks of rows of one length take more lanes per row where that length is a multiple of four; one odd row in between."""
+    for lens in ([length] * (20000 // length + 3), [length] * 501 + [length + 1] + [length] * 700):
+        p = w.exact_integer(lens, 9000, seed=length, alpha=1.0, beta=1.0)
+        y_ref, _ = oracle.spmv_problem(p)
+        d = DeviceProblem(p)
+        A = d.matrix(dict(plan=s.SPMV_PLAN_TWOPHASE))
+        assert np.array_equal(d.run(A).astype(np.float64), y_ref), (length, len(lens))
+        A.close()
