@@ -253,8 +253,7 @@ spmv_status_t spmv_csr_create(spmv_handle_t* out, int64_t m, int64_t n, int64_t 
  *     walking the merge path as for mp_row / mp_nz and cutting every tp_items (= 8192) steps, except
  *     that a cut which falls inside a row of at most SPMV_TP_SNAP entries - some of its entries
  *     taken, the row not finished - is moved back to that row's first entry, and the next tp_items
- *     steps are counted from there: a chunk cuts only rows longer than SPMV_TP_SNAP, and where no
- *     row is cut at all, run() launches no fix-up kernel.  Tile (c, p) = the entries of column block c in chunk
+ *     steps are counted from there: a chunk cuts only rows longer than SPMV_TP_SNAP.  Tile (c, p) = the entries of column block c in chunk
  *     p, in CSR order, padded to a multiple of four slots.  The multiply order lists the tiles by
  *     (c, p), the reduce order by (p, c); S slots each.  Per slot of the multiply order: tp_col
  *     (column - c * 2^tp_col_shift; padding: 2^tp_col_shift), tp_src (position k in colidx / vals;
