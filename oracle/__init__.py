@@ -67,6 +67,14 @@ def _load():
         _lib.oracle_spmm_pack.restype = None
         _lib.oracle_spmm_packed_choice.argtypes = [i64, i64]
         _lib.oracle_spmm_packed_choice.restype = C.c_int
+        _lib.oracle_spmm_pair_row_order.argtypes = [i64, vp, i64, vp]
+        _lib.oracle_spmm_pair_row_order.restype = None
+        _lib.oracle_spmm_pair_layout.argtypes = [i64, vp, vp, vp]
+        _lib.oracle_spmm_pair_layout.restype = i64
+        _lib.oracle_spmm_pair_choice.argtypes = [i64, i64, i64, vp]
+        _lib.oracle_spmm_pair_choice.restype = C.c_int
+        _lib.oracle_spmm_pair_pack.argtypes = [i64, vp, vp, vp, vp, i64, vp, vp]
+        _lib.oracle_spmm_pair_pack.restype = None
         _lib.oracle_spmv_coo.argtypes = [i64, i64, i64, vp, vp, vp, C.c_int, vp, vp, f32, f32, vp, vp]
         _lib.oracle_spmv_csc.argtypes = [i64, i64, vp, vp, vp, C.c_int, vp, vp, f32, f32, vp, vp]
         _lib.oracle_spmv_ell.argtypes = [i64, i64, i64, vp, vp, C.c_int, vp, vp, f32, f32, vp, vp]
@@ -393,6 +401,38 @@ def spmm_pack(rowptr, colidx, vals, rows, desc):
 
 def spmm_packed_choice(nnz, blocks):
     return bool(_load().oracle_spmm_packed_choice(nnz, blocks))
+
+
+def spmm_pair_row_order(rowptr, window=4096):
+    """Inside every window: row ids by decreasing min(len, 1023), rows of equal key ascending (int32[m])."""
+    m = rowptr.size - 1
+    _chk(rowptr, np.int32, m + 1)
+    rows = np.empty(m, dtype=np.int32)
+    _load().oracle_spmm_pair_row_order(m, _p(rowptr), window, _p(rows))
+    return rows
+
+
+def spmm_pair_layout(rowptr, rows):
+    """(desc int32[2G+2], number of blocks) of the pairs form for the row order `rows`, G = ceil(m / 32)."""
+    m = rowptr.size - 1
+    _chk(rowptr, np.int32, m + 1), _chk(rows, np.int32, m)
+    desc = np.zeros(2 * ((m + 31) // 32) + 2, dtype=np.int32)
+    blocks = _load().oracle_spmm_pair_layout(m, _p(rowptr), _p(rows), _p(desc))
+    return desc, int(blocks)
+
+
+def spmm_pair_choice(m, n, pair_blocks, packed_desc):
+    _chk(packed_desc, np.int32, 2 * ((m + 15) // 16) + 2)
+    return bool(_load().oracle_spmm_pair_choice(m, n, pair_blocks, _p(packed_desc)))
+
+
+def spmm_pair_pack(rowptr, colidx, rows, desc, segment=256):
+    """(byte offsets, positions in colidx with -1 as padding) of the pairs form, int32[128 * blocks] each."""
+    m = rowptr.size - 1
+    _chk(rowptr, np.int32, m + 1), _chk(colidx, np.int32), _chk(rows, np.int32, m)
+    off, src = np.full(int(desc[-2]) * 128, -7, dtype=np.int32), np.full(int(desc[-2]) * 128, -7, dtype=np.int32)
+    _load().oracle_spmm_pair_pack(m, _p(rowptr), _p(colidx), _p(rows), _p(desc), segment, _p(off), _p(src))
+    return off, src
 
 
 def column_block_choice(n, nnz, dtype, plan, vectors, entries):

@@ -107,6 +107,19 @@ MUTANTS = [
     ("spmm_oracle.cpp", "desc[2 * g + 1] = static_cast<int32_t>((L + 3) / 4);", "desc[2 * g + 1] = static_cast<int32_t>((L + 4) / 4);", "packed copy: one step too many"),
     ("spmm_oracle.cpp", "blocks += (L + 15) / 16;", "blocks += (L + 16) / 16;", "packed copy: one block too many for rows of 16"),
     ("spmm_oracle.cpp", "256 * blocks <= 2 * nnz", "256 * blocks <= nnz", "packed copy: size rule without its factor 2"),
+    ("spmm_oracle.cpp", "static_cast<int64_t>(rowptr[i + 1]) - rowptr[i], 1023); };", "static_cast<int64_t>(rowptr[i + 1]) - rowptr[i], 1024); };", "pairs: row order tells 1023 from 1024 entries"),
+    ("spmm_oracle.cpp", "blocks += std::max<int64_t>(1, (L + 3) / 4);", "blocks += (L + 3) / 4;", "pairs: no block for a group of empty rows"),
+    ("spmm_oracle.cpp", "std::max<int64_t>(1, (L + 1) / 2)", "std::max<int64_t>(1, (L + 3) / 4)", "pairs: steps of four entries"),
+    ("spmm_oracle.cpp", "<= 1.25 * static_cast<double>(packed_slots)", "< 1.25 * static_cast<double>(packed_slots)", "pairs: size rule off by one"),
+    ("spmm_oracle.cpp", "return n <= 2048 && pair_blocks", "return pair_blocks", "pairs: taken for any n"),
+    ("spmm_oracle.cpp", "{2, 3, 4, 5, 8, 9, 14, 15}};", "{2, 3, 4, 5, 9, 8, 14, 15}};", "pairs: two rows of a set change places"),
+    ("spmm_oracle.cpp", "int64_t score = 2 * static_cast<int64_t>(waiting[r][c].size()) - 2 * open;", "int64_t score = 2 * static_cast<int64_t>(waiting[r][c].size());", "pairs: the row's other choices do not count"),
+    ("spmm_oracle.cpp", "open += !waiting[r][c].empty() && taken[c] == 0;", "open += !waiting[r][c].empty();", "pairs: taken slots counted as choices"),
+    ("spmm_oracle.cpp", "taken[c] < taken[best_c] || (taken[c] == taken[best_c] && score >= best_score)", "score >= best_score", "pairs: taken slots picked again"),
+    ("spmm_oracle.cpp", "for (int64_t e = std::min(len[r], t0 + segment) - 1; e >= t0; --e)", "for (int64_t e = t0; e < std::min(len[r], t0 + segment); ++e)", "pairs: a slot's entries in reverse order"),
+    ("spmm_oracle.cpp", "while (taken[zero] > 0) ++zero;", ";", "pairs: zero rows in slots that are read"),
+    ("spmm_oracle.cpp", "32 * zero++;", "32 * zero;", "pairs: one zero row for all"),
+    ("spmm_oracle.cpp", "2 * in_group[r] + t % 2) * 2 + (t % 4) / 2;", "2 * in_group[r] + (t % 4) / 2) * 2 + t % 2;", "pairs: positions of a lane side by side"),
     ("formats_oracle.cpp", "const double p = widen_at(vals, e, dtype) * widen_at(x, col[e], dtype);", "const double p = widen_at(vals, e, dtype) * widen_at(x, row[e] < n ? row[e] : col[e], dtype);", "COO: x taken at the row index"),
     ("formats_oracle.cpp", "const double p = widen_at(vals, e, dtype) * widen_at(x, j, dtype);", "const double p = widen_at(vals, e, dtype) * widen_at(x, row[e] < n ? row[e] : j, dtype);", "CSC: x taken at the row index"),
     ("formats_oracle.cpp", "if (j == -1) continue;", "if (j == -1) return 1;", "ELL: padding refused"),

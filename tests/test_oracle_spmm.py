@@ -188,6 +188,130 @@ def test_packed_copy_entry_order_on_rows_with_every_residue_equally_often():
             assert np.all(np.diff(pos) > 0), (p, r)
 
 
+# ---- the pairs form ------------------------------------------------------------------------------
+PAIR_SETS = [[0, 1, 6, 7, 10, 11, 12, 13], [2, 3, 4, 5, 8, 9, 14, 15]]
+PAIR_SETS += [[i + 16 for i in rows] for rows in PAIR_SETS]
+ZERO_ROWS = 512 * 256                                                    # offset of zero row 0
+
+
+def pair_place(i, t, first=0):
+    return ((first + t // 4) * 64 + 2 * i + t % 2) * 2 + t % 4 // 2
+
+
+def test_pairs_handworked(golden_dir):
+    h = json.loads((golden_dir / "spmm_pairs_handworked.json").read_text())
+    rp = rowptr_from(h["lens"])
+    rows = oracle.spmm_pair_row_order(rp)
+    assert rows.tolist() == h["rows"]
+    desc, blocks = oracle.spmm_pair_layout(rp, rows)
+    assert desc.tolist() == h["desc"] and blocks == 1
+    off, src = oracle.spmm_pair_pack(rp, np.array(h["colidx"], np.int32), rows, desc)
+    want_off, want_src = np.zeros(128, np.int32), np.full(128, -1, np.int32)
+    for q, members in enumerate(PAIR_SETS):
+        for t in range(4):
+            slots = h["zero_slots"].get(f"{q},{t}", list(range(8)))
+            for i, slot in zip(members, slots):
+                want_off[pair_place(i, t)] = ZERO_ROWS + 32 * (slot or 0)
+    for place, k, offset in h["live"]:
+        want_off[place], want_src[place] = offset, k
+    assert np.array_equal(off, want_off) and np.array_equal(src, want_src)
+
+
+def test_pairs_layout_and_choice_by_hand():
+    """Lengths 1023, 1024, 2000 share a key; 33 rows make two groups; a group of empty rows keeps one block and one step."""
+    lens = [1023, 5, 1024, 2000] + [4] * 28 + [0]
+    rp = rowptr_from(lens)
+    rows = oracle.spmm_pair_row_order(rp)
+    assert rows.tolist() == [0, 2, 3, 1] + list(range(4, 33))
+    desc, blocks = oracle.spmm_pair_layout(rp, rows)
+    assert desc.tolist() == [0, 1000, 500, 1, 501, 1] and blocks == 501
+    assert oracle.spmm_pair_row_order(rp, 2).tolist() == [0, 1, 2, 3] + list(range(4, 33))
+    packed = np.array([0, 5, 1, 5, 2, 0], np.int32)                       # 640 slots: up to 800, that is 6 blocks of 128
+    assert oracle.spmm_pair_choice(32, 2048, 6, packed) and not oracle.spmm_pair_choice(32, 2048, 7, packed)
+    assert not oracle.spmm_pair_choice(32, 2049, 6, packed)
+    wide = np.array([0, 2 ** 28, 0, 0], np.int32)
+    assert oracle.spmm_pair_choice(16, 8, 2 ** 22, wide) and not oracle.spmm_pair_choice(16, 8, 2 ** 22 + 1, wide)
+    exact = np.array([0, 8, 0, 0], np.int32)                              # 512 slots: 640 allowed, five blocks exactly
+    assert oracle.spmm_pair_choice(16, 8, 5, exact) and not oracle.spmm_pair_choice(16, 8, 6, exact)
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_pairs_hold_every_entry_once_and_order_them_by_slot(seed):
+    """Every entry once, in its row's places, repeats of a slot in storage order; padding points at zero rows in slots that
+    nobody of the set uses in that step; the shared slots of a step are fewer than in storage order."""
+    rng = np.random.default_rng(200 + seed)
+    m = int(rng.integers(1, 140))
+    segment = int(rng.choice([8, 64, 256]))
+    lens = rng.poisson(rng.choice([3, 20, 70]), m)
+    p = w.from_row_lengths(lens, 300, seed=seed, allow_dup=True, sort_cols=bool(seed % 2))
+    rows = oracle.spmm_pair_row_order(p.rowptr, int(rng.choice([32, 64, 4096])))
+    desc, blocks = oracle.spmm_pair_layout(p.rowptr, rows)
+    off, src = oracle.spmm_pair_pack(p.rowptr, p.colidx, rows, desc, segment)
+    live = src >= 0
+    assert off.size == 128 * blocks and np.array_equal(np.sort(src[live]), np.arange(p.nnz)) and np.all(src[~live] == -1)
+    col = p.colidx[src[live]].astype(np.int64)
+    assert np.array_equal(off[live], 512 * (col // 8) + 32 * (col % 8))
+    shared = plain = 0
+    for g in range((m + 31) // 32):
+        positions = 4 * int(desc[2 * g + 2] - desc[2 * g])
+        for members in PAIR_SETS:
+            slots = np.zeros((8, positions), np.int64)
+            stored = np.full((8, positions), -1)
+            for r, i in enumerate(members):
+                at = np.array([pair_place(i, t, int(desc[2 * g])) for t in range(positions)])
+                k = src[at]
+                slots[r] = off[at] // 32 % 8
+                pos = 32 * g + i
+                first, last = (p.rowptr[rows[pos]], p.rowptr[rows[pos] + 1]) if pos < m else (0, 0)
+                assert np.array_equal(np.sort(k[k >= 0]), np.arange(first, last))
+                assert np.all(k[last - first:] == -1)                     # a row's entries fill its first positions
+                stored[r, :last - first] = p.colidx[first:last] % 8
+                for t0 in range(0, positions, segment):                   # a stretch holds its own entries, a slot's in storage order
+                    part = k[t0:t0 + segment]
+                    part = part[part >= 0]
+                    assert np.array_equal(np.sort(part), np.arange(first + t0, first + t0 + part.size))
+                    for c in range(8):
+                        assert np.all(np.diff(part[p.colidx[part] % 8 == c]) > 0)
+                pad = off[at][k < 0]
+                assert np.all((pad >= ZERO_ROWS) & (pad < ZERO_ROWS + 256) & (pad % 32 == 0))
+            for t in range(positions):
+                live_r = stored[:, t] >= 0
+                taken = np.bincount(slots[live_r, t], minlength=8)
+                zeros = slots[~live_r, t]
+                assert np.all(taken[zeros] == 0) and np.all(np.diff(zeros) > 0)
+                if live_r.all():
+                    shared += taken.max() - 1
+                    plain += np.bincount(stored[:, t], minlength=8).max() - 1
+    assert shared <= 0.5 * plain or plain < 40
+
+
+def test_pairs_a_rows_other_choices_count_by_hand():
+    """First step, worked by hand.  Row 0 has two entries in slot 0 and one in each of 1, 2, 3, row 1 one in slot 0: slot 0 has
+    three left, row 0 scores 3 + 4 - 8 there, row 1 3 + 2 - 2: row 1 takes it, row 0 the highest of its equal others.
+    Then rows 0, 1, 6 (one set) with slots 0 0 | 0 1 | 1 2: row 0 takes slot 0 (3 + 4 - 2); of row 1's slots only 1 is
+    untaken now, so it scores 2 + 2 - 2 there, row 6, which has slot 2 as well, 2 + 2 - 4."""
+    rp = rowptr_from([5, 1])
+    desc, _ = oracle.spmm_pair_layout(rp, np.array([0, 1], np.int32))
+    _, src = oracle.spmm_pair_pack(rp, np.array([0, 8, 1, 2, 3, 16], np.int32), np.array([0, 1], np.int32), desc)
+    assert (src[pair_place(0, 0)], src[pair_place(1, 0)]) == (4, 5)
+    rp = rowptr_from([2] * 7)
+    rows = np.arange(7, dtype=np.int32)
+    desc, _ = oracle.spmm_pair_layout(rp, rows)
+    _, src = oracle.spmm_pair_pack(rp, np.array([0, 8, 16, 1] + [5] * 8 + [9, 2], np.int32), rows, desc)
+    assert (src[pair_place(0, 0)], src[pair_place(1, 0)], src[pair_place(6, 0)]) == (0, 3, 13)
+
+
+def test_pairs_of_rows_with_all_columns_in_one_slot():
+    """No order helps: every step takes the slot eight times, and each row keeps its storage order."""
+    rp = rowptr_from([6] * 32)
+    colidx = (8 * (np.arange(192) * 7 % 30)).astype(np.int32)
+    rows = oracle.spmm_pair_row_order(rp)
+    desc, _ = oracle.spmm_pair_layout(rp, rows)
+    off, src = oracle.spmm_pair_pack(rp, colidx, rows, desc)
+    for i in range(32):
+        assert [int(src[pair_place(i, t)]) for t in range(8)] == list(range(6 * i, 6 * i + 6)) + [-1, -1]
+
+
 # ---- bf16 storage --------------------------------------------------------------------------------
 def test_bf16_handworked_and_against_the_pinned_oracles():
     """Values that bf16 holds exactly, worked by hand: A = [[1.5, 0, -2], [0, 0.25, 0]], B = [[2, -1], [4, 8], [0.5, 3]]
