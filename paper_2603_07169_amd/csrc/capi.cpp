@@ -874,8 +874,9 @@ spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* par
             st = SPMV_ERR_ALLOC;
     }
     if (st == SPMV_OK && plan_has_scratch(a.info.plan) &&
-        // nothing on the host reads what the runs wrote on this event's account: no system-scope fence with it
-        hip_failed(hipEventCreateWithFlags(&h->scratch_free, hipEventDisableTiming | hipEventDisableSystemFence)))
+        // A query of this event lets a run on another stream of the same device use the scratch, so what the run wrote has to be
+        // visible there: a device-scope release.  Nothing on the host reads it on this event's account.
+        hip_failed(hipEventCreateWithFlags(&h->scratch_free, hipEventDisableTiming | hipEventReleaseToDevice)))
         st = SPMV_ERR_HIP;
     if (st == SPMV_OK && hip_failed(hipDeviceSynchronize())) st = SPMV_ERR_HIP;
     if (st != SPMV_OK) {

@@ -85,8 +85,9 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
     return die * q + (die < r ? die : r) + slot;
 }
 
-// Launches a kernel; done, if not null, is recorded at its end by the dispatch itself (an event recorded behind the kernel is
-// a packet of its own: 2.9 us a run; with the event in the dispatch and without its system-scope fence nothing is measured).
+// Launches a kernel; done, if not null, is recorded at its end by the dispatch itself.  An event recorded behind the kernel is a
+// packet of its own: 2.9 us a run.  In the dispatch, with a device-scope release, it costs nothing on the merge plan (20.4 us
+// on 2.7 M power-law entries with or without any fence) and 1.2 us on the two passes (122.7 -> 123.9 us on 32 M entries).
 template <typename Args>
 hipError_t launch_with_event(void (*kernel)(const Args), dim3 grid, dim3 block, size_t lds, hipStream_t st, hipEvent_t done, const Args& a) {
     if (!done) {

@@ -1,6 +1,8 @@
 """GPU: rows that chunk boundaries cut into pieces (merge-path and two-pass plans, and the product without a handle).  Inputs
 are small integers, so every order of summation gives the same numbers: the results equal the oracle's bit for bit, run after
 run (the arrival counters wrap by themselves)."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -78,3 +80,37 @@ def test_two_pass_rows_of_one_length(length):
         A = d.matrix(dict(plan=s.SPMV_PLAN_TWOPHASE))
         assert np.array_equal(d.run(A).astype(np.float64), y_ref), (length, len(lens))
         A.close()
+
+
+@pytest.mark.parametrize("plan", [s.SPMV_PLAN_MERGE, s.SPMV_PLAN_TWOPHASE])
+def test_second_stream_as_soon_as_the_first_run_reports_completion(plan):
+    """One handle on two streams, ordered by nothing but the refusals: the second stream's run is asked for until it is no
+    longer refused, so all that stands between two runs that share the plan's scratch is the query of the first one's event.
+    Different inputs on the two streams; integers, so both results equal the oracle's bit for bit, every time."""
+    lens = [9] * 60000 + [30000, 700, 0, 5000] + [9] * 60000
+    p = w.exact_integer(lens, 120000, seed=21, alpha=1.0, beta=1.0)
+    d = DeviceProblem(p)
+    A = d.matrix(dict(plan=plan))
+    x2 = (-2 * p.x).astype(np.float32)
+    y1_ref, _ = oracle.spmv_problem(p)
+    y2_ref, _ = oracle.spmv_csr("f32", p.m, p.n, p.rowptr, p.colidx, p.vals, x2, p.y0, p.alpha, p.beta)
+    x2_t = torch.from_numpy(x2).cuda()
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    refused = 0
+    for rep in range(20):
+        y1, y2 = d.y0.clone(), d.y0.clone()
+        torch.cuda.synchronize()
+        s.check(s.spmv_csr_run(A.handle, d.x.data_ptr(), y1.data_ptr(), p.alpha, p.beta, s1.cuda_stream))
+        deadline = time.monotonic() + 20
+        while True:
+            status = s.spmv_csr_run(A.handle, x2_t.data_ptr(), y2.data_ptr(), p.alpha, p.beta, s2.cuda_stream)
+            if status != s.SPMV_ERR_BUSY:
+                break
+            refused += 1
+            assert time.monotonic() < deadline
+        s.check(status)
+        torch.cuda.synchronize()
+        assert np.array_equal(y1.cpu().numpy().astype(np.float64), y1_ref), rep
+        assert np.array_equal(y2.cpu().numpy().astype(np.float64), y2_ref), rep
+    assert refused > 0
+    A.close()
