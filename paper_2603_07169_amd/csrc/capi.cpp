@@ -866,7 +866,7 @@ spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* par
     }
     if (st == SPMV_OK && p.plan == SPMV_PLAN_SELL) st = build_sell(h, rowptr_host, &a);
     if (st == SPMV_OK && p.prepare_spmm) st = build_spmm_order(h, rowptr_host, &a);
-    if (st == SPMV_OK) {
+    if (st == SPMV_OK && a.info.plan == SPMV_PLAN_MERGE) {  // the only plan whose run writes these
         const size_t P = static_cast<size_t>(a.info.num_chunks > 0 ? a.info.num_chunks : 1);
         if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_arrivals), sizeof(unsigned) * P)) ||
             hip_failed(hipMemset(h->d_arrivals, 0, sizeof(unsigned) * P)) ||
