@@ -693,6 +693,7 @@ spmv_status_t build_spmm_order(spmv_csr_s* h, const HostRowptr& rowptr_host, spm
         if (st != SPMV_OK) return st;
         h->pairs.num_groups = static_cast<int32_t>((h->m + 31) / 32);
         h->pairs.num_blocks = pair_blocks;
+        for (size_t g = 0; 2 * g + 1 < pair_desc.size(); ++g) h->pairs.longest_steps = std::max(h->pairs.longest_steps, pair_desc[2 * g + 1]);
         const size_t nb = static_cast<size_t>(pair_blocks);  // and one closing block that is only ever read ahead: offset 0, value 0
         if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->pairs.ent), 1024 * (nb + 1))) ||
             hip_failed(hipMalloc(reinterpret_cast<void**>(&h->pairs.src), 512 * nb)))

@@ -105,6 +105,7 @@ struct PairRows {
     uint32_t* ent;        // [(num_blocks + 1) * 256]
     int32_t* src;         // [num_blocks * 128]
     int32_t num_groups;
+    int32_t longest_steps;  // most steps of any group
     int64_t num_blocks;
 };
 hipError_t launch_spmm_pair_pack(const MatrixView& A, const PairRows& P, hipStream_t st);    // off, src and val from the CSR arrays

@@ -824,54 +824,73 @@ __global__ __launch_bounds__(kSpmmWG) void spmm_pair_kernel(const SpmmPairArgs a
     }
 }
 
-// The largest of the 64 lanes' values (all active), as a scalar: permutes inside rows of 16 lanes, then a lane of each row.
+// The largest of the 64 lanes' values (all active), as a scalar: permutes inside rows of 16 lanes, then every row hands its
+// maximum on to the next, so that lane 63 ends up with the largest.
 __device__ __forceinline__ int wave_max(int v) {
     auto step = [&](int other) { v = other > v ? other : v; };
     step(__builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
     step(__builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
     step(__builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false));  // row_half_mirror
     step(__builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false));  // row_mirror
-    const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
-    const int c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
-    const int ab = a > b ? a : b, cd = c > d ? c : d;
-    return ab > cd ? ab : cd;
+    step(__builtin_amdgcn_update_dpp(INT32_MIN, v, 0x142, 0xA, 0xF, false));  // row_bcast15: rows 0, 2 to rows 1, 3
+    step(__builtin_amdgcn_update_dpp(INT32_MIN, v, 0x143, 0xC, 0xF, false));  // row_bcast31: row 1 to rows 2, 3
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
-// Fills the pairs form: one wavefront per eight rows that share a phase of the LDS (pair_phase_row).
-// Lane (r, c) = (lane / 8, lane mod 8) stands for row r's entries whose B row falls into slot c.  Steps are filled one after
-// another: in a step every row that still has entries takes one of them, picked by a greedy matching - the (row, slot) with
-// the fewest rows already in that slot, then the most entries left for the slot (less twice the row's number of other
-// choices, plus twice the entries the row itself has there).  Rows of more than kPairSegment entries are ordered one
-// stretch of that many entries at a time, so a long row costs time in proportion to its length.  src: the entry a slot holds, or -1.
+// Fills the pairs form: one wavefront per eight rows that share a phase of the LDS (pair_phase_row) and per stretch of
+// kPairSegment entries (blockIdx.y, in strides).  Lane (r, c) = (lane / 8, lane mod 8) stands for row r's entries whose B row
+// falls into slot c.  Steps are filled one after another: in a step every row that still has entries takes one of them,
+// picked by a greedy matching - the (row, slot) with the fewest rows already in that slot, then the most entries left for the
+// slot (less twice the row's number of other choices, plus twice the entries the row itself has there).
+// src: the entry a slot holds, or -1.
+// Bound: a chain of up to eight picks per step, each a maximum over the wavefront, one wavefront to itself.  So nothing but
+// the pick stands in that chain: the entries lie in LDS slot by slot, which rows and slots are still open are scalar masks,
+// and what a row took is written after the step's last pick.  With a load of the column inside the chain and the stretches
+// one after another: 228 us for 65536 rows of 20 entries, 502 for 3000 of up to 200, 4900 for 64 of 2000; now 102, 196, 250.
 __global__ __launch_bounds__(64) void spmm_pair_pack_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
                                                             const int32_t* __restrict__ rows, const int32_t* __restrict__ desc, int m,
                                                             uint32_t* __restrict__ ent, int32_t* __restrict__ src) {
-    __shared__ uint16_t list[8][kPairSegment];  // the stretch's entries, slot by slot
+    __shared__ __align__(16) uint16_t cols[8][kPairSegment];  // the stretch's columns in storage order (from 2048 on: 2048)
+    __shared__ uint32_t list[8][kPairSegment];                // the same slot by slot: column and place in the stretch
     const int lane = threadIdx.x, r = lane >> 3, c = lane & 7;
     const int set = blockIdx.x, g = set >> 2;
     const int first = desc[2 * g], blocks = desc[2 * g + 2] - first;
-    const int pos = kPairRows * g + pair_phase_row(set & 3, r);
+    const int in_group = pair_phase_row(set & 3, r);
+    const int pos = kPairRows * g + in_group;
     int rs = 0, len = 0;
     if (pos < m) {
         const int row = rows[pos];
         rs = rowptr[row];
         len = rowptr[row + 1] - rs;
     }
-    auto slot_of = [&](int row, int t) {  // place of the group's row `row`, position t
-        return (static_cast<size_t>(first) + (t >> 2)) * 64 + 2 * pair_phase_row(set & 3, row) + (t & 1);
-    };
-    auto put = [&](int row, int t, uint32_t offset, int k) {
-        const size_t s = slot_of(row, t);
+    auto put = [&](int t, uint32_t offset, int k) {  // this lane's row, position t
+        const size_t s = (static_cast<size_t>(first) + (t >> 2)) * 64 + 2 * in_group + (t & 1);
         ent[4 * s + ((t >> 1) & 1)] = offset;
         src[2 * s + ((t >> 1) & 1)] = k;
     };
-    const int positions = 4 * blocks;
-    for (int t0 = 0; t0 < positions; t0 += kPairSegment) {
+    const int64_t positions = 4 * static_cast<int64_t>(blocks);
+    const int64_t stride = static_cast<int64_t>(gridDim.y) * kPairSegment;
+    for (int64_t start = static_cast<int64_t>(blockIdx.y) * kPairSegment; start < positions; start += stride) {
+        const int t0 = static_cast<int>(start);
         int left = len - t0;  // of this row, in this stretch
         left = left < 0 ? 0 : (left > kPairSegment ? kPairSegment : left);
-        // counts per (row, slot), then the entries listed slot by slot; lanes of a row share the walk over its entries
+        for (int i = c; i < left; i += 8) {
+            const uint32_t col = static_cast<uint32_t>(colidx[rs + t0 + i]);
+            cols[r][i] = static_cast<uint16_t>(col < static_cast<uint32_t>(kSpmmNB) ? col : static_cast<uint32_t>(kSpmmNB));
+        }
+        __syncthreads();
+        auto walk = [&](auto&& mine) {  // the row's entries in slot c, in storage order
+            for (int i = 0; i < left; i += 8) {
+                const u32x4v w = *reinterpret_cast<const u32x4v*>(&cols[r][i]);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const uint32_t col = (w[u >> 1] >> (16 * (u & 1))) & 0xFFFFu;
+                    if (i + u < left && static_cast<int>(col & 7u) == c) mine(i + u, col);
+                }
+            }
+        };
         int cnt = 0;
-        for (int i = 0; i < left; ++i) cnt += (colidx[rs + t0 + i] & 7) == c ? 1 : 0;
+        walk([&](int, uint32_t) { ++cnt; });
         int begin = cnt;  // exclusive prefix over the row's eight lanes
 #pragma unroll
         for (int d = 1; d < 8; d <<= 1) {
@@ -881,51 +900,50 @@ __global__ __launch_bounds__(64) void spmm_pair_pack_kernel(const int32_t* __res
         begin -= cnt;
         {
             int at = begin;
-            for (int i = 0; i < left; ++i)
-                if ((colidx[rs + t0 + i] & 7) == c) list[r][at++] = static_cast<uint16_t>(i);
+            walk([&](int i, uint32_t col) { list[r][at++] = col << 16 | static_cast<uint32_t>(i); });
         }
-        __builtin_amdgcn_wave_barrier();
         int total = cnt;  // entries left for slot c in all rows
 #pragma unroll
         for (int d = 8; d < 64; d <<= 1) total += __shfl_xor(total, d);
-        const int stretch = positions - t0 < kPairSegment ? positions - t0 : kPairSegment;
+        __syncthreads();
+        uint32_t next = cnt > 0 ? list[r][begin] : 0;  // the entry this lane takes next
+        const int stretch = positions - t0 < kPairSegment ? static_cast<int>(positions - t0) : kPairSegment;
         for (int t = 0; t < stretch; ++t) {
-            unsigned long long todo = __builtin_amdgcn_ballot_w64(cnt > 0);  // rows with entries left: a byte each
-            unsigned used = 0;                                               // slots taken in this step
-            int load = 0;                                                    // rows in slot c in this step
-            unsigned long long live = todo;
+            unsigned long long live = __builtin_amdgcn_ballot_w64(cnt > 0);  // (row, slot) pairs that can still be picked in this step
+            unsigned long long picked = 0;
+            // the row's slots that have entries and are not taken in this step
+            unsigned open = ((r < 4 ? static_cast<unsigned>(live) : static_cast<unsigned>(live >> 32)) >> (8 * (r & 3))) & 0xFFu;
+            // score of the pair, 26 bits; a slot that is taken once more, and so has an entry less, comes after every one taken less often
+            int score = ((1 << 16) + 16 + total + 2 * cnt - 2 * __popc(open)) * 64 + lane;
             while (live != 0) {
-                const bool mine = cnt > 0 && ((live >> (8 * r)) & 0xFFull) != 0;
-                const unsigned long long open = __builtin_amdgcn_ballot_w64(mine && load == 0);
-                const int flex = __popcll((open >> (8 * r)) & 0xFFull);
-                int key = mine ? ((1 << 16) - (load << 12) + total + 2 * cnt - 2 * flex + 16) * 64 + lane : -1;
-                const int win = wave_max(key) & 63;
-                const int wr = win >> 3, wc = win & 7;
-                if (lane == win) {
-                    const int i = list[r][begin];
-                    const int k = rs + t0 + i;
-                    const uint32_t col = static_cast<uint32_t>(colidx[k]);
-                    put(r, t0 + t, pair_offset(col < static_cast<uint32_t>(kSpmmNB) ? col : static_cast<uint32_t>(kSpmmNB)), k);
-                    ++begin;
-                    --cnt;
-                }
-                if (c == wc) {
-                    --total;
-                    ++load;
-                }
-                used |= 1u << wc;
-                live &= ~(0xFFull << (8 * wr));
+                const int win = wave_max(__builtin_amdgcn_inverse_ballot_w64(live) ? score : -1) & 63;
+                const int wc = win & 7;
+                picked |= 1ull << win;
+                live &= ~(0xFFull << (win & 56));
+                score += static_cast<int>((open >> wc) & 1u) << 7;  // one slot less to choose from
+                open &= ~(1u << wc);
+                score = c == wc ? score - ((1 << 12) + 1) * 64 : score;
             }
-            // rows without an entry here: zero rows in slots nobody reads (as many are free as rows remain)
-            unsigned free_slots = ~used & 0xFFu;
-            for (int row = 0; row < 8; ++row) {
-                if (((todo >> (8 * row)) & 0xFFull) != 0) continue;
-                const int slot = __builtin_ctz(free_slots);
-                free_slots &= free_slots - 1;
-                if (lane == 8 * row) put(row, t0 + t, pair_offset(kSpmmNB + slot), -1);
+            const unsigned long long column = picked >> c & 0x0101010101010101ull;
+            total -= __popcll(column);
+            const bool won = __builtin_amdgcn_inverse_ballot_w64(picked);
+            if (won) {
+                put(t0 + t, pair_offset(next >> 16), rs + t0 + static_cast<int>(next & 0xFFFFu));
+                ++begin;
+                --cnt;
+                if (cnt > 0) next = list[r][begin];
+            }
+            // rows without an entry here: zero rows in slots nobody reads, ascending (as many are free as rows remain)
+            const unsigned long long empty = __builtin_amdgcn_ballot_w64(c == 0 && t >= left);
+            if (empty != 0 && c == 0 && t >= left) {
+                unsigned taken = static_cast<unsigned>(picked | picked >> 32);
+                taken |= taken >> 16;
+                unsigned free_slots = ~(taken | taken >> 8) & 0xFFu;
+                for (int below = __popcll(empty & ((1ull << lane) - 1)); below > 0; --below) free_slots &= free_slots - 1;
+                put(t0 + t, pair_offset(kSpmmNB + __ffs(free_slots) - 1), -1);
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        __syncthreads();
     }
 }
 
@@ -1137,7 +1155,11 @@ int capped_grid(int64_t items) {
 
 hipError_t launch_spmm_pair_pack(const MatrixView& A, const PairRows& P, hipStream_t st) {
     if (P.num_groups <= 0) return hipSuccess;
-    hipLaunchKernelGGL(spmm_pair_pack_kernel, dim3(4 * P.num_groups), dim3(64), 0, st, A.rowptr, A.colidx, P.rows, P.desc, A.m, P.ent, P.src);
+    // a stretch of a long row is a workgroup of its own, as far as that does not make much more than 65536 of them
+    const int64_t stretches = (2 * static_cast<int64_t>(P.longest_steps) + kPairSegment - 1) / kPairSegment;
+    const int64_t most = 16384 / P.num_groups;
+    const int per_row = static_cast<int>(stretches < most ? stretches : (most > 1 ? most : 1));
+    hipLaunchKernelGGL(spmm_pair_pack_kernel, dim3(4 * P.num_groups, per_row), dim3(64), 0, st, A.rowptr, A.colidx, P.rows, P.desc, A.m, P.ent, P.src);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? launch_spmm_pair_values(A, P, st) : e;
 }
