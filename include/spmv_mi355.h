@@ -134,6 +134,7 @@ typedef struct {
     int32_t tp_group;                  /* TWOPHASE plan: entries a slot stands for, 1 or 8 (see analyze); 0 otherwise */
     int32_t tp_piece_groups;           /* TWOPHASE plan: most groups of four slots in a piece of the multiply pass     */
     int32_t tp_resident;               /* ... and the workgroups of that pass the device holds at once, for which it was chosen */
+    int64_t spmm_pair_blocks;          /* pairs form: blocks of 32 rows x 4 entries; 0 without it                         */
 } spmv_analysis_info_t;
 
 /* Caller-allocated HOST buffers for spmv_csr_get_analysis(); a NULL member is skipped. */
@@ -181,6 +182,13 @@ typedef struct {
     int32_t* sell_ptr;   /* [ns+1] slots of the slices before slice s                  */
     int32_t* sell_col;   /* [sell_slots] column of every slot, -1 = padding            */
     int32_t* sell_src;   /* [sell_slots] its position in colidx / vals, -1 = padding   */
+    /* With the pairs form only (spmm_pair_blocks > 0; G2 = ceil(m / 32) groups): */
+    int32_t* spmm_pair_rows; /* [m] inside each window of SPMV_SPMM_WINDOW consecutive rows: row ids by decreasing
+                                min(len, 1023), ties ascending                             */
+    int32_t* spmm_pair_desc; /* [2*G2+2] pairs (blocks of the groups before g, steps of two entries), then
+                                (spmm_pair_blocks, 1)                                      */
+    uint32_t* spmm_pair_ent; /* [spmm_pair_blocks * 256] offsets and values (see analyze)  */
+    int32_t* spmm_pair_src;  /* [spmm_pair_blocks * 128] position in colidx / vals, -1 = padding */
 } spmv_analysis_host_t;
 
 /* Records the matrix (paper App. C task 12: values / col_indices / row_offsets).
@@ -320,9 +328,24 @@ spmv_status_t spmv_csr_create(spmv_handle_t* out, int64_t m, int64_t n, int64_t 
  *     (column - p) mod 4: the entries are dealt out by column residue, turned by the row's position, so that the 16 rows
  *     a wavefront reads at once ask for different quarters of the LDS banks.  It is built when it has at most 2 * nnz slots and 2^22 blocks (spmm_prepared = 2);
  *     otherwise only spmm_rows is (spmm_prepared = 1) and spmm_csr_run() reads CSR.  The copy
- *     holds the values as they were at analyze time, as binary32 (bf16 values widened).  While n <= 2048 and the rows of
- *     like length suffice for groups of 32, spmm_csr_run() works from another form of the same copy (32-row groups, two
- *     lanes per row, entries ordered against LDS bank conflicts) and the packed copy is made when it is read back.
+ *     holds the values as they were at analyze time, as binary32 (bf16 values widened): 6 or 8 bytes per slot.
+ *     The pairs form, next to the packed copy (spmm_pair_blocks > 0): kept while n <= 2048, it has at most 2^22 blocks and at
+ *     most 1.25 times as many slots (128 per block) as the packed copy's groups of 16 rows take in steps of four entries, and
+ *     its memory can be had (16 bytes per two slots, and 4 per slot for spmm_pair_src).  Group g = the rows at positions 32g ..
+ *     32g+31 of spmm_pair_rows (positions from m on: empty rows), L_g its longest row: max(1, ceil(L_g / 4)) blocks,
+ *     max(1, ceil(L_g / 2)) steps.  Position t of the group's i-th row is lane q = (first_g + t / 4) * 64 + 2 i + t mod 2,
+ *     element e = (t mod 4) / 2: spmm_pair_ent[4 q + e] is the byte offset of the entry's row of B in the kernel's LDS,
+ *     512 * (column / 8) + 32 * (column mod 8), spmm_pair_ent[4 q + 2 + e] the value's bits (binary32, as at analyze time),
+ *     spmm_pair_src[2 q + e] the entry's position; without an entry: the offset of one of the zero rows 2048 .. 2055, 0, -1.
+ *     The order of a row's entries: the rows of a group fall into four sets of eight whose lanes share a phase of a 128-bit
+ *     LDS read, {0,1,6,7,10,11,12,13}, {2,3,4,5,8,9,14,15} and the same plus 16; the slot of a column is column mod 8.  A set's
+ *     rows are taken a stretch of 256 entries at a time.  At every position the rows that have entries of the stretch left
+ *     take one each, one row after another: always the (row, slot) whose slot has been taken least often at this position;
+ *     among those the one with the largest (entries left for the slot in all eight rows) + 2 * (entries the row has left
+ *     there) - 2 * (the row's slots that have entries and are not taken at this position); among those the last row of the
+ *     set, then the highest slot.  A row's entries of a slot go in storage order.  Rows without an entry take, ascending, the
+ *     zero rows 2048 + s of the slots s nobody took, ascending.  spmm_csr_run() chooses between the two forms for every
+ *     product, by an estimate of both times from the sizes, the row lengths and the alignment (spmm_csr_kernel_name()).
  * params == NULL means all defaults.  May be called again to re-plan (old metadata is freed).
  * Synchronises the device.  Errors: INVALID_ARG, BAD_STRUCTURE, ALLOC, HIP. */
 spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* params);
@@ -343,7 +366,7 @@ spmv_status_t spmv_csr_run(spmv_handle_t h, const void* x, float* y, float alpha
  *        product itself uses rowptr / colidx / vals as they are.  A wavefront works on 16 rows
  *        at a time, for as long as the longest of them lasts: analysed with prepare_spmm = 1
  *        it takes them from spmm_rows, where rows of like length are neighbours (and from the
- *        packed copy where that was built: then vals as they were at analyze time);
+ *        packed copy or the pairs form where those were built: then vals as they were at analyze time);
  *        otherwise in their natural order.  The result is the same to rounding either way.
  *   B    device, elements of the handle's storage type (float, or uint16 bf16 bit patterns), n rows
  *        of K used columns, row-major, leading dimension ldb >= K (in elements).
@@ -351,7 +374,8 @@ spmv_status_t spmv_csr_run(spmv_handle_t h, const void* x, float* y, float alpha
  *        if beta != 0 (or when n exceeds 2048, where B is taken in several passes that accumulate
  *        into C).  B and C must not overlap.
  * Wide accesses are used when C is 16-byte aligned, B 16-byte (float) or 8-byte (bf16) aligned and
- * ldb, ldc are multiples of 4; any other layout works element by element.  m == 0 or K == 0 is a no-op.
+ * ldb, ldc are multiples of 4; any other layout works element by element (from the pairs form: 16 bytes at a time as
+ * well, aligned to the element).  m == 0 or K == 0 is a no-op.
  * Errors: INVALID_ARG (null B or C, K < 0, ldb or ldc < K), UNSUPPORTED (K > SPMV_MAX_SIZE,
  * pointers not aligned to their element size), NOT_ANALYZED, HIP. */
 spmv_status_t spmm_csr_run(spmv_handle_t h, const void* B, int64_t ldb, float* C, int64_t ldc, int64_t K, float alpha,
@@ -383,7 +407,7 @@ spmv_status_t spmv_ell_run(int64_t m, int64_t n, int64_t width, const int32_t* c
 /* Brings the library's own copies of the matrix values up to date after the caller has changed vals
  * in place (same structure, new numbers: the case of a nonlinear or time-stepping solver).  Four
  * things hold such copies: the COLBLOCK, TWOPHASE and SELL plans (values regrouped by column blocks / by
- * tiles / by slices) and the packed copy of the sparse-times-dense product; with none of them, this does nothing.  Enqueues on `stream`: no
+ * tiles / by slices) and the packed copy and pairs form of the sparse-times-dense product; with none of them, this does nothing.  Enqueues on `stream`: no
  * allocation, no copy to the host, no synchronisation.  rowptr and colidx must be unchanged.
  * Errors: INVALID_ARG (null handle), NOT_ANALYZED, HIP. */
 spmv_status_t spmv_csr_refresh_values(spmv_handle_t h, void* stream);
@@ -413,10 +437,11 @@ spmv_status_t spmv_destroy(spmv_handle_t h);
 /* Sizes and scalars of the analysis, so the caller can size read-back buffers. */
 spmv_status_t spmv_csr_get_analysis_info(spmv_handle_t h, spmv_analysis_info_t* out);
 
-/* Copies the integer analysis outputs to the host buffers in `out`: from the device what the kernels read (x windows, row
- * patterns, column blocks, the two-pass layout, the sparse-times-dense order and packed copy), from the handle's own host
- * memory what was derived from rowptr on the host and is read by the kernels only through the interleaved descriptors
- * (bin_rows unless the plan is BINNED, row_blocks, mp_row, mp_nz). */
+/* Copies the analysis outputs to the host buffers in `out`: from the device what the kernels read (x windows, row
+ * patterns, column blocks, the two-pass layout, the sparse-times-dense orders, packed copy and pairs form), from the handle's
+ * own host memory what was derived from rowptr on the host and is read by the kernels only through the interleaved descriptors
+ * (bin_rows unless the plan is BINNED, row_blocks, mp_row, mp_nz; of the merge-path splits the descriptors hold, with
+ * items_per_chunk >= 1024, those inside a row of at most 256 entries moved back to the row's first entry). */
 spmv_status_t spmv_csr_get_analysis(spmv_handle_t h, const spmv_analysis_host_t* out);
 
 /* The analysis of spmv_csr_analyze() on a HOST copy of rowptr, with HOST outputs and no device
@@ -440,6 +465,10 @@ spmv_status_t spmv_selftest_reduce(const float* in_dev, float* out_dev, void* st
 /* Name of the kernel that carries the nnz stream for the handle's current plan ("" before
  * analyze); lets a profiler summary be matched to the plan. */
 const char* spmv_csr_main_kernel_name(spmv_handle_t h);
+
+/* Name of the kernel that spmm_csr_run() launches for these arguments (only the addresses' alignment is looked at); "" before
+ * analyze or when nothing is launched for K. */
+const char* spmm_csr_kernel_name(spmv_handle_t h, const void* B, int64_t ldb, const float* C, int64_t ldc, int64_t K);
 
 const char* spmv_status_string(spmv_status_t s);
 

@@ -535,4 +535,86 @@ bool spmm_pair_layout(int64_t m, const int32_t* rowptr, const std::vector<int32_
     return blocks <= kSpmmMaxBlocks && 4 * 128 * blocks <= 5 * packed_slots;
 }
 
+GroupSteps spmm_group_steps(const std::vector<int32_t>& desc, int rows_per_group) {
+    GroupSteps s;
+    s.groups = static_cast<int64_t>(desc.size() / 2) - 1;
+    const int per_window = SPMV_SPMM_WINDOW / rows_per_group;
+    std::vector<double> sum(static_cast<size_t>(per_window), 0.);
+    std::vector<int64_t> count(sum.size(), 0);
+    for (int64_t g = 0; g < s.groups; ++g) {
+        const double steps = std::max(1, desc[static_cast<size_t>(2 * g + 1)]);
+        s.steps += steps;
+        s.longest = std::max(s.longest, steps);
+        sum[static_cast<size_t>(g % per_window)] += steps;
+        count[static_cast<size_t>(g % per_window)] += 1;
+    }
+    // from one distance between a wavefront's groups, 16 * 2^e, to half of it: the places of both halves fall together
+    int top = 0;
+    while ((16 << (top + 1)) <= per_window) ++top;
+    for (int e = 4; e >= 0; --e) {
+        if (e > top) continue;
+        const size_t distance = size_t{16} << e;
+        for (size_t p = 0; p < distance; ++p) {
+            if (e < top) {
+                sum[p] += sum[p + distance];
+                count[p] += count[p + distance];
+            }
+            if (count[p] > 0) s.place[e] = std::max(s.place[e], sum[p] / static_cast<double>(count[p]));
+        }
+    }
+    for (int e = top + 1; e < 5; ++e) s.place[e] = s.place[top];
+    return s;
+}
+
+double spmm_busiest(const GroupSteps& g, int64_t S) {
+    const int e = std::min(4, __builtin_ctzll(static_cast<unsigned long long>(S)));
+    return std::max(g.longest, g.place[e] * static_cast<double>((g.groups + 16 * S - 1) / (16 * S)));
+}
+
+int spmm_packed_splits(int64_t slices, int64_t groups) {
+    // one workgroup fits a compute unit (its B slice takes most of the LDS): one per unit or more
+    return static_cast<int>(std::min<int64_t>(slices >= 256 ? 1 : (256 + slices - 1) / slices, std::max<int64_t>(1, groups)));
+}
+
+// One workgroup fits a compute unit, so slices * splits workgroups take ceil(slices * splits / 256) rounds; a round costs the
+// staging of B's slice (about what 250 blocks of entries take) and the blocks of the wavefront with the most groups.
+// Rounding the number of workgroups up to one more than the units instead (63 slices in 5 parts: 315) cost 78 us where
+// 63 * 4 = 252 take 56 (20011 x 2048 x 1000 at density 0.01, bf16).
+int spmm_pair_splits(int64_t slices, int64_t groups, int64_t blocks) {
+    int64_t best = 1;
+    double best_cost = 0;
+    const double per_group = static_cast<double>(blocks) / static_cast<double>(groups);
+    for (int64_t s = 1;;) {
+        const int64_t held = (groups + 16 * s - 1) / (16 * s);  // groups of the wavefront with the most
+        const double cost = static_cast<double>((slices * s + 255) / 256) * (250. + per_group * 16 * static_cast<double>(held));
+        if (s == 1 || cost < best_cost) {
+            best = s;
+            best_cost = cost;
+        }
+        if (held == 1) break;
+        s = (groups + 16 * (held - 1) - 1) / (16 * (held - 1));  // the fewest parts with which it has fewer
+        if (s > 256 || s > groups) break;
+    }
+    return static_cast<int>(best);
+}
+
+// Times in us, by rounds of workgroups, of staging B's slice, of the wavefront with the most steps (a step has a latency:
+// two entries in the pairs form, four in the packed copy), of all steps (the LDS and vector units have a rate), and of C.
+// The constants are fitted to measured products of both kernels (13 distributions of row lengths, 64 to 65536 rows, 1 to
+// 4096 columns, FP32).  Over 1452 of them the pick takes as long as the better of the two (7 % more at the 95th percentile);
+// always the pairs form 14 % more on average and up to 2.8 times, never 25 % (profiles/spmm_forms.md).
+// go to the packed copy, whose chains are half as long; rows of C that are not 16-byte aligned mostly to the pairs form, which
+// stores them 16 bytes at a time all the same.
+bool spmm_pairs_choice(const GroupSteps& packed, const GroupSteps& pairs, int64_t pair_blocks, int64_t m, int64_t K, bool vec_ok) {
+    const int64_t slices = (K + 15) / 16;
+    const int64_t sk = spmm_packed_splits(slices, packed.groups), sp = spmm_pair_splits(slices, pairs.groups, pair_blocks);
+    const double rk = static_cast<double>((slices * sk + 255) / 256), rp = static_cast<double>((slices * sp + 255) / 256);
+    const double c = 1e-6 * static_cast<double>(m) * static_cast<double>(K);
+    const double by_pairs = rp * (7.9 + 0.076 * spmm_busiest(pairs, sp) + 0.066 * pairs.steps / static_cast<double>(16 * sp)) +
+                            (vec_ok ? 0.82 : 2.1) * c;
+    const double by_packed = rk * (6.0 + 0.049 * spmm_busiest(packed, sk) + 0.16 * packed.steps / static_cast<double>(16 * sk)) +
+                             (vec_ok ? 0.81 * c : 2.75 + 2.8 * c);
+    return by_pairs < by_packed;
+}
+
 }  // namespace spmv

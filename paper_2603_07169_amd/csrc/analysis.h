@@ -134,12 +134,32 @@ bool spmm_packed_layout(int64_t m, int64_t nnz, const int32_t* rowptr, const int
 // Layout of the pairs form of the sparse-times-dense product: rows by decreasing length inside every window of
 // SPMV_SPMM_WINDOW consecutive rows (lengths from kSpmmPairMaxKey on count as equal; ties ascending), groups of 32
 // positions stored as max(1, ceil(longest row / 4)) blocks of 32 rows x 4 entries.  desc[2g] = blocks of the groups before
-// g, desc[2g+1] = max(1, ceil(longest row / 2)); one closing pair (all blocks, 1).  Returns whether the form is to be used in
-// place of the packed copy described by packed_desc: it takes more rows to a group, so on skewed rows it pads more; its
-// kernel needs about 1.4 times less per padded slot, so it is taken up to 1.25 times the packed copy's slots.  May throw
-// std::bad_alloc.
+// g, desc[2g+1] = max(1, ceil(longest row / 2)); one closing pair (all blocks, 1).  Returns whether the form is to be kept
+// next to the packed copy described by packed_desc: it takes more rows to a group, so on skewed rows it pads more, and from
+// 1.25 times the packed copy's slots on spmm_pairs_choice would hardly ever pick it.  May throw std::bad_alloc.
 constexpr int kSpmmPairMaxKey = 1023;
 bool spmm_pair_layout(int64_t m, const int32_t* rowptr, const std::vector<int32_t>& packed_desc, std::vector<int32_t>* rows,
                       std::vector<int32_t>* desc, int64_t* num_blocks);
+
+// What the choice between the packed copy and the pairs form knows of either's groups: a workgroup deals its groups to its
+// 16 wavefronts in turn, and the rows lie in decreasing length inside windows of SPMV_SPMM_WINDOW rows, so with the rows in S
+// parts a wavefront keeps meeting the same places of the windows.  place[e]: the steps of a group, averaged over the groups
+// a wavefront meets at its worst place when gcd(S, groups per window / 16) = 2^e.
+struct GroupSteps {
+    int64_t groups = 0;
+    double steps = 0;    // of all groups; a group without entries takes one
+    double longest = 0;  // of any group
+    double place[5] = {0, 0, 0, 0, 0};
+};
+// desc: pairs (first block, steps) of the groups, and a closing pair; rows_per_group: 16 or 32.
+GroupSteps spmm_group_steps(const std::vector<int32_t>& desc, int rows_per_group);
+// About the steps of the wavefront that has most of them, with the groups in S parts.
+double spmm_busiest(const GroupSteps& g, int64_t S);
+// Into how many parts the rows are cut, per slice of 16 columns: the packed copy's and the pairs form's kernels.
+int spmm_packed_splits(int64_t slices, int64_t groups);
+int spmm_pair_splits(int64_t slices, int64_t groups, int64_t blocks);
+// Whether a product with K columns of C runs from the pairs form, where a handle has both.  vec_ok: B's and C's addresses
+// and leading dimensions allow 16-byte accesses.
+bool spmm_pairs_choice(const GroupSteps& packed, const GroupSteps& pairs, int64_t pair_blocks, int64_t m, int64_t K, bool vec_ok);
 
 }  // namespace spmv

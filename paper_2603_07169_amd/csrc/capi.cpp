@@ -95,10 +95,18 @@ struct spmv_csr_s {
     int32_t* d_spmm_desc = nullptr;  // packed copy of A in that order (spmm_prepared == 2)
     void* d_spmm_col = nullptr;
     float* d_spmm_val = nullptr;
-    spmv::PairRows pairs{};          // the pairs form, in place of d_spmm_col / d_spmm_val where spmm_csr_run works from it
+    spmv::PairRows pairs{};          // the pairs form next to it (pairs.ent: null without it)
+    spmv::GroupSteps packed_steps, pair_steps;  // what the choice between the two goes by
 };
 
 namespace {
+
+void free_pairs(spmv_csr_s* h) {
+    void* ptrs[] = {const_cast<int32_t*>(h->pairs.rows), const_cast<int32_t*>(h->pairs.desc), h->pairs.ent, h->pairs.src};
+    for (void* p : ptrs)
+        if (p) (void)hipFree(p);
+    h->pairs = spmv::PairRows{};
+}
 
 void free_metadata(spmv_csr_s* h) {
     void* ptrs[] = {h->d_bin_rows, h->d_block_nz,
@@ -108,8 +116,7 @@ void free_metadata(spmv_csr_s* h) {
                     h->d_spmm_val,  h->d_tp_desc,   h->d_tp_piece_c, h->d_tp_piece_g, h->d_tp_chunk_g,
                     h->d_tp_col,    h->d_tp_val,    h->d_tp_src,    h->d_tp_from,    h->d_tp_pos,
                     h->d_tp_prod,   h->d_tp_cuts, h->d_tp_arrivals, h->d_tp_carry_val, h->d_lidx8, h->d_run_desc, h->d_pat_pad,
-                    h->d_sell_ptr,  h->d_sell_col,  h->d_sell_src,  h->d_sell_val,
-                    const_cast<int32_t*>(h->pairs.rows), const_cast<int32_t*>(h->pairs.desc), h->pairs.ent, h->pairs.src};
+                    h->d_sell_ptr,  h->d_sell_col,  h->d_sell_src,  h->d_sell_val};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     h->d_tp_desc = h->d_tp_piece_c = h->d_tp_piece_g = h->d_tp_chunk_g = h->d_tp_src = h->d_tp_from = nullptr;
@@ -139,7 +146,7 @@ void free_metadata(spmv_csr_s* h) {
     h->d_spmm_rows = h->d_spmm_desc = nullptr;
     h->d_spmm_col = nullptr;
     h->d_spmm_val = nullptr;
-    h->pairs = spmv::PairRows{};
+    free_pairs(h);
     if (h->scratch_free) (void)hipEventDestroy(h->scratch_free);
     h->scratch_free = nullptr;
     h->scratch_used = false;
@@ -664,6 +671,35 @@ spmv::TwoPhase two_phase_of(const spmv_csr_s* h) {
     return t;
 }
 
+// The pairs form next to the packed copy described by packed_desc, where it is to be kept (else pairs.ent stays null).
+spmv_status_t build_pairs(spmv_csr_s* h, const HostRowptr& rowptr_host, const std::vector<int32_t>& packed_desc, spmv::Analysis* a) try {
+    std::vector<int32_t> rows, desc;
+    int64_t blocks = 0;
+    if (h->n > spmv::kSpmmPairMaxN || !spmv::spmm_pair_layout(h->m, rowptr_host.data(), packed_desc, &rows, &desc, &blocks)) return SPMV_OK;
+    int32_t *d_rows = nullptr, *d_desc = nullptr;
+    spmv_status_t st = upload(rows, &d_rows);
+    h->pairs.rows = d_rows;
+    if (st == SPMV_OK) st = upload(desc, &d_desc);
+    h->pairs.desc = d_desc;
+    if (st != SPMV_OK) return st;
+    h->packed_steps = spmv::spmm_group_steps(packed_desc, 16);
+    h->pair_steps = spmv::spmm_group_steps(desc, 32);
+    h->pairs.num_groups = static_cast<int32_t>(h->pair_steps.groups);
+    h->pairs.longest_steps = static_cast<int32_t>(h->pair_steps.longest);
+    h->pairs.num_blocks = blocks;
+    const size_t nb = static_cast<size_t>(blocks);  // and one closing block that is only ever read ahead: offset 0, value 0
+    if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->pairs.src), 512 * nb)) ||
+        hip_failed(hipMalloc(reinterpret_cast<void**>(&h->pairs.ent), 1024 * (nb + 1))))
+        return SPMV_ERR_ALLOC;
+    if (hip_failed(hipMemset(h->pairs.ent + 256 * nb, 0, 1024)) ||
+        hip_failed(spmv::launch_spmm_pair_pack(view_of(h), h->pairs, nullptr)))
+        return SPMV_ERR_HIP;
+    a->info.spmm_pair_blocks = blocks;
+    return SPMV_OK;
+} catch (const std::bad_alloc&) {
+    return SPMV_ERR_ALLOC;
+}
+
 // Row order of the sparse-times-dense product and, where it pays, the packed copy of A in that order.
 spmv_status_t build_spmm_order(spmv_csr_s* h, const HostRowptr& rowptr_host, spmv::Analysis* a) try {
     std::vector<int32_t> order, desc;
@@ -681,28 +717,6 @@ spmv_status_t build_spmm_order(spmv_csr_s* h, const HostRowptr& rowptr_host, spm
     a->info.spmm_prepared = 2;
     a->info.spmm_col_bytes = static_cast<int32_t>(col_bytes);
     a->info.spmm_num_blocks = blocks;
-    // B in one LDS block: the product works from the pairs form, and the packed copy is made only when it is read back
-    std::vector<int32_t> pair_rows, pair_desc;
-    int64_t pair_blocks = 0;
-    if (h->n <= spmv::kSpmmPairMaxN && spmv::spmm_pair_layout(h->m, rowptr_host.data(), desc, &pair_rows, &pair_desc, &pair_blocks)) {
-        int32_t *d_rows = nullptr, *d_desc = nullptr;
-        st = upload(pair_rows, &d_rows);
-        h->pairs.rows = d_rows;
-        if (st == SPMV_OK) st = upload(pair_desc, &d_desc);
-        h->pairs.desc = d_desc;
-        if (st != SPMV_OK) return st;
-        h->pairs.num_groups = static_cast<int32_t>((h->m + 31) / 32);
-        h->pairs.num_blocks = pair_blocks;
-        for (size_t g = 0; 2 * g + 1 < pair_desc.size(); ++g) h->pairs.longest_steps = std::max(h->pairs.longest_steps, pair_desc[2 * g + 1]);
-        const size_t nb = static_cast<size_t>(pair_blocks);  // and one closing block that is only ever read ahead: offset 0, value 0
-        if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->pairs.ent), 1024 * (nb + 1))) ||
-            hip_failed(hipMalloc(reinterpret_cast<void**>(&h->pairs.src), 512 * nb)))
-            return SPMV_ERR_ALLOC;
-        if (hip_failed(hipMemset(h->pairs.ent + 256 * nb, 0, 1024)) ||
-            hip_failed(spmv::launch_spmm_pair_pack(view_of(h), h->pairs, nullptr)))
-            return SPMV_ERR_HIP;
-        return SPMV_OK;
-    }
     if (hip_failed(hipMalloc(&h->d_spmm_col, col_bytes * slots)) ||
         hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_spmm_val), sizeof(float) * slots)))
         return SPMV_ERR_ALLOC;
@@ -711,40 +725,15 @@ spmv_status_t build_spmm_order(spmv_csr_s* h, const HostRowptr& rowptr_host, spm
         hip_failed(spmv::launch_spmm_pack(view_of(h), h->d_spmm_rows, h->d_spmm_desc, static_cast<int32_t>((h->m + 15) / 16),
                                           col16, h->d_spmm_col, h->d_spmm_val, nullptr)))
         return SPMV_ERR_HIP;
-    return SPMV_OK;
+    st = build_pairs(h, rowptr_host, desc, a);
+    if (st == SPMV_ERR_ALLOC) {  // no room for a second form: the products run from the packed copy
+        free_pairs(h);
+        (void)hipGetLastError();
+        st = SPMV_OK;
+    }
+    return st;
 } catch (const std::bad_alloc&) {
     return SPMV_ERR_ALLOC;
-}
-
-// The packed copy of a handle that works from the pairs form, for the read-back: the values as the pairs form holds them,
-// packed by the kernel that packs them elsewhere.
-struct ReadBackCopy {
-    void* col = nullptr;
-    float* val = nullptr;
-    float* vals = nullptr;  // in CSR order
-    ReadBackCopy() = default;
-    ReadBackCopy(const ReadBackCopy&) = delete;
-    ReadBackCopy& operator=(const ReadBackCopy&) = delete;
-    ~ReadBackCopy() {
-        (void)hipFree(col);
-        (void)hipFree(val);
-        (void)hipFree(vals);
-    }
-};
-spmv_status_t packed_copy_of_pairs(const spmv_csr_s* h, size_t slots, ReadBackCopy* c) {
-    const bool col16 = h->info.spmm_col_bytes == 2;
-    if (hip_failed(hipMalloc(&c->col, static_cast<size_t>(h->info.spmm_col_bytes) * slots)) ||
-        hip_failed(hipMalloc(reinterpret_cast<void**>(&c->val), sizeof(float) * slots)) ||
-        hip_failed(hipMalloc(reinterpret_cast<void**>(&c->vals), sizeof(float) * static_cast<size_t>(h->nnz))))
-        return SPMV_ERR_ALLOC;
-    spmv::MatrixView A = view_of(h);
-    A.vals = c->vals;
-    A.bf16 = false;
-    if (hip_failed(hipDeviceSynchronize()) || hip_failed(spmv::launch_spmm_pair_unpack(h->pairs, c->vals, nullptr)) ||
-        hip_failed(spmv::launch_spmm_pack(A, h->d_spmm_rows, h->d_spmm_desc, static_cast<int32_t>((h->m + 15) / 16), col16, c->col,
-                                          c->val, nullptr)))
-        return SPMV_ERR_HIP;
-    return SPMV_OK;
 }
 
 // Lanes per row the binned plan gives to length bin b (b >= 4: rows of 2^(b-2)+1 .. 2^(b-1) entries).
@@ -982,6 +971,11 @@ spmv_status_t spmv_csr_run(spmv_handle_t h, const void* x, float* y, float alpha
     return hip_failed(e) ? SPMV_ERR_HIP : SPMV_OK;
 }
 
+static bool spmm_from_pairs(const spmv_csr_s* h, const void* B, int64_t ldb, const float* C, int64_t ldc, int64_t K) {
+    return h->pairs.ent && spmv::spmm_pairs_choice(h->packed_steps, h->pair_steps, h->pairs.num_blocks, h->m, K,
+                                                   spmv::spmm_vec_ok(h->dtype == SPMV_BF16, B, ldb, C, ldc));
+}
+
 spmv_status_t spmm_csr_run(spmv_handle_t h, const void* B, int64_t ldb, float* C, int64_t ldc, int64_t K, float alpha,
                            float beta, void* stream) {
     if (!h) return SPMV_ERR_INVALID_ARG;
@@ -993,7 +987,7 @@ spmv_status_t spmm_csr_run(spmv_handle_t h, const void* B, int64_t ldb, float* C
     if (h->n > 0 && (!B || ldb < K)) return SPMV_ERR_INVALID_ARG;
     if (reinterpret_cast<uintptr_t>(B) % (h->dtype == SPMV_F32 ? 4 : 2) || reinterpret_cast<uintptr_t>(C) % 4) return SPMV_ERR_UNSUPPORTED;
     hipError_t e;
-    if (h->pairs.ent) {
+    if (spmm_from_pairs(h, B, ldb, C, ldc, K)) {
         e = spmv::launch_spmm_pair(view_of(h), h->pairs, B, ldb, C, ldc, static_cast<int32_t>(K), spmv::Scalars{alpha, beta},
                                    static_cast<hipStream_t>(stream));
     } else if (h->info.spmm_prepared == 2) {
@@ -1078,9 +1072,8 @@ spmv_status_t spmv_csr_refresh_values(spmv_handle_t h, void* stream) {
     if (h->info.plan == SPMV_PLAN_TWOPHASE)
         e = spmv::launch_two_phase_values(A, h->d_tp_src, h->d_tp_val, h->info.tp_slots, h->info.tp_group > 1 ? h->info.tp_group : 1, st);
     if (h->info.plan == SPMV_PLAN_SELL) e = spmv::launch_sell_values(A, h->d_sell_src, h->d_sell_val, h->info.sell_slots, st);
-    if (e == hipSuccess && h->pairs.ent)
-        e = spmv::launch_spmm_pair_values(A, h->pairs, st);
-    else if (e == hipSuccess && h->info.spmm_prepared == 2)
+    if (e == hipSuccess && h->pairs.ent) e = spmv::launch_spmm_pair_values(A, h->pairs, st);
+    if (e == hipSuccess && h->info.spmm_prepared == 2)
         e = spmv::launch_spmm_pack(A, h->d_spmm_rows, h->d_spmm_desc, static_cast<int32_t>((h->m + 15) / 16),
                                    h->info.spmm_col_bytes == 2, h->d_spmm_col, h->d_spmm_val, st);
     return hip_failed(e) ? SPMV_ERR_HIP : SPMV_OK;
@@ -1136,20 +1129,22 @@ spmv_status_t spmv_csr_get_analysis(spmv_handle_t h, const spmv_analysis_host_t*
         if (out->spmm_desc &&
             hip_failed(hipMemcpy(out->spmm_desc, h->d_spmm_desc, sizeof(int32_t) * (2 * groups + 2), hipMemcpyDeviceToHost)))
             return SPMV_ERR_HIP;
-        const void* col = h->d_spmm_col;
-        const float* val = h->d_spmm_val;
-        ReadBackCopy made;
-        if (h->pairs.ent && slots > 0 && (out->spmm_col || out->spmm_val)) {
-            const spmv_status_t st = packed_copy_of_pairs(h, slots, &made);
-            if (st != SPMV_OK) return st;
-            col = made.col;
-            val = made.val;
-        }
         if (out->spmm_col && slots > 0 &&
-            hip_failed(hipMemcpy(out->spmm_col, col, static_cast<size_t>(h->info.spmm_col_bytes) * slots, hipMemcpyDeviceToHost)))
+            hip_failed(hipMemcpy(out->spmm_col, h->d_spmm_col, static_cast<size_t>(h->info.spmm_col_bytes) * slots, hipMemcpyDeviceToHost)))
             return SPMV_ERR_HIP;
-        if (out->spmm_val && slots > 0 && hip_failed(hipMemcpy(out->spmm_val, val, sizeof(float) * slots, hipMemcpyDeviceToHost)))
+        if (out->spmm_val && slots > 0 &&
+            hip_failed(hipMemcpy(out->spmm_val, h->d_spmm_val, sizeof(float) * slots, hipMemcpyDeviceToHost)))
             return SPMV_ERR_HIP;
+    }
+    if (h->pairs.ent) {
+        const int64_t blocks = h->info.spmm_pair_blocks, groups = h->pairs.num_groups;
+        const Copy pcopies[] = {{out->spmm_pair_rows, h->pairs.rows, h->info.m}, {out->spmm_pair_desc, h->pairs.desc, 2 * groups + 2},
+                                {reinterpret_cast<int32_t*>(out->spmm_pair_ent), reinterpret_cast<const int32_t*>(h->pairs.ent), 256 * blocks},
+                                {out->spmm_pair_src, h->pairs.src, 128 * blocks}};
+        for (const Copy& c : pcopies)
+            if (c.dst && c.count > 0 &&
+                hip_failed(hipMemcpy(c.dst, c.src, sizeof(int32_t) * static_cast<size_t>(c.count), hipMemcpyDeviceToHost)))
+                return SPMV_ERR_HIP;
     }
     if (h->info.plan == SPMV_PLAN_COLBLOCK) {
         if (out->cb_ptr) std::memcpy(out->cb_ptr, h->cb_ptr.data(), sizeof(int32_t) * h->cb_ptr.size());
@@ -1272,6 +1267,12 @@ const char* spmv_csr_main_kernel_name(spmv_handle_t h) {
         case SPMV_PLAN_SELL: return spmv::sell_kernel_name();
         default: return "";
     }
+}
+
+const char* spmm_csr_kernel_name(spmv_handle_t h, const void* B, int64_t ldb, const float* C, int64_t ldc, int64_t K) {
+    if (!h || !h->analyzed || K <= 0 || K > kMaxCount) return "";
+    if (spmm_from_pairs(h, B, ldb, C, ldc, K)) return spmv::spmm_pair_kernel_name();
+    return h->info.spmm_prepared == 2 ? spmv::spmm_packed_kernel_name() : spmv::spmm_kernel_name();
 }
 
 const char* spmv_status_string(spmv_status_t s) {

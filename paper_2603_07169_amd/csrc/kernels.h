@@ -94,7 +94,10 @@ hipError_t launch_spmm_pack(const MatrixView& A, const int32_t* rows, const int3
 hipError_t launch_spmm_packed(const MatrixView& A, const PackedRows& P, const void* B, int64_t ldb, float* C, int64_t ldc,
                               int32_t K, Scalars s, hipStream_t st);
 const char* spmm_packed_kernel_name();
-// The pairs form of A that the product runs from while B's slice fits one LDS block (n <= kSpmmPairMaxN; device pointers):
+const char* spmm_pair_kernel_name();
+// Whether 128-bit (float) or 64-bit (bf16) accesses to B and 128-bit ones to C are possible.
+bool spmm_vec_ok(bool bf16, const void* B, int64_t ldb, const float* C, int64_t ldc);
+// The pairs form of A, kept next to the packed copy while B's slice fits one LDS block (n <= kSpmmPairMaxN; device pointers):
 // groups of 32 rows of the order rows[], blocks of 32 rows x 4 entries, two lanes per row.  Position t of the group's row i
 // belongs to lane q = ((first + t / 4) * 64 + 2 i + t mod 2), element (t mod 4) / 2: ent[4 q + element] is the LDS offset of
 // the entry's row of B, ent[4 q + 2 + element] its value, src[2 q + element] its place in colidx / vals, -1 in padding.
@@ -110,7 +113,6 @@ struct PairRows {
 };
 hipError_t launch_spmm_pair_pack(const MatrixView& A, const PairRows& P, hipStream_t st);    // off, src and val from the CSR arrays
 hipError_t launch_spmm_pair_values(const MatrixView& A, const PairRows& P, hipStream_t st);  // val from the CSR values
-hipError_t launch_spmm_pair_unpack(const PairRows& P, float* vals, hipStream_t st);          // vals[nnz] as val holds them
 hipError_t launch_spmm_pair(const MatrixView& A, const PairRows& P, const void* B, int64_t ldb, float* C, int64_t ldc, int32_t K,
                             Scalars s, hipStream_t st);
 // Whole aligned groups of eight entries (groups = nnz / 8): lidx8[g] = lidx[8g]; *flag (device int32, 0 on entry) is set to 1

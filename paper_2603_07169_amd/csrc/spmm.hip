@@ -1,6 +1,7 @@
 // gfx950 kernel for the sparse-times-dense product C <- alpha*A*B + beta*C (paper App. C task 13).
 #include <hip/hip_runtime.h>
 
+#include "analysis.h"
 #include "device_common.h"
 #include "kernels.h"
 
@@ -957,24 +958,15 @@ __global__ __launch_bounds__(kWG) void spmm_pair_values_kernel(const E* __restri
     }
 }
 
-// The other way round: the values as the pairs form holds them, in CSR order (for the read-back of the packed copy).
-__global__ __launch_bounds__(kWG) void spmm_pair_unpack_kernel(const uint32_t* __restrict__ ent, const int32_t* __restrict__ src,
-                                                               float* __restrict__ vals, int64_t slots) {
-    for (int64_t s = static_cast<int64_t>(blockIdx.x) * kWG + threadIdx.x; s < slots; s += static_cast<int64_t>(gridDim.x) * kWG) {
-        const int k = src[s];
-        if (k >= 0) vals[k] = __uint_as_float(ent[4 * (s >> 1) + 2 + (s & 1)]);
-    }
-}
-
 }  // namespace
 
-namespace {
-
-// 128-bit (float) or 64-bit (bf16) accesses to B, 128-bit ones to C: base addresses and leading dimensions must allow them.
+// Base addresses and leading dimensions must allow them.
 bool spmm_vec_ok(bool bf16, const void* B, int64_t ldb, const float* C, int64_t ldc) {
     return reinterpret_cast<uintptr_t>(B) % (bf16 ? 8 : 16) == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0 && ldb % 4 == 0 &&
            ldc % 4 == 0;
 }
+
+namespace {
 
 template <typename K>
 hipError_t allow_lds(K kernel, size_t lds) {
@@ -1096,8 +1088,7 @@ hipError_t launch_spmm_packed(const MatrixView& A, const PackedRows& P, const vo
     a.beta = s.beta;
     a.vec_ok = spmm_vec_ok(A.bf16, B, ldb, C, ldc) ? 1 : 0;
     const int slices = ceil_div(K, kSpmmKT);
-    int splits = slices >= 256 ? 1 : ceil_div(256, slices);
-    if (splits > P.num_groups) splits = P.num_groups;
+    const int splits = spmm_packed_splits(slices, P.num_groups);
     a.row_splits = splits;
     const size_t lds = sizeof(float) * (kSpmmNB + 1) * kSpmmKT;
     const dim3 grid(slices * splits);
@@ -1124,26 +1115,6 @@ hipError_t launch_spmm_pair_t(const SpmmPairArgs& a, dim3 grid, hipStream_t st) 
     const bool c32 = a.m <= (1 << 24) && a.ldc < (1 << 22) && static_cast<int64_t>(a.m) * a.ldc * 4 <= (int64_t{1} << 32);
     if (c32) return a.beta != 0.f ? launch_spmm_pair_k<T, true, true>(a, grid, st) : launch_spmm_pair_k<T, false, true>(a, grid, st);
     return a.beta != 0.f ? launch_spmm_pair_k<T, true, false>(a, grid, st) : launch_spmm_pair_k<T, false, false>(a, grid, st);
-}
-
-// Into how many parts the rows are split.  One workgroup fits a compute unit, so slices * splits workgroups take
-// ceil(slices * splits / 256) rounds; a round costs the staging of B's slice (about what 250 blocks of entries take) and the
-// blocks of the wavefront with the most groups.  Rounding the number of workgroups up to one more than the units instead
-// (63 slices in 5 parts: 315) cost 78 us where 63 * 4 = 252 take 56 (20011 x 2048 x 1000 at density 0.01, bf16).
-int pair_splits(int slices, const PairRows& P) {
-    int best = 1;
-    double best_cost = 0;
-    const double per_group = static_cast<double>(P.num_blocks) / P.num_groups;
-    for (int s = 1; s <= 256 && s <= P.num_groups; ++s) {
-        const double rounds = static_cast<double>((static_cast<int64_t>(slices) * s + 255) / 256);
-        const int groups = (P.num_groups + s - 1) / s;
-        const double cost = rounds * (250. + per_group * 16 * ((groups + 15) / 16));
-        if (s == 1 || cost < best_cost) {
-            best = s;
-            best_cost = cost;
-        }
-    }
-    return best;
 }
 
 int capped_grid(int64_t items) {
@@ -1176,19 +1147,12 @@ hipError_t launch_spmm_pair_values(const MatrixView& A, const PairRows& P, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_spmm_pair_unpack(const PairRows& P, float* vals, hipStream_t st) {
-    const int64_t slots = P.num_blocks * 128;
-    if (slots <= 0) return hipSuccess;
-    hipLaunchKernelGGL(spmm_pair_unpack_kernel, dim3(capped_grid(slots)), dim3(kWG), 0, st, P.ent, P.src, vals, slots);
-    return hipGetLastError();
-}
-
 hipError_t launch_spmm_pair(const MatrixView& A, const PairRows& P, const void* B, int64_t ldb, float* C, int64_t ldc, int32_t K,
                             Scalars s, hipStream_t st) {
     if (A.m <= 0 || K <= 0) return hipSuccess;
     if (A.n > kSpmmNB) return hipErrorInvalidValue;
     const int slices = ceil_div(K, kSpmmKT);
-    const int splits = pair_splits(slices, P);
+    const int splits = spmm_pair_splits(slices, P.num_groups, P.num_blocks);
     const SpmmPairArgs a{P.desc, P.ent, P.rows, B, C, ldb, ldc, A.m, A.n, K, P.num_groups, splits, s.alpha, s.beta};
     const dim3 grid(slices * splits);
     return A.bf16 ? launch_spmm_pair_t<BF16>(a, grid, st) : launch_spmm_pair_t<F32>(a, grid, st);
@@ -1196,5 +1160,6 @@ hipError_t launch_spmm_pair(const MatrixView& A, const PairRows& P, const void* 
 
 const char* spmm_kernel_name() { return "spmm_csr_kernel"; }
 const char* spmm_packed_kernel_name() { return "spmm_packed_kernel"; }
+const char* spmm_pair_kernel_name() { return "spmm_pair_kernel"; }
 
 }  // namespace spmv

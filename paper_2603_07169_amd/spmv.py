@@ -31,7 +31,7 @@ SPMV_STATIC_MAX_ITEMS = 2 ** 28 - 2048
 EXPORTS = [
     "spmv_csr_create", "spmv_csr_analyze", "spmv_csr_run", "spmv_csr_refresh_values", "spmm_csr_run", "spmv_coo_run", "spmv_csc_run", "spmv_ell_run", "spmv_csr_run_static", "spmv_destroy", "spmv_csr_get_analysis_info",
     "spmv_csr_get_analysis", "spmv_analyze_host", "spmv_selftest_reduce", "spmv_csr_main_kernel_name",
-    "spmv_status_string", "spmv_last_hip_error",
+    "spmm_csr_kernel_name", "spmv_status_string", "spmv_last_hip_error",
 ]
 
 
@@ -52,7 +52,8 @@ class spmv_analysis_info_t(C.Structure):
                 ("tp_items", C.c_int32), ("tp_num_col_blocks", C.c_int32), ("tp_num_chunks", C.c_int32),
                 ("tp_num_pieces", C.c_int32), ("lidx_grouped", C.c_int32), ("lidx_patterned", C.c_int32),
                 ("pat_cap", C.c_int32), ("pat_entries", C.c_int64), ("sell_slots", C.c_int64), ("sell_num_slices", C.c_int32),
-                ("tp_group", C.c_int32), ("tp_piece_groups", C.c_int32), ("tp_resident", C.c_int32)]
+                ("tp_group", C.c_int32), ("tp_piece_groups", C.c_int32), ("tp_resident", C.c_int32),
+                ("spmm_pair_blocks", C.c_int64)]
 
     def as_dict(self):
         return {k: int(getattr(self, k)) for k, _ in self._fields_ if k != "reserved"}
@@ -68,7 +69,9 @@ class spmv_analysis_host_t(C.Structure):
                 ("tp_chunk_g", C.c_void_p), ("tp_col", C.c_void_p), ("tp_src", C.c_void_p), ("tp_from", C.c_void_p),
                 ("tp_pos", C.c_void_p),
                 ("spmm_rows", C.c_void_p), ("spmm_desc", C.c_void_p), ("spmm_col", C.c_void_p), ("spmm_val", C.c_void_p),
-                ("sell_ptr", C.c_void_p), ("sell_col", C.c_void_p), ("sell_src", C.c_void_p)]
+                ("sell_ptr", C.c_void_p), ("sell_col", C.c_void_p), ("sell_src", C.c_void_p),
+                ("spmm_pair_rows", C.c_void_p), ("spmm_pair_desc", C.c_void_p), ("spmm_pair_ent", C.c_void_p),
+                ("spmm_pair_src", C.c_void_p)]
 
 
 class SpmvError(RuntimeError):
@@ -115,6 +118,8 @@ def _load():
         getattr(lib, name).restype = C.c_int
     lib.spmv_csr_main_kernel_name.argtypes = [vp]
     lib.spmv_csr_main_kernel_name.restype = C.c_char_p
+    lib.spmm_csr_kernel_name.argtypes = [vp, vp, i64, vp, i64, i64]
+    lib.spmm_csr_kernel_name.restype = C.c_char_p
     lib.spmv_status_string.argtypes = [C.c_int]
     lib.spmv_status_string.restype = C.c_char_p
     lib.spmv_last_hip_error.argtypes = []
@@ -225,6 +230,10 @@ def _host_buffers(info):
         bufs.update(spmm_desc=np.zeros(2 * ((info.m + 15) // 16) + 2, np.int32),
                     spmm_col=np.zeros(slots, np.uint16 if info.spmm_col_bytes == 2 else np.int32),
                     spmm_val=np.zeros(slots, np.float32))
+    if info.spmm_pair_blocks:
+        bufs.update(spmm_pair_rows=np.zeros(info.m, np.int32), spmm_pair_desc=np.zeros(2 * ((info.m + 31) // 32) + 2, np.int32),
+                    spmm_pair_ent=np.zeros(256 * info.spmm_pair_blocks, np.uint32),
+                    spmm_pair_src=np.zeros(128 * info.spmm_pair_blocks, np.int32))
     out = spmv_analysis_host_t(**{k: v.ctypes.data for k, v in bufs.items()})
     return bufs, out
 
@@ -258,6 +267,10 @@ def spmv_selftest_reduce(in_dev, out_dev, stream=None):
 
 def spmv_csr_main_kernel_name(handle) -> str:
     return _load().spmv_csr_main_kernel_name(handle).decode()
+
+
+def spmm_csr_kernel_name(handle, B, ldb, C_, ldc, K) -> str:
+    return _load().spmm_csr_kernel_name(handle, B, ldb, C_, ldc, K).decode()
 
 
 def check(status, where="spmv"):
