@@ -1,0 +1,216 @@
+"""CPU: the host rules of csrc/analysis.cpp that no entry point hands out - the chunk descriptors of the merge path, the
+chunks of a cut row, the pairs form's layout and the choice between the two forms of the sparse-times-dense product - each
+against its definition written out (or the oracle's).  The file is compiled on its own, with a few plain functions around it."""
+import ctypes as C
+import math
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2603_07169_amd import build as lib_build
+
+WRAPPER = r"""
+#include "analysis.h"
+#include <cstring>
+using std::vector;
+template <typename T> static void out(const vector<T>& v, T* p) { if (!v.empty()) std::memcpy(p, v.data(), sizeof(T) * v.size()); }
+extern "C" {
+void chunk_desc(int64_t m, const int32_t* rp, int64_t P, const int32_t* row, const int32_t* nz, int64_t snap, int32_t* desc) {
+    vector<int32_t> d;
+    spmv::merge_chunk_desc(m, rp, vector<int32_t>(row, row + P + 1), vector<int32_t>(nz, nz + P + 1), snap, &d);
+    out(d, desc);
+}
+void cuts(int64_t m, const int32_t* rp, int64_t P, const int32_t* row, const int32_t* nz, int32_t* ranges) {
+    vector<int32_t> r;
+    spmv::cut_ranges(m, rp, vector<int32_t>(row, row + P + 1), vector<int32_t>(nz, nz + P + 1), &r);
+    out(r, ranges);
+}
+int pair_layout(int64_t m, const int32_t* rp, const int32_t* packed, int32_t* rows, int32_t* desc, int64_t* blocks) {
+    vector<int32_t> r, d;
+    const bool kept = spmv::spmm_pair_layout(m, rp, vector<int32_t>(packed, packed + 2 * ((m + 15) / 16) + 2), &r, &d, blocks);
+    out(r, rows);
+    out(d, desc);
+    return kept;
+}
+double busiest(const int32_t* desc, int64_t groups, int rows_per_group, int64_t S) {
+    return spmv::spmm_busiest(spmv::spmm_group_steps(vector<int32_t>(desc, desc + 2 * groups + 2), rows_per_group), S);
+}
+int packed_splits(int64_t slices, int64_t groups) { return spmv::spmm_packed_splits(slices, groups); }
+int pair_splits(int64_t slices, int64_t groups, int64_t blocks) { return spmv::spmm_pair_splits(slices, groups, blocks); }
+int choice(const int32_t* pk, int64_t gk, const int32_t* pp, int64_t gp, int64_t blocks, int64_t m, int64_t K, int vec) {
+    return spmv::spmm_pairs_choice(spmv::spmm_group_steps(vector<int32_t>(pk, pk + 2 * gk + 2), 16),
+                                   spmv::spmm_group_steps(vector<int32_t>(pp, pp + 2 * gp + 2), 32), blocks, m, K, vec != 0);
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host_rules")
+    (d / "wrapper.cpp").write_text(WRAPPER)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-pthread", f"-I{lib_build.INCLUDE}", f"-I{lib_build.CSRC}",
+                    str(d / "wrapper.cpp"), str(lib_build.CSRC / "analysis.cpp"), "-o", str(d / "rules.so")], check=True)
+    lib = C.CDLL(str(d / "rules.so"))
+    lib.busiest.restype = C.c_double
+    return lib
+
+
+def P(a):
+    return a.ctypes.data_as(C.c_void_p)
+
+
+i64 = C.c_int64
+
+
+def rowptr_of(lens):
+    return np.concatenate(([0], np.cumsum(np.asarray(lens, dtype=np.int64)))).astype(np.int32)
+
+
+def row_lengths(seed):
+    """Rows around the snap length, empty rows, rows over many chunks and rows that end on a cut, shuffled differently."""
+    rng = np.random.default_rng(seed)
+    kinds = [rng.integers(0, 4, 300), np.array([255, 256, 257, 512, 513, 2047, 2048, 0, 0, 5000]), rng.integers(200, 700, 30),
+             np.array([], int), rng.integers(0, 2, 50)]
+    lens = np.concatenate([kinds[i] for i in rng.permutation(len(kinds))[:rng.integers(1, 6)]]).astype(int)
+    return lens if lens.size else np.array([3])
+
+
+@pytest.mark.parametrize("items,snap", [(7, 0), (1023, 0), (1024, 256), (2048, 256), (8192, 256), (100, 30)])
+@pytest.mark.parametrize("seed", range(8))
+def test_chunk_descriptors_move_cuts_inside_short_rows(rules, seed, items, snap):
+    lens = row_lengths(seed)
+    rp = rowptr_of(lens)
+    row, nz = oracle.merge_path(rp, items)
+    n = row.size
+    desc = np.zeros(2 * n, np.int32)
+    rules.chunk_desc(i64(lens.size), P(rp), i64(n - 1), P(row), P(nz), i64(snap), P(desc))
+    want = []
+    for i, k in zip(row.tolist(), nz.tolist()):
+        if i < lens.size and k > rp[i] and lens[i] <= snap:
+            k = int(rp[i])
+        want += [i, k]
+    assert desc.tolist() == want
+    grown = np.diff(desc[0::2].astype(np.int64) + desc[1::2])
+    assert np.all(np.diff(desc[1::2]) >= 0) and (grown.size == 0 or grown.max() <= items + snap)  # what the chunks' LDS is sized for
+
+
+@pytest.mark.parametrize("seed", range(8))
+@pytest.mark.parametrize("items", [5, 64, 2048])
+def test_chunks_of_a_cut_row(rules, seed, items):
+    """Per split that falls inside a row: the first and the last chunk holding a part of it.  On the unmoved splits the same
+    two numbers follow from the steps that take the row's first entry and finish it, as the merge-path kernel computes them."""
+    lens = row_lengths(seed)
+    rp = rowptr_of(lens)
+    for snapped in (False, True):
+        row, nz = oracle.merge_path_snapped(rp, items, min(30, items - 2)) if snapped else oracle.merge_path(rp, items)
+        n = row.size
+        got = np.zeros(2 * n, np.int32)
+        rules.cuts(i64(lens.size), P(rp), i64(n - 1), P(row), P(nz), P(got))
+        parts = {}
+        for p in range(n - 1):                      # chunk p: its rows' pieces and the piece it cuts off at its end
+            for i in range(row[p], min(row[p + 1], lens.size - 1) + 1):
+                first, last = max(rp[i], nz[p]), min(rp[i + 1], nz[p + 1])
+                if last > first or (row[p] <= i < row[p + 1]):
+                    parts.setdefault(i, []).append(p)
+        for q in range(n):
+            i = int(row[q])
+            inside = i < lens.size and nz[q] > rp[i]
+            assert got[2 * q:2 * q + 2].tolist() == ([parts[i][0], parts[i][-1]] if inside else [-1, -1]), (q, i)
+            if inside and not snapped:
+                assert got[2 * q:2 * q + 2].tolist() == [(i + rp[i]) // items, (i + rp[i + 1]) // items]
+
+
+@pytest.mark.parametrize("seed", range(10))
+def test_pairs_layout_equals_the_oracles(rules, seed):
+    rng = np.random.default_rng(seed)
+    m = int(rng.choice([1, 31, 32, 33, 500, 4096, 9000]))
+    lens = rng.choice([rng.poisson(20, m), rng.integers(0, 3000, m), np.where(rng.random(m) < 0.1, 300, 4)])
+    rp = rowptr_of(lens)
+    packed, _ = oracle.spmm_packed_layout(rp, oracle.spmm_row_order(rp))
+    rows, desc, blocks = np.zeros(m, np.int32), np.zeros(2 * ((m + 31) // 32) + 2, np.int32), i64()
+    kept = rules.pair_layout(i64(m), P(rp), P(packed), P(rows), P(desc), C.byref(blocks))
+    want_rows = oracle.spmm_pair_row_order(rp)
+    want_desc, want_blocks = oracle.spmm_pair_layout(rp, want_rows)
+    assert np.array_equal(rows, want_rows) and np.array_equal(desc, want_desc) and blocks.value == want_blocks
+    assert bool(kept) == oracle.spmm_pair_choice(m, 2048, want_blocks, packed)
+
+
+def desc_of(steps):
+    return np.stack([np.zeros(len(steps) + 1), np.append(steps, 1)], 1).astype(np.int32).reshape(-1).copy()
+
+
+@pytest.mark.parametrize("rows_per_group", [16, 32])
+def test_busiest_wavefront(rules, rows_per_group):
+    """Against the average over the places a wavefront meets, taken at the worst of its starts; exact where every wavefront
+    meets whole windows of the same lengths."""
+    per_window = 4096 // rows_per_group
+    rng = np.random.default_rng(3)
+    for groups in (1, 15, 40, per_window, 3 * per_window + 17):
+        steps = np.sort(rng.integers(0, 50, groups))[::-1]
+        desc = desc_of(steps)
+        taken = np.maximum(steps, 1)
+        for S in (1, 2, 3, 4, 6, 8, 12, 16, 24, 64, 100, 256):
+            distance = 16 * math.gcd(S, per_window // 16)
+            place = np.arange(groups) % per_window % distance
+            worst = max(taken[place == p].mean() for p in set(place.tolist()))
+            want = max(taken.max(), worst * -(-groups // (16 * S)))
+            got = rules.busiest(P(desc), i64(groups), rows_per_group, i64(S))
+            assert abs(got - want) <= 1e-9 * want, (groups, S)
+    window = np.sort(rng.integers(1, 90, per_window))[::-1]
+    desc = desc_of(np.tile(window, 32))
+    for S in (1, 2, 4, 8):
+        exact = max(np.tile(window, 32)[split::S][wave::16].sum() for split in range(S) for wave in range(16))
+        assert rules.busiest(P(desc), i64(32 * per_window), rows_per_group, i64(S)) == pytest.approx(exact)
+
+
+def test_splits(rules):
+    """The pairs form's: the fewest parts of all that are cheapest by the stated cost; the packed copy's: one workgroup per
+    unit or more."""
+    rng = np.random.default_rng(4)
+    for _ in range(1500):
+        slices, groups = int(np.exp(rng.uniform(0, 7))), int(np.exp(rng.uniform(0, 9)))
+        blocks = int(groups * np.exp(rng.uniform(0, 5)))
+        cost = [-(-slices * s // 256) * (250.0 + blocks / groups * 16 * -(-groups // (16 * s))) for s in range(1, min(256, groups) + 1)]
+        assert rules.pair_splits(i64(slices), i64(groups), i64(blocks)) == 1 + int(np.argmin(cost)), (slices, groups, blocks)
+        want = 1 if slices >= 256 else -(-256 // slices)
+        assert rules.packed_splits(i64(slices), i64(groups)) == min(want, groups)
+
+
+def test_choice_of_the_form(rules):
+    """The estimate of both times, written out; and what it is for: few columns and very unequal rows take the packed copy,
+    many columns and unaligned rows of C the pairs form."""
+    rng = np.random.default_rng(5)
+
+    def layouts(lens):
+        rp = rowptr_of(lens)
+        pk, _ = oracle.spmm_packed_layout(rp, oracle.spmm_row_order(rp))
+        pp, blocks = oracle.spmm_pair_layout(rp, oracle.spmm_pair_row_order(rp))
+        return pk, pp, blocks
+
+    def pick(m, pk, pp, blocks, K, vec):
+        return bool(rules.choice(P(pk), i64(pk.size // 2 - 1), P(pp), i64(pp.size // 2 - 1), i64(blocks), i64(m), i64(K), int(vec)))
+
+    for m, lens in ((1, [5]), (700, rng.poisson(20, 700)), (5000, rng.integers(0, 200, 5000)), (4096, np.full(4096, 17)), (3000, rng.poisson(300, 3000))):
+        pk, pp, blocks = layouts(lens)
+        for K in (1, 16, 17, 64, 333, 1000, 4096, 20000, 2 ** 31 - 2 ** 22):
+            for vec in (False, True):
+                slices = -(-K // 16)
+                sk = rules.packed_splits(i64(slices), i64(pk.size // 2 - 1))
+                sp = rules.pair_splits(i64(slices), i64(pp.size // 2 - 1), i64(blocks))
+                rk, rpairs = -(-slices * sk // 256), -(-slices * sp // 256)
+                ek = rules.busiest(P(pk), i64(pk.size // 2 - 1), 16, i64(sk))
+                ep = rules.busiest(P(pp), i64(pp.size // 2 - 1), 32, i64(sp))
+                tk, tp = np.maximum(pk[1:-2:2], 1).sum(), pp[1:-2:2].sum()
+                c = 1e-6 * m * K
+                pairs = rpairs * (7.9 + 0.076 * ep + 0.066 * tp / (16 * sp)) + (0.82 if vec else 2.1) * c
+                packed = rk * (6.0 + 0.049 * ek + 0.16 * tk / (16 * sk)) + (0.81 * c if vec else 2.75 + 2.8 * c)
+                if abs(pairs - packed) > 1e-9 * packed:
+                    assert pick(m, pk, pp, blocks, K, vec) == (pairs < packed), (m, K, vec)
+    m = 16384
+    usual = layouts(rng.poisson(20, m))
+    assert not pick(m, *usual, 16, True) and not pick(m, *usual, 64, True) and pick(m, *usual, 4096, True) and pick(m, *usual, 333, False)
+    tail = layouts(np.where(np.arange(m) % 200 == 0, 600, 20))
+    assert not any(pick(m, *tail, K, True) for K in (16, 64, 1024, 4096))
