@@ -723,8 +723,8 @@ __global__ __launch_bounds__(kSpmmWG) void spmm_pair_kernel(const SpmmPairArgs a
     auto pieces_of_c = [&](int row, char* (&dst)[2]) {  // this lane's piece of C in the rows of the quad's first and second pair
         if constexpr (C32) {
             const int at_row = static_cast<int>(__umul24(static_cast<unsigned>(row), static_cast<unsigned>(a.ldc) * 4u));
-            dst[0] = C0 + static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, at_row, 0x44, 0xF, 0xF, true) + 4 * c);  // quad_perm [0,1,0,1]
-            dst[1] = C0 + static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, at_row, 0xEE, 0xF, 0xF, true) + 4 * c);  // quad_perm [2,3,2,3]
+            dst[0] = C0 + (static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, at_row, 0x44, 0xF, 0xF, true)) + 4u * static_cast<unsigned>(c));  // quad_perm [0,1,0,1]
+            dst[1] = C0 + (static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, at_row, 0xEE, 0xF, 0xF, true)) + 4u * static_cast<unsigned>(c));  // quad_perm [2,3,2,3]
         } else {
             dst[0] = C0 + 4 * (static_cast<size_t>(__builtin_amdgcn_update_dpp(0, row, 0x44, 0xF, 0xF, true)) * a.ldc + c);
             dst[1] = C0 + 4 * (static_cast<size_t>(__builtin_amdgcn_update_dpp(0, row, 0xEE, 0xF, 0xF, true)) * a.ldc + c);
