@@ -114,3 +114,25 @@ def test_second_stream_as_soon_as_the_first_run_reports_completion(plan):
         assert np.array_equal(y2.cpu().numpy().astype(np.float64), y2_ref), rep
     assert refused > 0
     A.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_cut_rows_of_the_two_pass_plan_on_groups(dtype):
+    """Group-aligned matrices with rows of more than 512 groups: the chunks then count groups, and so do the cuts."""
+    groups = {"around_the_snap": [511, 512, 513, 0, 3, 700] * 30, "long_rows_between_short_ones": [5] * 300 + [3000, 0, 20000] + [1] * 500 + [8193, 2, 9000],
+              "starts_and_ends_long": [9000] + [2] * 5000 + [9000]}
+    for name, per_row in groups.items():
+        p = w.exact_integer([8 * g for g in per_row], 200000, seed=13, dtype=dtype, alpha=2.0, beta=-1.0)
+        first = np.random.default_rng(14).integers(0, p.n // 8, p.nnz // 8)
+        p.colidx[:] = (8 * first[:, None] + np.arange(8)).reshape(-1)
+        y_ref, _ = oracle.spmv_problem(p)
+        d = DeviceProblem(p)
+        A = d.matrix(dict(plan=s.SPMV_PLAN_TWOPHASE))
+        assert A.info.tp_group == 8
+        got = A.analysis()
+        cut = got["tp_nz"] > p.rowptr[np.minimum(got["tp_row"], p.m)] // 8
+        assert cut[got["tp_row"] < p.m].sum() >= 2, name           # some chunks do cut a row
+        for rep in range(4):
+            y = d.run(A)
+            assert np.array_equal(y.astype(np.float64), y_ref), (name, rep)
+        A.close()
