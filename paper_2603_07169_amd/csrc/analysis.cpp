@@ -138,14 +138,13 @@ void merge_path_splits(int64_t m, int64_t nnz, const int32_t* rowptr, int64_t ip
     });
 }
 
-bool merge_path_splits_snapped(int64_t m, int64_t nnz, const int32_t* rowptr, int64_t ipc, int64_t snap, std::vector<int32_t>* rows,
+void merge_path_splits_snapped(int64_t m, int64_t nnz, const int32_t* rowptr, int64_t ipc, int64_t snap, std::vector<int32_t>* rows,
                                std::vector<int32_t>* entries) {
     const int64_t T = m + nnz;
     rows->clear();
     entries->clear();
     rows->push_back(0);
     entries->push_back(0);
-    bool cuts = false;
     int64_t i = 0, j = 0;
     while (i + j < T) {
         // the point ipc steps on: the rows finished there lie within ipc rows of the split before (a bisection as in
@@ -161,16 +160,11 @@ bool merge_path_splits_snapped(int64_t m, int64_t nnz, const int32_t* rowptr, in
         }
         i = a;
         j = d - i;
-        if (i < m && rowptr[i] < j) {  // entries of row i taken, row i not finished
-            if (static_cast<int64_t>(rowptr[i + 1]) - rowptr[i] <= snap)
-                j = rowptr[i];
-            else
-                cuts = true;
-        }
+        // entries of row i taken, row i not finished
+        if (i < m && rowptr[i] < j && static_cast<int64_t>(rowptr[i + 1]) - rowptr[i] <= snap) j = rowptr[i];
         rows->push_back(static_cast<int32_t>(i));
         entries->push_back(static_cast<int32_t>(j));
     }
-    return cuts;
 }
 
 void merge_chunk_desc(int64_t m, const int32_t* rowptr, const std::vector<int32_t>& mp_row, const std::vector<int32_t>& mp_nz,

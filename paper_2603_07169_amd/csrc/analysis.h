@@ -84,8 +84,8 @@ constexpr int kTpGroup = 8;
 int two_phase_group_shift(spmv_dtype_t dtype);
 // The chunks of the two-pass plan: the merge path cut every ipc steps, a cut that falls inside a row of at most snap
 // entries (some of its entries taken, the row not finished) moved back to that row's first entry, the next ipc steps
-// counted from there (snap < ipc).  Returns whether any chunk still cuts a row: without one there are no carries.
-bool merge_path_splits_snapped(int64_t m, int64_t nnz, const int32_t* rowptr, int64_t ipc, int64_t snap, std::vector<int32_t>* rows,
+// counted from there (snap < ipc).
+void merge_path_splits_snapped(int64_t m, int64_t nnz, const int32_t* rowptr, int64_t ipc, int64_t snap, std::vector<int32_t>* rows,
                                std::vector<int32_t>* entries);
 void two_phase_pieces(int64_t C, const int32_t* block_first, int32_t piece_groups, std::vector<int32_t>* piece_c,
                       std::vector<int32_t>* piece_g);
