@@ -440,8 +440,8 @@ spmv_status_t spmv_csr_get_analysis_info(spmv_handle_t h, spmv_analysis_info_t* 
 /* Copies the analysis outputs to the host buffers in `out`: from the device what the kernels read (x windows, row
  * patterns, column blocks, the two-pass layout, the sparse-times-dense orders, packed copy and pairs form), from the handle's
  * own host memory what was derived from rowptr on the host and is read by the kernels only through the interleaved descriptors
- * (bin_rows unless the plan is BINNED, row_blocks, mp_row, mp_nz; of the merge-path splits the descriptors hold, with
- * items_per_chunk >= 1024, those inside a row of at most 256 entries moved back to the row's first entry). */
+ * (bin_rows unless the plan is BINNED, row_blocks, mp_row, mp_nz; the descriptors hold the merge-path splits that fall inside
+ * a row of at most min(256, items_per_chunk - 1) entries moved back to the row's first entry). */
 spmv_status_t spmv_csr_get_analysis(spmv_handle_t h, const spmv_analysis_host_t* out);
 
 /* The analysis of spmv_csr_analyze() on a HOST copy of rowptr, with HOST outputs and no device

@@ -572,14 +572,17 @@ __global__ __launch_bounds__(kSpmmWG) void spmm_packed_kernel(const SpmmPackedAr
 //     on, so both reads of an entry share one address (the 256 is an instruction offset) and a row occupies one of eight
 //     32-byte slots of the banks.  A phase holds eight rows.
 //   - The entries of eight rows that share a phase are put, at analysis time, in an order in which as few of a step's eight
-//     entries as possible meet in one slot (spmm_pair_pack_kernel): 1.41 cycles per phase and step on the benchmark's
-//     matrices (simulated) against 2.6 for storage order; padding points at zero rows in slots that are free.
+//     entries as possible meet in one slot (spmm_pair_pack_kernel): 1.41 cycles per phase on the benchmark's matrices (5.65 LDS
+//     cycles per read, counted) against 2.6 for storage order (simulated); padding points at zero rows in slots that are free.
 //   - Offsets are stored ready for use (32 bits), so an entry costs no unpacking.
 //   - A wavefront works through its blocks as one stream, across the ends of groups: the LDS reads of a step go out before
 //     the multiply-adds of the step before, the entries are fetched kPairAhead blocks ahead, an old C a group ahead.
 // 65536 x 2048 x 4096 at density 0.01, FP32: 432 us with the four-lane kernel, 368 with this one (30 TFLOP/s); without its
-// stores of C 287: a row of C is written in 64-byte pieces, one per slice, and the pieces (2.9 TB/s) are what is left over
-// the multiplication, whose LDS and vector units are busy 72 and 79 % of the time.  20011 x 2048 x 1000, bf16, C kept: 78 -> 55 us.
+// stores of C 287: a row of C is written in 64-byte pieces, one per slice, a quarter of which leave in two requests (1.32 GB
+// written for a C of 1.07), and that is what is left over the multiplication, whose LDS and vector units are busy 70 and
+// 77 % of the time.  20011 x 2048 x 1000, bf16, C kept: 78 -> 55 us.
+// A chain of steps per row is twice as long as the four-lane kernel's and a group twice as large: with few columns of C or
+// rows of very different lengths that kernel is the faster one (spmm_pairs_choice).
 constexpr int kPairRows = 32;                 // rows of a group: one wavefront, two lanes each
 constexpr int kPairZeroRows = 8;              // one zero row per slot, behind the 2048 rows of B
 constexpr int kPairLdsBytes = (kSpmmNB + kPairZeroRows) * kSpmmKT * 4;

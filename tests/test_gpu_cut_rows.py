@@ -14,7 +14,7 @@ from gpu_util import DTYPE_CODE, DeviceProblem
 
 pytestmark = pytest.mark.gpu
 
-SNAP = 256        # merge-path cuts inside rows of at most this many entries are moved to the row's first entry
+SNAP = 256        # merge-path cuts inside rows of at most this many entries (or items_per_chunk - 1) are moved to the row's first entry
 LENGTHS = {
     "around_the_snap": [255, 256, 257, 3, 0, 512, 513] * 40,
     "one_row_over_many_chunks": [5] * 700 + [60000] + [1] * 300,
@@ -31,7 +31,7 @@ def test_cut_rows_bit_for_bit_run_after_run(name, dtype):
     p = w.exact_integer(lens, 70000, seed=11, dtype=dtype, alpha=2.0, beta=-1.0)
     y_ref, _ = oracle.spmv_problem(p)
     d = DeviceProblem(p)
-    cases = [dict(plan=s.SPMV_PLAN_MERGE, items_per_chunk=i) for i in (0, 7, 1023, 1024, 8192)] + [dict(plan=s.SPMV_PLAN_TWOPHASE)]
+    cases = [dict(plan=s.SPMV_PLAN_MERGE, items_per_chunk=i) for i in (0, 1, 7, 255, 256, 257, 258, 1023, 1024, 8192)] + [dict(plan=s.SPMV_PLAN_TWOPHASE)]
     for params in cases:
         A = d.matrix(params)
         for _ in range(4):

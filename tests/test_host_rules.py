@@ -78,7 +78,7 @@ def row_lengths(seed):
     return lens if lens.size else np.array([3])
 
 
-@pytest.mark.parametrize("items,snap", [(7, 0), (1023, 0), (1024, 256), (2048, 256), (8192, 256), (100, 30)])
+@pytest.mark.parametrize("items,snap", [(1, 0), (7, 6), (100, 99), (256, 255), (257, 256), (2048, 256), (8192, 256), (100, 30)])
 @pytest.mark.parametrize("seed", range(8))
 def test_chunk_descriptors_move_cuts_inside_short_rows(rules, seed, items, snap):
     lens = row_lengths(seed)
@@ -95,6 +95,7 @@ def test_chunk_descriptors_move_cuts_inside_short_rows(rules, seed, items, snap)
     assert desc.tolist() == want
     grown = np.diff(desc[0::2].astype(np.int64) + desc[1::2])
     assert np.all(np.diff(desc[1::2]) >= 0) and (grown.size == 0 or grown.max() <= items + snap)  # what the chunks' LDS is sized for
+    assert grown.size == 0 or grown.min() > 0                                                      # and none is empty
 
 
 @pytest.mark.parametrize("seed", range(8))
