@@ -56,8 +56,7 @@ struct spmv_csr_s {
     void* d_cb_vals = nullptr;
     std::vector<int32_t> cb_ptr;   // host: [C+1]
     int32_t max_block_entries = 0;  // most entries of any row block that is not a single over-long row
-    unsigned* d_arrivals = nullptr;  // merge path: see finish_cut
-    float* d_carry_val = nullptr;
+    spmv::CutScratch cut{};  // merge path
     int32_t* d_xv_ptr = nullptr;  // x windows (WINDOWED plan)
     int32_t* d_xv_start = nullptr;
     int32_t* d_xv_pad = nullptr;
@@ -77,8 +76,7 @@ struct spmv_csr_s {
     uint16_t* d_tp_pos = nullptr;
     float* d_tp_prod = nullptr;
     int32_t* d_tp_cuts = nullptr;      // [2*(P+1)] first and last chunk of the row each split cuts
-    unsigned* d_tp_arrivals = nullptr;
-    float* d_tp_carry_val = nullptr;
+    spmv::CutScratch tp_cut{};
     size_t tp_reduce_lds = 0;
     std::vector<int32_t> tp_row, tp_nz;  // host copies for the read-back
     // The MERGE and TWOPHASE plans keep scratch in the handle (carries, products): a run on another stream while one is
@@ -110,30 +108,29 @@ void free_pairs(spmv_csr_s* h) {
 
 void free_metadata(spmv_csr_s* h) {
     void* ptrs[] = {h->d_bin_rows, h->d_block_nz,
-                    h->d_arrivals, h->d_carry_val, h->d_xv_ptr,   h->d_xv_start, h->d_lidx,
+                    h->cut.arrivals, h->cut.carry_row, h->cut.carry_val, h->d_xv_ptr,   h->d_xv_start, h->d_lidx,
                     h->d_xv_pad,    h->d_block_desc, h->d_chunk_desc, h->d_cb_row, h->d_cb_col,
                     h->d_cb_src,    h->d_cb_vals,   h->d_spmm_rows, h->d_spmm_desc, h->d_spmm_col,
                     h->d_spmm_val,  h->d_tp_desc,   h->d_tp_piece_c, h->d_tp_piece_g, h->d_tp_chunk_g,
                     h->d_tp_col,    h->d_tp_val,    h->d_tp_src,    h->d_tp_from,    h->d_tp_pos,
-                    h->d_tp_prod,   h->d_tp_cuts, h->d_tp_arrivals, h->d_tp_carry_val, h->d_lidx8, h->d_run_desc, h->d_pat_pad,
+                    h->d_tp_prod,   h->d_tp_cuts, h->tp_cut.arrivals, h->tp_cut.carry_row, h->tp_cut.carry_val, h->d_lidx8, h->d_run_desc, h->d_pat_pad,
                     h->d_sell_ptr,  h->d_sell_col,  h->d_sell_src,  h->d_sell_val};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     h->d_tp_desc = h->d_tp_piece_c = h->d_tp_piece_g = h->d_tp_chunk_g = h->d_tp_src = h->d_tp_from = nullptr;
     h->d_tp_cuts = nullptr;
-    h->d_tp_arrivals = nullptr;
+    h->tp_cut = spmv::CutScratch{};
     h->d_tp_col = h->d_tp_pos = nullptr;
     h->d_tp_val = nullptr;
-    h->d_tp_prod = h->d_tp_carry_val = nullptr;
+    h->d_tp_prod = nullptr;
     h->tp_row.clear();
     h->tp_nz.clear();
     h->d_bin_rows = h->d_block_nz = nullptr;
-    h->d_arrivals = nullptr;
+    h->cut = spmv::CutScratch{};
     h->bin_rows.clear();
     h->row_blocks.clear();
     h->mp_row.clear();
     h->mp_nz.clear();
-    h->d_carry_val = nullptr;
     h->d_xv_ptr = h->d_xv_start = h->d_xv_pad = h->d_block_desc = h->d_chunk_desc = nullptr;
     h->d_cb_row = h->d_cb_col = h->d_cb_src = nullptr;
     h->d_cb_vals = nullptr;
@@ -182,6 +179,16 @@ spmv_status_t upload(const std::vector<T>& src, T** dst) {
     if (!src.empty() && hip_failed(hipMemcpy(*dst, src.data(), sizeof(T) * src.size(), hipMemcpyHostToDevice)))
         return SPMV_ERR_HIP;
     return SPMV_OK;
+}
+
+// Scratch for chunks of which `cuts` begin inside a row.
+hipError_t alloc_cut_scratch(spmv::CutScratch* c, int64_t cuts, int64_t chunks) {
+    const size_t bytes = 4 * static_cast<size_t>(chunks > 0 ? chunks : 1);
+    const hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->carry_val), bytes);
+    if (e != hipSuccess) return e;
+    if (spmv::use_cut_rows_kernel(cuts, chunks)) return hipMalloc(reinterpret_cast<void**>(&c->carry_row), bytes);
+    const hipError_t f = hipMalloc(reinterpret_cast<void**>(&c->arrivals), bytes);
+    return f == hipSuccess ? hipMemset(c->arrivals, 0, bytes) : f;
 }
 
 spmv::MatrixView view_of(const spmv_csr_s* h) {
@@ -525,6 +532,8 @@ spmv_status_t build_two_phase(spmv_csr_s* h, const HostRowptr& rowptr_host, spmv
     if (st != SPMV_OK) return st;
     std::vector<int32_t> cuts;
     spmv::cut_ranges(h->m, rowptr_used, h->tp_row, h->tp_nz, &cuts);
+    int64_t num_cuts = 0;
+    for (size_t q = 0; 2 * q < cuts.size(); ++q) num_cuts += cuts[2 * q] >= 0;
     st = upload(cuts, &h->d_tp_cuts);
     if (st != SPMV_OK) return st;
 
@@ -582,9 +591,7 @@ spmv_status_t build_two_phase(spmv_csr_s* h, const HostRowptr& rowptr_host, spmv
          hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_from), S)) ||
          hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_pos), 2 * S)) ||
          hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_prod), 4 * S)) ||
-         hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_arrivals), 4 * static_cast<size_t>(P))) ||
-         hip_failed(hipMemset(h->d_tp_arrivals, 0, 4 * static_cast<size_t>(P))) ||
-         hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_tp_carry_val), 4 * static_cast<size_t>(P)))))
+         hip_failed(alloc_cut_scratch(&h->tp_cut, num_cuts, P))))
         st = SPMV_ERR_ALLOC;
     if (st == SPMV_OK &&
         (hip_failed(spmv::launch_two_phase_place(A, shift, static_cast<int32_t>(C), static_cast<int32_t>(P), w, h->d_tp_desc,
@@ -666,8 +673,7 @@ spmv::TwoPhase two_phase_of(const spmv_csr_s* h) {
     t.chunk_g = h->d_tp_chunk_g;
     t.prod = h->d_tp_prod;
     t.cut_range = h->d_tp_cuts;
-    t.arrivals = h->d_tp_arrivals;
-    t.carry_val = h->d_tp_carry_val;
+    t.cut = h->tp_cut;
     return t;
 }
 
@@ -800,6 +806,7 @@ spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* par
         if (flag != 0) return SPMV_ERR_BAD_STRUCTURE;
     }
 
+    int64_t merge_cuts = 0;  // chunks that begin inside a row
     if (p.plan == SPMV_PLAN_BINNED) st = upload(a.bin_rows, &h->d_bin_rows);
     if (st == SPMV_OK) {
         try {
@@ -818,6 +825,8 @@ spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* par
             }
             if (st == SPMV_OK) st = upload(desc, &h->d_block_desc);
             spmv::merge_chunk_desc(h->m, rowptr_host.data(), a.mp_row, a.mp_nz, spmv::merge_snap(a.info.items_per_chunk), &desc);
+            for (size_t q = 0; 2 * q < desc.size(); ++q)
+                if (desc[2 * q] < h->m && desc[2 * q + 1] > rowptr_host[static_cast<size_t>(desc[2 * q])]) ++merge_cuts;
             if (st == SPMV_OK) st = upload(desc, &h->d_chunk_desc);
         } catch (const std::bad_alloc&) {
             st = SPMV_ERR_ALLOC;
@@ -856,13 +865,9 @@ spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* par
     }
     if (st == SPMV_OK && p.plan == SPMV_PLAN_SELL) st = build_sell(h, rowptr_host, &a);
     if (st == SPMV_OK && p.prepare_spmm) st = build_spmm_order(h, rowptr_host, &a);
-    if (st == SPMV_OK && a.info.plan == SPMV_PLAN_MERGE) {  // the only plan whose run writes these
-        const size_t P = static_cast<size_t>(a.info.num_chunks > 0 ? a.info.num_chunks : 1);
-        if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_arrivals), sizeof(unsigned) * P)) ||
-            hip_failed(hipMemset(h->d_arrivals, 0, sizeof(unsigned) * P)) ||
-            hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_carry_val), sizeof(float) * P)))
-            st = SPMV_ERR_ALLOC;
-    }
+    // the only plan whose run writes this
+    if (st == SPMV_OK && a.info.plan == SPMV_PLAN_MERGE && hip_failed(alloc_cut_scratch(&h->cut, merge_cuts, a.info.num_chunks)))
+        st = SPMV_ERR_ALLOC;
     if (st == SPMV_OK && plan_has_scratch(a.info.plan) &&
         // A query of this event lets a run on another stream of the same device use the scratch, so what the run wrote has to be
         // visible there: a device-scope release.  Nothing on the host reads it on this event's account.
@@ -958,7 +963,7 @@ spmv_status_t spmv_csr_run(spmv_handle_t h, const void* x, float* y, float alpha
             break;
         case SPMV_PLAN_MERGE:
             e = spmv::launch_merge(A, h->d_chunk_desc, static_cast<int32_t>(h->info.num_chunks),
-                                   h->info.items_per_chunk, h->d_arrivals, h->d_carry_val, x, y, s, st,
+                                   h->info.items_per_chunk, h->cut, x, y, s, st,
                                    tracked ? h->scratch_free : nullptr);
             break;
         default:

@@ -69,10 +69,25 @@ hipError_t launch_window_build(const MatrixView& A, const int32_t* block_nz, int
 // empty, since a row that starts with a chunk and is shorter than it ends inside it.
 constexpr int32_t kMergeSnap = 256;  // chunks of 512 steps, 4.8 M entries in rows of 16, 32: without it 71 and 145 us, with it 27 and 51
 inline __host__ __device__ int32_t merge_snap(int32_t items_per_chunk) { return items_per_chunk > kMergeSnap ? kMergeSnap : items_per_chunk - 1; }
-// chunk_desc: device [2*(P+1)], pairs (mp_row[p], mp_nz[p]) moved back as said above; arrivals (zero before the first run) and
-// carry_val: device [P] scratch of the caller's (see finish_cut).  done: null, or an event that the launch records at its end.
-hipError_t launch_merge(const MatrixView& A, const int32_t* chunk_desc, int32_t P, int32_t items_per_chunk, unsigned* arrivals,
-                        float* carry_val, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done);
+// Scratch for the rows that chunks cut, device [chunks] each: carry_val, and either arrivals (zero before the first run, see
+// finish_cut) or carry_row (the pieces are added by a kernel of its own), the other null.
+struct CutScratch {
+    unsigned* arrivals;
+    int32_t* carry_row;
+    float* carry_val;
+};
+// Whether the pieces of `cuts` chunks that begin inside a row are left to a kernel of its own.  That kernel costs 2 to 5 us whatever
+// it finds, finish_cut some 12 us in every chunk that takes part, during which its place stays taken: nothing while all
+// chunks run at once, more the more rounds there are.  Both, us (FP32, rows of 300 or 16 entries, left without and right with the
+// kernel): 1.5 M entries, 290 cuts 14.1 / 14.8, 730 cuts 15.5 / 14.4; 6 M entries, 590 cuts 36.0 / 37.4, 1170 cuts 39.6 / 37.6, 2930
+// cuts 55.2 / 37.2; 24 M entries, 1170 cuts 116.2 / 118.3, 2340 cuts 117.8 / 116.4, 11700 cuts 185 / 118; two passes, rows of 700: 24 M
+// entries, 260 cuts 78.8 / 79.0, 1140 cuts 82.6 / 78.0, 2930 cuts 92 / 78.6.
+inline bool use_cut_rows_kernel(int64_t cuts, int64_t chunks) { return 12 * (cuts - 600) > chunks; }
+// chunk_desc: device [2*(P+1)], pairs (mp_row[p], mp_nz[p]) moved back as said above.  done: null, or an event that is recorded
+// at the end of the last dispatch.
+hipError_t launch_merge(const MatrixView& A, const int32_t* chunk_desc, int32_t P, int32_t items_per_chunk, const CutScratch& cut,
+                        const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done);
+hipError_t launch_cut_rows(const CutScratch& cut, int32_t P, float* y, float alpha, hipStream_t st, hipEvent_t done);
 // C <- alpha*A*B + beta*C; A CSR, B device [n x ldb] in A's storage type, C device float[m x ldc], row-major, K columns used.
 // rows: device int32[m], the order in which the rows are handed to the wavefronts (a permutation
 // of 0..m-1), or NULL for the natural order.
@@ -171,8 +186,7 @@ struct TwoPhase {
     const int32_t* chunk_g;     // [num_chunks+1] first group of each chunk in the reduce order
     float* prod;                // [slots] scratch: the products between the two passes, in the multiply order
     const int32_t* cut_range;   // [2*(num_chunks+1)] per cut that falls inside a row: first and last chunk of that row (else -1)
-    unsigned* arrivals;         // [num_chunks] scratch, zero before the first run
-    float* carry_val;           // [num_chunks] scratch
+    CutScratch cut;             // [num_chunks]
 };
 constexpr int kTpMaxShift = 15;  // column blocks of at most 32768 columns (16-bit columns, one more value for padding)
 size_t two_phase_reduce_lds(int32_t entries, int32_t rows);

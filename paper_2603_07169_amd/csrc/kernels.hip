@@ -8,6 +8,7 @@
 //   spmv_tile_kernel    a workgroup copies a contiguous entry range (a row block, or a merge-path
 //                       chunk whose cut-off tail leaves as a carry) to LDS with 128-bit loads and
 //                       lets teams of lanes take one row each, gathering x through the caches
+//   cut_rows_kernel     adds the carries of cut rows to y, in chunk order, where most chunks cut one
 //   spmv_window_kernel  the same with the block's window of x in LDS and 16-bit window positions
 //                       in place of the column indices (built by window_build_kernel at analysis)
 // No matrix cores: nothing here is a dense contraction.
@@ -183,6 +184,7 @@ struct TileArgs {
     int32_t x_vec_ok;          // x is 16-byte aligned
     const int32_t* colidx;
     unsigned* arrivals;        // merge path only, [nparts] (see finish_cut)
+    int32_t* carry_row;        // merge path only: null, or [nparts] (see CutOut)
     float* carry_val;          // merge path only, [nparts]
 };
 
@@ -346,9 +348,9 @@ __global__ __launch_bounds__(WG, 8) void spmv_tile_kernel(const TileArgs a) {
     // ---- 2. rows
     if constexpr (MERGE) {
         __shared__ float cut_sums[2];
-        const RowOut o{a.y, y0_l, a.alpha, a.beta, cut_sums, nr > 0 && a.rowptr[r0] < k0};
+        const RowOut o{a.y, y0_l, a.alpha, a.beta, cut_sums, !a.carry_row && nr > 0 && a.rowptr[r0] < k0};
         tile_rows<MERGE, WG>(cols_l, vals_l, x, seg, nr, r0, k1 - k0, o, deferred, &n_deferred, tid);
-        finish_cuts(o, CutOut{a.carry_val, a.arrivals, nullptr, a.rowptr, a.tile_cap}, seg, nr, r0, part, tid);
+        finish_cuts(o, CutOut{a.carry_val, a.arrivals, nullptr, a.rowptr, a.tile_cap, a.carry_row}, seg, nr, r0, part, tid);
     } else {
         const RowOut o{a.y, y0_l, a.alpha, a.beta, nullptr, false};
         tile_rows<MERGE, WG>(cols_l, vals_l, x, seg, nr, r0, k1 - k0, o, deferred, &n_deferred, tid);
@@ -1130,6 +1132,25 @@ __global__ __launch_bounds__(256) void pattern_totals_kernel(const int32_t* __re
     }
 }
 
+// Adds the carries of rows that were cut by chunk boundaries, where the chunks left them (CutOut::carry_row).  Chunks that cut
+// the same row are consecutive; the thread of the first of them sums the run in chunk order.
+struct CutRowsArgs {
+    const int32_t* carry_row;
+    const float* carry_val;
+    float* y;
+    int32_t P;
+    float alpha;
+};
+__global__ __launch_bounds__(kWG) void cut_rows_kernel(const CutRowsArgs a) {
+    const int p = blockIdx.x * kWG + threadIdx.x;
+    if (p >= a.P) return;
+    const int r = a.carry_row[p];
+    if (r < 0 || (p > 0 && a.carry_row[p - 1] == r)) return;
+    float s = 0.f;
+    for (int q = p; q < a.P && a.carry_row[q] == r; ++q) s += a.carry_val[q];
+    a.y[r] += a.alpha * s;
+}
+
 // lidx8[g] = lidx[8g] for every whole aligned group of eight entries; *flag = 1 if some group's positions are not
 // eight consecutive numbers (then lidx8 is of no use).
 __global__ __launch_bounds__(kWG) void lidx_groups_kernel(const uint16_t* __restrict__ lidx, int groups, uint16_t* __restrict__ lidx8,
@@ -1387,20 +1408,28 @@ hipError_t launch_pattern_build(const int32_t* block_desc, int32_t nb, const int
     return hipGetLastError();
 }
 
-hipError_t launch_merge(const MatrixView& A, const int32_t* chunk_desc, int32_t P, int32_t items_per_chunk, unsigned* arrivals,
-                        float* carry_val, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done) {
+hipError_t launch_merge(const MatrixView& A, const int32_t* chunk_desc, int32_t P, int32_t items_per_chunk, const CutScratch& cut,
+                        const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done) {
     if (P <= 0) return hipSuccess;
     TileArgs a = tile_args(A, x, y, s);
     a.part_desc = chunk_desc;
-    a.arrivals = arrivals;
-    a.carry_val = carry_val;
+    a.arrivals = cut.arrivals;
+    a.carry_row = cut.carry_row;
+    a.carry_val = cut.carry_val;
     a.nparts = P;
     a.tile_cap = items_per_chunk;
     // entries + finished rows of a chunk add up to at most items_per_chunk, and what its end was moved back over is the next
     // chunk's; size for whichever of the two needs more LDS per item (an entry: colidx + value; a row: bound + old y)
     const int32_t most = items_per_chunk + merge_snap(items_per_chunk);
-    return A.bf16 ? launch_tiles<BF16, true>(a, merge_lds_bytes<BF16>(most), st, done)
-                  : launch_tiles<F32, true>(a, merge_lds_bytes<F32>(most), st, done);
+    const hipEvent_t tiles_done = cut.carry_row ? nullptr : done;
+    const hipError_t e = A.bf16 ? launch_tiles<BF16, true>(a, merge_lds_bytes<BF16>(most), st, tiles_done)
+                                : launch_tiles<F32, true>(a, merge_lds_bytes<F32>(most), st, tiles_done);
+    return e == hipSuccess && cut.carry_row ? launch_cut_rows(cut, P, y, s.alpha, st, done) : e;
+}
+
+hipError_t launch_cut_rows(const CutScratch& cut, int32_t P, float* y, float alpha, hipStream_t st, hipEvent_t done) {
+    const CutRowsArgs a{cut.carry_row, cut.carry_val, y, P, alpha};
+    return launch_with_event(cut_rows_kernel, dim3(ceil_div(P, kWG)), dim3(kWG), 0, st, done, a);
 }
 
 hipError_t launch_lidx_groups(const uint16_t* lidx, int32_t groups, uint16_t* lidx8, int32_t* flag, hipStream_t st) {

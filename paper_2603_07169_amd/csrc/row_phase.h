@@ -77,7 +77,7 @@ struct RowOut {
     const float* y0;  // LDS: y0[i] = old y of row r0+i when beta != 0 (fetched while the tile was loading)
     float alpha, beta;
     float* cut_sums;  // merge path only, LDS: [0] the finished part of a first row that began in an earlier chunk, [1] the sum of the cut-off piece
-    bool head_cut;    // merge path only: the chunk's first row began in an earlier chunk
+    bool head_cut;    // merge path only: the chunk's first row began in an earlier chunk and its part goes to cut_sums
 };
 
 // Where the parts of rows that are cut by chunk boundaries are put together (finish_cut).
@@ -87,6 +87,7 @@ struct CutOut {
     const int32_t* cut_range;  // [2*(chunks+1)] per cut: first and last chunk of the row it cuts; null: they follow from rowptr and items
     const int32_t* rowptr;
     int items;                 // merge-path steps between cuts
+    int32_t* carry_row;        // [chunks] not null: the pieces are left to cut_rows_kernel, with the row each belongs to (-1: none)
 };
 
 // A row in pieces: the chunks p0 .. p1 - 1 cut it at their ends and chunk p1 finishes it.  Every one of them leaves its part
@@ -94,7 +95,9 @@ struct CutOut {
 // comes last adds the carries to y in chunk order, so the result does not depend on who that is.  The counter wraps to 0 with the
 // last arrival, so nothing has to be cleared between runs.  What one die writes another reads: the accesses are agent-scope
 // atomics, which go past the dies' own L2s, and the part is in place (vmcnt 0) before its arrival is counted.
-// This was a kernel of its own behind the tiles (merge_fixup_kernel): 4.8 us a run for a few dozen rows.
+// A kernel behind the tiles that adds the carries (cut_rows_kernel) takes 4.8 us a run for a few dozen rows, this less than can be
+// measured; but every chunk that takes part stays on for a store, an atomic and a load of its own that other dies must see
+// (use_cut_rows_kernel).
 __device__ __forceinline__ void finish_cut(const RowOut& o, const CutOut& c, int r, int part, bool head, float value) {
     int p0, p1;
     if (c.cut_range) {
@@ -224,6 +227,14 @@ __device__ __forceinline__ void tile_rows(const I* cols, const E* vals, const E*
 // in an earlier chunk, and the piece cut off at its end, if there is one.  One lane each, in different wavefronts.
 __device__ __forceinline__ void finish_cuts(const RowOut& o, const CutOut& c, const int* seg, int nr, int r0, int part, int tid) {
     const bool tail_cut = seg[nr + 1] > seg[nr];
+    if (c.carry_row) {
+        __syncthreads();
+        if (tid == 0) {
+            c.carry_row[part] = tail_cut ? r0 + nr : -1;
+            c.carry_val[part] = o.cut_sums[1];
+        }
+        return;
+    }
     if (!o.head_cut && !tail_cut) return;
     __syncthreads();
     if (tid == 0 && o.head_cut) finish_cut(o, c, r0, part, true, o.cut_sums[0]);

@@ -15,7 +15,7 @@ namespace {
 
 // Layout of the array for P chunks (P <= kStaticMaxChunks):
 //   int32 desc[2 * (kStaticMaxChunks + 1)]   pairs (rows finished, entries taken) at every split
-//   uint32 arrivals[kStaticMaxChunks]
+//   uint32 arrivals[kStaticMaxChunks], or int32 carry_row[kStaticMaxChunks] (CutScratch)
 //   float carry_val[kStaticMaxChunks]
 constexpr int64_t kStaticMaxChunks = SPMV_STATIC_MAX_ITEMS / spmv::kDefaultItemsPerChunk;
 constexpr size_t kScratchBytes = 4 * (2 * (kStaticMaxChunks + 1) + 2 * kStaticMaxChunks);
@@ -108,7 +108,12 @@ extern "C" spmv_status_t spmv_csr_run_static(int64_t m, int64_t n, int64_t nnz, 
     const int P = static_cast<int>((m + nnz + ipc - 1) / ipc);  // >= 1 and <= kStaticMaxChunks
     hipLaunchKernelGGL(static_splits_kernel, dim3((P + 1 + 255) / 256), dim3(256), 0, st, rowptr, A.m, A.nnz, ipc, P, desc, arrivals);
     if (spmv::note_hip_error(hipGetLastError())) return SPMV_ERR_HIP;
-    if (spmv::note_hip_error(spmv::launch_merge(A, desc, P, ipc, arrivals, carry_val, x, y, spmv::Scalars{alpha, beta}, st, nullptr)))
+    // How many chunks cut a row is known on the device only.  A kernel for them costs 3 us (24 M entries in rows of 16: 124 -> 127),
+    // none up to 17 where two chunks in five cut one (rows of 300 among them: 118 -> 135), and 1 to 2 as long as all chunks run at
+    // once if all cut one (1.5 M entries in rows of 300: 15.5 -> 17.4; in rows of 16 without the kernel 14.5, with it 17.2).
+    const bool cut_rows = P >= 1024 || nnz > m * spmv::merge_snap(ipc);
+    const spmv::CutScratch cut{cut_rows ? nullptr : arrivals, cut_rows ? reinterpret_cast<int32_t*>(arrivals) : nullptr, carry_val};
+    if (spmv::note_hip_error(spmv::launch_merge(A, desc, P, ipc, cut, x, y, spmv::Scalars{alpha, beta}, st, nullptr)))
         return SPMV_ERR_HIP;
     return SPMV_OK;
 }

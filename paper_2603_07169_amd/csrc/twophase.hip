@@ -210,8 +210,7 @@ struct TpReduceArgs {
     const int32_t* rowptr;
     float* y;
     const int32_t* cut_range;  // [2*(P+1)] (see finish_cut)
-    unsigned* arrivals;
-    float* carry_val;
+    CutScratch cut;
     int32_t nparts;
     int32_t row_shift;  // 0, or 3 when a slot stands for a group of eight entries: rowptr is then counted in groups
     float alpha, beta;
@@ -269,12 +268,12 @@ __global__ __launch_bounds__(WG) void tp_reduce_kernel(const TpReduceArgs a) {
             }
     }
     __syncthreads();
-    const bool head_cut = nr > 0 && (a.rowptr[r0] >> a.row_shift) < k0;
+    const bool head_cut = !a.cut.carry_row && nr > 0 && (a.rowptr[r0] >> a.row_shift) < k0;
     __shared__ float cut_sums[2];
     const RowOut o{a.y, y0_l, a.alpha, a.beta, cut_sums, head_cut};
     tile_rows<true, WG>(static_cast<const NoGather*>(nullptr), vals_l, static_cast<const float*>(nullptr), seg, nr, r0,
                         ent, o, deferred, &n_deferred, tid);
-    finish_cuts(o, CutOut{a.carry_val, a.arrivals, a.cut_range, nullptr, 0}, seg, nr, r0, part, tid);
+    finish_cuts(o, CutOut{a.cut.carry_val, a.cut.arrivals, a.cut_range, nullptr, 0, a.cut.carry_row}, seg, nr, r0, part, tid);
 }
 
 // ---------------------------------------------------------------------------- analysis time
@@ -671,12 +670,13 @@ hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* 
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const TpReduceArgs a{t.chunk_desc, t.chunk_g, t.tp_from, t.tp_pos, t.prod, A.rowptr, y, t.cut_range, t.arrivals, t.carry_val, t.num_chunks,
+    const TpReduceArgs a{t.chunk_desc, t.chunk_g, t.tp_from, t.tp_pos, t.prod, A.rowptr, y, t.cut_range, t.cut, t.num_chunks,
                          t.group == 8 ? 3 : 0, s.alpha, s.beta};
     auto k = tp_reduce_kernel<kTpRedWG, kTpRedGroups>;
     static thread_local size_t allowed = 0;
     if ((e = allow_lds(k, t.reduce_lds, &allowed)) != hipSuccess) return e;
-    return launch_with_event(k, dim3(t.num_chunks), dim3(kTpRedWG), t.reduce_lds, st, done, a);
+    e = launch_with_event(k, dim3(t.num_chunks), dim3(kTpRedWG), t.reduce_lds, st, t.cut.carry_row ? nullptr : done, a);
+    return e == hipSuccess && t.cut.carry_row ? launch_cut_rows(t.cut, t.num_chunks, y, s.alpha, st, done) : e;
 }
 
 hipError_t launch_two_phase_groups(const int32_t* colidx, int32_t ngroups, int32_t* gcol, int32_t* flag, hipStream_t st) {

@@ -46,6 +46,42 @@ def test_cut_rows_bit_for_bit_run_after_run(name, dtype):
         assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref), name
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("plan,length,rows", [(s.SPMV_PLAN_MERGE, 300, 9000), (s.SPMV_PLAN_TWOPHASE, 700, 8300)])
+def test_most_chunks_cut_a_row(plan, length, rows, dtype):
+    """12 * (cuts - 600) > chunks: the pieces are left to a kernel behind the chunks, in the handle and (2048 steps a chunk, 1024
+    chunks or more) without one.  Repeated, on a stream, and replayed from a graph."""
+    lens = np.full(rows, length)
+    lens[100:300], lens[rows // 2] = 1, 9 * length
+    p = w.exact_integer(lens, 70000, seed=31, dtype=dtype, alpha=2.0, beta=-1.0)
+    row, nz = oracle.merge_path(p.rowptr, 2048) if plan == s.SPMV_PLAN_MERGE else oracle.merge_path_snapped(p.rowptr, 8192, 512)
+    inside = (row < p.m) & (nz > p.rowptr[np.minimum(row, p.m - 1)])
+    cuts = int((inside & (lens[np.minimum(row, p.m - 1)] > (256 if plan == s.SPMV_PLAN_MERGE else 512))).sum())
+    assert 12 * (cuts - 600) > row.size - 1
+    y_ref, _ = oracle.spmv_problem(p)
+    d = DeviceProblem(p)
+    A = d.matrix(dict(plan=plan))
+    for _ in range(3):
+        assert np.array_equal(d.run(A).astype(np.float64), y_ref)
+    y = d.y0.clone()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        A.run(d.x, y, p.alpha, p.beta, torch.cuda.current_stream().cuda_stream)
+    for _ in range(3):
+        y.copy_(d.y0)
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref)
+        assert np.array_equal(d.run(A).astype(np.float64), y_ref)
+    A.close()
+    y = d.y0.clone()
+    s.check(s.spmv_csr_run_static(p.m, p.n, p.nnz, d.rowptr.data_ptr(), d.colidx.data_ptr(), d.vals.data_ptr(), DTYPE_CODE[dtype],
+                                  d.x.data_ptr(), y.data_ptr(), p.alpha, p.beta))
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy().astype(np.float64), y_ref)
+
+
 def test_cut_rows_replayed_from_a_graph():
     p = w.exact_integer([4] * 3000 + [20000, 600, 9000], 30000, seed=12)
     y_ref, _ = oracle.spmv_problem(p)
