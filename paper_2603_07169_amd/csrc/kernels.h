@@ -76,7 +76,7 @@ struct CutScratch {
     int32_t* carry_row;
     float* carry_val;
 };
-// Whether the pieces of `cuts` chunks that begin inside a row are left to a kernel of its own.  That kernel costs 2 to 5 us whatever
+// Whether the pieces of `cuts` chunks that begin inside a row are left to a kernel of their own.  That kernel costs 1 to 3 us whatever
 // it finds, finish_cut some 12 us in every chunk that takes part, during which its place stays taken: nothing while all
 // chunks run at once, more the more rounds there are.  Both, us (FP32, rows of 300 or 16 entries, left without and right with the
 // kernel): 1.5 M entries, 290 cuts 14.1 / 14.8, 730 cuts 15.5 / 14.4; 6 M entries, 590 cuts 36.0 / 37.4, 1170 cuts 39.6 / 37.6, 2930

@@ -1147,7 +1147,22 @@ __global__ __launch_bounds__(kWG) void cut_rows_kernel(const CutRowsArgs a) {
     const int r = a.carry_row[p];
     if (r < 0 || (p > 0 && a.carry_row[p - 1] == r)) return;
     float s = 0.f;
-    for (int q = p; q < a.P && a.carry_row[q] == r; ++q) s += a.carry_val[q];
+    bool more = true;  // eight at a time: a row over a hundred chunks is a hundred round trips to memory otherwise
+    for (int q = p; more; q += 8) {
+        int row[8];
+        float val[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int at = q + u < a.P ? q + u : a.P - 1;
+            row[u] = a.carry_row[at];
+            val[u] = a.carry_val[at];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            more = more && q + u < a.P && row[u] == r;
+            if (more) s += val[u];
+        }
+    }
     a.y[r] += a.alpha * s;
 }
 

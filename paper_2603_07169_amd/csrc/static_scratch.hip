@@ -108,9 +108,10 @@ extern "C" spmv_status_t spmv_csr_run_static(int64_t m, int64_t n, int64_t nnz, 
     const int P = static_cast<int>((m + nnz + ipc - 1) / ipc);  // >= 1 and <= kStaticMaxChunks
     hipLaunchKernelGGL(static_splits_kernel, dim3((P + 1 + 255) / 256), dim3(256), 0, st, rowptr, A.m, A.nnz, ipc, P, desc, arrivals);
     if (spmv::note_hip_error(hipGetLastError())) return SPMV_ERR_HIP;
-    // How many chunks cut a row is known on the device only.  A kernel for them costs 3 us (24 M entries in rows of 16: 124 -> 127),
-    // none up to 17 where two chunks in five cut one (rows of 300 among them: 118 -> 135), and 1 to 2 as long as all chunks run at
-    // once if all cut one (1.5 M entries in rows of 300: 15.5 -> 17.4; in rows of 16 without the kernel 14.5, with it 17.2).
+    // How many chunks cut a row is known on the device only.  A kernel for them costs 1 to 4 us (24 M entries in rows of 16: 124 ->
+    // 126; 12 M in power-law rows 106 -> 110), none up to 77 (24 M entries in rows of 300 196 -> 119, two fifths of them in such
+    // rows 135 -> 120), but little as long as all chunks run at once (1.5 M entries in rows of 16: 17.2 with the kernel, 14.5
+    // without); there the mean length decides, since with all entries in rows of 300 it is 16.1 and 19.1.
     const bool cut_rows = P >= 1024 || nnz > m * spmv::merge_snap(ipc);
     const spmv::CutScratch cut{cut_rows ? nullptr : arrivals, cut_rows ? reinterpret_cast<int32_t*>(arrivals) : nullptr, carry_val};
     if (spmv::note_hip_error(spmv::launch_merge(A, desc, P, ipc, cut, x, y, spmv::Scalars{alpha, beta}, st, nullptr)))
