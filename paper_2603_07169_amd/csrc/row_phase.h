@@ -95,9 +95,9 @@ struct CutOut {
 // comes last adds the carries to y in chunk order, so the result does not depend on who that is.  The counter wraps to 0 with the
 // last arrival, so nothing has to be cleared between runs.  What one die writes another reads: the accesses are agent-scope
 // atomics, which go past the dies' own L2s, and the part is in place (vmcnt 0) before its arrival is counted.
-// A kernel behind the tiles that adds the carries (cut_rows_kernel) takes 4.8 us a run for a few dozen rows, this less than can be
-// measured; but every chunk that takes part stays on for a store, an atomic and a load of its own that other dies must see
-// (use_cut_rows_kernel).
+// A kernel behind the tiles that adds the carries (cut_rows_kernel) takes 1 to 3 us a run, this less than can be measured for a few
+// dozen rows; but every chunk that takes part stays on for a store, an atomic and a load that other dies must see, so where many
+// do the kernel is the cheaper way (use_cut_rows_kernel).
 __device__ __forceinline__ void finish_cut(const RowOut& o, const CutOut& c, int r, int part, bool head, float value) {
     int p0, p1;
     if (c.cut_range) {

@@ -12,7 +12,8 @@
 //             their cache lines), drops each into LDS at its CSR position within the chunk
 //             (16-bit), and then runs the row phase of the tile kernels over them: teams of lanes
 //             add up one row each, the piece of a row that the chunk cuts off leaves as a carry
-//             (chunks cut only rows of more than SPMV_TP_SNAP entries; finish_cut adds the carries).
+//             (chunks cut only rows of more than SPMV_TP_SNAP entries; finish_cut or, where many
+//             chunks do, cut_rows_kernel adds the carries).
 //
 // A tile is the set of entries that share a column block and a chunk.  Its entries keep their CSR
 // order, and every tile is padded to a multiple of four entries (value 0, column = the zero slot
