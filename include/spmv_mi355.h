@@ -331,7 +331,7 @@ spmv_status_t spmv_csr_create(spmv_handle_t* out, int64_t m, int64_t n, int64_t 
  *     holds the values as they were at analyze time, as binary32 (bf16 values widened): 6 or 8 bytes per slot.
  *     The pairs form, next to the packed copy (spmm_pair_blocks > 0): kept while n <= 2048, it has at most 2^22 blocks and at
  *     most 1.25 times as many slots (128 per block) as the packed copy's groups of 16 rows take in steps of four entries, and
- *     its memory can be had (16 bytes per two slots, and 4 per slot for spmm_pair_src).  Group g = the rows at positions 32g ..
+ *     its memory can be had (16 bytes per two slots, 4 per slot for spmm_pair_src and 4 per slot of the packed copy).  Group g = the rows at positions 32g ..
  *     32g+31 of spmm_pair_rows (positions from m on: empty rows), L_g its longest row: max(1, ceil(L_g / 4)) blocks,
  *     max(1, ceil(L_g / 2)) steps.  Position t of the group's i-th row is lane q = (first_g + t / 4) * 64 + 2 i + t mod 2,
  *     element e = (t mod 4) / 2: spmm_pair_ent[4 q + e] is the byte offset of the entry's row of B in the kernel's LDS,

@@ -596,7 +596,7 @@ int spmm_pair_splits(int64_t slices, int64_t groups, int64_t blocks) {
 // two entries in the pairs form, four in the packed copy), of all steps (the LDS and vector units have a rate), and of C.
 // The constants are fitted to measured products of both kernels (13 distributions of row lengths, 64 to 65536 rows, 1 to
 // 4096 columns, FP32).  Over 1452 of them the pick takes as long as the better of the two (7 % more at the 95th percentile);
-// always the pairs form 14 % more on average and up to 2.8 times, never 25 % (profiles/spmm_forms.md).
+// always the pairs form 14 % more on average and up to 2.8 times, never 25 %.
 // go to the packed copy, whose chains are half as long; rows of C that are not 16-byte aligned mostly to the pairs form, which
 // stores them 16 bytes at a time all the same.
 bool spmm_pairs_choice(const GroupSteps& packed, const GroupSteps& pairs, int64_t pair_blocks, int64_t m, int64_t K, bool vec_ok) {

@@ -93,6 +93,7 @@ struct spmv_csr_s {
     int32_t* d_spmm_desc = nullptr;  // packed copy of A in that order (spmm_prepared == 2)
     void* d_spmm_col = nullptr;
     float* d_spmm_val = nullptr;
+    int32_t* d_spmm_src = nullptr;   // with the pairs form: where every slot's value comes from
     spmv::PairRows pairs{};          // the pairs form next to it (pairs.ent: null without it)
     spmv::GroupSteps packed_steps, pair_steps;  // what the choice between the two goes by
 };
@@ -100,10 +101,11 @@ struct spmv_csr_s {
 namespace {
 
 void free_pairs(spmv_csr_s* h) {
-    void* ptrs[] = {const_cast<int32_t*>(h->pairs.rows), const_cast<int32_t*>(h->pairs.desc), h->pairs.ent, h->pairs.src};
+    void* ptrs[] = {const_cast<int32_t*>(h->pairs.rows), const_cast<int32_t*>(h->pairs.desc), h->pairs.ent, h->pairs.src, h->d_spmm_src};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     h->pairs = spmv::PairRows{};
+    h->d_spmm_src = nullptr;
 }
 
 void free_metadata(spmv_csr_s* h) {
@@ -677,8 +679,10 @@ spmv::TwoPhase two_phase_of(const spmv_csr_s* h) {
     return t;
 }
 
-// The pairs form next to the packed copy described by packed_desc, where it is to be kept (else pairs.ent stays null).
-spmv_status_t build_pairs(spmv_csr_s* h, const HostRowptr& rowptr_host, const std::vector<int32_t>& packed_desc, spmv::Analysis* a) try {
+// The pairs form next to the packed copy of packed_slots slots described by packed_desc, where it is to be kept (else pairs.ent and
+// d_spmm_src stay null).
+spmv_status_t build_pairs(spmv_csr_s* h, const HostRowptr& rowptr_host, const std::vector<int32_t>& packed_desc, size_t packed_slots,
+                          spmv::Analysis* a) try {
     std::vector<int32_t> rows, desc;
     int64_t blocks = 0;
     if (h->n > spmv::kSpmmPairMaxN || !spmv::spmm_pair_layout(h->m, rowptr_host.data(), packed_desc, &rows, &desc, &blocks)) return SPMV_OK;
@@ -694,7 +698,8 @@ spmv_status_t build_pairs(spmv_csr_s* h, const HostRowptr& rowptr_host, const st
     h->pairs.longest_steps = static_cast<int32_t>(h->pair_steps.longest);
     h->pairs.num_blocks = blocks;
     const size_t nb = static_cast<size_t>(blocks);  // and one closing block that is only ever read ahead: offset 0, value 0
-    if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->pairs.src), 512 * nb)) ||
+    if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_spmm_src), sizeof(int32_t) * packed_slots)) ||
+        hip_failed(hipMalloc(reinterpret_cast<void**>(&h->pairs.src), 512 * nb)) ||
         hip_failed(hipMalloc(reinterpret_cast<void**>(&h->pairs.ent), 1024 * (nb + 1))))
         return SPMV_ERR_ALLOC;
     if (hip_failed(hipMemset(h->pairs.ent + 256 * nb, 0, 1024)) ||
@@ -726,18 +731,19 @@ spmv_status_t build_spmm_order(spmv_csr_s* h, const HostRowptr& rowptr_host, spm
     if (hip_failed(hipMalloc(&h->d_spmm_col, col_bytes * slots)) ||
         hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_spmm_val), sizeof(float) * slots)))
         return SPMV_ERR_ALLOC;
-    if (hip_failed(hipMemset(static_cast<char*>(h->d_spmm_col) + col_bytes * (slots - 256), 0, col_bytes * 256)) ||
-        hip_failed(hipMemset(h->d_spmm_val + (slots - 256), 0, sizeof(float) * 256)) ||
-        hip_failed(spmv::launch_spmm_pack(view_of(h), h->d_spmm_rows, h->d_spmm_desc, static_cast<int32_t>((h->m + 15) / 16),
-                                          col16, h->d_spmm_col, h->d_spmm_val, nullptr)))
-        return SPMV_ERR_HIP;
-    st = build_pairs(h, rowptr_host, desc, a);
+    st = build_pairs(h, rowptr_host, desc, slots - 256, a);
     if (st == SPMV_ERR_ALLOC) {  // no room for a second form: the products run from the packed copy
         free_pairs(h);
         (void)hipGetLastError();
         st = SPMV_OK;
     }
-    return st;
+    if (st != SPMV_OK) return st;
+    if (hip_failed(hipMemset(static_cast<char*>(h->d_spmm_col) + col_bytes * (slots - 256), 0, col_bytes * 256)) ||
+        hip_failed(hipMemset(h->d_spmm_val + (slots - 256), 0, sizeof(float) * 256)) ||
+        hip_failed(spmv::launch_spmm_pack(view_of(h), h->d_spmm_rows, h->d_spmm_desc, static_cast<int32_t>((h->m + 15) / 16),
+                                          col16, h->d_spmm_col, h->d_spmm_val, h->d_spmm_src, nullptr)))
+        return SPMV_ERR_HIP;
+    return SPMV_OK;
 } catch (const std::bad_alloc&) {
     return SPMV_ERR_ALLOC;
 }
@@ -1077,10 +1083,13 @@ spmv_status_t spmv_csr_refresh_values(spmv_handle_t h, void* stream) {
     if (h->info.plan == SPMV_PLAN_TWOPHASE)
         e = spmv::launch_two_phase_values(A, h->d_tp_src, h->d_tp_val, h->info.tp_slots, h->info.tp_group > 1 ? h->info.tp_group : 1, st);
     if (h->info.plan == SPMV_PLAN_SELL) e = spmv::launch_sell_values(A, h->d_sell_src, h->d_sell_val, h->info.sell_slots, st);
-    if (e == hipSuccess && h->pairs.ent) e = spmv::launch_spmm_pair_values(A, h->pairs, st);
-    if (e == hipSuccess && h->info.spmm_prepared == 2)
+    if (e == hipSuccess && h->pairs.ent) {
+        e = spmv::launch_spmm_pair_values(A, h->pairs, st);
+        if (e == hipSuccess) e = spmv::launch_spmm_packed_values(A, h->d_spmm_src, h->d_spmm_val, h->info.spmm_num_blocks * 256, st);
+    } else if (e == hipSuccess && h->info.spmm_prepared == 2) {
         e = spmv::launch_spmm_pack(A, h->d_spmm_rows, h->d_spmm_desc, static_cast<int32_t>((h->m + 15) / 16),
-                                   h->info.spmm_col_bytes == 2, h->d_spmm_col, h->d_spmm_val, st);
+                                   h->info.spmm_col_bytes == 2, h->d_spmm_col, h->d_spmm_val, nullptr, st);
+    }
     return hip_failed(e) ? SPMV_ERR_HIP : SPMV_OK;
 }
 

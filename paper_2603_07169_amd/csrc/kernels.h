@@ -103,9 +103,11 @@ struct PackedRows {
     int32_t num_groups;
     bool col16;
 };
-// Fills pcol / pval of all blocks of all groups from the CSR arrays (the extra closing block is not written).
+// Fills pcol / pval of all blocks of all groups from the CSR arrays (the extra closing block is not written), and psrc, if not
+// null, with every slot's place in colidx / vals, -1 in padding.
 hipError_t launch_spmm_pack(const MatrixView& A, const int32_t* rows, const int32_t* desc, int32_t num_groups, bool col16,
-                            void* pcol, float* pval, hipStream_t st);
+                            void* pcol, float* pval, int32_t* psrc, hipStream_t st);
+hipError_t launch_spmm_packed_values(const MatrixView& A, const int32_t* psrc, float* pval, int64_t slots, hipStream_t st);  // pval from the CSR values
 hipError_t launch_spmm_packed(const MatrixView& A, const PackedRows& P, const void* B, int64_t ldb, float* C, int64_t ldc,
                               int32_t K, Scalars s, hipStream_t st);
 const char* spmm_packed_kernel_name();

@@ -337,7 +337,7 @@ template <typename CT, typename E>
 __global__ __launch_bounds__(64) void spmm_pack_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
                                                        const E* __restrict__ vals, const int32_t* __restrict__ rows,
                                                        const int32_t* __restrict__ desc, int m, int n, CT* __restrict__ pcol,
-                                                       float* __restrict__ pval) {
+                                                       float* __restrict__ pval, int32_t* __restrict__ psrc) {
     const int g = blockIdx.x, lane = threadIdx.x, rsub = lane >> 2, q = lane & 3;
     const int first = desc[2 * g], nblocks = desc[2 * g + 2] - first;
     const int pos = 16 * g + rsub;
@@ -355,6 +355,7 @@ __global__ __launch_bounds__(64) void spmm_pack_kernel(const int32_t* __restrict
             if (16 * b + 4 * q + e >= len) {
                 pcol[slot0 + e] = pad;
                 pval[slot0 + e] = 0.f;
+                if (psrc) psrc[slot0 + e] = -1;
             }
         }
     }
@@ -378,6 +379,7 @@ __global__ __launch_bounds__(64) void spmm_pack_kernel(const int32_t* __restrict
             const size_t slot = ((static_cast<size_t>(first + (t >> 4)) * 64 + 4 * rsub + ((t >> 2) & 3)) * 4) + (t & 3);
             pcol[slot] = static_cast<CT>(c);
             pval[slot] = widen(vals[rs + k]);
+            if (psrc) psrc[slot] = rs + k;
         }
     }
 }
@@ -951,13 +953,14 @@ __global__ __launch_bounds__(64) void spmm_pair_pack_kernel(const int32_t* __res
     }
 }
 
-// The values of the pairs form: ent[4 q + 2 + i] = vals[src[2 q + i]], 0 in padding.
-template <typename E>
-__global__ __launch_bounds__(kWG) void spmm_pair_values_kernel(const E* __restrict__ vals, const int32_t* __restrict__ src,
-                                                               uint32_t* __restrict__ ent, int64_t slots) {
+// The values of the packed copy (PAIRS = false): out[s] = vals[src[s]]; of the pairs form: out[4 q + 2 + i] = vals[src[2 q + i]]; 0 in
+// padding.  65536 rows of 20 entries: 9 us each, packing the copy anew takes 50.
+template <typename E, bool PAIRS>
+__global__ __launch_bounds__(kWG) void spmm_values_kernel(const E* __restrict__ vals, const int32_t* __restrict__ src,
+                                                          uint32_t* __restrict__ out, int64_t slots) {
     for (int64_t s = static_cast<int64_t>(blockIdx.x) * kWG + threadIdx.x; s < slots; s += static_cast<int64_t>(gridDim.x) * kWG) {
         const int k = src[s];
-        ent[4 * (s >> 1) + 2 + (s & 1)] = k >= 0 ? __float_as_uint(widen(vals[k])) : 0u;
+        out[PAIRS ? 4 * (s >> 1) + 2 + (s & 1) : s] = k >= 0 ? __float_as_uint(widen(vals[k])) : 0u;
     }
 }
 
@@ -1020,13 +1023,13 @@ hipError_t launch_spmm_packed_t(const SpmmPackedArgs& a, bool col16, bool single
 
 template <typename CT>
 hipError_t launch_spmm_pack_t(const MatrixView& A, const int32_t* rows, const int32_t* desc, int32_t num_groups, CT* pcol, float* pval,
-                              hipStream_t st) {
+                              int32_t* psrc, hipStream_t st) {
     if (A.bf16)
         hipLaunchKernelGGL((spmm_pack_kernel<CT, uint16_t>), dim3(num_groups), dim3(64), 0, st, A.rowptr, A.colidx,
-                           static_cast<const uint16_t*>(A.vals), rows, desc, A.m, A.n, pcol, pval);
+                           static_cast<const uint16_t*>(A.vals), rows, desc, A.m, A.n, pcol, pval, psrc);
     else
         hipLaunchKernelGGL((spmm_pack_kernel<CT, float>), dim3(num_groups), dim3(64), 0, st, A.rowptr, A.colidx,
-                           static_cast<const float*>(A.vals), rows, desc, A.m, A.n, pcol, pval);
+                           static_cast<const float*>(A.vals), rows, desc, A.m, A.n, pcol, pval, psrc);
     return hipGetLastError();
 }
 
@@ -1065,10 +1068,10 @@ hipError_t launch_spmm(const MatrixView& A, const int32_t* rows, const void* B, 
 }
 
 hipError_t launch_spmm_pack(const MatrixView& A, const int32_t* rows, const int32_t* desc, int32_t num_groups, bool col16,
-                            void* pcol, float* pval, hipStream_t st) {
+                            void* pcol, float* pval, int32_t* psrc, hipStream_t st) {
     if (num_groups <= 0) return hipSuccess;
-    return col16 ? launch_spmm_pack_t(A, rows, desc, num_groups, static_cast<uint16_t*>(pcol), pval, st)
-                 : launch_spmm_pack_t(A, rows, desc, num_groups, static_cast<int32_t*>(pcol), pval, st);
+    return col16 ? launch_spmm_pack_t(A, rows, desc, num_groups, static_cast<uint16_t*>(pcol), pval, psrc, st)
+                 : launch_spmm_pack_t(A, rows, desc, num_groups, static_cast<int32_t*>(pcol), pval, psrc, st);
 }
 
 hipError_t launch_spmm_packed(const MatrixView& A, const PackedRows& P, const void* B, int64_t ldb, float* C, int64_t ldc,
@@ -1138,16 +1141,28 @@ hipError_t launch_spmm_pair_pack(const MatrixView& A, const PairRows& P, hipStre
     return e == hipSuccess ? launch_spmm_pair_values(A, P, st) : e;
 }
 
-hipError_t launch_spmm_pair_values(const MatrixView& A, const PairRows& P, hipStream_t st) {
-    const int64_t slots = P.num_blocks * 128;
+namespace {
+
+template <bool PAIRS>
+hipError_t launch_spmm_values(const MatrixView& A, const int32_t* src, uint32_t* out, int64_t slots, hipStream_t st) {
     if (slots <= 0) return hipSuccess;
     if (A.bf16)
-        hipLaunchKernelGGL(spmm_pair_values_kernel<uint16_t>, dim3(capped_grid(slots)), dim3(kWG), 0, st,
-                           static_cast<const uint16_t*>(A.vals), P.src, P.ent, slots);
+        hipLaunchKernelGGL((spmm_values_kernel<uint16_t, PAIRS>), dim3(capped_grid(slots)), dim3(kWG), 0, st,
+                           static_cast<const uint16_t*>(A.vals), src, out, slots);
     else
-        hipLaunchKernelGGL(spmm_pair_values_kernel<float>, dim3(capped_grid(slots)), dim3(kWG), 0, st,
-                           static_cast<const float*>(A.vals), P.src, P.ent, slots);
+        hipLaunchKernelGGL((spmm_values_kernel<float, PAIRS>), dim3(capped_grid(slots)), dim3(kWG), 0, st,
+                           static_cast<const float*>(A.vals), src, out, slots);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_spmm_pair_values(const MatrixView& A, const PairRows& P, hipStream_t st) {
+    return launch_spmm_values<true>(A, P.src, P.ent, P.num_blocks * 128, st);
+}
+
+hipError_t launch_spmm_packed_values(const MatrixView& A, const int32_t* psrc, float* pval, int64_t slots, hipStream_t st) {
+    return launch_spmm_values<false>(A, psrc, reinterpret_cast<uint32_t*>(pval), slots, st);
 }
 
 hipError_t launch_spmm_pair(const MatrixView& A, const PairRows& P, const void* B, int64_t ldb, float* C, int64_t ldc, int32_t K,
