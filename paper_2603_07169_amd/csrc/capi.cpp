@@ -62,8 +62,11 @@ struct spmv_csr_s {
     int32_t* d_xv_pad = nullptr;
     uint16_t* d_lidx = nullptr;
     uint16_t* d_lidx8 = nullptr;  // lidx[8g], kept when the window positions are grouped (info.lidx_grouped)
-    int32_t* d_run_desc = nullptr;  // row patterns of the window positions, kept when info.lidx_patterned
+    int32_t* d_run_desc = nullptr;  // row patterns of the window positions (of use when info.lidx_patterned), then analysis scratch
     uint16_t* d_pat_pad = nullptr;
+    unsigned char* d_sheets = nullptr;  // the blocks' sheets, where every block has one
+    int32_t sheet_stride = 0;
+    int32_t cus = 0;  // compute units of the device (with sheets)
     // the two-pass plan (TWOPHASE)
     int32_t* d_tp_desc = nullptr;     // pairs (tp_row[p], tp_nz[p])
     int32_t* d_tp_piece_c = nullptr;
@@ -115,7 +118,7 @@ void free_metadata(spmv_csr_s* h) {
                     h->d_cb_src,    h->d_cb_vals,   h->d_spmm_rows, h->d_spmm_desc, h->d_spmm_col,
                     h->d_spmm_val,  h->d_tp_desc,   h->d_tp_piece_c, h->d_tp_piece_g, h->d_tp_chunk_g,
                     h->d_tp_col,    h->d_tp_val,    h->d_tp_src,    h->d_tp_from,    h->d_tp_pos,
-                    h->d_tp_prod,   h->d_tp_cuts, h->tp_cut.arrivals, h->tp_cut.carry_row, h->tp_cut.carry_val, h->d_lidx8, h->d_run_desc, h->d_pat_pad,
+                    h->d_tp_prod,   h->d_tp_cuts, h->tp_cut.arrivals, h->tp_cut.carry_row, h->tp_cut.carry_val, h->d_lidx8, h->d_run_desc, h->d_pat_pad, h->d_sheets,
                     h->d_sell_ptr,  h->d_sell_col,  h->d_sell_src,  h->d_sell_val};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -138,6 +141,8 @@ void free_metadata(spmv_csr_s* h) {
     h->d_cb_vals = nullptr;
     h->cb_ptr.clear();
     h->d_lidx = h->d_lidx8 = h->d_pat_pad = nullptr;
+    h->d_sheets = nullptr;
+    h->sheet_stride = 0;
     h->d_run_desc = nullptr;
     h->d_sell_ptr = h->d_sell_col = h->d_sell_src = nullptr;
     h->d_sell_val = nullptr;
@@ -365,20 +370,36 @@ spmv_status_t build_x_windows(spmv_csr_s* h, bool forced, bool count_only, const
     if (!a->info.lidx_grouped && nb > 0) {
         struct Counts {
             unsigned long long covered;
-            int32_t max_table, pad;
+            int32_t max_table, max_sheet;
         } counts{0, 0, 0};
-        Counts* d_counts = nullptr;
-        if (hip_failed(hipMalloc(reinterpret_cast<void**>(&d_counts), sizeof(Counts))) ||
-            hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_run_desc), 32 * static_cast<size_t>(nb)))) {
-            (void)hipFree(d_counts);
+        // one allocation, kept with the handle: the packed runs, then scratch (the counts, the sheets' runs, bytes and maps)
+        const size_t NB = static_cast<size_t>(nb);
+        const int32_t map_bytes = spmv::sheet_map_bytes(a->info.rows_max);
+        const size_t counts_at = 32 * NB, runs_at = counts_at + 64, need_at = runs_at + sizeof(spmv::SheetRun) * spmv::kMaxSheetRuns * NB,
+                     map_at = need_at + 4 * NB;
+        if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_run_desc), map_at + NB * static_cast<size_t>(map_bytes))))
             return SPMV_ERR_ALLOC;
-        }
+        char* const scratch = reinterpret_cast<char*>(h->d_run_desc);
+        Counts* const d_counts = reinterpret_cast<Counts*>(scratch + counts_at);
+        const spmv::SheetPlan sheets{h->dtype == SPMV_F32 ? 4 : 2, map_bytes, &d_counts->max_sheet, reinterpret_cast<int32_t*>(scratch + need_at),
+                                     reinterpret_cast<unsigned char*>(scratch + map_at), reinterpret_cast<spmv::SheetRun*>(scratch + runs_at)};
         bool failed = hip_failed(hipMemcpy(d_counts, &counts, sizeof counts, hipMemcpyHostToDevice));
         failed = failed || hip_failed(spmv::launch_pattern_build(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx,
                                                                  a->info.block_nnz, false, h->d_run_desc, &d_counts->max_table,
-                                                                 &d_counts->covered, nullptr, 0, nullptr));
+                                                                 &d_counts->covered, nullptr, 0, &sheets, nullptr));
         failed = failed || hip_failed(hipMemcpy(&counts, d_counts, sizeof counts, hipMemcpyDeviceToHost));
-        (void)hipFree(d_counts);
+        const int64_t stride = (static_cast<int64_t>(counts.max_sheet) + 15) & ~int64_t{15};
+        if (!failed && counts.max_sheet < INT32_MAX && nb * stride <= kMaxCount) {
+            int dev = 0;
+            if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_sheets), NB * static_cast<size_t>(stride)))) {
+                h->d_sheets = nullptr;  // the product then runs from the positions or the packed runs
+            } else {
+                failed = hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev)) ||
+                         hip_failed(spmv::launch_sheet_fill(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx, sheets,
+                                                            static_cast<int32_t>(stride), h->d_sheets, nullptr));
+                h->sheet_stride = static_cast<int32_t>(stride);
+            }
+        }
         if (failed) return SPMV_ERR_HIP;
         const int64_t covered = static_cast<int64_t>(counts.covered);
         const int32_t pt_cap = counts.max_table > 0 ? (counts.max_table + 7) / 8 * 8 : 8;
@@ -386,12 +407,12 @@ spmv_status_t build_x_windows(spmv_csr_s* h, bool forced, bool count_only, const
             if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_pat_pad), 2 * static_cast<size_t>(nb) * static_cast<size_t>(pt_cap))))
                 return SPMV_ERR_ALLOC;
             if (hip_failed(spmv::launch_pattern_build(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx, a->info.block_nnz,
-                                                      true, h->d_run_desc, nullptr, nullptr, h->d_pat_pad, pt_cap, nullptr)))
+                                                      true, h->d_run_desc, nullptr, nullptr, h->d_pat_pad, pt_cap, nullptr, nullptr)))
                 return SPMV_ERR_HIP;
             a->info.lidx_patterned = 1;
             a->info.pat_cap = pt_cap;
             a->info.pat_entries = covered;
-        } else {
+        } else if (!h->d_sheets) {
             (void)hipFree(h->d_run_desc);
             h->d_run_desc = nullptr;
         }
@@ -943,7 +964,7 @@ spmv_status_t spmv_csr_run(spmv_handle_t h, const void* x, float* y, float alpha
             break;
         case SPMV_PLAN_WINDOWED: {
             const spmv::XWindows w{h->d_xv_ptr, h->d_xv_start, h->d_xv_pad, h->d_lidx8, h->d_lidx, h->info.max_x_vectors,
-                                   h->d_run_desc, h->d_pat_pad, h->info.pat_cap};
+                                   h->info.lidx_patterned ? h->d_run_desc : nullptr, h->d_pat_pad, h->info.pat_cap, h->d_sheets, h->sheet_stride, h->cus};
             e = spmv::launch_windowed(A, h->d_block_desc, static_cast<int32_t>(h->info.num_row_blocks),
                                       h->info.block_nnz, h->max_block_entries, h->info.rows_max, w, x, y, s, st);
             break;
@@ -1275,7 +1296,7 @@ const char* spmv_csr_main_kernel_name(spmv_handle_t h) {
         case SPMV_PLAN_BINNED: return spmv::vector_kernel_name();
         case SPMV_PLAN_ADAPTIVE:
         case SPMV_PLAN_MERGE: return spmv::tile_kernel_name();
-        case SPMV_PLAN_WINDOWED: return h->info.lidx_patterned ? spmv::pattern_kernel_name() : spmv::window_kernel_name();
+        case SPMV_PLAN_WINDOWED: return h->info.lidx_patterned || h->d_sheets ? spmv::pattern_kernel_name() : spmv::window_kernel_name();
         case SPMV_PLAN_COLBLOCK: return "spmv_coo_kernel";
         case SPMV_PLAN_TWOPHASE: return h->info.tp_group > 1 ? "tp_multiply_group_kernel" : "tp_multiply_kernel";
         case SPMV_PLAN_SELL: return spmv::sell_kernel_name();

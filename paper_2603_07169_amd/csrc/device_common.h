@@ -85,6 +85,25 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
     return die * q + (die < r ? die : r) + slot;
 }
 
+// Copies straight from memory to LDS, past the registers: lane l of the wavefront fetches 16 (4) bytes and they land 16 l (4 l)
+// bytes behind `lds`, a byte address that is the same in all lanes.  Lanes that are switched off copy nothing.  The compiler
+// does not know these loads: lds_copies_done() waits for all that this wavefront has asked for, and a barrier is
+// needed before another wavefront reads them.  (m0 is the compiler's to set before each of its own uses; none of these kernels has one.)
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));
+}
+__device__ __forceinline__ void copy16_to_lds_nt(uint32_t lds, const void* base, uint32_t lane_offset) {  // base the same in all lanes
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory");
+}
+__device__ __forceinline__ void copy16_to_lds(uint32_t lds, const void* src) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory");
+}
+__device__ __forceinline__ void copy4_to_lds(uint32_t lds, const void* base, uint32_t lane_offset) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory");
+}
+// All memory accesses of this wavefront have ended, and all wavefronts of the workgroup have come here.
+__device__ __forceinline__ void wait_all_and_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Launches a kernel; done, if not null, is recorded at its end by the dispatch itself.  An event recorded behind the kernel is a
 // packet of its own: 2.9 us a run.  In the dispatch, with a device-scope release, it costs nothing on the merge plan (20.4 us
 // on 2.7 M power-law entries with or without any fence) and 1.2 us on the two passes (122.7 -> 123.9 us on 32 M entries).

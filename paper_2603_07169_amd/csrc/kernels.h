@@ -34,7 +34,23 @@ struct XWindows {
     const int32_t* run_desc;  // [8 * nb] packed runs of the row patterns (see launch_pattern_build), or null: no patterns
     const uint16_t* pat_pad;  // [nb * pt_cap] the blocks' pattern lists
     int32_t pt_cap;           // a multiple of 8, at most kMaxPatternRuns * kMaxPatternLen
+    const unsigned char* sheets;  // [nb * sheet_stride] (see SheetRun), or null: some block has none
+    int32_t sheet_stride;
+    int32_t cus;              // compute units of the device (with sheets)
 };
+
+// What the stream kernel needs to know of a row block besides its values and its x vectors, in one piece (a "sheet"): a byte per
+// row with the number of its run (sheet_map_bytes of them), the runs, and their lists: 16-bit byte offsets from the x value of a row's
+// first entry, every list from a multiple of four bytes on, runs with equal lists sharing one.  Runs as in run_desc, up to
+// kMaxSheetRuns of them.  For row i of the block:
+constexpr int kMaxSheetRuns = 16;  // a line of a grid is three runs: all blocks of 128 rows in grids of lines of 32 points and more
+struct SheetRun {
+    int32_t value;        // value + i * len: its first entry's place among the block's values, counted from a 16-byte boundary of vals
+    int32_t pos;          // pos + i * (stride_list >> 16): byte position of its first entry's x value in the window
+    int32_t len;          // its entries
+    int32_t stride_list;  // the step in bytes (high half, signed), and where its list starts in the sheet (low half)
+};
+inline int32_t sheet_map_bytes(int32_t rows_max) { return (rows_max + 15) & ~15; }
 
 struct Scalars {
     float alpha, beta;
@@ -142,7 +158,18 @@ hipError_t launch_lidx_groups(const uint16_t* lidx, int32_t groups, uint16_t* li
 // of the patterned blocks.  fill == true: pat_pad[b * pt_cap ..] = block b's list (rel of the first row of every run), then zeros.
 hipError_t launch_pattern_build(const int32_t* block_desc, int32_t nb, const int32_t* rowptr, const uint16_t* lidx, int32_t block_nnz,
                                 bool fill, int32_t* run_desc, int32_t* max_table, unsigned long long* covered, uint16_t* pat_pad,
-                                int32_t pt_cap, hipStream_t st);
+                                int32_t pt_cap, const struct SheetPlan* sheets, hipStream_t st);
+// With fill == false the blocks' sheets are planned as well: what launch_sheet_fill reads, and *largest (device int32, 0 on entry) =
+// bytes of the largest, INT32_MAX if a block cannot have one.
+struct SheetPlan {
+    int32_t elem_bytes, map_bytes;
+    int32_t* largest;
+    int32_t* need;        // [nb]
+    unsigned char* map;   // [nb * map_bytes]
+    SheetRun* runs;       // [nb * kMaxSheetRuns]
+};
+hipError_t launch_sheet_fill(const int32_t* block_desc, int32_t nb, const int32_t* rowptr, const uint16_t* lidx, const SheetPlan& p,
+                             int32_t stride, unsigned char* sheets, hipStream_t st);
 // flag: device int32, must be 0 on entry; set to 1 if any colidx is outside [0, n).
 hipError_t launch_validate_columns(const MatrixView& A, int32_t* flag, hipStream_t st);
 

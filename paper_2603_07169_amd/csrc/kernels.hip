@@ -182,6 +182,9 @@ struct TileArgs {
     float alpha, beta;
     int32_t vec_ok;            // colidx and vals are 16-byte aligned
     int32_t x_vec_ok;          // x is 16-byte aligned
+    const unsigned char* sheets;  // stream kernel: [nparts * sheet_stride] (StreamSheets)
+    int32_t sheet_stride, map_bytes;
+    int32_t val_bytes, buf_bytes;  // stream kernel: LDS bytes of a block's values, of everything that is held of a block
     const int32_t* colidx;
     unsigned* arrivals;        // merge path only, [nparts] (see finish_cut)
     int32_t* carry_row;        // merge path only: null, or [nparts] (see CutOut)
@@ -534,7 +537,8 @@ __global__ __launch_bounds__(WG, (XPL == 4 && NG == 2) ? 4 : 8) void spmv_window
     window_block<T, WG, XPL, NG, GROUPED>(a, part, xs);
 }
 
-// The window kernel for matrices whose window positions follow row patterns (stencils).  The analysis has cut the
+// The window kernel for matrices whose window positions follow row patterns (stencils), where some block has no sheet or the
+// arrays do not allow 16-byte copies (spmv_pattern_kernel takes the others).  The analysis has cut the
 // rows of a block into at most four runs; inside a run every row has the same number of entries, and the window
 // position of its j-th entry is  base + (row's place in the run) * stride + pat[j]  (run_desc: eight words per block,
 // one scalar load; pat_pad: the blocks' pattern lists, a few dozen 16-bit numbers each, at a fixed stride).  Such a block
@@ -584,6 +588,32 @@ struct RunTable {
     int tab[4];     // where the run's pattern starts in the block's list
 };
 
+// The runs of a block, unpacked with scalar arithmetic (rd: its eight words).  first: staged slot of the block's first entry.
+__device__ __forceinline__ RunTable unpack_runs(const int32_t* rd, int first) {
+    RunTable rt;
+    rt.n = rd[7];
+    const int rows[4] = {rd[0] & 0xFFFF, static_cast<int>(static_cast<unsigned>(rd[0]) >> 16), rd[1] & 0xFFFF,
+                         static_cast<int>(static_cast<unsigned>(rd[1]) >> 16)};
+    const int base[4] = {rd[3] & 0xFFFF, static_cast<int>(static_cast<unsigned>(rd[3]) >> 16), rd[4] & 0xFFFF,
+                         static_cast<int>(static_cast<unsigned>(rd[4]) >> 16)};
+    const int stride[4] = {static_cast<int16_t>(rd[5] & 0xFFFF), rd[5] >> 16, static_cast<int16_t>(rd[6] & 0xFFFF), rd[6] >> 16};
+    int row_first = 0, entry_first = first, tab = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int len = (rd[2] >> (8 * r)) & 0xFF;
+        rt.len[r] = len;
+        rt.slot[r] = entry_first - row_first * len;
+        rt.pos[r] = base[r] - row_first * stride[r];
+        rt.stride[r] = stride[r];
+        rt.tab[r] = tab;
+        row_first += rows[r];
+        entry_first += rows[r] * len;
+        tab += len;
+        if (r < 3) rt.cut[r] = r + 1 < rt.n ? row_first : 0x7FFFFFFF;
+    }
+    return rt;
+}
+
 template <int WG, int G, typename E>
 __device__ __forceinline__ void pattern_rows_g(const E* vals_l, const E* xbuf, const uint16_t* pat_l, const float* y0_l,
                                                const RunTable& rt, int nr, int r0, float* y, float alpha, float beta, int tid) {
@@ -608,6 +638,24 @@ __device__ __forceinline__ void pattern_rows_g(const E* vals_l, const E* xbuf, c
         float acc = pattern_dot<G>(vals_l, xbuf, pat_l + tab, slot + row * len, pos + row * stride, len, tl);
         acc = group_sum<G>(acc);  // every lane takes part
         if (live && tl == 0) y[r0 + row] = epilogue(acc, alpha, beta, y0_l, row);
+    }
+}
+
+// The rows of a patterned block whose values, x vectors and pattern list are in LDS.
+template <int WG, typename E>
+__device__ __forceinline__ void pattern_rows(const E* vals_l, const E* xbuf, const uint16_t* pat_l, const float* y0_l, const RunTable& rt,
+                                             int nr, int r0, int tile_nnz, float* y, float alpha, float beta, int tid) {
+    // Lanes per row: as many as fill the workgroup in one sweep over the block's rows (what is in LDS is then taken by
+    // the most lanes at once: measured 35 us on the 27-point stencil with two lanes for each of its 128 rows, 58 us
+    // with one, 38 us with four), but at least four entries for every lane.
+    int G = 1;
+    while (G < 16 && 2 * G * nr <= WG && 8 * G * nr <= tile_nnz) G <<= 1;
+    switch (G) {
+        case 1: pattern_rows_g<WG, 1>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, y, alpha, beta, tid); break;
+        case 2: pattern_rows_g<WG, 2>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, y, alpha, beta, tid); break;
+        case 4: pattern_rows_g<WG, 4>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, y, alpha, beta, tid); break;
+        case 8: pattern_rows_g<WG, 8>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, y, alpha, beta, tid); break;
+        default: pattern_rows_g<WG, 16>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, y, alpha, beta, tid); break;
     }
 }
 
@@ -684,28 +732,7 @@ __device__ __forceinline__ void pattern_block(const TileArgs& a, int part, int (
     }
     __builtin_amdgcn_sched_barrier(0);
 
-    // the runs, unpacked with scalar arithmetic while the loads are in flight
-    RunTable rt;
-    rt.n = rd[7];
-    const int rows[4] = {rd[0] & 0xFFFF, static_cast<int>(static_cast<unsigned>(rd[0]) >> 16), rd[1] & 0xFFFF,
-                         static_cast<int>(static_cast<unsigned>(rd[1]) >> 16)};
-    const int base[4] = {rd[3] & 0xFFFF, static_cast<int>(static_cast<unsigned>(rd[3]) >> 16), rd[4] & 0xFFFF,
-                         static_cast<int>(static_cast<unsigned>(rd[4]) >> 16)};
-    const int stride[4] = {static_cast<int16_t>(rd[5] & 0xFFFF), rd[5] >> 16, static_cast<int16_t>(rd[6] & 0xFFFF), rd[6] >> 16};
-    int row_first = 0, entry_first = k0 - k0a, tab = 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int len = (rd[2] >> (8 * r)) & 0xFF;
-        rt.len[r] = len;
-        rt.slot[r] = entry_first - row_first * len;
-        rt.pos[r] = base[r] - row_first * stride[r];
-        rt.stride[r] = stride[r];
-        rt.tab[r] = tab;
-        row_first += rows[r];
-        entry_first += rows[r] * len;
-        tab += len;
-        if (r < 3) rt.cut[r] = r + 1 < rt.n ? row_first : 0x7FFFFFFF;
-    }
+    const RunTable rt = unpack_runs(rd, k0 - k0a);  // while the loads are in flight
 
     if (tid < pt_vecs) *reinterpret_cast<u32x4*>(pat_l + 8 * tid) = ptab;
     if (tid < nr) y0_l[tid] = y0v;
@@ -730,23 +757,11 @@ __device__ __forceinline__ void pattern_block(const TileArgs& a, int part, int (
     }
     __syncthreads();
 
-    // Lanes per row: as many as fill the workgroup in one sweep over the block's rows (what is in LDS is then taken by
-    // the most lanes at once: measured 35 us on the 27-point stencil with two lanes for each of its 128 rows, 58 us
-    // with one, 38 us with four), but at least four entries for every lane.
-    const int tile_nnz = k1 - k0;
-    int G = 1;
-    while (G < 16 && 2 * G * nr <= WG && 8 * G * nr <= tile_nnz) G <<= 1;
-    switch (G) {
-        case 1: pattern_rows_g<WG, 1>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, a.y, a.alpha, a.beta, tid); break;
-        case 2: pattern_rows_g<WG, 2>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, a.y, a.alpha, a.beta, tid); break;
-        case 4: pattern_rows_g<WG, 4>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, a.y, a.alpha, a.beta, tid); break;
-        case 8: pattern_rows_g<WG, 8>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, a.y, a.alpha, a.beta, tid); break;
-        default: pattern_rows_g<WG, 16>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, a.y, a.alpha, a.beta, tid); break;
-    }
+    pattern_rows<WG>(vals_l, xbuf, pat_l, y0_l, rt, nr, r0, k1 - k0, a.y, a.alpha, a.beta, tid);
 }
 
 template <typename T, int WG, int XPL, int NG>
-__global__ __launch_bounds__(WG, (XPL == 4 && NG == 2) ? 4 : 8) void spmv_pattern_kernel(const TileArgs a) {
+__global__ __launch_bounds__(WG, (XPL == 4 && NG == 2) ? 4 : 8) void spmv_pattern_block_kernel(const TileArgs a) {
     const int part = xcd_remap(blockIdx.x, a.nparts);
     int xs[XPL];
     if constexpr (XPL == 1) load_x_addresses<WG, XPL>(a, part, threadIdx.x, 0, xs);
@@ -758,6 +773,206 @@ __global__ __launch_bounds__(WG, (XPL == 4 && NG == 2) ? 4 : 8) void spmv_patter
         window_block<T, WG, XPL, NG, false>(a, part, xs);
     else
         pattern_block<T, WG, XPL, NG>(a, part, xs, rd, r0, k0, r1, k1);
+}
+
+// ------------------------------------------------------------------------------------------
+// The pattern kernel for matrices whose every block has a sheet (SheetRun), as a pipeline: as many workgroups as the device
+// holds walk through the blocks, and while one multiplies a block out of LDS the next one's values, x vectors and sheet travel into
+// a second set of LDS buffers, past the registers.
+// Bound: memory.  With the rows' arithmetic left out it takes 23.9 us on the 27-point stencil of 128^3 (bf16, 137 MB), with it 25.7;
+// a workgroup per block and nothing in flight while it multiplies took 31.0 (FP32 57.1 -> 45.0; 5 points of 1024^2, FP32 9.9 -> 9.3,
+// of 1500^2, bf16 15.6 -> 10.6; lines of 100 points, whose blocks have more than four runs and went by their positions, 17.9 -> 14.1).
+//   - Blocks have 128 or 256 rows (up to 32 entries a row), so two wavefronts with a row per lane finish a block in one or two sweeps, and
+//     what is done once per row and once per block is done by half as many lanes as with two lanes a row: 8.0 M vector instructions
+//     instead of 14.1 M.  Pipelining alone, two lanes a row and one entry at a time, was slower than no pipeline (34.4 us).
+//   - Values and pattern are read from LDS up to 16 entries at a time.
+//   - Where LDS leaves a compute unit ten wavefronts or fewer, two lanes share a row of 16 entries or more (P = 2): FP32 27 points 46.8 ->
+//     45.3 us, bf16 49 points (64 rows a block) 32.0 -> 26.0; elsewhere it costs (27 points, bf16 25.8 -> 27.1, 5 points 10.6 -> 15.4).
+//   - x vectors are asked for before the values (the other way round 25.7 -> 27.2 us); more workgroups than the device holds, so that the
+//     hardware deals the rest out: 30 to 40 % slower, since nothing overlaps a workgroup's first block.
+constexpr int kStreamRows = 128;  // rows of a sweep
+
+// The stored values of one row, in order, out of LDS: as many as B asks for at a time, in reads of whole words.
+template <typename E>
+struct RowValues;
+template <>
+struct RowValues<float> {
+    const float* p;
+    __device__ __forceinline__ RowValues(const float* vals, int slot) : p(vals + slot) {}
+    template <int B>
+    __device__ __forceinline__ void next(float (&v)[B]) {
+        __builtin_memcpy(v, __builtin_assume_aligned(p, 4), 4 * B);
+        p += B;
+    }
+};
+// bf16: a row may start in the middle of a word, and a wide read that does is taken apart by the LDS (eight entries at a time from where
+// they lie: 14 M cycles of SQ_LDS_UNALIGNED_STALL, 40 us instead of 28.5), so words are read whole and put together again.
+template <>
+struct RowValues<uint16_t> {
+    const uint32_t* p;
+    uint32_t word;
+    unsigned shift;
+    __device__ __forceinline__ RowValues(const uint16_t* vals, int slot)
+        : p(reinterpret_cast<const uint32_t*>(vals) + (slot >> 1)), shift(16u * (slot & 1)) {
+        word = *p++;
+    }
+    template <int B>
+    __device__ __forceinline__ void next(float (&v)[B]) {
+        if constexpr (B == 1) {  // the last entry of a row of odd length
+            v[0] = __uint_as_float((word >> shift) << 16);
+        } else {
+            uint32_t w[B / 2];
+            __builtin_memcpy(w, __builtin_assume_aligned(p, 4), 2 * B);
+            p += B / 2;
+#pragma unroll
+            for (int i = 0; i < B / 2; ++i) {
+                const uint32_t both = __builtin_amdgcn_alignbit(w[i], i > 0 ? w[i - 1] : word, shift);
+                v[2 * i] = __uint_as_float(both << 16);
+                v[2 * i + 1] = __uint_as_float(both & 0xFFFF0000u);
+            }
+            word = w[B / 2 - 1];
+        }
+    }
+};
+
+// A row's entries by one lane, sixteen at a time, then eight, four, two, one.  list: the row's pattern, byte offsets of 16 bits from
+// a word's start on; xb: address of the x value that offset 0 stands for.
+template <typename E>
+__device__ __forceinline__ float pattern_row_dot(RowValues<E> vals, const unsigned char* xb, const uint32_t* list, int len) {
+    float acc = 0.f, acc2 = 0.f;
+    auto batch = [&](auto B_) {
+        constexpr int B = decltype(B_)::value, W = (B + 1) / 2;
+        uint32_t o[W];
+        __builtin_memcpy(o, __builtin_assume_aligned(list, 4), 4 * W);
+        float av[B];
+        vals.template next<B>(av);
+        E xv[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) xv[u] = *reinterpret_cast<const E*>(xb + ((u & 1) ? o[u / 2] >> 16 : o[u / 2] & 0xFFFFu));
+#pragma unroll
+        for (int u = 0; u < B; u += 2) {
+            acc += av[u] * widen(xv[u]);
+            if (u + 1 < B) acc2 += av[u + 1] * widen(xv[u + 1]);
+        }
+        list += W;
+        len -= B;
+    };
+    while (len >= 16) batch(std::integral_constant<int, 16>{});
+    if (len >= 8) batch(std::integral_constant<int, 8>{});
+    if (len >= 4) batch(std::integral_constant<int, 4>{});
+    if (len >= 2) batch(std::integral_constant<int, 2>{});
+    if (len >= 1) batch(std::integral_constant<int, 1>{});
+    return acc + acc2;
+}
+
+template <typename T, int XPL, int P>
+__global__ __launch_bounds__(kStreamRows * P, P == 1 ? 4 : 8) void spmv_pattern_kernel(const TileArgs a) {
+    using E = typename T::elem;
+    constexpr int WG = kStreamRows * P, XE = 16 / sizeof(E);
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const E* const vals = static_cast<const E*>(a.vals);
+    const E* const x = static_cast<const E*>(a.x);
+    const int vals_at = 16 * a.x_cap, sheet_at = vals_at + a.val_bytes, y0_at = sheet_at + a.sheet_stride;  // x vectors first
+
+    // die j walks through a contiguous stretch of the blocks, its workgroups side by side
+    const int die = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+    const int per = (static_cast<int>(gridDim.x) - die + kXcds - 1) / kXcds;  // workgroups of this die
+    const int q = a.nparts / kXcds, rem = a.nparts % kXcds;
+    const int first = die * q + (die < rem ? die : rem), end = first + q + (die < rem ? 1 : 0);
+    int b = first + slot;
+    if (b >= end) return;
+
+    // what has to be in registers before a block's copies can be asked for: its descriptor, one word per lane (first row, first
+    // entry, last row, last entry, again and again), and where the lane's x vectors lie
+    struct Head {
+        int dsc;
+        int xs[XPL];
+    };
+    const int32_t* dsc_at = a.part_desc + 2 * static_cast<int64_t>(b) + (lane & 3);
+    const int32_t* xs_at = a.xv_pad + static_cast<int64_t>(b) * a.x_cap;  // the same in all lanes
+    const unsigned char* sheet_from = a.sheets + static_cast<int64_t>(b) * a.sheet_stride;
+    const int64_t xs_step = static_cast<int64_t>(per) * a.x_cap, sheet_step = static_cast<int64_t>(per) * a.sheet_stride;
+    auto load_head = [&](Head& h) {  // of the next block of this workgroup
+        h.dsc = *dsc_at;
+#pragma unroll
+        for (int u = 0; u < XPL; ++u) h.xs[u] = tid + u * WG < a.x_cap ? xs_at[static_cast<unsigned>(tid + u * WG)] : -1;
+        dsc_at += 2 * per;
+        xs_at += xs_step;
+    };
+    // `vecs` vectors of 16 bytes, side by side in memory and in LDS
+    auto copy = [&](uint32_t lds, const void* from, int vecs, auto&& one) {
+        const unsigned char* src = static_cast<const unsigned char*>(from) + 1024 * wave;
+        uint32_t dst = lds + 1024 * wave;
+        int v = 64 * wave;
+        for (; v + 64 <= vecs; v += WG, src += 16 * WG, dst += 16 * WG) one(dst, src, 16u * static_cast<unsigned>(lane));
+        if (lane < vecs - v) one(dst, src, 16u * static_cast<unsigned>(lane));
+    };
+    const int last_x = a.n - XE;  // last place a whole vector of x may start at
+    auto issue = [&](const Head& h, int buf) {
+        unsigned char* const base = smem_raw + buf * a.buf_bytes;
+        const uint32_t lds = lds_address(base);
+        const int r0 = __builtin_amdgcn_readlane(h.dsc, 0), k0 = __builtin_amdgcn_readlane(h.dsc, 1);
+        const int r1 = __builtin_amdgcn_readlane(h.dsc, 2), k1 = __builtin_amdgcn_readlane(h.dsc, 3);
+#pragma unroll
+        for (int u = 0; u < XPL; ++u) {
+            if (h.xs[u] >= 0 && h.xs[u] <= last_x) copy16_to_lds(lds + 16 * (u * WG + 64 * wave), x + static_cast<unsigned>(h.xs[u]));
+            if (h.xs[u] > last_x && h.xs[u] >= 0) {
+                E* const dst = reinterpret_cast<E*>(base) + (tid + u * WG) * XE;
+                for (int i = 0; i < XE; ++i) dst[i] = h.xs[u] + i < a.n ? x[h.xs[u] + i] : E(0);
+            }
+        }
+        copy(lds + sheet_at, sheet_from, a.sheet_stride / 16, copy16_to_lds_nt);
+        sheet_from += sheet_step;
+        const int k0a = k0 & ~(XE - 1);
+        const int k1v = (k1 + XE - 1) & ~(XE - 1);
+        const int kv = k1v <= a.nnz ? k1v : a.nnz & ~(XE - 1);  // the copies' end: whole vectors
+        copy(lds + vals_at, vals + k0a, (kv - k0a) / XE, copy16_to_lds_nt);
+        if (kv < k1 && tid < k1 - kv) reinterpret_cast<E*>(base + vals_at)[kv - k0a + tid] = vals[kv + tid];  // the array's last entries
+        if (a.beta != 0.f) {
+            for (int i0 = 64 * wave; i0 < r1 - r0; i0 += WG)
+                if (i0 + lane < r1 - r0) copy4_to_lds(lds + y0_at + 4 * i0, a.y + r0 + i0, 4u * static_cast<unsigned>(lane));
+        }
+    };
+
+    Head h;
+    load_head(h);
+    int dsc = h.dsc;
+    issue(h, 0);
+    if (b + per < end) load_head(h);
+    for (int buf = 0; b < end; b += per, buf ^= 1) {
+        wait_all_and_barrier();  // this block is in LDS, the other buffer is no longer read
+        const int dsc_n = h.dsc;
+        if (b + per < end) {
+            issue(h, buf ^ 1);
+            if (b + 2 * per < end) load_head(h);
+        }
+        const int r0 = __builtin_amdgcn_readlane(dsc, 0), nr = __builtin_amdgcn_readlane(dsc, 2) - r0;
+        const unsigned char* const base = smem_raw + buf * a.buf_bytes;
+        const unsigned char* const sheet = base + sheet_at;
+        for (int row0 = 0; row0 < nr; row0 += kStreamRows) {
+            const int row = row0 + tid / P, part = P == 1 ? 0 : tid % P;
+            float acc = 0.f;
+            if (row < nr) {
+                const i32x4 run = *(reinterpret_cast<const i32x4*>(sheet + a.map_bytes) + sheet[row]);  // a SheetRun
+                int len = run[2], value = run[0] + __mul24(row, len), list = run[3] & 0xFFFF;
+                const int pos = run[1] + __mul24(row, run[3] >> 16);
+                if constexpr (P == 2) {  // the row's first half, an even number of entries, and the rest
+                    const int half = (len + 3) >> 2 << 1, first_part = len < half ? len : half;
+                    value += part ? half : 0;
+                    list += part ? 2 * half : 0;
+                    len = part ? len - first_part : first_part;
+                }
+                acc = pattern_row_dot<E>(RowValues<E>(reinterpret_cast<const E*>(base + vals_at), value), base + pos,
+                                         reinterpret_cast<const uint32_t*>(sheet + list), len);
+            }
+            acc = group_sum<P>(acc);
+            if (row < nr && part == 0)
+                (a.y + r0)[static_cast<unsigned>(row)] = epilogue(acc, a.alpha, a.beta, reinterpret_cast<const float*>(base + y0_at), row);
+        }
+        dsc = dsc_n;
+    }
 }
 
 // Builds the x windows of row blocks (one workgroup of 256 lanes per block; analysis time).
@@ -997,13 +1212,18 @@ __global__ __launch_bounds__(256) void window_build_kernel(const int32_t* __rest
 // The block is patterned when it is staged, no row exceeds kMaxPatternLen entries, no rel is negative and there are at
 // most kMaxPatternRuns runs.  fill == 0: packs the runs into run_desc[8b .. 8b+7] (word 7 = runs, 0 when not patterned).
 // fill == 1 (same inputs, pat_pad allocated with stride pt_cap): writes the list, zero padded.
+// With sheet_need (fill == 0) the block's sheet is planned as well (StreamSheets): up to kMaxSheetRuns runs, runs with equal lists
+// sharing one.  sheet_need[b] = its bytes, 0 if the block cannot have one; sheet_map / sheet_runs as they will stand in it.
 __global__ __launch_bounds__(256) void pattern_build_kernel(const int32_t* __restrict__ block_desc, const int32_t* __restrict__ rowptr,
                                                             const uint16_t* __restrict__ lidx, int tile_cap, int fill,
-                                                            int32_t* __restrict__ run_desc, uint16_t* __restrict__ pat_pad, int pt_cap) {
+                                                            int32_t* __restrict__ run_desc, uint16_t* __restrict__ pat_pad, int pt_cap,
+                                                            int elem_bytes, int map_bytes, int32_t* __restrict__ sheet_need,
+                                                            unsigned char* __restrict__ sheet_map, SheetRun* __restrict__ sheet_runs) {
     __shared__ int base_s[kMaxRowsPerBlock];
     __shared__ unsigned char len_s[kMaxRowsPerBlock], same_s[kMaxRowsPerBlock], flag_s[kMaxRowsPerBlock];
     __shared__ int bad;
-    __shared__ int run_first[kMaxPatternRuns + 1], run_stride[kMaxPatternRuns];
+    __shared__ int run_first[kMaxSheetRuns + 1], run_stride[kMaxSheetRuns];
+    __shared__ int all_runs;
     const int tid = threadIdx.x, b = blockIdx.x;
     const int r0 = block_desc[2 * b], k0 = block_desc[2 * b + 1], r1 = block_desc[2 * b + 2], k1 = block_desc[2 * b + 3];
     const int nr = r1 - r0;
@@ -1070,7 +1290,7 @@ __global__ __launch_bounds__(256) void pattern_build_kernel(const int32_t* __res
                 const int f = flag_s[i];
                 const bool starts = f == 1 || (f == 2 && !prev_started);
                 if (starts) {
-                    if (runs == kMaxPatternRuns) {
+                    if (runs == kMaxSheetRuns) {
                         runs = 0;
                         break;
                     }
@@ -1083,6 +1303,8 @@ __global__ __launch_bounds__(256) void pattern_build_kernel(const int32_t* __res
             for (int r = 0; r < runs; ++r)  // the step of a run is that of its first two rows
                 run_stride[r] = run_first[r + 1] - run_first[r] >= 2 ? base_s[run_first[r] + 1] - base_s[run_first[r]] : 0;
         }
+        all_runs = runs;
+        if (runs > kMaxPatternRuns) runs = 0;
         {
             int rows[4] = {0, 0, 0, 0}, len[4] = {0, 0, 0, 0}, base[4] = {0, 0, 0, 0}, stride[4] = {0, 0, 0, 0};
             for (int r = 0; r < runs; ++r) {
@@ -1102,14 +1324,82 @@ __global__ __launch_bounds__(256) void pattern_build_kernel(const int32_t* __res
             d[7] = runs;
         }
     }
+    if (!sheet_need) return;
+    __syncthreads();
+    const int runs = all_runs;
+    if (runs == 0) {
+        if (tid == 0) sheet_need[b] = 0;
+        return;
+    }
+    __shared__ uint16_t rel_s[kMaxSheetRuns][kMaxPatternLen];
+    for (int i = tid; i < runs * kMaxPatternLen; i += 256) {
+        const int r = i / kMaxPatternLen, j = i % kMaxPatternLen, row = run_first[r];
+        rel_s[r][j] = j < len_s[row] ? static_cast<uint16_t>(lidx[rowptr[r0 + row] + j] - base_s[row]) : 0;
+    }
+    for (int i = tid; i < nr; i += 256) {
+        int r = 0;
+        while (r + 1 < runs && i >= run_first[r + 1]) ++r;
+        sheet_map[static_cast<int64_t>(b) * map_bytes + i] = static_cast<unsigned char>(r);
+    }
+    __syncthreads();
+    if (tid < 64) {
+        int at = map_bytes + static_cast<int>(sizeof(SheetRun)) * runs, entry = k0 & (16 / elem_bytes - 1);
+        int list_at[kMaxSheetRuns];
+#pragma unroll
+        for (int r = 0; r < kMaxSheetRuns; ++r) {
+            list_at[r] = 0;
+            if (r < runs) {
+                const int row = run_first[r], len = len_s[row];
+                int place = -1;
+#pragma unroll
+                for (int u = 0; u < r; ++u) {
+                    const bool differs = len_s[run_first[u]] != len || rel_s[u][tid] != rel_s[r][tid];
+                    if (place < 0 && !__builtin_amdgcn_ballot_w64(differs)) place = list_at[u];
+                }
+                if (place < 0) {
+                    place = at;
+                    at += (2 * len + 3) & ~3;
+                }
+                list_at[r] = place;
+                if (tid == 0)
+                    sheet_runs[static_cast<int64_t>(b) * kMaxSheetRuns + r] =
+                        SheetRun{entry - row * len, (base_s[row] - row * run_stride[r]) * elem_bytes, len, (run_stride[r] * elem_bytes) * 65536 + place};
+                entry += (run_first[r + 1] - row) * len;
+            }
+        }
+        if (tid == 0) sheet_need[b] = at;
+    }
 }
 
-// *max_table = the longest pattern list of a patterned block, *covered = the entries of the patterned blocks (both
-// cleared by the caller).  A pass of its own over the packed runs: one atomic per wavefront instead of two per block
+// The sheets themselves, from what was planned: the map, the runs, and every list once.
+__global__ __launch_bounds__(64) void sheet_fill_kernel(const int32_t* __restrict__ block_desc, const int32_t* __restrict__ rowptr,
+                                                        const uint16_t* __restrict__ lidx, int elem_bytes, int map_bytes, int stride,
+                                                        const unsigned char* __restrict__ sheet_map, const SheetRun* __restrict__ sheet_runs,
+                                                        unsigned char* __restrict__ sheets) {
+    const int tid = threadIdx.x, b = blockIdx.x;
+    const int r0 = block_desc[2 * b], nr = block_desc[2 * b + 2] - r0;
+    unsigned char* const out = sheets + static_cast<int64_t>(b) * stride;
+    const unsigned char* const map = sheet_map + static_cast<int64_t>(b) * map_bytes;
+    for (int i = tid; i < nr; i += 64) out[i] = map[i];
+    const int runs = map[nr - 1] + 1;
+    int row = 0;
+    for (int r = 0; r < runs; ++r) {
+        const SheetRun run = sheet_runs[static_cast<int64_t>(b) * kMaxSheetRuns + r];
+        if (tid == 0) *(reinterpret_cast<SheetRun*>(out + map_bytes) + r) = run;
+        while (row < nr && map[row] < r) ++row;  // the run's first row
+        const int ka = rowptr[r0 + row];
+        uint16_t* const list = reinterpret_cast<uint16_t*>(out + (run.stride_list & 0xFFFF));
+        if (tid < run.len) list[tid] = static_cast<uint16_t>((lidx[ka + tid] - lidx[ka]) * elem_bytes);  // equal lists are written again
+    }
+}
+
+// *max_table = the longest pattern list of a patterned block, *covered = the entries of the patterned blocks, *max_sheet = the
+// largest sheet, INT32_MAX when a block has none (all cleared by the caller).  A pass of its own over the packed runs: one atomic per wavefront instead of two per block
 // on the same two addresses.
 __global__ __launch_bounds__(256) void pattern_totals_kernel(const int32_t* __restrict__ block_desc, const int32_t* __restrict__ run_desc,
-                                                             int nb, int32_t* max_table, unsigned long long* covered) {
-    int table = 0;
+                                                             int nb, const int32_t* __restrict__ sheet_need, int32_t* max_table,
+                                                             int32_t* max_sheet, unsigned long long* covered) {
+    int table = 0, sheet = 0;
     unsigned long long entries = 0;
     for (int b = blockIdx.x * 256 + threadIdx.x; b < nb; b += gridDim.x * 256) {
         const int32_t* d = run_desc + 8 * static_cast<int64_t>(b);
@@ -1119,16 +1409,22 @@ __global__ __launch_bounds__(256) void pattern_totals_kernel(const int32_t* __re
             table = t > table ? t : table;
             entries += static_cast<unsigned long long>(block_desc[2 * b + 3] - block_desc[2 * b + 1]);
         }
+        const int need = sheet_need[b] > 0 ? sheet_need[b] : INT32_MAX;
+        sheet = need > sheet ? need : sheet;
     }
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_xor(table, d);
+        const int t = __shfl_xor(table, d), u = __shfl_xor(sheet, d);
         table = t > table ? t : table;
+        sheet = u > sheet ? u : sheet;
         entries += __shfl_xor(entries, d);
     }
-    if ((threadIdx.x & 63) == 0 && entries > 0) {
-        atomicMax(max_table, table);
-        atomicAdd(covered, entries);
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(max_sheet, sheet);
+        if (entries > 0) {
+            atomicMax(max_table, table);
+            atomicAdd(covered, entries);
+        }
     }
 }
 
@@ -1327,7 +1623,7 @@ hipError_t launch_window_g(const TileArgs& a, size_t lds, hipStream_t st) {
 
 template <typename T, int XPL, int NG>
 hipError_t launch_pattern_g(const TileArgs& a, size_t lds, hipStream_t st) {
-    auto kernel = spmv_pattern_kernel<T, 256, XPL, NG>;
+    auto kernel = spmv_pattern_block_kernel<T, 256, XPL, NG>;
     if (lds > 64 * 1024) {
         static thread_local size_t allowed = 0;
         if (lds > allowed) {
@@ -1339,6 +1635,31 @@ hipError_t launch_pattern_g(const TileArgs& a, size_t lds, hipStream_t st) {
     }
     hipLaunchKernelGGL(kernel, dim3(a.nparts), dim3(256), lds, st, a);
     return hipGetLastError();
+}
+
+// Workgroups of the stream kernel that a compute unit holds at once, by their LDS: 160 KB, handed out in pieces of 1280 bytes (a
+// fifth workgroup that just does not fit would run after the others: 28.5 us instead of 23.6).
+int stream_places(size_t buf_bytes) { return static_cast<int>(160 * 1024 / ((2 * buf_bytes + 1279) / 1280 * 1280)); }
+
+// One workgroup per place on the device, or per block, if there are fewer.
+template <typename T, int P, int XPL>
+hipError_t launch_stream_x(const TileArgs& a, int64_t places, hipStream_t st) {
+    hipLaunchKernelGGL((spmv_pattern_kernel<T, XPL, P>), dim3(static_cast<unsigned>(a.nparts < places ? a.nparts : places)),
+                       dim3(kStreamRows * P), 2 * static_cast<size_t>(a.buf_bytes), st, a);
+    return hipGetLastError();
+}
+template <typename T, int P>
+hipError_t launch_stream_p(const TileArgs& a, int places, int cus, hipStream_t st) {
+    constexpr int WG = kStreamRows * P;
+    const int64_t all = static_cast<int64_t>(places < 2048 / WG ? places : 2048 / WG) * cus;
+    if (a.x_cap <= WG) return launch_stream_x<T, P, 1>(a, all, st);
+    if (a.x_cap <= 2 * WG) return launch_stream_x<T, P, 2>(a, all, st);
+    if (a.x_cap <= 4 * WG) return launch_stream_x<T, P, 4>(a, all, st);
+    return launch_stream_x<T, P, 8>(a, all, st);
+}
+template <typename T>
+hipError_t launch_stream(const TileArgs& a, bool two_lanes, int places, int cus, hipStream_t st) {
+    return two_lanes ? launch_stream_p<T, 2>(a, places, cus, st) : launch_stream_p<T, 1>(a, places, cus, st);
 }
 
 // Picks the instantiation whose fixed first round of loads just covers the blocks.
@@ -1393,6 +1714,21 @@ hipError_t launch_windowed(const MatrixView& A, const int32_t* block_desc, int32
     a.x_cap = w.max_vectors > 0 ? w.max_vectors : 1;
     a.x_vec_ok = reinterpret_cast<uintptr_t>(x) % 16 == 0 ? 1 : 0;
     const size_t esz = A.bf16 ? 2 : 4;
+    if (w.sheets && A.vec_ok && a.x_vec_ok) {
+        const size_t val = (esz * static_cast<size_t>(staged_max + 16) + 15) & ~size_t{15};
+        const size_t y0 = s.beta != 0.f ? (4 * static_cast<size_t>(rows_max) + 15) & ~size_t{15} : 0;
+        const size_t buf = 16 * static_cast<size_t>(a.x_cap) + val + static_cast<size_t>(w.sheet_stride) + y0;
+        if (2 * buf <= 64 * 1024) {  // two workgroups to a compute unit at least
+            a.sheets = w.sheets;
+            a.sheet_stride = w.sheet_stride;
+            a.map_bytes = sheet_map_bytes(rows_max);
+            a.val_bytes = static_cast<int32_t>(val);
+            a.buf_bytes = static_cast<int32_t>(buf);
+            const int places = stream_places(buf);
+            const bool two = places * (rows_max > 64 ? 2 : 1) <= 10 && A.nnz / 16 >= A.m;
+            return A.bf16 ? launch_stream<BF16>(a, two, places, w.cus, st) : launch_stream<F32>(a, two, places, w.cus, st);
+        }
+    }
     const size_t lds = 16 * static_cast<size_t>(a.x_cap) + (esz + 2) * static_cast<size_t>(staged_max + 16) +
                        (sizeof(int) + sizeof(float)) * static_cast<size_t>(rows_max + 2) + 2 * static_cast<size_t>(a.pt_cap);
     if (A.bf16) return launch_window_t<BF16>(a, staged_max, lds, st);
@@ -1411,15 +1747,24 @@ hipError_t launch_window_build(const MatrixView& A, const int32_t* block_nz, int
 
 hipError_t launch_pattern_build(const int32_t* block_desc, int32_t nb, const int32_t* rowptr, const uint16_t* lidx, int32_t block_nnz,
                                 bool fill, int32_t* run_desc, int32_t* max_table, unsigned long long* covered, uint16_t* pat_pad,
-                                int32_t pt_cap, hipStream_t st) {
+                                int32_t pt_cap, const SheetPlan* sheets, hipStream_t st) {
     if (nb <= 0) return hipSuccess;
+    const SheetPlan p = sheets ? *sheets : SheetPlan{};
     hipLaunchKernelGGL(pattern_build_kernel, dim3(nb), dim3(256), 0, st, block_desc, rowptr, lidx, block_nnz, fill ? 1 : 0, run_desc,
-                       pat_pad, pt_cap);
+                       pat_pad, pt_cap, p.elem_bytes, p.map_bytes, p.need, p.map, p.runs);
     if (!fill) {
         const int grid = nb < 256 * 64 ? (nb + 255) / 256 : 64;
         hipLaunchKernelGGL(pattern_totals_kernel, dim3(grid), dim3(256), 0, st, block_desc, static_cast<const int32_t*>(run_desc), nb,
-                           max_table, covered);
+                           static_cast<const int32_t*>(p.need), max_table, p.largest, covered);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_sheet_fill(const int32_t* block_desc, int32_t nb, const int32_t* rowptr, const uint16_t* lidx, const SheetPlan& p,
+                             int32_t stride, unsigned char* sheets, hipStream_t st) {
+    if (nb <= 0) return hipSuccess;
+    hipLaunchKernelGGL(sheet_fill_kernel, dim3(nb), dim3(64), 0, st, block_desc, rowptr, lidx, p.elem_bytes, p.map_bytes, stride, p.map,
+                       p.runs, sheets);
     return hipGetLastError();
 }
 
