@@ -9,6 +9,7 @@
 namespace spmv {
 namespace {
 
+constexpr int kEllTileSlots = 4096;  // most slots a workgroup of the ELL tile kernel stages
 constexpr int kCscLdsRows = 16384;  // CSC: up to this many rows a workgroup keeps a private y in LDS (64 KB)
 
 // ------------------------------------------------------------------------------------------
@@ -190,12 +191,63 @@ __global__ __launch_bounds__(kWG) void spmv_ell_kernel(const int32_t* __restrict
 }
 
 
-// ELL rows of moderate width, the CSR tile kernel's way: a workgroup copies the slots of a run of
-// rows (a contiguous stretch of col_ids / vals, since the layout is row-major) to LDS with 128-bit
-// non-temporal loads, turning padding slots into (column 0, value 0) on the way, and then runs the
-// shared row phase on them, rows being segments of equal length `width`.  Against a team of lanes
-// reading its row straight from memory this keeps the global reads fully coalesced whatever the
-// width, and issues the x gathers with neighbouring lanes on neighbouring rows.
+// Four consecutive stored values from slot `at` on, out of LDS, in reads of whole words.
+__device__ __forceinline__ f32x4 four_values(const float* vals, int at) {
+    f32x4 v;
+    __builtin_memcpy(&v, __builtin_assume_aligned(vals + at, 4), 16);
+    return v;
+}
+__device__ __forceinline__ f32x4 four_values(const uint16_t* vals, int at) {
+    uint32_t w[3];
+    __builtin_memcpy(w, __builtin_assume_aligned(vals + (at & ~1), 4), 12);
+    const unsigned shift = 16u * (at & 1);
+    const uint32_t lo = __builtin_amdgcn_alignbit(w[1], w[0], shift), hi = __builtin_amdgcn_alignbit(w[2], w[1], shift);
+    return f32x4{__uint_as_float(lo << 16), __uint_as_float(lo & 0xFFFF0000u), __uint_as_float(hi << 16), __uint_as_float(hi & 0xFFFF0000u)};
+}
+
+// The rows of a staged tile: a wavefront takes 64 / G rows at a time, and its k-th 64 / G lanes every G-th four slots of them from the
+// k-th on, K fours in all, so that the lanes of a gather stand for neighbouring rows and, in a band or a stencil, read
+// neighbouring x.  (Measured on x in the caches: 64 neighbouring values cost a compute unit 2.4 ns, 32 pairs of neighbours 15, 64 values
+// far apart 27.)  All of a lane's gathers are in flight at once; slots past the row's end are treated as padding, whose value and x
+// count for nothing, whatever they hold.
+template <int G, int K, typename E>
+__device__ __forceinline__ void ell_rows(const int* cols_l, int col_stride, const E* vals_l, int val_stride, const E* x, const float* y0_l, float* y,
+                                         int nr, int r0, int width, float alpha, float beta, int tid) {
+    constexpr int RPW = 64 / G;
+    const int lane = tid & 63, part = lane / RPW;
+    for (int first = 0; first < nr; first += kWG / G) {
+        const int row = first + (tid >> 6) * RPW + lane % RPW;
+        const int len = row < nr ? width - 4 * part : 0;
+        const int col_at = row < nr ? row * col_stride + 4 * part : 0, val_at = row < nr ? row * val_stride + 4 * part : 0;
+        int c[4 * K];
+        E xv[4 * K];
+#pragma unroll
+        for (int q = 0; q < K; ++q) __builtin_memcpy(c + 4 * q, __builtin_assume_aligned(cols_l + col_at + 4 * G * q, 4), 16);
+#pragma unroll
+        for (int u = 0; u < 4 * K; ++u) {
+            c[u] = 4 * G * (u / 4) + u % 4 < len ? c[u] : -1;
+            xv[u] = x[static_cast<unsigned>(c[u] < 0 ? 0 : c[u])];
+        }
+        float acc[2] = {0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            const f32x4 v = four_values(vals_l, val_at + 4 * G * q);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc[u & 1] += (c[4 * q + u] < 0 ? 0.f : v[u]) * (c[4 * q + u] < 0 ? 0.f : widen(xv[4 * q + u]));
+        }
+        float sum = acc[0] + acc[1];
+        if constexpr (G >= 4) sum = add_swap16(sum);
+        if constexpr (G >= 2) sum = add_swap32(sum);
+        if (row < nr && part == 0) y[r0 + row] = epilogue(sum, alpha, beta, y0_l, row);
+    }
+}
+
+// ELL rows of moderate width: a workgroup copies the slots of a run of rows (a contiguous stretch of col_ids / vals, since the layout
+// is row-major) to LDS as they are, past the registers, and then every lane takes a stretch of a row.  Against a team of lanes
+// reading its row straight from memory this keeps the global reads fully coalesced whatever the width.
+// Bound: memory (27 points of 128^3: bf16 52.9 us, 6.5 TB/s of the 6.9 a kernel that only reads reaches; FP32 74.7).  With the slots
+// staged through registers and a row's gathers in batches of 8, 4, 2 and 1, each waited for, 67.2 and 96; the copies alone 66, a
+// lane's gathers all at once the rest.  Tiles of 3072 or 2048 slots instead of 4096: 53.9, 61.
 // rows_per_tile is a multiple of 8, so a tile's first slot is 16-byte aligned in both arrays.
 template <typename T>
 __global__ __launch_bounds__(kWG, 8) void spmv_ell_tile_kernel(const int32_t* __restrict__ col_ids,
@@ -206,65 +258,59 @@ __global__ __launch_bounds__(kWG, 8) void spmv_ell_tile_kernel(const int32_t* __
     using E = typename T::elem;
     constexpr int VEC = T::VEC;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ int deferred[kMaxDeferred];
-    __shared__ int n_deferred;
     const int tid = threadIdx.x;
     const int r0 = xcd_remap(blockIdx.x, gridDim.x) * rows_per_tile;  // a die works through a contiguous stretch of rows
     const int nr = m - r0 < rows_per_tile ? m - r0 : rows_per_tile;
     const size_t k0 = static_cast<size_t>(r0) * width;
     const int span = nr * width;
-    const int slots = (span + VEC - 1) & ~(VEC - 1);
+    // Rows of 32 or 64 slots would all begin on the same LDS banks: 16 bytes are left between them (100000 banded rows of 32, bf16:
+    // 13.0 -> 5.6 us).
+    const int pad = width % 32 == 0 ? 1 : 0;
+    const int col_stride = width + 4 * pad, val_stride = width + VEC * pad;
     int* cols_l = reinterpret_cast<int*>(smem_raw);
-    E* vals_l = reinterpret_cast<E*>(smem_raw + sizeof(int) * slots);
-    int* seg = reinterpret_cast<int*>(smem_raw + (sizeof(int) + sizeof(E)) * slots);  // nr + 1 bounds
-    float* y0_l = reinterpret_cast<float*>(seg + nr + 1);                             // nr old values of y
+    E* vals_l = reinterpret_cast<E*>(smem_raw + sizeof(int) * ((rows_per_tile * col_stride + VEC - 1) & ~(VEC - 1)));
+    float* y0_l = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(vals_l) + sizeof(E) * ((rows_per_tile * val_stride + VEC - 1) & ~(VEC - 1)) +
+                                           64 * sizeof(E) + 16);  // nr old values of y; a lane reads up to 64 slots past the tile's
 
     const float y0v = (beta != 0.f && tid < nr) ? y[r0 + tid] : 0.f;
     const int whole = vec_ok ? span & ~(VEC - 1) : 0;  // slots of the tile that whole vectors cover
-    for (int off = tid * VEC; off < whole; off += kWG * VEC) {
-        i32x4 c[VEC / 4];
-#pragma unroll
-        for (int v = 0; v < VEC / 4; ++v)
-            c[v] = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(col_ids + k0 + off) + v);
-        if constexpr (VEC == 4) {
-            f32x4 a = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(vals + k0 + off));
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = c[0][i] < 0 ? 0.f : a[i];
-                c[0][i] = c[0][i] < 0 ? 0 : c[0][i];
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto copy = [&](const void* to, const void* from, int vecs, int per_row) {  // whole vectors of 16 bytes; per_row of them to a padded row
+        const uint32_t lds = lds_address(to);
+        if (!pad) {
+            for (int v = 64 * wave; v < vecs; v += kWG)
+                if (lane < vecs - v) copy16_to_lds_nt(lds + 16 * v, static_cast<const unsigned char*>(from) + 16 * v, 16u * static_cast<unsigned>(lane));
+        } else {  // the gap behind a row is filled with its last vector again
+            const int held = vecs + vecs / per_row, step = (1 << 20) / (per_row + 1) + 1;  // v * step >> 20 = v / (per_row + 1) while v < 2^12
+            for (int v0 = 64 * wave; v0 < held; v0 += kWG) {
+                const int v = v0 + lane, row = v * step >> 20, in_row = v - row * (per_row + 1);
+                if (v < held)
+                    copy16_to_lds_nt(lds + 16 * v0, from, 16u * static_cast<unsigned>(row * per_row + (in_row < per_row ? in_row : per_row - 1)));
             }
-            *reinterpret_cast<f32x4*>(vals_l + off) = a;
-            *reinterpret_cast<i32x4*>(cols_l + off) = c[0];
-        } else {
-            u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vals + k0 + off));
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {  // dword i holds elements 2i (low half) and 2i+1
-                const int lo = c[i / 2][2 * (i % 2)], hi = c[i / 2][2 * (i % 2) + 1];
-                a[i] &= (lo < 0 ? 0xFFFF0000u : 0xFFFFFFFFu) & (hi < 0 ? 0x0000FFFFu : 0xFFFFFFFFu);
-            }
-#pragma unroll
-            for (int v = 0; v < 2; ++v)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) c[v][i] = c[v][i] < 0 ? 0 : c[v][i];
-            *reinterpret_cast<u32x4*>(vals_l + off) = a;
-            *reinterpret_cast<i32x4*>(cols_l + off) = c[0];
-            *reinterpret_cast<i32x4*>(cols_l + off + 4) = c[1];
         }
-    }
+    };
+    copy(cols_l, col_ids + k0, whole / 4, width / 4);
+    copy(vals_l, vals + k0, whole / VEC, width / VEC);
     for (int off = whole + tid; off < span; off += kWG) {  // what no whole vector covers (everything, if unaligned)
-        const int c = col_ids[k0 + off];
-        cols_l[off] = c < 0 ? 0 : c;
-        vals_l[off] = c < 0 ? E(0) : vals[k0 + off];
+        const int row = pad ? off / width : 0;
+        cols_l[off + 4 * pad * row] = col_ids[k0 + off];
+        vals_l[off + VEC * pad * row] = vals[k0 + off];
     }
-    if (tid == 0) n_deferred = 0;
-    for (int i = tid; i <= nr; i += kWG) seg[i] = i * width;
     if (tid < nr) y0_l[tid] = y0v;
     if (beta != 0.f)
         for (int i = tid + kWG; i < nr; i += kWG) y0_l[i] = y[r0 + i];
-    __syncthreads();
+    wait_all_and_barrier();
 
-    const RowOut o{y, y0_l, alpha, beta, nullptr, false};
-    tile_rows<false, kWG>(cols_l, vals_l, x, seg, nr, r0, span, o, deferred, &n_deferred, tid);
+#define ELL_ROWS(G, K) ell_rows<G, K>(cols_l, col_stride, vals_l, val_stride, x, y0_l, y, nr, r0, width, alpha, beta, tid)
+    if (width <= 4) ELL_ROWS(1, 1);
+    else if (width <= 8) ELL_ROWS(1, 2);
+    else if (width <= 12) ELL_ROWS(1, 3);
+    else if (width <= 16) ELL_ROWS(1, 4);
+    else if (width <= 24) ELL_ROWS(2, 3);
+    else if (width <= 32) ELL_ROWS(2, 4);
+    else if (width <= 48) ELL_ROWS(4, 3);
+    else ELL_ROWS(4, 4);
+#undef ELL_ROWS
 }
 
 }  // namespace
@@ -390,7 +436,6 @@ hipError_t launch_csc(bool bf16, int32_t m, int32_t n, int32_t nnz, const int32_
 
 namespace {
 
-constexpr int kEllTileSlots = 4096;    // most slots a workgroup of the ELL tile kernel stages
 constexpr int kEllTileMaxWidth = 64;  // widest rows that kernel is used for
 
 template <typename T>
@@ -399,9 +444,9 @@ hipError_t launch_ell_tile(int32_t m, int32_t width, const int32_t* col_ids, con
     using E = typename T::elem;
     int rows = kEllTileSlots / width;
     rows = rows > kWG ? kWG : rows & ~7;
-    // The row phase gives a row G lanes (tile_rows: G doubles while 16 G < width) and takes kWG / G rows a sweep.  A last sweep
+    // The row phase gives a row G lanes (1 up to 16 slots, 2 up to 32, 4 up to 64) and takes kWG / G rows a sweep.  A last sweep
     // that is less than three quarters full is left to the next tile: of the 144 rows of 27 slots that fit, 16 made a sweep
-    // of their own (2 M rows, bf16: 82 -> 67 us with 128; two dies sharing a stretch of rows less is 2 of the 15).
+    // of their own (2 M rows, bf16, with the row phase of the CSR tiles, as are the figures below: 82 -> 67 us with 128; two dies sharing a stretch of rows less is 2 of the 15).
     // 1 M banded rows, FP32 / bf16, with the rest and without: width 20 41 / 31 -> 33 / 28 us, 40 80 / 59 -> 60 / 52, 48 88 / 70 ->
     // 71 / 62, 56 118 / 82 -> 91 / 72, 60 101 / 83 -> 97 / 79; of 54 further shapes (5000 to 200000 rows, banded and scattered
     // columns, widths 12 to 64) the worst took 3 % more (200000 scattered rows of 24: 50.4 -> 52.1), the best 19 % less.
@@ -410,8 +455,9 @@ hipError_t launch_ell_tile(int32_t m, int32_t width, const int32_t* col_ids, con
     const int sweep = kWG / G, rest = rows % sweep;
     if (rows > sweep && 4 * rest < 3 * sweep) rows -= rest;
     const bool vec_ok = reinterpret_cast<uintptr_t>(col_ids) % 16 == 0 && reinterpret_cast<uintptr_t>(vals) % 16 == 0;
-    const size_t lds = (sizeof(int) + sizeof(E)) * static_cast<size_t>(rows * width + T::VEC) +
-                       (sizeof(int) + sizeof(float)) * static_cast<size_t>(rows + 2);
+    const int pad = width % 32 == 0 ? 1 : 0;
+    const size_t lds = sizeof(int) * static_cast<size_t>(rows * (width + 4 * pad) + T::VEC) + sizeof(E) * static_cast<size_t>(rows * (width + T::VEC * pad) + T::VEC) +
+                       64 * sizeof(E) + 16 + sizeof(float) * static_cast<size_t>(rows);
     hipLaunchKernelGGL((spmv_ell_tile_kernel<T>), dim3(ceil_div(m, rows)), dim3(kWG), lds, st, col_ids,
                        static_cast<const E*>(vals), static_cast<const E*>(x), y, m, width, rows, s.alpha, s.beta,
                        vec_ok ? 1 : 0);
