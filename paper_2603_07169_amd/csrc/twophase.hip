@@ -156,6 +156,43 @@ __global__ __launch_bounds__(kTpMulWG) void tp_multiply_group_kernel(const int32
     const int g0 = piece_g[piece], g1 = piece_g[piece + 1];
     const int runs = 1 << shift;
     const int64_t first = (static_cast<int64_t>(c) << shift) * 8;  // first column of the block
+    // One slot per lane and trip: neighbouring lanes read neighbouring 16-byte (32-byte) value runs and write neighbouring products.
+    // U trips at a time, all their loads before the first use and the first of them before the block of x; what is left in the end is
+    // taken two trips at a time, since a trip past the end still reads (600000 rows of 16 groups, whose pieces are 9.2 trips: 62.8 us with
+    // two trips, 64.0 with eight always, 61.7 so).  1 M rows of 16 groups, bf16, both passes: 95.3 us with two trips, 91.3 with
+    // four, 90.8 with six, 89.0 with eight; a lane may hold 64 registers, which FP32 fills with four (160.4 -> 156.6).
+    constexpr int U = VPR == 1 ? 8 : 4;
+    const u32x4* vals = reinterpret_cast<const u32x4*>(tp_val);
+    const int s0 = 4 * g0, s1 = 4 * g1;
+    u32x4 v[U][VPR];
+    int cc[U];
+    auto fetch = [&](int sb, auto N) {
+#pragma unroll
+        for (int u = 0; u < decltype(N)::value; ++u) {  // past the end: the piece's last slot again, not stored
+            const int sl = sb + u * kTpMulWG < s1 ? sb + u * kTpMulWG : s1 - 1;
+#pragma unroll
+            for (int i = 0; i < VPR; ++i) v[u][i] = __builtin_nontemporal_load(vals + static_cast<int64_t>(sl) * VPR + i);
+            cc[u] = __builtin_nontemporal_load(tp_col + sl);
+        }
+    };
+    auto multiply = [&](int sb, auto N) {
+#pragma unroll
+        for (int u = 0; u < decltype(N)::value; ++u) {
+            const int sl = sb + u * kTpMulWG;
+            float p;
+            if constexpr (VPR == 1) {
+                p = dot8(v[u][0], xs_raw[cc[u]]);
+            } else {
+                p = dot8(__builtin_bit_cast(f32x4, v[u][0]), __builtin_bit_cast(f32x4, v[u][1]),
+                         __builtin_bit_cast(f32x4, xs_raw[2 * cc[u]]), __builtin_bit_cast(f32x4, xs_raw[2 * cc[u] + 1]));
+            }
+            if (sl < s1) prod[sl] = p;
+        }
+    };
+    const std::integral_constant<int, U> all{};
+    const std::integral_constant<int, 2> few{};
+    if (s0 >= s1) return;
+    fetch(s0 + tid, all);
     // the block of x: whole aligned runs where x allows 16-byte loads and the run lies inside the matrix
     const bool x_vec = reinterpret_cast<uintptr_t>(x) % 16 == 0;
     for (int r = tid; r <= runs; r += kTpMulWG) {
@@ -172,33 +209,14 @@ __global__ __launch_bounds__(kTpMulWG) void tp_multiply_group_kernel(const int32
         }
     }
     __syncthreads();
-    // One slot per lane and trip, U trips in flight: neighbouring lanes read neighbouring 16-byte (32-byte) value runs and
-    // write neighbouring products.
-    constexpr int U = 2;
-    const u32x4* vals = reinterpret_cast<const u32x4*>(tp_val);
-    const int s0 = 4 * g0, s1 = 4 * g1;
-    for (int sb = s0 + tid; sb < s1; sb += U * kTpMulWG) {
-        u32x4 v[U][VPR];
-        int cc[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {  // past the end: the piece's last slot again, not stored
-            const int sl = sb + u * kTpMulWG < s1 ? sb + u * kTpMulWG : s1 - 1;
-#pragma unroll
-            for (int i = 0; i < VPR; ++i) v[u][i] = __builtin_nontemporal_load(vals + static_cast<int64_t>(sl) * VPR + i);
-            cc[u] = __builtin_nontemporal_load(tp_col + sl);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int sl = sb + u * kTpMulWG;
-            float p;
-            if constexpr (VPR == 1) {
-                p = dot8(v[u][0], xs_raw[cc[u]]);
-            } else {
-                p = dot8(__builtin_bit_cast(f32x4, v[u][0]), __builtin_bit_cast(f32x4, v[u][1]),
-                         __builtin_bit_cast(f32x4, xs_raw[2 * cc[u]]), __builtin_bit_cast(f32x4, xs_raw[2 * cc[u] + 1]));
-            }
-            if (sl < s1) prod[sl] = p;
-        }
+    int sb = s0;
+    for (; s1 - sb > U / 2 * kTpMulWG || sb == s0; sb += U * kTpMulWG) {
+        if (sb != s0) fetch(sb + tid, all);
+        multiply(sb + tid, all);
+    }
+    for (; sb < s1; sb += 2 * kTpMulWG) {
+        fetch(sb + tid, few);
+        multiply(sb + tid, few);
     }
 }
 
