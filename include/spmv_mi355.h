@@ -464,8 +464,11 @@ spmv_status_t spmv_analyze_host(int64_t m, int64_t n, int64_t nnz, const int32_t
  * the run-time-group-size variant.  Enqueues one wavefront on `stream`. */
 spmv_status_t spmv_selftest_reduce(const float* in_dev, float* out_dev, void* stream);
 
-/* Name of the kernel that carries the nnz stream for the handle's current plan ("" before
- * analyze); lets a profiler summary be matched to the plan. */
+/* Name of the kernel that carries the nnz stream in a spmv_csr_run() with this x and beta ("" before analyze); lets a
+ * profiler summary be matched to the plan.  Only x's alignment and whether beta is 0 are looked at, and only the WINDOWED plan
+ * depends on them. */
+const char* spmv_csr_kernel_name(spmv_handle_t h, const void* x, float beta);
+/* The same for an x on a 16-byte boundary and beta = 0. */
 const char* spmv_csr_main_kernel_name(spmv_handle_t h);
 
 /* Name of the kernel that spmm_csr_run() launches for these arguments (only the addresses' alignment is looked at); "" before

@@ -451,6 +451,23 @@ bool window_choice(const int32_t* nv, int64_t nb, int64_t nnz, int64_t* total, i
     return nnz > 0 && mx <= SPMV_MAX_X_VECTORS && 4 * nb * static_cast<int64_t>(mx) <= nnz;
 }
 
+int64_t stream_val_bytes(int elem_bytes, int32_t staged_max) {
+    return (elem_bytes * (static_cast<int64_t>(staged_max) + 16) + 15) & ~int64_t{15};
+}
+
+int64_t stream_buf_bytes(int elem_bytes, int32_t staged_max, int32_t rows_max, int32_t x_vectors, int32_t sheet_stride, bool y_kept) {
+    const int64_t y0 = y_kept ? (4 * static_cast<int64_t>(rows_max) + 15) & ~int64_t{15} : 0;
+    return 16 * static_cast<int64_t>(std::max(x_vectors, 1)) + stream_val_bytes(elem_bytes, staged_max) + sheet_stride + y0;
+}
+
+WindowKernel window_kernel(int elem_bytes, int32_t staged_max, int32_t rows_max, int32_t x_vectors, int32_t sheet_stride, bool has_runs,
+                           bool vec_ok, bool y_kept) {
+    if (sheet_stride > 0 && vec_ok &&
+        2 * stream_buf_bytes(elem_bytes, staged_max, rows_max, x_vectors, sheet_stride, y_kept) <= kStreamMaxLds)
+        return WindowKernel::sheets;
+    return has_runs ? WindowKernel::runs : WindowKernel::positions;
+}
+
 void spmm_row_order(int64_t m, const int32_t* rowptr, std::vector<int32_t>* rows) {
     // window after window, a counting sort: one pass to size the classes, one to place the rows
     // (ascending inside a class)

@@ -106,6 +106,18 @@ int32_t two_phase_piece_groups(int64_t C, const int32_t* block_first, int32_t re
 // (one slot per block and possible vector) no longer than a quarter of the entries.
 bool window_choice(const int32_t* nv, int64_t nb, int64_t nnz, int64_t* total, int32_t* largest);
 
+// The kernel a product of the WINDOWED plan runs from: the positions of its entries, the packed runs of its row patterns, or the blocks'
+// sheets.  From the sheets where every block has one (sheet_stride > 0), vals, colidx and x allow 16-byte copies and two sets of a
+// block's buffers leave a compute unit room for two workgroups at least: each product for itself, since x and beta (a y that is kept
+// is held in the buffers too) are the call's.
+enum class WindowKernel { positions, runs, sheets };
+constexpr int64_t kStreamMaxLds = 64 * 1024;  // LDS of a workgroup that works from sheets, at most
+// LDS bytes of the values, and of all that is held, of a block of at most staged_max entries and rows_max rows.
+int64_t stream_val_bytes(int elem_bytes, int32_t staged_max);
+int64_t stream_buf_bytes(int elem_bytes, int32_t staged_max, int32_t rows_max, int32_t x_vectors, int32_t sheet_stride, bool y_kept);
+WindowKernel window_kernel(int elem_bytes, int32_t staged_max, int32_t rows_max, int32_t x_vectors, int32_t sheet_stride, bool has_runs,
+                           bool vec_ok, bool y_kept);
+
 // The chunks as the merge-path kernels take them: pairs (mp_row[p], mp_nz[p]) with every split that falls inside a row of at most
 // `snap` entries moved back to the row's first entry.  May throw std::bad_alloc.
 void merge_chunk_desc(int64_t m, const int32_t* rowptr, const std::vector<int32_t>& mp_row, const std::vector<int32_t>& mp_nz,

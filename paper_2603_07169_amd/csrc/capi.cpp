@@ -211,6 +211,11 @@ spmv::MatrixView view_of(const spmv_csr_s* h) {
     return A;
 }
 
+spmv::XWindows windows_of(const spmv_csr_s* h) {
+    return {h->d_xv_ptr, h->d_xv_start, h->d_xv_pad, h->d_lidx8, h->d_lidx, h->info.max_x_vectors,
+            h->info.lidx_patterned ? h->d_run_desc : nullptr, h->d_pat_pad, h->info.pat_cap, h->d_sheets, h->sheet_stride, h->cus};
+}
+
 // Counts the x vectors of every row block on the device, settles the plan (AUTO: ADAPTIVE or
 // WINDOWED) and, for WINDOWED, builds xv_ptr / xv_start / lidx.  Needs d_block_nz.
 // count_only: stop after the count (it also says how scattered the columns are).
@@ -962,13 +967,10 @@ spmv_status_t spmv_csr_run(spmv_handle_t h, const void* x, float* y, float alpha
             e = spmv::launch_adaptive(A, h->d_block_desc, static_cast<int32_t>(h->info.num_row_blocks),
                                       h->info.block_nnz, h->info.rows_max, x, y, s, st);
             break;
-        case SPMV_PLAN_WINDOWED: {
-            const spmv::XWindows w{h->d_xv_ptr, h->d_xv_start, h->d_xv_pad, h->d_lidx8, h->d_lidx, h->info.max_x_vectors,
-                                   h->info.lidx_patterned ? h->d_run_desc : nullptr, h->d_pat_pad, h->info.pat_cap, h->d_sheets, h->sheet_stride, h->cus};
-            e = spmv::launch_windowed(A, h->d_block_desc, static_cast<int32_t>(h->info.num_row_blocks),
-                                      h->info.block_nnz, h->max_block_entries, h->info.rows_max, w, x, y, s, st);
+        case SPMV_PLAN_WINDOWED:
+            e = spmv::launch_windowed(A, h->d_block_desc, static_cast<int32_t>(h->info.num_row_blocks), h->info.block_nnz,
+                                      h->max_block_entries, h->info.rows_max, windows_of(h), x, y, s, st);
             break;
-        }
         case SPMV_PLAN_COLBLOCK: {
             // y <- beta*y once, then every block adds its part; block b reads x from its first column on
             e = spmv::launch_scale_y(y, m, beta, st);
@@ -1288,7 +1290,9 @@ spmv_status_t spmv_selftest_reduce(const float* in_dev, float* out_dev, void* st
                                                                                                        : SPMV_OK;
 }
 
-const char* spmv_csr_main_kernel_name(spmv_handle_t h) {
+const char* spmv_csr_main_kernel_name(spmv_handle_t h) { return spmv_csr_kernel_name(h, nullptr, 0.f); }
+
+const char* spmv_csr_kernel_name(spmv_handle_t h, const void* x, float beta) {
     if (!h || !h->analyzed) return "";
     switch (h->info.plan) {
         case SPMV_PLAN_SCALAR: return spmv::scalar_kernel_name();
@@ -1296,7 +1300,9 @@ const char* spmv_csr_main_kernel_name(spmv_handle_t h) {
         case SPMV_PLAN_BINNED: return spmv::vector_kernel_name();
         case SPMV_PLAN_ADAPTIVE:
         case SPMV_PLAN_MERGE: return spmv::tile_kernel_name();
-        case SPMV_PLAN_WINDOWED: return h->info.lidx_patterned || h->d_sheets ? spmv::pattern_kernel_name() : spmv::window_kernel_name();
+        case SPMV_PLAN_WINDOWED:
+            return spmv::windowed_kernel_name(
+                spmv::windowed_kernel(view_of(h), h->max_block_entries, h->info.rows_max, windows_of(h), x, beta));
         case SPMV_PLAN_COLBLOCK: return "spmv_coo_kernel";
         case SPMV_PLAN_TWOPHASE: return h->info.tp_group > 1 ? "tp_multiply_group_kernel" : "tp_multiply_kernel";
         case SPMV_PLAN_SELL: return spmv::sell_kernel_name();

@@ -4,6 +4,8 @@
 
 #include <cstdint>
 
+#include "analysis.h"
+
 namespace spmv {
 
 struct MatrixView {
@@ -74,6 +76,8 @@ hipError_t launch_adaptive(const MatrixView& A, const int32_t* block_desc, int32
 hipError_t launch_windowed(const MatrixView& A, const int32_t* block_desc, int32_t nb,
                            int32_t block_nnz, int32_t staged_max, int32_t rows_max, const XWindows& w, const void* x,
                            float* y, Scalars s, hipStream_t st);
+// The kernel that launch_windowed launches for these arguments.
+WindowKernel windowed_kernel(const MatrixView& A, int32_t staged_max, int32_t rows_max, const XWindows& w, const void* x, float beta);
 // Analysis-time construction of the x windows.  fill == false: nv[b] = distinct x vectors of
 // block b.  fill == true: writes xv_start, xv_pad (stride x_cap >= every nv[b]) and lidx given
 // xv_ptr = exclusive prefix sums of nv.
@@ -266,8 +270,7 @@ hipError_t launch_reduce_selftest(const float* in, float* out, hipStream_t st);
 const char* scalar_kernel_name();
 const char* vector_kernel_name();
 const char* tile_kernel_name();  // kernel of the adaptive and merge plans
-const char* window_kernel_name();
-const char* pattern_kernel_name();
+const char* windowed_kernel_name(WindowKernel k);
 const char* spmm_kernel_name();
 const char* sell_kernel_name();
 

@@ -1650,6 +1650,11 @@ hipError_t launch_adaptive(const MatrixView& A, const int32_t* block_desc, int32
     return launch_tiles<F32, false>(a, tile_lds_bytes<F32>(block_nnz, rows_max), st);
 }
 
+WindowKernel windowed_kernel(const MatrixView& A, int32_t staged_max, int32_t rows_max, const XWindows& w, const void* x, float beta) {
+    return window_kernel(A.bf16 ? 2 : 4, staged_max, rows_max, w.max_vectors, w.sheets ? w.sheet_stride : 0, w.run_desc != nullptr,
+                         A.vec_ok && reinterpret_cast<uintptr_t>(x) % 16 == 0, beta != 0.f);
+}
+
 hipError_t launch_windowed(const MatrixView& A, const int32_t* block_desc, int32_t nb,
                            int32_t block_nnz, int32_t staged_max, int32_t rows_max, const XWindows& w, const void* x,
                            float* y, Scalars s, hipStream_t st) {
@@ -1671,20 +1676,16 @@ hipError_t launch_windowed(const MatrixView& A, const int32_t* block_desc, int32
     a.x_cap = w.max_vectors > 0 ? w.max_vectors : 1;
     a.x_vec_ok = reinterpret_cast<uintptr_t>(x) % 16 == 0 ? 1 : 0;
     const size_t esz = A.bf16 ? 2 : 4;
-    if (w.sheets && A.vec_ok && a.x_vec_ok) {
-        const size_t val = (esz * static_cast<size_t>(staged_max + 16) + 15) & ~size_t{15};
-        const size_t y0 = s.beta != 0.f ? (4 * static_cast<size_t>(rows_max) + 15) & ~size_t{15} : 0;
-        const size_t buf = 16 * static_cast<size_t>(a.x_cap) + val + static_cast<size_t>(w.sheet_stride) + y0;
-        if (2 * buf <= 64 * 1024) {  // two workgroups to a compute unit at least
-            a.sheets = w.sheets;
-            a.sheet_stride = w.sheet_stride;
-            a.map_bytes = sheet_map_bytes(rows_max);
-            a.val_bytes = static_cast<int32_t>(val);
-            a.buf_bytes = static_cast<int32_t>(buf);
-            const int places = stream_places(buf);
-            const bool two = places * (rows_max > 64 ? 2 : 1) <= 10 && A.nnz / 16 >= A.m;
-            return A.bf16 ? launch_stream<BF16>(a, two, places, w.cus, st) : launch_stream<F32>(a, two, places, w.cus, st);
-        }
+    if (windowed_kernel(A, staged_max, rows_max, w, x, s.beta) == WindowKernel::sheets) {
+        const int64_t buf = stream_buf_bytes(static_cast<int>(esz), staged_max, rows_max, w.max_vectors, w.sheet_stride, s.beta != 0.f);
+        a.sheets = w.sheets;
+        a.sheet_stride = w.sheet_stride;
+        a.map_bytes = sheet_map_bytes(rows_max);
+        a.val_bytes = static_cast<int32_t>(stream_val_bytes(static_cast<int>(esz), staged_max));
+        a.buf_bytes = static_cast<int32_t>(buf);
+        const int places = stream_places(static_cast<size_t>(buf));
+        const bool two = places * (rows_max > 64 ? 2 : 1) <= 10 && A.nnz / 16 >= A.m;
+        return A.bf16 ? launch_stream<BF16>(a, two, places, w.cus, st) : launch_stream<F32>(a, two, places, w.cus, st);
     }
     const size_t lds = 16 * static_cast<size_t>(a.x_cap) + (esz + 2) * static_cast<size_t>(staged_max + 16) +
                        (sizeof(int) + sizeof(float)) * static_cast<size_t>(rows_max + 2) + 2 * static_cast<size_t>(a.pt_cap);
@@ -1772,7 +1773,8 @@ hipError_t launch_reduce_selftest(const float* in, float* out, hipStream_t st) {
 const char* scalar_kernel_name() { return "spmv_scalar_kernel"; }
 const char* vector_kernel_name() { return "spmv_vector_kernel"; }
 const char* tile_kernel_name() { return "spmv_tile_kernel"; }
-const char* window_kernel_name() { return "spmv_window_kernel"; }
-const char* pattern_kernel_name() { return "spmv_pattern_kernel"; }
+const char* windowed_kernel_name(WindowKernel k) {
+    return k == WindowKernel::sheets ? "spmv_pattern_kernel" : k == WindowKernel::runs ? "spmv_pattern_block_kernel" : "spmv_window_kernel";
+}
 
 }  // namespace spmv

@@ -30,7 +30,7 @@ SPMV_STATIC_MAX_ITEMS = 2 ** 28 - 2048
 
 EXPORTS = [
     "spmv_csr_create", "spmv_csr_analyze", "spmv_csr_run", "spmv_csr_refresh_values", "spmm_csr_run", "spmv_coo_run", "spmv_csc_run", "spmv_ell_run", "spmv_csr_run_static", "spmv_destroy", "spmv_csr_get_analysis_info",
-    "spmv_csr_get_analysis", "spmv_analyze_host", "spmv_selftest_reduce", "spmv_csr_main_kernel_name",
+    "spmv_csr_get_analysis", "spmv_analyze_host", "spmv_selftest_reduce", "spmv_csr_main_kernel_name", "spmv_csr_kernel_name",
     "spmm_csr_kernel_name", "spmv_status_string", "spmv_last_hip_error",
 ]
 
@@ -118,6 +118,8 @@ def _load():
         getattr(lib, name).restype = C.c_int
     lib.spmv_csr_main_kernel_name.argtypes = [vp]
     lib.spmv_csr_main_kernel_name.restype = C.c_char_p
+    lib.spmv_csr_kernel_name.argtypes = [vp, vp, C.c_float]
+    lib.spmv_csr_kernel_name.restype = C.c_char_p
     lib.spmm_csr_kernel_name.argtypes = [vp, vp, i64, vp, i64, i64]
     lib.spmm_csr_kernel_name.restype = C.c_char_p
     lib.spmv_status_string.argtypes = [C.c_int]
@@ -267,6 +269,10 @@ def spmv_selftest_reduce(in_dev, out_dev, stream=None):
 
 def spmv_csr_main_kernel_name(handle) -> str:
     return _load().spmv_csr_main_kernel_name(handle).decode()
+
+
+def spmv_csr_kernel_name(handle, x, beta) -> str:
+    return _load().spmv_csr_kernel_name(handle, x, beta).decode()
 
 
 def spmm_csr_kernel_name(handle, B, ldb, C_, ldc, K) -> str:

@@ -62,7 +62,7 @@ def test_create_argument_errors():
     assert s.spmv_csr_refresh_values(h) == s.SPMV_ERR_NOT_ANALYZED
     assert s.spmv_csr_refresh_values(None) == s.SPMV_ERR_INVALID_ARG
     assert s.spmv_csr_get_analysis_info(h)[0] == s.SPMV_ERR_NOT_ANALYZED
-    assert s.spmv_csr_main_kernel_name(h) == ""
+    assert s.spmv_csr_main_kernel_name(h) == "" and s.spmv_csr_kernel_name(h, A, 1.0) == ""
     assert s.spmv_destroy(h) == s.SPMV_OK
     assert s.spmv_destroy(None) == s.SPMV_OK
     assert s.spmv_csr_analyze(None) == s.SPMV_ERR_INVALID_ARG

@@ -232,7 +232,11 @@ def test_row_patterns_of_window_positions(dtype, shape):
     A = d.matrix(params)
     assert A.info.plan == s.SPMV_PLAN_WINDOWED
     assert A.info.lidx_patterned == (0 if shape == "reversed" else 1)
-    assert s.spmv_csr_main_kernel_name(A.handle) == ("spmv_window_kernel" if shape == "reversed" else "spmv_pattern_kernel")
+    kernel = {"reversed": "spmv_window_kernel", "unaligned": "spmv_pattern_block_kernel"}.get(shape, "spmv_pattern_kernel")
+    assert s.spmv_csr_main_kernel_name(A.handle) == kernel
+    assert s.spmv_csr_kernel_name(A.handle, d.x.data_ptr(), q.beta) == kernel
+    if kernel == "spmv_pattern_kernel":       # an x off its alignment goes by the packed runs
+        assert s.spmv_csr_kernel_name(A.handle, d.x.data_ptr() + 4, q.beta) == "spmv_pattern_block_kernel"
     got = A.analysis()
     ve = 8 if dtype == "bf16" else 4
     _, _, _, lidx = oracle.x_windows(q.rowptr, q.colidx, got["row_blocks"], A.info.block_nnz, ve)

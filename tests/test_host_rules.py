@@ -43,6 +43,9 @@ int choice(const int32_t* pk, int64_t gk, const int32_t* pp, int64_t gp, int64_t
     return spmv::spmm_pairs_choice(spmv::spmm_group_steps(vector<int32_t>(pk, pk + 2 * gk + 2), 16),
                                    spmv::spmm_group_steps(vector<int32_t>(pp, pp + 2 * gp + 2), 32), blocks, m, K, vec != 0);
 }
+int window_kernel(int elem, int staged, int rows, int xv, int sheet, int runs, int vec, int kept) {
+    return static_cast<int>(spmv::window_kernel(elem, staged, rows, xv, sheet, runs != 0, vec != 0, kept != 0));
+}
 }
 """
 
@@ -215,3 +218,23 @@ def test_choice_of_the_form(rules):
     assert not pick(m, *usual, 16, True) and not pick(m, *usual, 64, True) and pick(m, *usual, 4096, True) and pick(m, *usual, 333, False)
     tail = layouts(np.where(np.arange(m) % 200 == 0, 600, 20))
     assert not any(pick(m, *tail, K, True) for K in (16, 64, 1024, 4096))
+
+
+POSITIONS, RUNS, SHEETS = range(3)
+
+
+@pytest.mark.parametrize("elem", [2, 4])
+@pytest.mark.parametrize("runs", [0, 1])
+def test_kernel_of_a_windowed_product(rules, elem, runs):
+    """From sheets only where there are some, the call's arrays allow 16-byte copies and two blocks' buffers (x vectors, values
+    and 16 more, sheet, kept y) fit 64 KB; otherwise from the packed runs, or the positions."""
+    other = RUNS if runs else POSITIONS
+    for staged, rows, sheet in ((1024, 64, 192), (4096, 256, 304), (4095, 1023, 1040)):
+        held = (elem * (staged + 16) + 15) // 16 * 16 + sheet
+        kept = (4 * rows + 15) // 16 * 16
+        fit, fit_kept = (32768 - held) // 16, (32768 - held - kept) // 16   # most x vectors
+        k = lambda xv, vec=1, y=0, s=sheet: rules.window_kernel(elem, staged, rows, xv, s, runs, vec, y)
+        assert k(fit) == SHEETS and k(fit + 1) == other
+        assert k(fit_kept, y=1) == SHEETS and k(fit_kept + 1, y=1) == other and k(fit_kept + 1) == SHEETS
+        assert k(fit, vec=0) == other and k(fit, s=0) == other
+        assert k(0) == k(1) == SHEETS
