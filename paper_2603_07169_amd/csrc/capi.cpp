@@ -62,7 +62,7 @@ struct spmv_csr_s {
     int32_t* d_xv_pad = nullptr;
     uint16_t* d_lidx = nullptr;
     uint16_t* d_lidx8 = nullptr;  // lidx[8g], kept when the window positions are grouped (info.lidx_grouped)
-    int32_t* d_run_desc = nullptr;  // row patterns of the window positions (of use when info.lidx_patterned), then analysis scratch
+    int32_t* d_run_desc = nullptr;  // row patterns of the window positions, kept when info.lidx_patterned
     uint16_t* d_pat_pad = nullptr;
     unsigned char* d_sheets = nullptr;  // the blocks' sheets, where every block has one
     int32_t sheet_stride = 0;
@@ -213,7 +213,7 @@ spmv::MatrixView view_of(const spmv_csr_s* h) {
 
 spmv::XWindows windows_of(const spmv_csr_s* h) {
     return {h->d_xv_ptr, h->d_xv_start, h->d_xv_pad, h->d_lidx8, h->d_lidx, h->info.max_x_vectors,
-            h->info.lidx_patterned ? h->d_run_desc : nullptr, h->d_pat_pad, h->info.pat_cap, h->d_sheets, h->sheet_stride, h->cus};
+            h->d_run_desc, h->d_pat_pad, h->info.pat_cap, h->d_sheets, h->sheet_stride, h->cus};
 }
 
 // Counts the x vectors of every row block on the device, settles the plan (AUTO: ADAPTIVE or
@@ -377,50 +377,64 @@ spmv_status_t build_x_windows(spmv_csr_s* h, bool forced, bool count_only, const
             unsigned long long covered;
             int32_t max_table, max_sheet;
         } counts{0, 0, 0};
-        // one allocation, kept with the handle: the packed runs, then scratch (the counts, the sheets' runs, bytes and maps)
         const size_t NB = static_cast<size_t>(nb);
-        const int32_t map_bytes = spmv::sheet_map_bytes(a->info.rows_max);
-        const size_t counts_at = 32 * NB, runs_at = counts_at + 64, need_at = runs_at + sizeof(spmv::SheetRun) * spmv::kMaxSheetRuns * NB,
-                     map_at = need_at + 4 * NB;
-        if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_run_desc), map_at + NB * static_cast<size_t>(map_bytes))))
+        Counts* d_counts = nullptr;
+        if (hip_failed(hipMalloc(reinterpret_cast<void**>(&d_counts), sizeof(Counts))) ||
+            hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_run_desc), 32 * NB))) {
+            (void)hipFree(d_counts);
             return SPMV_ERR_ALLOC;
-        char* const scratch = reinterpret_cast<char*>(h->d_run_desc);
-        Counts* const d_counts = reinterpret_cast<Counts*>(scratch + counts_at);
-        const spmv::SheetPlan sheets{h->dtype == SPMV_F32 ? 4 : 2, map_bytes, &d_counts->max_sheet, reinterpret_cast<int32_t*>(scratch + need_at),
-                                     reinterpret_cast<unsigned char*>(scratch + map_at), reinterpret_cast<spmv::SheetRun*>(scratch + runs_at)};
+        }
+        // what the sheets are planned in (runs, bytes, maps), given back below; without it, or without memory for the sheets, the
+        // product runs from the packed runs or the positions
+        const int elem_bytes = h->dtype == SPMV_F32 ? 4 : 2;
+        auto buffers_fit = [&](int32_t stride) {
+            return spmv::window_kernel(elem_bytes, h->max_block_entries, a->info.rows_max, largest, stride, false, h->vec_ok, false) ==
+                   spmv::WindowKernel::sheets;
+        };
+        const int32_t map_bytes = spmv::sheet_map_bytes(a->info.rows_max);
+        const size_t need_at = sizeof(spmv::SheetRun) * spmv::kMaxSheetRuns * NB, map_at = need_at + 4 * NB;
+        char* scratch = nullptr;
+        if (buffers_fit(map_bytes) &&
+            hip_failed(hipMalloc(reinterpret_cast<void**>(&scratch), map_at + NB * static_cast<size_t>(map_bytes))))
+            scratch = nullptr;
+        spmv::SheetPlan sheets{};
+        if (scratch)
+            sheets = {elem_bytes, map_bytes, &d_counts->max_sheet, reinterpret_cast<int32_t*>(scratch + need_at),
+                      reinterpret_cast<unsigned char*>(scratch + map_at), reinterpret_cast<spmv::SheetRun*>(scratch)};
         bool failed = hip_failed(hipMemcpy(d_counts, &counts, sizeof counts, hipMemcpyHostToDevice));
         failed = failed || hip_failed(spmv::launch_pattern_build(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx,
                                                                  a->info.block_nnz, false, h->d_run_desc, &d_counts->max_table,
-                                                                 &d_counts->covered, nullptr, 0, &sheets, nullptr));
+                                                                 &d_counts->covered, nullptr, 0, scratch ? &sheets : nullptr, nullptr));
         failed = failed || hip_failed(hipMemcpy(&counts, d_counts, sizeof counts, hipMemcpyDeviceToHost));
-        const int64_t stride = (static_cast<int64_t>(counts.max_sheet) + 15) & ~int64_t{15};
-        if (!failed && counts.max_sheet < INT32_MAX && nb * stride <= kMaxCount) {
-            int dev = 0;
-            if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_sheets), NB * static_cast<size_t>(stride)))) {
-                h->d_sheets = nullptr;  // the product then runs from the positions or the packed runs
-            } else {
-                failed = hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev)) ||
-                         hip_failed(spmv::launch_sheet_fill(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx, sheets,
-                                                            static_cast<int32_t>(stride), h->d_sheets, nullptr));
-                h->sheet_stride = static_cast<int32_t>(stride);
-            }
-        }
-        if (failed) return SPMV_ERR_HIP;
+        (void)hipFree(d_counts);
         const int64_t covered = static_cast<int64_t>(counts.covered);
         const int32_t pt_cap = counts.max_table > 0 ? (counts.max_table + 7) / 8 * 8 : 8;
-        if (h->nnz > 0 && 2 * covered >= h->nnz && nb * static_cast<int64_t>(pt_cap) <= kMaxCount) {
-            if (hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_pat_pad), 2 * static_cast<size_t>(nb) * static_cast<size_t>(pt_cap))))
-                return SPMV_ERR_ALLOC;
-            if (hip_failed(spmv::launch_pattern_build(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx, a->info.block_nnz,
-                                                      true, h->d_run_desc, nullptr, nullptr, h->d_pat_pad, pt_cap, nullptr, nullptr)))
-                return SPMV_ERR_HIP;
+        bool no_memory = false;
+        if (!failed && h->nnz > 0 && 2 * covered >= h->nnz && nb * static_cast<int64_t>(pt_cap) <= kMaxCount) {
+            no_memory = hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_pat_pad), 2 * NB * static_cast<size_t>(pt_cap)));
+            failed = no_memory || hip_failed(spmv::launch_pattern_build(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx,
+                                                                        a->info.block_nnz, true, h->d_run_desc, nullptr, nullptr,
+                                                                        h->d_pat_pad, pt_cap, nullptr, nullptr));
             a->info.lidx_patterned = 1;
             a->info.pat_cap = pt_cap;
             a->info.pat_entries = covered;
-        } else if (!h->d_sheets) {
+        } else {
             (void)hipFree(h->d_run_desc);
             h->d_run_desc = nullptr;
         }
+        if (!failed && scratch && counts.max_sheet < INT32_MAX) {
+            const int32_t stride = (counts.max_sheet + 15) & ~15;
+            int dev = 0;
+            if (nb * static_cast<int64_t>(stride) <= kMaxCount && buffers_fit(stride) &&
+                !hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_sheets), NB * static_cast<size_t>(stride)))) {
+                h->sheet_stride = stride;
+                failed = hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev)) ||
+                         hip_failed(spmv::launch_sheet_fill(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx, sheets, stride,
+                                                            h->d_sheets, nullptr));
+            }
+        }
+        (void)hipFree(scratch);  // waits for the kernels that read it
+        if (failed) return no_memory ? SPMV_ERR_ALLOC : SPMV_ERR_HIP;
     }
     a->info.plan = SPMV_PLAN_WINDOWED;
     a->info.num_x_vectors = total;

@@ -163,8 +163,8 @@ hipError_t launch_lidx_groups(const uint16_t* lidx, int32_t groups, uint16_t* li
 hipError_t launch_pattern_build(const int32_t* block_desc, int32_t nb, const int32_t* rowptr, const uint16_t* lidx, int32_t block_nnz,
                                 bool fill, int32_t* run_desc, int32_t* max_table, unsigned long long* covered, uint16_t* pat_pad,
                                 int32_t pt_cap, const struct SheetPlan* sheets, hipStream_t st);
-// With fill == false the blocks' sheets are planned as well: what launch_sheet_fill reads, and *largest (device int32, 0 on entry) =
-// bytes of the largest, INT32_MAX if a block cannot have one.
+// With fill == false and sheets not null the blocks' sheets are planned as well: what launch_sheet_fill reads, and *largest (device
+// int32, 0 on entry) = bytes of the largest, INT32_MAX if a block cannot have one.
 struct SheetPlan {
     int32_t elem_bytes, map_bytes;
     int32_t* largest;

@@ -1351,7 +1351,7 @@ __global__ __launch_bounds__(64) void sheet_fill_kernel(const int32_t* __restric
 }
 
 // *max_table = the longest pattern list of a patterned block, *covered = the entries of the patterned blocks, *max_sheet = the
-// largest sheet, INT32_MAX when a block has none (all cleared by the caller).  A pass of its own over the packed runs: one atomic per wavefront instead of two per block
+// largest sheet, INT32_MAX when a block has none (all cleared by the caller; with sheet_need null the sheets are left out).  A pass of its own over the packed runs: one atomic per wavefront instead of two per block
 // on the same two addresses.
 __global__ __launch_bounds__(256) void pattern_totals_kernel(const int32_t* __restrict__ block_desc, const int32_t* __restrict__ run_desc,
                                                              int nb, const int32_t* __restrict__ sheet_need, int32_t* max_table,
@@ -1366,8 +1366,10 @@ __global__ __launch_bounds__(256) void pattern_totals_kernel(const int32_t* __re
             table = t > table ? t : table;
             entries += static_cast<unsigned long long>(block_desc[2 * b + 3] - block_desc[2 * b + 1]);
         }
-        const int need = sheet_need[b] > 0 ? sheet_need[b] : INT32_MAX;
-        sheet = need > sheet ? need : sheet;
+        if (sheet_need) {
+            const int need = sheet_need[b] > 0 ? sheet_need[b] : INT32_MAX;
+            sheet = need > sheet ? need : sheet;
+        }
     }
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -1377,7 +1379,7 @@ __global__ __launch_bounds__(256) void pattern_totals_kernel(const int32_t* __re
         entries += __shfl_xor(entries, d);
     }
     if ((threadIdx.x & 63) == 0) {
-        atomicMax(max_sheet, sheet);
+        if (sheet_need) atomicMax(max_sheet, sheet);
         if (entries > 0) {
             atomicMax(max_table, table);
             atomicAdd(covered, entries);
