@@ -244,8 +244,9 @@ spmv_status_t spmv_csr_create(spmv_handle_t* out, int64_t m, int64_t n, int64_t 
  *     run 1, .., then zeros (pat_cap = the longest such list rounded up to a multiple of 8).  run() then reads neither the
  *     positions nor the row offsets of a patterned block: the position of entry j of the q-th row of a run is
  *     base + q * stride + rel[j].  Blocks without a pattern are served from lidx as before.
- *     Where every block has at most 16 such runs (and meets the other conditions), whether lidx_patterned is 1 or 0, the
- *     library also keeps the runs and lists in one piece per block, and run() reads those; they are not read back.
+ *     Where every block has at most 16 such runs (and meets the other conditions), whether lidx_patterned is 1 or 0, and the
+ *     rows' length and number do not speak against it, the library also keeps the runs and lists in one piece per block, and
+ *     run() reads those; they are not read back.
  *   - column blocks (plan AUTO that arrived at ADAPTIVE or MERGE, or plan COLBLOCK; built on the
  *     device).  Columns are cut into blocks of W = 4 MiB / element size columns; the entries are
  *     regrouped block after block, keeping their row-major order inside a block, each with its

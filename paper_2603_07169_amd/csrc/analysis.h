@@ -21,6 +21,7 @@ struct Analysis {
     std::vector<int32_t> row_blocks;  // [nb+1]
     std::vector<int32_t> mp_row;      // [P+1]
     std::vector<int32_t> mp_nz;       // [P+1]
+    int32_t common_len = 0;           // the row length (at most 64) whose rows hold half of the entries or more, 0 if there is none
     // How scattered the columns are, from the count pass of the x windows (-1: not counted): the distinct
     // 16-byte x vectors of the row blocks, summed, and the entries of the blocks that were counted
     // (all but single rows longer than block_nnz).
@@ -117,6 +118,25 @@ int64_t stream_val_bytes(int elem_bytes, int32_t staged_max);
 int64_t stream_buf_bytes(int elem_bytes, int32_t staged_max, int32_t rows_max, int32_t x_vectors, int32_t sheet_stride, bool y_kept);
 WindowKernel window_kernel(int elem_bytes, int32_t staged_max, int32_t rows_max, int32_t x_vectors, int32_t sheet_stride, bool has_runs,
                            bool vec_ok, bool y_kept);
+
+// Whether a windowed matrix gets sheets at all.  Not where the kernel that works from them was slower than the one it stands in for
+// (us per product out of a graph, every row of one length, sheets / packed runs, and beside them what a neighbouring length takes).
+//   - Rows that begin on the same LDS banks, read a row per lane, or half a row: FP32 64 entries 5.3 / 3.9 (1 M entries), 16.4 / 8.7
+//     (6 M), 50.1 / 22.6 (24 M; 62 entries 19.7 / 20.0); 48 entries 4.2 / 3.9, 8.2 / 7.7, 20.8 / 20.7 (52: 3.7 / 3.9, 6.8 / 7.3); 32
+//     entries in small blocks 4.8 / 3.9 (28: 3.3 / 4.0), while blocks of 128 of them break even, 10.5 / 10.5 and 30.7 / 31.6; bf16 64
+//     entries in small blocks 4.5 / 3.7 (62: 3.9 / 4.0), in blocks of 64 6.7 / 7.0; 16 entries in blocks of 256 5.6 / 4.7, 15.0 / 12.3 (20:
+//     12.0 / 16.9), in blocks of 64 3.4 / 3.7.  Scattered columns in rows of 64, which have sheets of sixteen lists: FP32 5.1 / 3.7,
+//     bf16 5.3 / 3.7 from the positions; of 61: 4.1 / 4.4, 3.9 / 4.1.
+//   - Rows of 32 entries or more in so few blocks that a compute unit gets one (bf16: two), where a lane's walk along a row is what the
+//     product waits for: 250 k entries FP32 40 / 48 / 56 / 62 entries 2.9 / 3.1 / 3.0 / 3.1 against 2.8 / 2.9 / 2.6 / 2.8, bf16 36 / 40 / 56 / 62
+//     3.0 / 3.2 / 3.3 / 3.6 against 2.6 / 2.8 / 2.8 / 3.1; 500 k entries FP32 3.4 / 3.7 / 3.6 / 3.8 against 3.5 / 3.5 / 3.6 / 3.7, bf16 3.4 / 3.5 / 3.8 /
+//     4.1 against 3.3 / 3.3 / 3.5 / 3.4; 1 M entries FP32 3.9 / - / 4.0 / 4.0 against 4.1 / - / 4.2 / 4.5, bf16 3.6 / 3.6 / 3.9 / 4.0 against 4.0 / 3.9 / 3.9 / 4.3.
+bool sheets_pay(int elem_bytes, int64_t m, int64_t nnz, int64_t nb, int32_t block_nnz, int32_t rows_max, int32_t common_len, int32_t cus);
+// Lanes of the sheets' kernel that share a row (1 or 2); places: workgroups that a compute unit holds by their LDS.  Two where that is
+// ten wavefronts or fewer and rows have 16 entries or more (27 points FP32 46.8 -> 45.3 us, 49 points bf16 32.0 -> 26.0; elsewhere two cost:
+// 27 points bf16 25.8 -> 27.1, 5 points 10.6 -> 15.4), and for FP32 rows of 24 entries in large blocks, which meet on the banks whole but
+// not halved (3 M / 12 M entries 4.9 -> 4.3 / 12.6 -> 11.5 us).
+int stream_lanes(int elem_bytes, int64_t m, int64_t nnz, int32_t rows_max, int places, int32_t common_len);
 
 // The chunks as the merge-path kernels take them: pairs (mp_row[p], mp_nz[p]) with every split that falls inside a row of at most
 // `snap` entries moved back to the row's first entry.  May throw std::bad_alloc.

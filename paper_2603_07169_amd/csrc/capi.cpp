@@ -66,7 +66,8 @@ struct spmv_csr_s {
     uint16_t* d_pat_pad = nullptr;
     unsigned char* d_sheets = nullptr;  // the blocks' sheets, where every block has one
     int32_t sheet_stride = 0;
-    int32_t cus = 0;  // compute units of the device (with sheets)
+    int32_t cus = 0;  // compute units of the device, and Analysis::common_len (of use with sheets)
+    int32_t common_len = 0;
     // the two-pass plan (TWOPHASE)
     int32_t* d_tp_desc = nullptr;     // pairs (tp_row[p], tp_nz[p])
     int32_t* d_tp_piece_c = nullptr;
@@ -213,7 +214,7 @@ spmv::MatrixView view_of(const spmv_csr_s* h) {
 
 spmv::XWindows windows_of(const spmv_csr_s* h) {
     return {h->d_xv_ptr, h->d_xv_start, h->d_xv_pad, h->d_lidx8, h->d_lidx, h->info.max_x_vectors,
-            h->d_run_desc, h->d_pat_pad, h->info.pat_cap, h->d_sheets, h->sheet_stride, h->cus};
+            h->d_run_desc, h->d_pat_pad, h->info.pat_cap, h->d_sheets, h->sheet_stride, h->cus, h->common_len};
 }
 
 // Counts the x vectors of every row block on the device, settles the plan (AUTO: ADAPTIVE or
@@ -394,14 +395,18 @@ spmv_status_t build_x_windows(spmv_csr_s* h, bool forced, bool count_only, const
         const int32_t map_bytes = spmv::sheet_map_bytes(a->info.rows_max);
         const size_t need_at = sizeof(spmv::SheetRun) * spmv::kMaxSheetRuns * NB, map_at = need_at + 4 * NB;
         char* scratch = nullptr;
-        if (buffers_fit(map_bytes) &&
+        int dev = 0;
+        bool failed = hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev));
+        h->common_len = a->common_len;
+        if (!failed && buffers_fit(map_bytes) &&
+            spmv::sheets_pay(elem_bytes, h->m, h->nnz, nb, a->info.block_nnz, a->info.rows_max, a->common_len, h->cus) &&
             hip_failed(hipMalloc(reinterpret_cast<void**>(&scratch), map_at + NB * static_cast<size_t>(map_bytes))))
             scratch = nullptr;
         spmv::SheetPlan sheets{};
         if (scratch)
             sheets = {elem_bytes, map_bytes, &d_counts->max_sheet, reinterpret_cast<int32_t*>(scratch + need_at),
                       reinterpret_cast<unsigned char*>(scratch + map_at), reinterpret_cast<spmv::SheetRun*>(scratch)};
-        bool failed = hip_failed(hipMemcpy(d_counts, &counts, sizeof counts, hipMemcpyHostToDevice));
+        failed = failed || hip_failed(hipMemcpy(d_counts, &counts, sizeof counts, hipMemcpyHostToDevice));
         failed = failed || hip_failed(spmv::launch_pattern_build(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx,
                                                                  a->info.block_nnz, false, h->d_run_desc, &d_counts->max_table,
                                                                  &d_counts->covered, nullptr, 0, scratch ? &sheets : nullptr, nullptr));
@@ -424,12 +429,10 @@ spmv_status_t build_x_windows(spmv_csr_s* h, bool forced, bool count_only, const
         }
         if (!failed && scratch && counts.max_sheet < INT32_MAX) {
             const int32_t stride = (counts.max_sheet + 15) & ~15;
-            int dev = 0;
             if (nb * static_cast<int64_t>(stride) <= kMaxCount && buffers_fit(stride) &&
                 !hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_sheets), NB * static_cast<size_t>(stride)))) {
                 h->sheet_stride = stride;
-                failed = hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev)) ||
-                         hip_failed(spmv::launch_sheet_fill(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx, sheets, stride,
+                failed = hip_failed(spmv::launch_sheet_fill(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx, sheets, stride,
                                                             h->d_sheets, nullptr));
             }
         }

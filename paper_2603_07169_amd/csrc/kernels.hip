@@ -786,8 +786,7 @@ __global__ __launch_bounds__(WG, (XPL == 4 && NG == 2) ? 4 : 8) void spmv_patter
 //     what is done once per row and once per block is done by half as many lanes as with two lanes a row: 8.0 M vector instructions
 //     instead of 14.1 M.  Pipelining alone, two lanes a row and one entry at a time, was slower than no pipeline (34.4 us).
 //   - Values and pattern are read from LDS up to 16 entries at a time.
-//   - Where LDS leaves a compute unit ten wavefronts or fewer, two lanes share a row of 16 entries or more (P = 2): FP32 27 points 46.8 ->
-//     45.3 us, bf16 49 points (64 rows a block) 32.0 -> 26.0; elsewhere it costs (27 points, bf16 25.8 -> 27.1, 5 points 10.6 -> 15.4).
+//   - Two lanes share a row (P = 2) where stream_lanes() says so; sheets_pay() says which matrices get sheets.
 //   - x vectors are asked for before the values (the other way round 25.7 -> 27.2 us); more workgroups than the device holds, so that the
 //     hardware deals the rest out: 30 to 40 % slower, since nothing overlaps a workgroup's first block.
 constexpr int kStreamRows = 128;  // rows of a sweep
@@ -1686,7 +1685,7 @@ hipError_t launch_windowed(const MatrixView& A, const int32_t* block_desc, int32
         a.val_bytes = static_cast<int32_t>(stream_val_bytes(static_cast<int>(esz), staged_max));
         a.buf_bytes = static_cast<int32_t>(buf);
         const int places = stream_places(static_cast<size_t>(buf));
-        const bool two = places * (rows_max > 64 ? 2 : 1) <= 10 && A.nnz / 16 >= A.m;
+        const bool two = stream_lanes(static_cast<int>(esz), A.m, A.nnz, rows_max, places, w.common_len) == 2;
         return A.bf16 ? launch_stream<BF16>(a, two, places, w.cus, st) : launch_stream<F32>(a, two, places, w.cus, st);
     }
     const size_t lds = 16 * static_cast<size_t>(a.x_cap) + (esz + 2) * static_cast<size_t>(staged_max + 16) +

@@ -74,6 +74,28 @@ def test_rows_of_a_block(rows_max):
     run_both(p, s.SPMV_PLAN_WINDOWED, dict(plan=s.SPMV_PLAN_WINDOWED, rows_max=rows_max, block_nnz=min(8192, 5 * rows_max)))
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kind", ["banded", "scattered"])
+@pytest.mark.parametrize("length", [60, 64])
+def test_rows_of_one_length(length, kind, dtype):
+    """Rows of 64 entries meet on the same LDS banks: they go by the packed runs, or by their positions where nothing repeats; rows of
+    60 go by their sheets, unless a block has more than sixteen different ones."""
+    m, rng = 10_000, np.random.Generator(np.random.Philox(key=[np.uint64(length), np.uint64(1)]))
+    n = m + 128
+    first = np.arange(m)[:, None]
+    if kind == "banded":
+        cols = first + np.sort(rng.choice(128, length, replace=False))
+    else:
+        cols = first + np.sort(rng.random((m, 128)).argsort(1)[:, :length], 1)
+    ints = lambda k: rng.integers(-4, 5, k).astype(np.float32)
+    vals, x, y0 = ints(m * length), ints(n), ints(m)
+    if dtype == "bf16":
+        vals, x = w.f32_to_bf16_bits(vals), w.f32_to_bf16_bits(x)
+    p = w.CsrProblem(f"rows_of_{length}_{kind}", dtype, m, n, (length * np.arange(m + 1)).astype(np.int32), cols.reshape(-1).astype(np.int32), vals, x, y0, 1.0, 2.0)
+    kernel = "spmv_window_kernel" if kind == "scattered" else "spmv_pattern_block_kernel" if length == 64 else "spmv_pattern_kernel"
+    run_both(p, s.SPMV_PLAN_WINDOWED, dict(plan=s.SPMV_PLAN_WINDOWED, block_nnz=1024, rows_max=64), kernel)
+
+
 def test_planning_memory_is_given_back():
     """250000 blocks of one row: a handle keeps about 40 MB for them; the sheets' plan takes 69 MB more while it is made."""
     p = grid(500, 500, FIVE, "f32")
@@ -89,11 +111,12 @@ def test_planning_memory_is_given_back():
     assert kept < 64 << 20, kept
 
 
-def run_both(p, plan, params=None):
+def run_both(p, plan, params=None, kernel=None):
     print("case", p.name, p.dtype, p.nnz, flush=True)
     aligned, general = DeviceProblem(p), DeviceProblem(p, offset_elems=1)
     params = params or dict(plan=plan)
     A, G = aligned.matrix(params), general.matrix(params)
+    assert kernel is None or s.spmv_csr_main_kernel_name(A.handle) == kernel
     for beta in (0.0, 2.0):
         want, _ = reference(p, 1.0, beta)
         got = aligned.run(A, 1.0, beta).astype(np.float64)

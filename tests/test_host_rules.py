@@ -46,6 +46,18 @@ int choice(const int32_t* pk, int64_t gk, const int32_t* pp, int64_t gp, int64_t
 int window_kernel(int elem, int staged, int rows, int xv, int sheet, int runs, int vec, int kept) {
     return static_cast<int>(spmv::window_kernel(elem, staged, rows, xv, sheet, runs != 0, vec != 0, kept != 0));
 }
+int sheets_pay(int elem, int64_t m, int64_t nnz, int64_t nb, int block_nnz, int rows_max, int common, int cus) {
+    return spmv::sheets_pay(elem, m, nnz, nb, block_nnz, rows_max, common, cus);
+}
+int stream_lanes(int elem, int64_t m, int64_t nnz, int rows_max, int places, int common) {
+    return spmv::stream_lanes(elem, m, nnz, rows_max, places, common);
+}
+int common_len(int64_t m, const int32_t* rp) {
+    spmv::Analysis a;
+    spmv_analyze_params_t p;
+    if (spmv::resolve_params(nullptr, &p) != SPMV_OK || spmv::analyze_rowptr(m, 8, rp[m], rp, p, &a, false) != SPMV_OK) return -1;
+    return a.common_len;
+}
 }
 """
 
@@ -238,3 +250,34 @@ def test_kernel_of_a_windowed_product(rules, elem, runs):
         assert k(fit_kept, y=1) == SHEETS and k(fit_kept + 1, y=1) == other and k(fit_kept + 1) == SHEETS
         assert k(fit, vec=0) == other and k(fit, s=0) == other
         assert k(0) == k(1) == SHEETS
+
+
+@pytest.mark.parametrize("elem", [2, 4])
+def test_which_matrices_get_sheets(rules, elem):
+    """Not for rows of one length that meet on the same LDS banks, nor for long rows in a few blocks."""
+    pay = lambda common, nnz, bn, rm, nb=10**6, m=None: rules.sheets_pay(elem, i64(m or nnz // max(common, 1)), i64(nnz), i64(nb), bn, rm, common, 256)
+    small = {4: {32, 48, 64}, 2: {64}}[elem]                  # blocks of 1024 entries and 64 rows
+    large = {4: {48, 64}, 2: {16}}[elem]                      # blocks as default_tile_shape makes them
+    for L in range(65):
+        assert pay(L, 1 << 20, 1024, 64) == (L not in small)
+        rm = 256 if L <= 16 else 128 if L <= 32 else 64
+        assert pay(L, 1 << 24, max(2048, (rm * L + 7) // 8 * 8), rm) == (L not in large)
+    few = 256 if elem == 4 else 512
+    for mean, none in ((31, False), (32, True), (61, True)):
+        assert pay(0, 100_000 * mean, 1024, 64, nb=few, m=100_000) == (not none)
+        assert pay(0, 100_000 * mean, 1024, 64, nb=few + 1, m=100_000)
+
+
+def test_lanes_of_a_row(rules):
+    lanes = lambda elem, mean, rm, places, common=0: rules.stream_lanes(elem, i64(1000), i64(1000 * mean), rm, places, common)
+    for elem in (2, 4):
+        assert [lanes(elem, 16, 128, p) for p in (5, 6)] == [2, 1] and [lanes(elem, 16, 64, p) for p in (10, 11)] == [2, 1]
+        assert lanes(elem, 15, 128, 2) == 1
+    assert lanes(4, 24, 128, 9, 24) == 2 and lanes(4, 24, 64, 11, 24) == 1 and lanes(2, 24, 128, 9, 24) == 1
+
+
+@pytest.mark.parametrize("lens,want", [([64] * 9, 64), ([65] * 9, 0), ([0] * 9, 0), ([32] * 8 + [64] * 4, 64), ([32] * 8 + [64] * 3, 32),
+                                       ([5] * 100 + [4] * 20 + [3], 5), (list(range(1, 60)), 0), ([16] * 10 + [161], 0)])
+def test_common_row_length(rules, lens, want):
+    rp = rowptr_of(lens)
+    assert rules.common_len(i64(len(lens)), P(rp)) == want
