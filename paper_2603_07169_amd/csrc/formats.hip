@@ -446,10 +446,9 @@ hipError_t launch_ell_tile(int32_t m, int32_t width, const int32_t* col_ids, con
     rows = rows > kWG ? kWG : rows & ~7;
     // The row phase gives a row G lanes (1 up to 16 slots, 2 up to 32, 4 up to 64) and takes kWG / G rows a sweep.  A last sweep
     // that is less than three quarters full is left to the next tile: of the 144 rows of 27 slots that fit, 16 made a sweep
-    // of their own (2 M rows, bf16, with the row phase of the CSR tiles, as are the figures below: 82 -> 67 us with 128; two dies sharing a stretch of rows less is 2 of the 15).
-    // 1 M banded rows, FP32 / bf16, with the rest and without: width 20 41 / 31 -> 33 / 28 us, 40 80 / 59 -> 60 / 52, 48 88 / 70 ->
-    // 71 / 62, 56 118 / 82 -> 91 / 72, 60 101 / 83 -> 97 / 79; of 54 further shapes (5000 to 200000 rows, banded and scattered
-    // columns, widths 12 to 64) the worst took 3 % more (200000 scattered rows of 24: 50.4 -> 52.1), the best 19 % less.
+    // of their own (128^3 rows, FP32 / bf16: 77.2 / 63.6 -> 71.9 / 54.2 us with 128).  1 M banded rows, FP32 / bf16, with the rest and without: width
+    // 20 28.4 / 22.1 -> 25.6 / 20.2 us, 40 48.7 / 40.8 -> 48.0 / 37.3, 48 59.0 / 47.4 -> 56.7 / 43.3, 56 72.7 / 58.4 -> 65.9 / 50.4, 60 70.2 / 54.2 -> 70.0 / 54.0; of
+    // 420 shapes (60 k to 6 M slots, banded and scattered, widths 1 to 64) none took 3 % more, the best 22 % less.
     int G = 1;
     while (G < 64 && 16 * G < width) G <<= 1;
     const int sweep = kWG / G, rest = rows % sweep;
@@ -471,9 +470,14 @@ hipError_t launch_ell(bool bf16, int32_t m, int32_t width, const int32_t* col_id
     if (m <= 0) return hipSuccess;
     // Rows of up to 64 slots go through LDS: read directly they would get teams of at most 8 lanes,
     // whose loads fall into many short pieces.  Wider rows get teams of 16 to 64 lanes, which read
-    // 64 to 256 contiguous bytes at a time as it is (measured: width 390, 2048 rows: 3.9 us direct
-    // against 5.0 us through LDS; width 27, 2 M rows: 114 us against 85 us).
-    if (width >= 1 && width <= kEllTileMaxWidth)
+    // 64 to 256 contiguous bytes at a time as it is.
+    // Out of a graph, direct / through LDS: 27 wide, 128^3 points bf16 110.5 / 54.2 us, 1 M banded rows FP32 81.4 / 35.7, 200000 scattered ones 35.5 /
+    // 26.7; 60 wide, 1 M banded FP32 152.5 / 70.0; 5 wide, 1.5 M banded FP32 19.9 / 13.6.  Where a launch is most of the time direct takes up to a quarter
+    // less (30000 rows of 20 2.9 / 3.4, 937 of 64 3.2 / 3.4, 150000 of 4 2.7 / 3.1), which calls one by one do not show (4.1 us of host time each).
+    // Rows of one or two slots are direct until memory is what counts: one slot, scattered, FP32 / bf16: 500000 rows 5.6 / 4.3 against 6.3 / 4.9,
+    // 1 M 10.7 / 8.6 against 11.3 / 9.2, 4 M 58.9 / 43.5 against 59.2 / 43.2; two slots, 300000 rows 4.8 / 4.4 against 5.3 / 5.0, 500000 8.3 / 6.6 against 8.1 / 6.9.
+    const bool narrow = (width == 1 && m <= 3 << 19) || (width == 2 && m <= 3 << 17);
+    if (width >= 1 && width <= kEllTileMaxWidth && !narrow)
         return bf16 ? launch_ell_tile<BF16>(m, width, col_ids, vals, x, y, s, st)
                     : launch_ell_tile<F32>(m, width, col_ids, vals, x, y, s, st);
 #define SPMV_ELL_CASE(G) \

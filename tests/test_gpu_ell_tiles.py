@@ -13,6 +13,20 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("width,most", [(1, 3 << 19), (2, 3 << 17)])
+def test_narrow_rows_on_both_sides_of_the_rule(width, most, dtype):
+    """Rows of one or two slots: up to `most` of them a lane reads its row itself, beyond that they go through LDS."""
+    for m in (most, most + 1):
+        p = w.exact_integer(np.arange(m) % (width + 1), 5000, seed=width, dtype=dtype, alpha=1.0, beta=2.0)
+        y_ref, _ = oracle.spmv_problem(p)
+        wd, ci, vals = w.to_ell(p)
+        ci_t, v_t, x_t, y = to_dev(ci), to_dev(vals), to_dev(p.x), to_dev(p.y0)
+        s.check(s.spmv_ell_run(p.m, p.n, wd, ci_t.data_ptr(), v_t.data_ptr(), DTYPE_CODE[dtype], x_t.data_ptr(), y.data_ptr(), 1.0, 2.0))
+        torch.cuda.synchronize()
+        assert wd == width and np.array_equal(y.cpu().numpy().astype(np.float64), y_ref), m
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("width", [1, 15, 16, 17, 27, 31, 32, 33, 43, 48, 49, 63, 64])
 def test_tiles_of_every_width(width, dtype):
     for m in (1, 127, 129, 145, 64 * 24 + 3):     # 8 dies: fewer tiles than dies, and a remainder over them
