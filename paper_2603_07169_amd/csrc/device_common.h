@@ -87,20 +87,25 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
 
 // Copies straight from memory to LDS, past the registers: lane l of the wavefront fetches 16 (4) bytes and they land 16 l (4 l)
 // bytes behind `lds`, a byte address that is the same in all lanes.  Lanes that are switched off copy nothing.  The compiler
-// does not know these loads: lds_copies_done() waits for all that this wavefront has asked for, and a barrier is
-// needed before another wavefront reads them.  (m0 is the compiler's to set before each of its own uses; none of these kernels has one.)
+// does not know these loads: wait_all_and_barrier() waits for all that this wavefront has asked for and for the other wavefronts.
+// The compiler does not look into the text either, so the wait states stand in it: one between the move and a copy that reads m0, five
+// between a vector instruction that writes a base's scalar registers (none does as the kernels are compiled) and the copy that reads
+// them (the move and s_nop 3: 27 points 128^3, bf16 as ELL 53.2 -> 53.5 us, the pattern kernel the same).
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
     return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));
 }
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // m0 is reserved and clobbered: the compiler must not keep a value of its own in it across a copy
 __device__ __forceinline__ void copy16_to_lds_nt(uint32_t lds, const void* base, uint32_t lane_offset) {  // base the same in all lanes
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(lane_offset), "s"(base) : "m0", "memory");
 }
 __device__ __forceinline__ void copy16_to_lds(uint32_t lds, const void* src) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "m0", "memory");
 }
 __device__ __forceinline__ void copy4_to_lds(uint32_t lds, const void* base, uint32_t lane_offset) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(lane_offset), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(lane_offset), "s"(base) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 // All memory accesses of this wavefront have ended, and all wavefronts of the workgroup have come here.
 __device__ __forceinline__ void wait_all_and_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
