@@ -4,7 +4,6 @@
 
 #include "device_common.h"
 #include "kernels.h"
-#include "row_phase.h"
 
 namespace spmv {
 namespace {

@@ -11,6 +11,9 @@
 //   cut_rows_kernel     adds the carries of cut rows to y, in chunk order, where most chunks cut one
 //   spmv_window_kernel  the same with the block's window of x in LDS and 16-bit window positions
 //                       in place of the column indices (built by window_build_kernel at analysis)
+//   spmv_pattern_block_kernel, spmv_pattern_kernel
+//                       the same with the positions given by row patterns (stencils): a workgroup per
+//                       block, and a pipeline over the blocks from sheets prepared at analysis
 // No matrix cores: nothing here is a dense contraction.
 #include <hip/hip_runtime.h>
 
@@ -182,7 +185,7 @@ struct TileArgs {
     float alpha, beta;
     int32_t vec_ok;            // colidx and vals are 16-byte aligned
     int32_t x_vec_ok;          // x is 16-byte aligned
-    const unsigned char* sheets;  // stream kernel: [nparts * sheet_stride] (StreamSheets)
+    const unsigned char* sheets;  // stream kernel: [nparts * sheet_stride] (see SheetRun)
     int32_t sheet_stride, map_bytes;
     int32_t val_bytes, buf_bytes;  // stream kernel: LDS bytes of a block's values, of everything that is held of a block
     const int32_t* colidx;
@@ -791,6 +794,49 @@ __global__ __launch_bounds__(WG, (XPL == 4 && NG == 2) ? 4 : 8) void spmv_patter
 //     hardware deals the rest out: 30 to 40 % slower, since nothing overlaps a workgroup's first block.
 constexpr int kStreamRows = 128;  // rows of a sweep
 
+// The stored values of one row, in order, out of LDS: as many as B asks for at a time, in reads of whole words.
+template <typename E>
+struct RowValues;
+template <>
+struct RowValues<float> {
+    const float* p;
+    __device__ __forceinline__ RowValues(const float* vals, int slot) : p(vals + slot) {}
+    template <int B>
+    __device__ __forceinline__ void next(float (&v)[B]) {
+        __builtin_memcpy(v, __builtin_assume_aligned(p, 4), 4 * B);
+        p += B;
+    }
+};
+// bf16: a row may start in the middle of a word, and a wide read that does is taken apart by the LDS (eight entries at a time from where
+// they lie: 14 M cycles of SQ_LDS_UNALIGNED_STALL, 40 us instead of 28.5), so words are read whole and put together again.
+template <>
+struct RowValues<uint16_t> {
+    const uint32_t* p;
+    uint32_t word;
+    unsigned shift;
+    __device__ __forceinline__ RowValues(const uint16_t* vals, int slot)
+        : p(reinterpret_cast<const uint32_t*>(vals) + (slot >> 1)), shift(16u * (slot & 1)) {
+        word = *p++;
+    }
+    template <int B>
+    __device__ __forceinline__ void next(float (&v)[B]) {
+        if constexpr (B == 1) {  // the last entry of a row of odd length
+            v[0] = __uint_as_float((word >> shift) << 16);
+        } else {
+            uint32_t w[B / 2];
+            __builtin_memcpy(w, __builtin_assume_aligned(p, 4), 2 * B);
+            p += B / 2;
+#pragma unroll
+            for (int i = 0; i < B / 2; ++i) {
+                const uint32_t both = __builtin_amdgcn_alignbit(w[i], i > 0 ? w[i - 1] : word, shift);
+                v[2 * i] = __uint_as_float(both << 16);
+                v[2 * i + 1] = __uint_as_float(both & 0xFFFF0000u);
+            }
+            word = w[B / 2 - 1];
+        }
+    }
+};
+
 // A row's entries by one lane, sixteen at a time, then eight, four, two, one.  list: the row's pattern, byte offsets of 16 bits from
 // a word's start on; xb: address of the x value that offset 0 stands for.
 template <typename E>
@@ -1168,7 +1214,7 @@ __global__ __launch_bounds__(256) void window_build_kernel(const int32_t* __rest
 // The block is patterned when it is staged, no row exceeds kMaxPatternLen entries, no rel is negative and there are at
 // most kMaxPatternRuns runs.  fill == 0: packs the runs into run_desc[8b .. 8b+7] (word 7 = runs, 0 when not patterned).
 // fill == 1 (same inputs, pat_pad allocated with stride pt_cap): writes the list, zero padded.
-// With sheet_need (fill == 0) the block's sheet is planned as well (StreamSheets): up to kMaxSheetRuns runs, runs with equal lists
+// With sheet_need (fill == 0) the block's sheet is planned as well (SheetPlan): up to kMaxSheetRuns runs, runs with equal lists
 // sharing one.  sheet_need[b] = its bytes, 0 if the block cannot have one; sheet_map / sheet_runs as they will stand in it.
 __global__ __launch_bounds__(256) void pattern_build_kernel(const int32_t* __restrict__ block_desc, const int32_t* __restrict__ rowptr,
                                                             const uint16_t* __restrict__ lidx, int tile_cap, int fill,

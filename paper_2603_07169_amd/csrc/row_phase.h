@@ -1,5 +1,5 @@
 // The row phase of the tile kernels: the entries of a tile sit in LDS and teams of lanes take one
-// row (segment) each.  Shared by the CSR tile kernels and the ELL kernel.  Internal linkage.
+// row (segment) each.  Shared by the CSR tile kernels.  Internal linkage.
 #pragma once
 #include <type_traits>
 
@@ -70,49 +70,6 @@ __device__ __forceinline__ float segment_dot(const I* cols, const E* vals, const
     if (cnt >= 1) acc += gather_batch<1, G>(cols, vals, x, j);
     return acc;
 }
-
-// The stored values of one row, in order, out of LDS: as many as B asks for at a time, in reads of whole words.
-template <typename E>
-struct RowValues;
-template <>
-struct RowValues<float> {
-    const float* p;
-    __device__ __forceinline__ RowValues(const float* vals, int slot) : p(vals + slot) {}
-    template <int B>
-    __device__ __forceinline__ void next(float (&v)[B]) {
-        __builtin_memcpy(v, __builtin_assume_aligned(p, 4), 4 * B);
-        p += B;
-    }
-};
-// bf16: a row may start in the middle of a word, and a wide read that does is taken apart by the LDS (eight entries at a time from where
-// they lie: 14 M cycles of SQ_LDS_UNALIGNED_STALL, 40 us instead of 28.5), so words are read whole and put together again.
-template <>
-struct RowValues<uint16_t> {
-    const uint32_t* p;
-    uint32_t word;
-    unsigned shift;
-    __device__ __forceinline__ RowValues(const uint16_t* vals, int slot)
-        : p(reinterpret_cast<const uint32_t*>(vals) + (slot >> 1)), shift(16u * (slot & 1)) {
-        word = *p++;
-    }
-    template <int B>
-    __device__ __forceinline__ void next(float (&v)[B]) {
-        if constexpr (B == 1) {  // the last entry of a row of odd length
-            v[0] = __uint_as_float((word >> shift) << 16);
-        } else {
-            uint32_t w[B / 2];
-            __builtin_memcpy(w, __builtin_assume_aligned(p, 4), 2 * B);
-            p += B / 2;
-#pragma unroll
-            for (int i = 0; i < B / 2; ++i) {
-                const uint32_t both = __builtin_amdgcn_alignbit(w[i], i > 0 ? w[i - 1] : word, shift);
-                v[2 * i] = __uint_as_float(both << 16);
-                v[2 * i + 1] = __uint_as_float(both & 0xFFFF0000u);
-            }
-            word = w[B / 2 - 1];
-        }
-    }
-};
 
 // Where the row phase of a tile sends its results.
 struct RowOut {
