@@ -199,8 +199,8 @@ def check_windows_equal_oracle(p, A):
 def test_row_patterns_of_window_positions(dtype, shape):
     """Stencils: the window positions of a row are those of the row before plus a constant, so the kernel works from a
     few runs per block instead of the position stream and the row offsets.  Rows that break the pattern in the middle
-    of a block (more than four runs: that block falls back to its positions; up to four: it stays patterned), arrays
-    off their allocations, blocks of more rows than a workgroup has lanes, columns stored in descending order (a row's
+    of a block (more than sixteen runs: the product goes by the packed runs and that block, in the same launch, by its positions; up
+    to four: it stays patterned), arrays off their allocations, blocks of more rows than a workgroup has lanes, columns stored in descending order (a row's
     first entry no longer sits lowest: no pattern).  The runs and pattern lists bit for bit, and the product, each time."""
     params = None
     if shape == "stencil27":
@@ -214,10 +214,10 @@ def test_row_patterns_of_window_positions(dtype, shape):
         p = w.laplace2d(160, dtype=dtype, alpha=-1.25, beta=0.5)
     colidx, vals = p.colidx.copy(), p.vals
     if shape == "broken":
-        # default blocks hold 64 rows here; blocks 10 and 20 start a grid line.  Block 10: three rows apart lose their
-        # pattern (eight runs: positions again).  Block 20: one row does (four runs: still patterned).  The right
+        # default blocks hold 64 rows here; blocks 10 and 20 start a grid line.  Block 10: eight rows apart lose their
+        # pattern (18 runs: positions again).  Block 20: one row does (four runs: still patterned).  The right
         # neighbour's column moves two further.
-        for r in (10 * 64 + 9, 10 * 64 + 30, 10 * 64 + 50, 20 * 64 + 33):
+        for r in (*range(10 * 64 + 4, 10 * 64 + 60, 7), 20 * 64 + 33):
             k = p.rowptr[r] + int(np.flatnonzero(colidx[p.rowptr[r]:p.rowptr[r + 1]] == r + 1)[0])
             colidx[k] = r + 3
     if shape == "reversed":
@@ -232,7 +232,7 @@ def test_row_patterns_of_window_positions(dtype, shape):
     A = d.matrix(params)
     assert A.info.plan == s.SPMV_PLAN_WINDOWED
     assert A.info.lidx_patterned == (0 if shape == "reversed" else 1)
-    kernel = {"reversed": "spmv_window_kernel", "unaligned": "spmv_pattern_block_kernel"}.get(shape, "spmv_pattern_kernel")
+    kernel = {"reversed": "spmv_window_kernel", "unaligned": "spmv_pattern_block_kernel", "broken": "spmv_pattern_block_kernel"}.get(shape, "spmv_pattern_kernel")
     assert s.spmv_csr_main_kernel_name(A.handle) == kernel
     assert s.spmv_csr_kernel_name(A.handle, d.x.data_ptr(), q.beta) == kernel
     if kernel == "spmv_pattern_kernel":       # an x off its alignment goes by the packed runs
@@ -242,6 +242,7 @@ def test_row_patterns_of_window_positions(dtype, shape):
     _, _, _, lidx = oracle.x_windows(q.rowptr, q.colidx, got["row_blocks"], A.info.block_nnz, ve)
     want = check_patterns_equal_oracle(q, A, got, lidx, False)
     if shape == "broken":
+        assert oracle.row_patterns(q.rowptr, got["row_blocks"], lidx, A.info.block_nnz, max_runs=18)["n_runs"][10] == 18
         assert want["n_runs"][10] == 0 and want["n_runs"][20] == 4 and (np.delete(want["n_runs"], 10) > 0).all()
     elif shape != "reversed":
         assert (want["n_runs"] > 0).all()
