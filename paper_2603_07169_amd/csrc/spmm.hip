@@ -578,7 +578,9 @@ __global__ __launch_bounds__(kSpmmWG) void spmm_packed_kernel(const SpmmPackedAr
 //     cycles per read, counted) against 2.6 for storage order (simulated); padding points at zero rows in slots that are free.
 //   - Offsets are stored ready for use (32 bits), so an entry costs no unpacking.
 //   - A wavefront works through its blocks as one stream, across the ends of groups: the LDS reads of a step go out before
-//     the multiply-adds of the step before, the entries are fetched kPairAhead blocks ahead, an old C a group ahead.
+//     the multiply-adds of the step before, the entries are asked for kPairAhead blocks ahead, an old C a group ahead.  As it is
+//     compiled this look-ahead ends with every group: the row number asked for there is moved to another register at once, and the wait
+//     for it takes in what was asked for before it, the group's two stores among it (loads and stores share one counter, in order).
 // 65536 x 2048 x 4096 at density 0.01, FP32: 432 us with the four-lane kernel, 368 with this one (30 TFLOP/s); without its
 // stores of C 287: a row of C is written in 64-byte pieces, one per slice, a quarter of which leave in two requests (1.32 GB
 // written for a C of 1.07), and that is what is left over the multiplication, whose LDS and vector units are busy 70 and
@@ -631,7 +633,7 @@ __device__ __forceinline__ void fma_pair(float (&acc)[8], unsigned v, f32x4 lo, 
     }
 }
 
-constexpr int kPairAhead = 7;  // 3, 5 and 7 measure the same; the entries' latency is covered
+constexpr int kPairAhead = 7;  // 3, 5 and 7 measure the same (see above: every group's end waits for what is on its way)
 
 // C32: every byte offset into C fits 32 bits, and row numbers and the row stride 24.
 template <typename T, bool READ_C, bool C32>
