@@ -244,7 +244,7 @@ __device__ __forceinline__ void ell_rows(const int* cols_l, int col_stride, cons
 // ELL rows of moderate width: a workgroup copies the slots of a run of rows (a contiguous stretch of col_ids / vals, since the layout
 // is row-major) to LDS as they are, past the registers, and then every lane takes a stretch of a row.  Against a team of lanes
 // reading its row straight from memory this keeps the global reads fully coalesced whatever the width.
-// Bound: memory (27 points of 128^3: bf16 52.9 us, 6.5 TB/s of the 6.9 a kernel that only reads reaches; FP32 74.7).  With the slots
+// Bound: memory (27 points of 128^3: bf16 53.4 us, 6.4 TB/s of the 6.9 a kernel that only reads reaches; FP32 72).  With the slots
 // staged through registers and a row's gathers in batches of 8, 4, 2 and 1, each waited for, 67.2 and 96; the copies alone 66, a
 // lane's gathers all at once the rest.  Tiles of 3072 or 2048 slots instead of 4096: 53.9, 61.
 // rows_per_tile is a multiple of 8, so a tile's first slot is 16-byte aligned in both arrays.

@@ -782,11 +782,11 @@ __global__ __launch_bounds__(WG, (XPL == 4 && NG == 2) ? 4 : 8) void spmv_patter
 // The pattern kernel for matrices whose every block has a sheet (SheetRun), as a pipeline: as many workgroups as the device
 // holds walk through the blocks, and while one multiplies a block out of LDS the next one's values, x vectors and sheet travel into
 // a second set of LDS buffers, past the registers.
-// Bound: memory.  With the rows' arithmetic left out it takes 23.9 us on the 27-point stencil of 128^3 (bf16, 137 MB), with it 25.7;
+// Bound: memory.  With the rows' arithmetic left out it takes 23.9 us on the 27-point stencil of 128^3 (bf16, 140 MB), with it 25.7;
 // a workgroup per block and nothing in flight while it multiplies took 31.0 (FP32 57.1 -> 45.0; 5 points of 1024^2, FP32 9.9 -> 9.3,
 // of 1500^2, bf16 15.6 -> 10.6; lines of 100 points, whose blocks have more than four runs and went by their positions, 17.9 -> 14.1).
 //   - Blocks have 128 or 256 rows (up to 32 entries a row), so two wavefronts with a row per lane finish a block in one or two sweeps, and
-//     what is done once per row and once per block is done by half as many lanes as with two lanes a row: 8.0 M vector instructions
+//     what is done once per row and once per block is done by half as many lanes as with two lanes a row: 6.3 M vector instructions
 //     instead of 14.1 M.  Pipelining alone, two lanes a row and one entry at a time, was slower than no pipeline (34.4 us).
 //   - Values and pattern are read from LDS up to 16 entries at a time.
 //   - Two lanes share a row (P = 2) where stream_lanes() says so; sheets_pay() says which matrices get sheets.
