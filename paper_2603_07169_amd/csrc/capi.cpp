@@ -379,37 +379,35 @@ spmv_status_t build_x_windows(spmv_csr_s* h, bool forced, bool count_only, const
             int32_t max_table, max_sheet;
         } counts{0, 0, 0};
         const size_t NB = static_cast<size_t>(nb);
-        Counts* d_counts = nullptr;
-        if (hip_failed(hipMalloc(reinterpret_cast<void**>(&d_counts), sizeof(Counts))) ||
-            hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_run_desc), 32 * NB))) {
-            (void)hipFree(d_counts);
-            return SPMV_ERR_ALLOC;
-        }
-        // what the sheets are planned in (runs, bytes, maps), given back below; without it, or without memory for the sheets, the
-        // product runs from the packed runs or the positions
         const int elem_bytes = h->dtype == SPMV_F32 ? 4 : 2;
         auto buffers_fit = [&](int32_t stride) {
             return spmv::window_kernel(elem_bytes, h->max_block_entries, a->info.rows_max, largest, stride, false, h->vec_ok, false) ==
                    spmv::WindowKernel::sheets;
         };
         const int32_t map_bytes = spmv::sheet_map_bytes(a->info.rows_max);
-        const size_t need_at = sizeof(spmv::SheetRun) * spmv::kMaxSheetRuns * NB, map_at = need_at + 4 * NB;
-        char* scratch = nullptr;
         int dev = 0;
         bool failed = hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev));
         h->common_len = a->common_len;
-        if (!failed && buffers_fit(map_bytes) &&
-            spmv::sheets_pay(elem_bytes, h->m, h->nnz, nb, a->info.block_nnz, a->info.rows_max, a->common_len, h->cus) &&
-            hip_failed(hipMalloc(reinterpret_cast<void**>(&scratch), map_at + NB * static_cast<size_t>(map_bytes))))
-            scratch = nullptr;
+        bool want_sheets = !failed && buffers_fit(map_bytes) &&
+                           spmv::sheets_pay(elem_bytes, h->m, h->nnz, nb, a->info.block_nnz, a->info.rows_max, a->common_len, h->cus);
+        Counts* d_counts = nullptr;
+        if (hip_failed(hipMalloc(reinterpret_cast<void**>(&d_counts), sizeof(Counts))) ||
+            hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_run_desc), 32 * NB))) {
+            (void)hipFree(d_counts);
+            return SPMV_ERR_ALLOC;
+        }
+        // what the sheets are planned in (38 bytes a block), given back below; without it, or without memory for the sheets, the
+        // product runs from the packed runs or the positions
+        char* plan = nullptr;
+        if (want_sheets && hip_failed(hipMalloc(reinterpret_cast<void**>(&plan), (4 + 2 * (spmv::kMaxSheetRuns + 1)) * NB)))
+            want_sheets = false;
         spmv::SheetPlan sheets{};
-        if (scratch)
-            sheets = {elem_bytes, map_bytes, &d_counts->max_sheet, reinterpret_cast<int32_t*>(scratch + need_at),
-                      reinterpret_cast<unsigned char*>(scratch + map_at), reinterpret_cast<spmv::SheetRun*>(scratch)};
+        if (want_sheets)
+            sheets = {elem_bytes, map_bytes, &d_counts->max_sheet, reinterpret_cast<int32_t*>(plan), reinterpret_cast<uint16_t*>(plan + 4 * NB)};
         failed = failed || hip_failed(hipMemcpy(d_counts, &counts, sizeof counts, hipMemcpyHostToDevice));
         failed = failed || hip_failed(spmv::launch_pattern_build(h->d_block_desc, static_cast<int32_t>(nb), h->rowptr, h->d_lidx,
                                                                  a->info.block_nnz, false, h->d_run_desc, &d_counts->max_table,
-                                                                 &d_counts->covered, nullptr, 0, scratch ? &sheets : nullptr, nullptr));
+                                                                 &d_counts->covered, nullptr, 0, want_sheets ? &sheets : nullptr, nullptr));
         failed = failed || hip_failed(hipMemcpy(&counts, d_counts, sizeof counts, hipMemcpyDeviceToHost));
         (void)hipFree(d_counts);
         const int64_t covered = static_cast<int64_t>(counts.covered);
@@ -427,7 +425,7 @@ spmv_status_t build_x_windows(spmv_csr_s* h, bool forced, bool count_only, const
             (void)hipFree(h->d_run_desc);
             h->d_run_desc = nullptr;
         }
-        if (!failed && scratch && counts.max_sheet < INT32_MAX) {
+        if (!failed && want_sheets && counts.max_sheet < INT32_MAX) {
             const int32_t stride = (counts.max_sheet + 15) & ~15;
             if (nb * static_cast<int64_t>(stride) <= kMaxCount && buffers_fit(stride) &&
                 !hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_sheets), NB * static_cast<size_t>(stride)))) {
@@ -436,7 +434,7 @@ spmv_status_t build_x_windows(spmv_csr_s* h, bool forced, bool count_only, const
                                                             h->d_sheets, nullptr));
             }
         }
-        (void)hipFree(scratch);  // waits for the kernels that read it
+        if (plan) (void)hipFree(plan);  // waits for the kernels that use it
         if (failed) return no_memory ? SPMV_ERR_ALLOC : SPMV_ERR_HIP;
     }
     a->info.plan = SPMV_PLAN_WINDOWED;

@@ -170,8 +170,7 @@ struct SheetPlan {
     int32_t elem_bytes, map_bytes;
     int32_t* largest;
     int32_t* need;        // [nb]
-    unsigned char* map;   // [nb * map_bytes]
-    SheetRun* runs;       // [nb * kMaxSheetRuns]
+    uint16_t* first;      // [nb * (kMaxSheetRuns + 1)] first rows of the runs, then the rows of the block
 };
 hipError_t launch_sheet_fill(const int32_t* block_desc, int32_t nb, const int32_t* rowptr, const uint16_t* lidx, const SheetPlan& p,
                              int32_t stride, unsigned char* sheets, hipStream_t st);

@@ -1208,19 +1208,45 @@ __global__ __launch_bounds__(256) void window_build_kernel(const int32_t* __rest
     }
 }
 
+// Where the lists of a sheet's runs lie, behind its map and its runs, runs with equal lists sharing one; returns the sheet's bytes.  All
+// lanes of one wavefront call it; rel_s: the lists, zeros from a run's length on.
+static_assert(kMaxPatternLen == 64, "a lane compares one entry of two lists");
+__device__ __forceinline__ int sheet_lists(const uint16_t (&rel_s)[kMaxSheetRuns][kMaxPatternLen], const int (&run_len)[kMaxSheetRuns], int runs,
+                                           int map_bytes, int lane, int (&list_at)[kMaxSheetRuns]) {
+    int at = map_bytes + static_cast<int>(sizeof(SheetRun)) * runs;
+#pragma unroll
+    for (int r = 0; r < kMaxSheetRuns; ++r) {
+        list_at[r] = 0;
+        if (r < runs) {
+            int place = -1;
+#pragma unroll
+            for (int u = 0; u < r; ++u) {
+                const bool differs = run_len[u] != run_len[r] || rel_s[u][lane] != rel_s[r][lane];
+                if (place < 0 && !__builtin_amdgcn_ballot_w64(differs)) place = list_at[u];
+            }
+            if (place < 0) {
+                place = at;
+                at += (2 * run_len[r] + 3) & ~3;
+            }
+            list_at[r] = place;
+        }
+    }
+    return at;
+}
+
 // Finds the row patterns of the window positions (one workgroup of 256 lanes per row block; analysis time).
 // Row i of the block has base_i = lidx of its first entry (0 when empty) and rel_i = its positions minus base_i.
 // A run takes the next row when rel repeats and, from its third row on, the bases keep the step of its first two rows.
 // The block is patterned when it is staged, no row exceeds kMaxPatternLen entries, no rel is negative and there are at
 // most kMaxPatternRuns runs.  fill == 0: packs the runs into run_desc[8b .. 8b+7] (word 7 = runs, 0 when not patterned).
 // fill == 1 (same inputs, pat_pad allocated with stride pt_cap): writes the list, zero padded.
-// With sheet_need (fill == 0) the block's sheet is planned as well (SheetPlan): up to kMaxSheetRuns runs, runs with equal lists
-// sharing one.  sheet_need[b] = its bytes, 0 if the block cannot have one; sheet_map / sheet_runs as they will stand in it.
+// With sheet_need (fill == 0) the block's sheet is planned as well: sheet_need[b] = its bytes, 0 if the block cannot have one, and
+// sheet_first[b * (kMaxSheetRuns + 1) ..] = the first rows of its runs (up to kMaxSheetRuns), then the block's number of rows.
 __global__ __launch_bounds__(256) void pattern_build_kernel(const int32_t* __restrict__ block_desc, const int32_t* __restrict__ rowptr,
                                                             const uint16_t* __restrict__ lidx, int tile_cap, int fill,
                                                             int32_t* __restrict__ run_desc, uint16_t* __restrict__ pat_pad, int pt_cap,
-                                                            int elem_bytes, int map_bytes, int32_t* __restrict__ sheet_need,
-                                                            unsigned char* __restrict__ sheet_map, SheetRun* __restrict__ sheet_runs) {
+                                                            int map_bytes, int32_t* __restrict__ sheet_need,
+                                                            uint16_t* __restrict__ sheet_first) {
     __shared__ int base_s[kMaxRowsPerBlock];
     __shared__ unsigned char len_s[kMaxRowsPerBlock], same_s[kMaxRowsPerBlock], flag_s[kMaxRowsPerBlock];
     __shared__ int bad;
@@ -1334,64 +1360,59 @@ __global__ __launch_bounds__(256) void pattern_build_kernel(const int32_t* __res
         return;
     }
     __shared__ uint16_t rel_s[kMaxSheetRuns][kMaxPatternLen];
+    __shared__ int run_len[kMaxSheetRuns];
     for (int i = tid; i < runs * kMaxPatternLen; i += 256) {
         const int r = i / kMaxPatternLen, j = i % kMaxPatternLen, row = run_first[r];
         rel_s[r][j] = j < len_s[row] ? static_cast<uint16_t>(lidx[rowptr[r0 + row] + j] - base_s[row]) : 0;
     }
-    for (int i = tid; i < nr; i += 256) {
-        int r = 0;
-        while (r + 1 < runs && i >= run_first[r + 1]) ++r;
-        sheet_map[static_cast<int64_t>(b) * map_bytes + i] = static_cast<unsigned char>(r);
-    }
+    if (tid < runs) run_len[tid] = len_s[run_first[tid]];
+    if (tid <= runs) sheet_first[static_cast<int64_t>(b) * (kMaxSheetRuns + 1) + tid] = static_cast<uint16_t>(run_first[tid]);
     __syncthreads();
     if (tid < 64) {
-        int at = map_bytes + static_cast<int>(sizeof(SheetRun)) * runs, entry = k0 & (16 / elem_bytes - 1);
         int list_at[kMaxSheetRuns];
-#pragma unroll
-        for (int r = 0; r < kMaxSheetRuns; ++r) {
-            list_at[r] = 0;
-            if (r < runs) {
-                const int row = run_first[r], len = len_s[row];
-                int place = -1;
-#pragma unroll
-                for (int u = 0; u < r; ++u) {
-                    const bool differs = len_s[run_first[u]] != len || rel_s[u][tid] != rel_s[r][tid];
-                    if (place < 0 && !__builtin_amdgcn_ballot_w64(differs)) place = list_at[u];
-                }
-                if (place < 0) {
-                    place = at;
-                    at += (2 * len + 3) & ~3;
-                }
-                list_at[r] = place;
-                if (tid == 0)
-                    sheet_runs[static_cast<int64_t>(b) * kMaxSheetRuns + r] =
-                        SheetRun{entry - row * len, (base_s[row] - row * run_stride[r]) * elem_bytes, len, (run_stride[r] * elem_bytes) * 65536 + place};
-                entry += (run_first[r + 1] - row) * len;
-            }
-        }
-        if (tid == 0) sheet_need[b] = at;
+        const int bytes = sheet_lists(rel_s, run_len, runs, map_bytes, tid, list_at);
+        if (tid == 0) sheet_need[b] = bytes;
     }
 }
 
-// The sheets themselves, from what was planned: the map, the runs, and every list once.
+// The sheets themselves: the map, the runs, and every list once.  As many bytes as were planned, from the first rows of the runs.
 __global__ __launch_bounds__(64) void sheet_fill_kernel(const int32_t* __restrict__ block_desc, const int32_t* __restrict__ rowptr,
                                                         const uint16_t* __restrict__ lidx, int elem_bytes, int map_bytes, int stride,
-                                                        const unsigned char* __restrict__ sheet_map, const SheetRun* __restrict__ sheet_runs,
-                                                        unsigned char* __restrict__ sheets) {
+                                                        const uint16_t* __restrict__ sheet_first, unsigned char* __restrict__ sheets) {
+    __shared__ uint16_t rel_s[kMaxSheetRuns][kMaxPatternLen];
+    __shared__ int first_s[kMaxSheetRuns + 1], run_len[kMaxSheetRuns];
     const int tid = threadIdx.x, b = blockIdx.x;
-    const int r0 = block_desc[2 * b], nr = block_desc[2 * b + 2] - r0;
+    const int r0 = block_desc[2 * b], k0 = block_desc[2 * b + 1], nr = block_desc[2 * b + 2] - r0;
+    const int staged_from = k0 & ~(16 / elem_bytes - 1);
     unsigned char* const out = sheets + static_cast<int64_t>(b) * stride;
-    const unsigned char* const map = sheet_map + static_cast<int64_t>(b) * map_bytes;
-    for (int i = tid; i < nr; i += 64) out[i] = map[i];
-    const int runs = map[nr - 1] + 1;
-    int row = 0;
+    const uint16_t* const first = sheet_first + static_cast<int64_t>(b) * (kMaxSheetRuns + 1);
+    int runs = 0;
+    while (first[runs] < nr) ++runs;
+    if (tid <= runs) first_s[tid] = first[tid];
+    __syncthreads();
     for (int r = 0; r < runs; ++r) {
-        const SheetRun run = sheet_runs[static_cast<int64_t>(b) * kMaxSheetRuns + r];
-        if (tid == 0) *(reinterpret_cast<SheetRun*>(out + map_bytes) + r) = run;
-        while (row < nr && map[row] < r) ++row;  // the run's first row
-        const int ka = rowptr[r0 + row];
-        uint16_t* const list = reinterpret_cast<uint16_t*>(out + (run.stride_list & 0xFFFF));
-        if (tid < run.len) list[tid] = static_cast<uint16_t>((lidx[ka + tid] - lidx[ka]) * elem_bytes);  // equal lists are written again
+        const int ka = rowptr[r0 + first_s[r]], len = rowptr[r0 + first_s[r] + 1] - ka;
+        if (tid == 0) run_len[r] = len;
+        rel_s[r][tid] = tid < len ? static_cast<uint16_t>(lidx[ka + tid] - lidx[ka]) : 0;
+    }
+    __syncthreads();
+    int list_at[kMaxSheetRuns];
+    sheet_lists(rel_s, run_len, runs, map_bytes, tid, list_at);
+#pragma unroll
+    for (int r = 0; r < kMaxSheetRuns; ++r) {
+        if (r >= runs) continue;
+        const int row = first_s[r], len = run_len[r], ka = rowptr[r0 + row];
+        const int base = len > 0 ? lidx[ka] : 0;
+        const int step = len > 0 && first_s[r + 1] - row >= 2 ? lidx[ka + len] - base : 0;  // the step of a run is that of its first two rows
+        if (tid == 0)
+            *(reinterpret_cast<SheetRun*>(out + map_bytes) + r) = SheetRun{ka - staged_from - row * len, (base - row * step) * elem_bytes, len,
+                                                                           step * elem_bytes * 65536 + list_at[r]};
+        if (tid < len) reinterpret_cast<uint16_t*>(out + list_at[r])[tid] = static_cast<uint16_t>(rel_s[r][tid] * elem_bytes);  // equal lists are written again
+    }
+    for (int i = tid; i < nr; i += 64) {
+        int r = 0;
+        while (r + 1 < runs && i >= first_s[r + 1]) ++r;
+        out[i] = static_cast<unsigned char>(r);
     }
 }
 
@@ -1756,7 +1777,7 @@ hipError_t launch_pattern_build(const int32_t* block_desc, int32_t nb, const int
     if (nb <= 0) return hipSuccess;
     const SheetPlan p = sheets ? *sheets : SheetPlan{};
     hipLaunchKernelGGL(pattern_build_kernel, dim3(nb), dim3(256), 0, st, block_desc, rowptr, lidx, block_nnz, fill ? 1 : 0, run_desc,
-                       pat_pad, pt_cap, p.elem_bytes, p.map_bytes, p.need, p.map, p.runs);
+                       pat_pad, pt_cap, p.map_bytes, p.need, p.first);
     if (!fill) {
         const int grid = nb < 256 * 64 ? (nb + 255) / 256 : 64;
         hipLaunchKernelGGL(pattern_totals_kernel, dim3(grid), dim3(256), 0, st, block_desc, static_cast<const int32_t*>(run_desc), nb,
@@ -1768,8 +1789,8 @@ hipError_t launch_pattern_build(const int32_t* block_desc, int32_t nb, const int
 hipError_t launch_sheet_fill(const int32_t* block_desc, int32_t nb, const int32_t* rowptr, const uint16_t* lidx, const SheetPlan& p,
                              int32_t stride, unsigned char* sheets, hipStream_t st) {
     if (nb <= 0) return hipSuccess;
-    hipLaunchKernelGGL(sheet_fill_kernel, dim3(nb), dim3(64), 0, st, block_desc, rowptr, lidx, p.elem_bytes, p.map_bytes, stride, p.map,
-                       p.runs, sheets);
+    hipLaunchKernelGGL(sheet_fill_kernel, dim3(nb), dim3(64), 0, st, block_desc, rowptr, lidx, p.elem_bytes, p.map_bytes, stride,
+                       static_cast<const uint16_t*>(p.first), sheets);
     return hipGetLastError();
 }
 

@@ -156,7 +156,7 @@ def test_rows_of_one_length(length, kind, dtype):
 
 
 def test_planning_memory_is_given_back():
-    """250000 blocks of one row: a handle keeps about 40 MB for them; the sheets' plan takes 69 MB more while it is made."""
+    """250000 blocks of one row: a handle keeps about 40 MB for them; what the sheets are planned in is not among it."""
     p = grid(500, 500, FIVE, "f32")
     d = DeviceProblem(p)
     torch.cuda.synchronize()
@@ -167,7 +167,7 @@ def test_planning_memory_is_given_back():
     want, _ = reference(p)
     assert np.array_equal(d.run(A).astype(np.float64), want)
     A.close()
-    assert kept < 64 << 20, kept
+    assert kept < 48 << 20, kept
 
 
 def run_both(p, params, wanted=None):
