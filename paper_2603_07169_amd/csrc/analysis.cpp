@@ -229,7 +229,6 @@ spmv_status_t analyze_rowptr(int64_t m, int64_t n, int64_t nnz, const int32_t* r
         int64_t min_len = INT64_MAX, max_len = 0, n_empty = 0;
         bool bad = false;
         int32_t hist[SPMV_NUM_BINS] = {};
-        int64_t of_len[65] = {};
     };
     std::vector<Part> parts(static_cast<size_t>(threads));
     parallel_pieces(m, threads, [&](int t, int64_t lo, int64_t hi) {
@@ -244,7 +243,6 @@ spmv_status_t analyze_rowptr(int64_t m, int64_t n, int64_t nnz, const int32_t* r
             q.max_len = std::max(q.max_len, len);
             q.n_empty += (len == 0);
             q.hist[length_bin(static_cast<uint32_t>(len))] += 1;
-            if (len <= 64) q.of_len[len] += 1;
         }
     });
     int64_t min_len = m > 0 ? INT64_MAX : 0, max_len = 0, n_empty = 0;
@@ -254,11 +252,6 @@ spmv_status_t analyze_rowptr(int64_t m, int64_t n, int64_t nnz, const int32_t* r
         max_len = std::max(max_len, q.max_len);
         n_empty += q.n_empty;
         for (int b = 0; b < SPMV_NUM_BINS; ++b) a.bin_count[b] += q.hist[b];
-    }
-    for (int64_t len = 1; len <= 64; ++len) {
-        int64_t rows = 0;
-        for (const Part& q : parts) rows += q.of_len[len];
-        if (rows > 0 && 2 * rows * len >= nnz) a.common_len = static_cast<int32_t>(len);
     }
 
     // ---- stable counting sort of the row ids by bin: thread t writes behind the rows of the threads before it.
@@ -473,6 +466,20 @@ WindowKernel window_kernel(int elem_bytes, int32_t staged_max, int32_t rows_max,
         2 * stream_buf_bytes(elem_bytes, staged_max, rows_max, x_vectors, sheet_stride, y_kept) <= kStreamMaxLds)
         return WindowKernel::sheets;
     return has_runs ? WindowKernel::runs : WindowKernel::positions;
+}
+
+int32_t common_row_length(int64_t m, const int32_t* rowptr) {
+    const int64_t rows = std::min<int64_t>(m, kSampledRows);
+    int64_t count[65] = {}, entries = 0;
+    for (int64_t i = 0; i < rows; ++i) {
+        const int64_t row = m <= kSampledRows ? i : static_cast<int64_t>(static_cast<uint64_t>(i) * 2654435761u % static_cast<uint64_t>(m));
+        const int64_t len = static_cast<int64_t>(rowptr[row + 1]) - rowptr[row];
+        entries += len;
+        if (len <= 64) count[len] += 1;
+    }
+    for (int32_t len = 64; len > 0; --len)
+        if (count[len] > 0 && 2 * len * count[len] >= entries) return len;
+    return 0;
 }
 
 bool sheets_pay(int elem_bytes, int64_t m, int64_t nnz, int64_t nb, int32_t block_nnz, int32_t rows_max, int32_t common_len, int32_t cus) {

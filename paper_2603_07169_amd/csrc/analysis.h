@@ -21,7 +21,6 @@ struct Analysis {
     std::vector<int32_t> row_blocks;  // [nb+1]
     std::vector<int32_t> mp_row;      // [P+1]
     std::vector<int32_t> mp_nz;       // [P+1]
-    int32_t common_len = 0;           // the row length (at most 64) whose rows hold half of the entries or more, 0 if there is none
     // How scattered the columns are, from the count pass of the x windows (-1: not counted): the distinct
     // 16-byte x vectors of the row blocks, summed, and the entries of the blocks that were counted
     // (all but single rows longer than block_nnz).
@@ -119,7 +118,13 @@ int64_t stream_buf_bytes(int elem_bytes, int32_t staged_max, int32_t rows_max, i
 WindowKernel window_kernel(int elem_bytes, int32_t staged_max, int32_t rows_max, int32_t x_vectors, int32_t sheet_stride, bool has_runs,
                            bool vec_ok, bool y_kept);
 
-// Whether a windowed matrix gets sheets at all.  Not where the kernel that works from them was slower than the one it stands in for
+// The row length (at most 64) whose rows hold half of the entries or more, 0 if there is none: of all rows, or, beyond kSampledRows of
+// them, of as many spread over the matrix by a multiplicative hash (counting all rows' lengths took 1.2 of 9.7 ms of analysis on 4 M rows;
+// rows at a fixed step would meet a grid's lines).  rowptr is a HOST array.
+constexpr int64_t kSampledRows = 4096;
+int32_t common_row_length(int64_t m, const int32_t* rowptr);
+
+// Whether a windowed matrix gets sheets at all; common_len: common_row_length().  Not where the kernel that works from them was slower than the one it stands in for
 // (us per product out of a graph, every row of one length, sheets / packed runs, and beside them what a neighbouring length takes).
 //   - Rows that begin on the same LDS banks, read a row per lane, or half a row: FP32 64 entries 5.3 / 3.9 (1 M entries), 16.4 / 8.7
 //     (6 M), 50.1 / 22.6 (24 M; 62 entries 19.7 / 20.0); 48 entries 4.2 / 3.9, 8.2 / 7.7, 20.8 / 20.7 (52: 3.7 / 3.9, 6.8 / 7.3); 32

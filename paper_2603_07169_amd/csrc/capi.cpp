@@ -66,7 +66,7 @@ struct spmv_csr_s {
     uint16_t* d_pat_pad = nullptr;
     unsigned char* d_sheets = nullptr;  // the blocks' sheets, where every block has one
     int32_t sheet_stride = 0;
-    int32_t cus = 0;  // compute units of the device, and Analysis::common_len (of use with sheets)
+    int32_t cus = 0;  // compute units of the device, and common_row_length() (of use with sheets)
     int32_t common_len = 0;
     // the two-pass plan (TWOPHASE)
     int32_t* d_tp_desc = nullptr;     // pairs (tp_row[p], tp_nz[p])
@@ -387,9 +387,9 @@ spmv_status_t build_x_windows(spmv_csr_s* h, bool forced, bool count_only, const
         const int32_t map_bytes = spmv::sheet_map_bytes(a->info.rows_max);
         int dev = 0;
         bool failed = hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev));
-        h->common_len = a->common_len;
+        h->common_len = spmv::common_row_length(h->m, rowptr_host.data());
         bool want_sheets = !failed && buffers_fit(map_bytes) &&
-                           spmv::sheets_pay(elem_bytes, h->m, h->nnz, nb, a->info.block_nnz, a->info.rows_max, a->common_len, h->cus);
+                           spmv::sheets_pay(elem_bytes, h->m, h->nnz, nb, a->info.block_nnz, a->info.rows_max, h->common_len, h->cus);
         Counts* d_counts = nullptr;
         if (hip_failed(hipMalloc(reinterpret_cast<void**>(&d_counts), sizeof(Counts))) ||
             hip_failed(hipMalloc(reinterpret_cast<void**>(&h->d_run_desc), 32 * NB))) {

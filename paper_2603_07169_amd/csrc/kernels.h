@@ -39,7 +39,7 @@ struct XWindows {
     const unsigned char* sheets;  // [nb * sheet_stride] (see SheetRun), or null: some block has none
     int32_t sheet_stride;
     int32_t cus;              // compute units of the device (with sheets)
-    int32_t common_len;       // Analysis::common_len (with sheets)
+    int32_t common_len;       // common_row_length() (with sheets)
 };
 
 // What the stream kernel needs to know of a row block besides its values and its x vectors, in one piece (a "sheet"): a byte per

@@ -52,12 +52,7 @@ int sheets_pay(int elem, int64_t m, int64_t nnz, int64_t nb, int block_nnz, int 
 int stream_lanes(int elem, int64_t m, int64_t nnz, int rows_max, int places, int common) {
     return spmv::stream_lanes(elem, m, nnz, rows_max, places, common);
 }
-int common_len(int64_t m, const int32_t* rp) {
-    spmv::Analysis a;
-    spmv_analyze_params_t p;
-    if (spmv::resolve_params(nullptr, &p) != SPMV_OK || spmv::analyze_rowptr(m, 8, rp[m], rp, p, &a, false) != SPMV_OK) return -1;
-    return a.common_len;
-}
+int common_len(int64_t m, const int32_t* rp) { return spmv::common_row_length(m, rp); }
 }
 """
 
@@ -281,3 +276,13 @@ def test_lanes_of_a_row(rules):
 def test_common_row_length(rules, lens, want):
     rp = rowptr_of(lens)
     assert rules.common_len(i64(len(lens)), P(rp)) == want
+
+
+@pytest.mark.parametrize("line", [64, 128, 129, 4096])
+def test_common_row_length_of_a_sample(rules, line):
+    """More rows than are looked at: lines of a grid whose end points have shorter rows, whatever the lines' length."""
+    for m in (4097, 64 * line, 4096 * line // 8 + 1):
+        at = np.arange(m) % line
+        for length in (5, 27, 64):
+            assert rules.common_len(i64(m), P(rowptr_of(np.where((at == 0) | (at == line - 1), length - 3, length)))) == length
+    assert rules.common_len(i64(9000), P(rowptr_of([7, 8, 9] * 3000))) == 0
