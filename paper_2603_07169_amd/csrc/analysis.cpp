@@ -167,6 +167,17 @@ void merge_path_splits_snapped(int64_t m, int64_t nnz, const int32_t* rowptr, in
     }
 }
 
+int64_t gather_snap(int32_t plan, int64_t max_len, int64_t items) {
+    return plan == SPMV_PLAN_ADAPTIVE ? max_len : std::min<int64_t>(kTwoPhaseSnap, items - 1);
+}
+
+bool gather_choice(int64_t m, int64_t nnz, int32_t plan, int64_t max_len, int32_t cus, int k) {
+    if (plan != SPMV_PLAN_MERGE && plan != SPMV_PLAN_ADAPTIVE) return false;
+    const int64_t items = (m + nnz + static_cast<int64_t>(cus) * k - 1) / (static_cast<int64_t>(cus) * k);
+    if (plan == SPMV_PLAN_ADAPTIVE) return nnz >= 3 << 17 && 2 * max_len <= items;
+    return nnz >= 1 << 16 && max_len <= 32 * std::max(items, kGatherMinItems);
+}
+
 void merge_chunk_desc(int64_t m, const int32_t* rowptr, const std::vector<int32_t>& mp_row, const std::vector<int32_t>& mp_nz,
                       int64_t snap, std::vector<int32_t>* desc) {
     desc->resize(2 * mp_row.size());

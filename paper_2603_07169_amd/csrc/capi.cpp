@@ -83,6 +83,7 @@ struct spmv_csr_s {
     spmv::CutScratch tp_cut{};
     size_t tp_reduce_lds = 0;
     std::vector<int32_t> tp_row, tp_nz;  // host copies for the read-back
+    spmv::GatherTiles gather{};  // MERGE and ADAPTIVE plans: x gathered in column order (words: null where the tile kernel runs)
     // The MERGE and TWOPHASE plans keep scratch in the handle (carries, products): a run on another stream while one is
     // still in flight would share it.  An event recorded behind every such run tells.
     hipEvent_t scratch_free = nullptr;
@@ -110,6 +111,13 @@ void free_pairs(spmv_csr_s* h) {
         if (p) (void)hipFree(p);
     h->pairs = spmv::PairRows{};
     h->d_spmm_src = nullptr;
+}
+
+void free_gather(spmv_csr_s* h) {
+    void* ptrs[] = {h->gather.chunk_desc, h->gather.words, h->gather.base, h->gather.cut_range, h->gather.cut.arrivals, h->gather.cut.carry_row, h->gather.cut.carry_val};
+    for (void* p : ptrs)
+        if (p) (void)hipFree(p);
+    h->gather = spmv::GatherTiles{};
 }
 
 void free_metadata(spmv_csr_s* h) {
@@ -152,6 +160,7 @@ void free_metadata(spmv_csr_s* h) {
     h->d_spmm_col = nullptr;
     h->d_spmm_val = nullptr;
     free_pairs(h);
+    free_gather(h);
     if (h->scratch_free) (void)hipEventDestroy(h->scratch_free);
     h->scratch_free = nullptr;
     h->scratch_used = false;
@@ -699,6 +708,70 @@ spmv_status_t build_sell(spmv_csr_s* h, const HostRowptr& rowptr_host, spmv::Ana
     return SPMV_ERR_ALLOC;
 }
 
+// The entries in column order chunk by chunk, for a MERGE or ADAPTIVE handle where gathering x in that order is the faster way.
+// Without room for them, or where 15 + 17 bits an entry cannot express them, the tile kernel runs.
+spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const spmv::Analysis& a) try {
+    const int32_t plan = a.info.plan;
+    const bool bf16 = h->dtype == SPMV_BF16, cuts_rows = plan == SPMV_PLAN_MERGE;
+    int dev = 0, cus = 0;
+    if (hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev))) return SPMV_ERR_HIP;
+    std::vector<int32_t> rows, entries, desc, cuts;
+    spmv::GatherTiles& t = h->gather;
+    int64_t P = 0;
+    // One chunk to a compute unit, or, where its LDS does not hold that, four, two at a time (FP32, 300 000 rows of 16: two chunks, one at a
+    // time, 22.3 us, three, two at a time, 22.4, four 22.1, the tile kernel 26.5; power law, 5.4 M entries: 33.5, 36.6, 31.3, 34.2).
+    for (int k = 1;; k += 3) {
+        if (k > 4) return SPMV_OK;
+        const int64_t places = static_cast<int64_t>(cus) * k, items = std::max((h->m + h->nnz + places - 1) / places, spmv::kGatherMinItems);
+        const int64_t snap = spmv::gather_snap(plan, a.info.max_len, items);
+        if (items + snap > spmv::kGatherMaxSlots) continue;
+        if (!spmv::gather_choice(h->m, h->nnz, plan, a.info.max_len, cus, k)) return SPMV_OK;
+        spmv::merge_path_splits(h->m, h->nnz, rowptr_host.data(), items, &rows, &entries);
+        spmv::merge_chunk_desc(h->m, rowptr_host.data(), rows, entries, snap, &desc);
+        P = static_cast<int64_t>(rows.size()) - 1;
+        int32_t most_rows = 0;
+        for (int64_t p = 0; p < P; ++p) most_rows = std::max(most_rows, rows[static_cast<size_t>(p) + 1] - rows[static_cast<size_t>(p)]);
+        t.slots = spmv::gather_slots(bf16, desc.data(), P);
+        t.lds = spmv::gather_lds(bf16, t.slots, most_rows);
+        if (t.lds <= (k == 1 ? spmv::kGatherMaxLds : spmv::kGatherMaxLds / 2) && t.slots <= spmv::kGatherMaxSlots) break;
+    }
+    t.num_chunks = static_cast<int32_t>(P);
+    t.stride = 1;
+    int64_t num_cuts = 0;
+    for (size_t p = 0; p < static_cast<size_t>(P); ++p) {
+        t.stride = std::max(t.stride, (desc[2 * p + 3] - desc[2 * p + 1] + 255) / 256);
+        entries[p] = desc[2 * p + 1];
+    }
+    if (cuts_rows) {
+        spmv::cut_ranges(h->m, rowptr_host.data(), rows, entries, &cuts);
+        for (size_t q = 0; 2 * q < cuts.size(); ++q) num_cuts += cuts[2 * q] >= 0;
+    }
+    const size_t groups = static_cast<size_t>(P) * static_cast<size_t>(t.stride);
+    int32_t* d_flag = nullptr;
+    int32_t flag = 0;
+    spmv_status_t st = upload(desc, &t.chunk_desc);
+    if (st == SPMV_OK && cuts_rows) st = upload(cuts, &t.cut_range);
+    if (st == SPMV_OK && (hip_failed(hipMalloc(reinterpret_cast<void**>(&t.words), 1024 * groups)) ||
+                          hip_failed(hipMalloc(reinterpret_cast<void**>(&t.base), 4 * groups)) ||
+                          hip_failed(hipMalloc(reinterpret_cast<void**>(&d_flag), sizeof(int32_t))) ||
+                          (cuts_rows && hip_failed(alloc_cut_scratch(&t.cut, num_cuts, P)))))
+        st = SPMV_ERR_ALLOC;
+    if (st == SPMV_OK && (hip_failed(hipMemcpy(d_flag, &flag, sizeof flag, hipMemcpyHostToDevice)) ||
+                          hip_failed(spmv::launch_gather_build(view_of(h), t, d_flag, nullptr)) ||
+                          hip_failed(hipMemcpy(&flag, d_flag, sizeof flag, hipMemcpyDeviceToHost))))
+        st = SPMV_ERR_HIP;
+    (void)hipFree(d_flag);
+    if (st != SPMV_OK || flag != 0) free_gather(h);
+    if (st == SPMV_ERR_ALLOC) {
+        (void)hipGetLastError();
+        st = SPMV_OK;
+    }
+    return st;
+} catch (const std::bad_alloc&) {
+    free_gather(h);
+    return SPMV_OK;
+}
+
 spmv::TwoPhase two_phase_of(const spmv_csr_s* h) {
     spmv::TwoPhase t{};
     t.shift = h->info.tp_col_shift;
@@ -912,8 +985,11 @@ spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* par
     }
     if (st == SPMV_OK && p.plan == SPMV_PLAN_SELL) st = build_sell(h, rowptr_host, &a);
     if (st == SPMV_OK && p.prepare_spmm) st = build_spmm_order(h, rowptr_host, &a);
+    // chunks and blocks that the caller shapes are the tile kernel's
+    const bool own_shape = params && (params->items_per_chunk != 0 || params->block_nnz != 0 || params->rows_max != 0);
+    if (st == SPMV_OK && p.plan == SPMV_PLAN_AUTO && !own_shape && h->nnz > 0) st = build_gather(h, rowptr_host, a);
     // the only plan whose run writes this
-    if (st == SPMV_OK && a.info.plan == SPMV_PLAN_MERGE && hip_failed(alloc_cut_scratch(&h->cut, merge_cuts, a.info.num_chunks)))
+    if (st == SPMV_OK && a.info.plan == SPMV_PLAN_MERGE && !h->gather.words && hip_failed(alloc_cut_scratch(&h->cut, merge_cuts, a.info.num_chunks)))
         st = SPMV_ERR_ALLOC;
     if (st == SPMV_OK && plan_has_scratch(a.info.plan) &&
         // A query of this event lets a run on another stream of the same device use the scratch, so what the run wrote has to be
@@ -979,6 +1055,10 @@ spmv_status_t spmv_csr_run(spmv_handle_t h, const void* x, float* y, float alpha
             break;
         }
         case SPMV_PLAN_ADAPTIVE:
+            if (h->gather.words) {
+                e = spmv::launch_gather(h->gather, A, x, y, s, st, nullptr);
+                break;
+            }
             e = spmv::launch_adaptive(A, h->d_block_desc, static_cast<int32_t>(h->info.num_row_blocks),
                                       h->info.block_nnz, h->info.rows_max, x, y, s, st);
             break;
@@ -1006,6 +1086,10 @@ spmv_status_t spmv_csr_run(spmv_handle_t h, const void* x, float* y, float alpha
             e = spmv::launch_sell(A, h->d_sell_ptr, h->info.sell_num_slices, h->d_sell_col, h->d_sell_val, x, y, s, st);
             break;
         case SPMV_PLAN_MERGE:
+            if (h->gather.words) {
+                e = spmv::launch_gather(h->gather, A, x, y, s, st, tracked ? h->scratch_free : nullptr);
+                break;
+            }
             e = spmv::launch_merge(A, h->d_chunk_desc, static_cast<int32_t>(h->info.num_chunks),
                                    h->info.items_per_chunk, h->cut, x, y, s, st,
                                    tracked ? h->scratch_free : nullptr);
@@ -1314,7 +1398,7 @@ const char* spmv_csr_kernel_name(spmv_handle_t h, const void* x, float beta) {
         case SPMV_PLAN_VECTOR:
         case SPMV_PLAN_BINNED: return spmv::vector_kernel_name();
         case SPMV_PLAN_ADAPTIVE:
-        case SPMV_PLAN_MERGE: return spmv::tile_kernel_name();
+        case SPMV_PLAN_MERGE: return h->gather.words ? spmv::gather_kernel_name() : spmv::tile_kernel_name();
         case SPMV_PLAN_WINDOWED:
             return spmv::windowed_kernel_name(
                 spmv::windowed_kernel(view_of(h), h->max_block_entries, h->info.rows_max, windows_of(h), x, beta));

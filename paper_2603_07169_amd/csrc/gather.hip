@@ -1,0 +1,315 @@
+// gfx950 kernels for the row-wise product with x gathered in column order: the MERGE and ADAPTIVE plans where the chip is full
+// and x too large for a compute unit's cache.
+#include <hip/hip_runtime.h>
+
+#include "analysis.h"
+#include "device_common.h"
+#include "kernels.h"
+#include "row_phase.h"
+
+namespace spmv {
+namespace {
+
+constexpr int kGatherWG = 1024;        // lanes of a workgroup
+constexpr int kGatherWords = 256;      // words of a group: a wavefront's load of 16 bytes a lane
+constexpr int kGatherPosBits = 15;     // low bits of a word: the entry's place in its chunk; above them its column less the group's first
+constexpr int kGatherDeferred = 512;   // rows far longer than the mean that a chunk can set aside (a chunk holds less than 2^15 entries)
+constexpr int kGatherBuckets = 16384;  // column intervals the entries of a chunk are sorted by, at most
+
+struct GatherArgs {
+    const int32_t* chunk_desc;  // [2*(P+1)] first row and first entry of each chunk
+    const uint32_t* words;      // [P * stride * 256]
+    const int32_t* base;        // [P * stride] first column of each group
+    const int32_t* rowptr;
+    const void* vals;
+    const void* x;
+    float* y;
+    const int32_t* cut_range;  // [2*(P+1)] (see finish_cut)
+    CutScratch cut;
+    int32_t stride;  // groups of words per chunk
+    int32_t cap;     // slots of a chunk in LDS; padding words point at the one behind them
+    int32_t nnz;
+    int32_t vec_ok;  // vals is 16-byte aligned
+    float alpha, beta;
+};
+
+// One workgroup per chunk of the merge path (MERGE; without cut rows for the ADAPTIVE plan), about as many chunks as compute units.
+//   1. The chunk's values are copied to LDS as they lie in CSR, past the registers.  At the same time its columns are read in
+//      ascending order, x is gathered in that order, and every value of x is put at its entry's place in CSR order.
+//   2. The row phase of the tile kernels, with both operands in LDS.
+// Bound: a gather of x out of a die's L2 brings a line of 128 bytes for 2 or 4 that are used, and the tile kernel asks for
+// one line per entry (340 MB for 2.7 M entries, 17 TB/s).  In column order the entries that share a line stand in the same
+// instruction, which asks for the line once; how often that happens grows with the entries a chunk holds, hence chunks as large
+// as the LDS allows, one to a compute unit (power law 333 333 rows, FP32, 1 / 2 / 3 / 4 chunks to a compute unit: 14.3 / 15.9 / 17.3 /
+// 17.7 us, the tile kernel 18.5; 300 000 rows of 16, bf16: 11.4 / 14.7 / 16.3 / 17.9, the tile kernel 22.8).
+// A lane's four words are 64 places apart, so that an instruction's 64 gathers are neighbours in the order.  A word is four bytes as colidx
+// is: the place, and the column less the first of 256 neighbours.  Chunks have a fixed stride in `words`, so that the words are
+// asked for at once and not after the chunk's bounds have come.  Values are read where the caller keeps them.
+// 512 lanes: the same up to 8000 entries a chunk, 10 to 20 % slower on 12000 and more.
+// The pieces of rows that the chunk's ends cut are summed first, so that their way through memory (finish_cut: three round trips) runs
+// beside the row phase: power law 333 333 rows 18.3 -> 16.6 us FP32, 14.8 -> 13.3 bf16.  Rows of more than 1024 entries in pieces for all
+// wavefronts: 17.1 and 13.8.  (Timed call by call on three matrices in turn: tile kernel 20.2 and 18.6.)
+template <typename T, bool MERGE, int U>
+__global__ __launch_bounds__(kGatherWG) void spmv_gather_kernel(const GatherArgs a) {
+    using E = typename T::elem;
+    constexpr int VEC = T::VEC, WG = kGatherWG, WAVES = WG / 64;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ int deferred[kGatherDeferred];
+    __shared__ int n_deferred;
+    __shared__ float part_sums[kGatherWG / 64];  // of the pieces that the chunk's ends cut: its first row's in the first half, its last row's in the second
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int part = xcd_remap(blockIdx.x, gridDim.x);
+    const E* const x = static_cast<const E*>(a.x);
+    const u32x4* const words = reinterpret_cast<const u32x4*>(a.words) + static_cast<size_t>(part) * a.stride * 64;
+    const int32_t* const base = a.base + static_cast<size_t>(part) * a.stride;
+
+    u32x4 w[U];
+    int first[U];
+    auto ask = [&](int g0) {  // the wavefront's groups of one round; past the chunk's: the last again, whose words are then not used
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int g = g0 + wave + u * WAVES;
+            const int held = g < a.stride ? g : a.stride - 1;
+            w[u] = __builtin_nontemporal_load(words + held * 64 + lane);
+            first[u] = base[held];
+        }
+    };
+    ask(0);
+
+    const int r0 = a.chunk_desc[2 * part];
+    const int k0 = a.chunk_desc[2 * part + 1];
+    const int nr = a.chunk_desc[2 * part + 2] - r0;
+    const int k1 = a.chunk_desc[2 * part + 3];
+    const int k0a = k0 & ~(VEC - 1);
+    const int span = k1 - k0a;
+    const int nseg = nr + (MERGE ? 1 : 0);
+    const bool first_row_began = MERGE && a.rowptr[r0] < k0;  // in an earlier chunk
+    E* const vals_l = reinterpret_cast<E*>(smem_raw);  // [cap]
+    E* const x_l = vals_l + a.cap;                     // [cap + VEC]
+    int* const seg = reinterpret_cast<int*>(x_l + a.cap + VEC);
+    float* const y0_l = reinterpret_cast<float*>(seg + nseg + 1);
+
+    const int rp0 = a.rowptr[r0 + (tid < nr ? tid : nr)];
+    const float y0v = (a.beta != 0.f && tid < nr) ? a.y[r0 + tid] : 0.f;
+    int whole = 0;  // vectors of vals that lie in the array as a whole
+    if (a.vec_ok) {
+        const int held = (span + VEC - 1) / VEC, there = (a.nnz - k0a) / VEC;
+        whole = held < there ? held : there;
+        const uint32_t to = lds_address(vals_l);
+        const unsigned char* const from = static_cast<const unsigned char*>(a.vals) + sizeof(E) * static_cast<size_t>(k0a);
+        for (int v = 64 * wave; v < whole; v += WG)
+            if (lane < whole - v) copy16_to_lds_nt(to + 16 * v, from + 16 * static_cast<size_t>(v), 16u * static_cast<unsigned>(lane));
+    }
+    for (int i = whole * VEC + tid; i < span; i += WG)
+        if (k0a + i >= k0) vals_l[i] = static_cast<const E*>(a.vals)[k0a + i];
+
+    for (int g0 = 0;;) {
+        E xv[U][4];
+        unsigned at[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                xv[u][i] = x[static_cast<unsigned>(first[u]) + (w[u][i] >> kGatherPosBits)];
+                at[u][i] = w[u][i] & ((1u << kGatherPosBits) - 1);
+            }
+        const int here = g0;
+        g0 += U * WAVES;
+        const bool more = g0 < a.stride;
+        if (more) ask(g0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (here + wave + u * WAVES < a.stride) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x_l[at[u][i]] = xv[u][i];
+            }
+        if (!more) break;
+    }
+
+    auto bound = [&](int v) {
+        v = v < k0 ? k0 : v;
+        v = v > k1 ? k1 : v;
+        return v - k0a;
+    };
+    if (tid == 0) {
+        n_deferred = 0;
+        if (MERGE) seg[nseg] = k1 - k0a;
+    }
+    if (tid <= nr) seg[tid] = bound(rp0);
+    if (tid < nr) y0_l[tid] = y0v;
+    for (int i = tid + WG; i <= nr; i += WG) seg[i] = bound(a.rowptr[r0 + i]);
+    if (a.beta != 0.f)
+        for (int i = tid + WG; i < nr; i += WG) y0_l[i] = a.y[r0 + i];
+    wait_all_and_barrier();
+
+    int done = 0;  // rows taken before the row phase
+    if constexpr (MERGE) {
+        const bool head_cut = !a.cut.carry_row && nr > 0 && first_row_began;
+        const bool tail_cut = seg[nr + 1] > seg[nr];
+        if (head_cut || tail_cut) {
+            float sum = 0.f;
+            const bool tail = wave >= WAVES / 2;
+            if (tail ? tail_cut : head_cut) {
+                const int b = tail ? seg[nr] : seg[0], e = tail ? seg[nr + 1] : seg[1];
+                sum = group_sum<64>(segment_dot<WG / 2>(static_cast<const AtSlot*>(nullptr), vals_l, x_l, b, e, tid % (WG / 2)));
+            }
+            if (lane == 0) part_sums[wave] = sum;
+            __syncthreads();
+            const RowOut o{a.y, y0_l, a.alpha, a.beta, nullptr, head_cut};
+            const CutOut c{a.cut.carry_val, a.cut.arrivals, a.cut_range, nullptr, 0, a.cut.carry_row};
+            // the last two wavefronts, which have no rows to spare for a last sweep
+            if (tid == WG - 128 && head_cut) {
+                float s = 0.f;
+                for (int v = 0; v < WAVES / 2; ++v) s += part_sums[v];
+                finish_cut(o, c, r0, part, true, epilogue(s, a.alpha, a.beta, y0_l, 0));
+            }
+            if (tid == WG - 64 && tail_cut) {
+                float s = 0.f;
+                for (int v = WAVES / 2; v < WAVES; ++v) s += part_sums[v];
+                if (a.cut.carry_row) a.cut.carry_val[part] = s;
+                else finish_cut(o, c, r0 + nr, part, false, s);
+            }
+            done = head_cut ? 1 : 0;
+        }
+        if (a.cut.carry_row && tid == WG - 64) a.cut.carry_row[part] = tail_cut ? r0 + nr : -1;
+    }
+    const RowOut o{a.y, y0_l + done, a.alpha, a.beta, nullptr, false};
+    tile_rows<false, WG>(static_cast<const AtSlot*>(nullptr), vals_l, x_l, seg + done, nr - done, r0 + done, seg[nr] - seg[done], o, deferred, &n_deferred, tid);
+}
+
+// Analysis: one workgroup per chunk sorts its entries by column interval (counts, prefix sums, places handed out with a counter per
+// interval, all in LDS) and writes the chunk's words.  Inside an interval - at least a line of x - the order does not matter, to
+// the gathers no more than to the result.  *flag is set where a column is out of range or too far from its group's first.
+__global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* __restrict__ colidx, const int32_t* __restrict__ chunk_desc,
+                                                                 int n, int shift, int vec, int stride, int cap,
+                                                                 uint32_t* __restrict__ words, int32_t* __restrict__ base, int32_t* flag) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    constexpr int WG = kGatherWG;
+    int* const place = reinterpret_cast<int*>(smem_raw);  // [buckets]
+    const int buckets = ((n - 1) >> shift) + 1;
+    __shared__ int group_first[(1 << kGatherPosBits) / kGatherWords];
+    __shared__ int wave_sums[WG / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int part = blockIdx.x;
+    const int k0 = chunk_desc[2 * part + 1], k1 = chunk_desc[2 * part + 3];
+    const int k0a = k0 & ~(vec - 1);
+    const int entries = k1 - k0;
+    bool bad = false;
+    auto bucket_of = [&](int c) {
+        if (c < 0 || c >= n) {
+            bad = true;
+            c = 0;
+        }
+        return c >> shift;
+    };
+    for (int i = tid; i < buckets; i += WG) place[i] = 0;
+    __syncthreads();
+    for (int k = k0 + tid; k < k1; k += WG) atomicAdd(place + bucket_of(colidx[k]), 1);
+    __syncthreads();
+    // exclusive prefix sums: a lane takes a run of buckets
+    const int run = (buckets + WG - 1) / WG, b0 = tid * run, b1 = b0 + run < buckets ? b0 + run : buckets;
+    int mine = 0;
+    for (int b = b0; b < b1; ++b) mine += place[b];
+    int before = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int up = __shfl_up(before, d);
+        if (lane >= d) before += up;
+    }
+    if (lane == 63) wave_sums[wave] = before;
+    __syncthreads();
+    int at = before - mine;
+    for (int v = 0; v < wave; ++v) at += wave_sums[v];
+    for (int b = b0; b < b1; ++b) {
+        const int count = place[b];
+        place[b] = at;
+        for (int g = (at + kGatherWords - 1) / kGatherWords; g * kGatherWords < at + count; ++g) group_first[g] = b << shift;
+        at += count;
+    }
+    __syncthreads();
+    for (int g = tid; g < stride; g += WG)
+        base[static_cast<size_t>(part) * stride + g] = g * kGatherWords < entries ? group_first[g] : 0;
+    uint32_t* const out = words + static_cast<size_t>(part) * stride * kGatherWords;
+    auto put = [&](int i, uint32_t word) { out[(i & ~(kGatherWords - 1)) + 4 * (i & 63) + ((i >> 6) & 3)] = word; };
+    for (int i = entries + tid; i < stride * kGatherWords; i += WG) put(i, static_cast<uint32_t>(cap));
+    for (int k = k0 + tid; k < k1; k += WG) {
+        const int c = colidx[k];
+        const int i = atomicAdd(place + bucket_of(c), 1);
+        const uint32_t off = static_cast<uint32_t>(c - group_first[i / kGatherWords]);
+        if (off >= 1u << (32 - kGatherPosBits)) bad = true;
+        put(i, off << kGatherPosBits | static_cast<uint32_t>(k - k0a));
+    }
+    if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) *flag = 1;  // plain store: every writer writes 1
+}
+
+template <typename K>
+hipError_t allow_lds(K kernel, size_t lds, size_t* allowed) {
+    if (lds <= 64 * 1024 || lds <= *allowed) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    if (e == hipSuccess) *allowed = lds;
+    return e;
+}
+
+template <typename T, bool MERGE, int U>
+hipError_t launch_gather_u(const GatherArgs& a, int32_t P, size_t lds, hipStream_t st, hipEvent_t done) {
+    auto k = spmv_gather_kernel<T, MERGE, U>;
+    static thread_local size_t allowed = 0;
+    const hipError_t e = allow_lds(k, lds, &allowed);
+    return e == hipSuccess ? launch_with_event(k, dim3(P), dim3(kGatherWG), lds, st, done, a) : e;
+}
+
+template <typename T, bool MERGE>
+hipError_t launch_gather_t(const GatherArgs& a, int32_t P, size_t lds, hipStream_t st, hipEvent_t done) {
+    // groups a wavefront asks for at once: all of them up to four, beyond that as many rounds of equal size (92 groups, three at a time 21.0, four 21.9 us)
+    constexpr int WAVES = kGatherWG / 64;
+    const int rounds = (a.stride + 4 * WAVES - 1) / (4 * WAVES);
+    switch ((a.stride + rounds * WAVES - 1) / (rounds * WAVES)) {
+        case 1: return launch_gather_u<T, MERGE, 1>(a, P, lds, st, done);
+        case 2: return launch_gather_u<T, MERGE, 2>(a, P, lds, st, done);
+        case 3: return launch_gather_u<T, MERGE, 3>(a, P, lds, st, done);
+        default: return launch_gather_u<T, MERGE, 4>(a, P, lds, st, done);
+    }
+}
+
+}  // namespace
+
+int32_t gather_slots(bool bf16, const int32_t* chunk_desc, int64_t P) {
+    const int vec = bf16 ? BF16::VEC : F32::VEC;
+    int32_t most = vec;
+    for (int64_t p = 0; p < P; ++p) {
+        const int32_t held = chunk_desc[2 * p + 3] - (chunk_desc[2 * p + 1] & ~(vec - 1));
+        if (held > most) most = held;
+    }
+    return (most + vec - 1) & ~(vec - 1);
+}
+
+size_t gather_lds(bool bf16, int32_t slots, int32_t rows) {
+    const size_t e = bf16 ? 2 : 4, vec = bf16 ? BF16::VEC : F32::VEC;
+    return e * (2 * static_cast<size_t>(slots) + vec) + 4 * (2 * static_cast<size_t>(rows) + 2);
+}
+
+hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_t* flag, hipStream_t st) {
+    const int line = A.bf16 ? 6 : 5;  // columns of a line of x
+    int shift = line;
+    while (((A.n - 1) >> shift) + 1 > kGatherBuckets) ++shift;
+    const size_t lds = sizeof(int) * static_cast<size_t>(((A.n - 1) >> shift) + 1);
+    static thread_local size_t allowed = 0;
+    const hipError_t e = allow_lds(gather_build_kernel, lds, &allowed);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(gather_build_kernel, dim3(t.num_chunks), dim3(kGatherWG), lds, st, A.colidx, t.chunk_desc, A.n, shift,
+                       A.bf16 ? BF16::VEC : F32::VEC, t.stride, t.slots, t.words, t.base, flag);
+    return hipGetLastError();
+}
+
+hipError_t launch_gather(const GatherTiles& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done) {
+    const GatherArgs a{t.chunk_desc, t.words, t.base, A.rowptr, A.vals, x, y, t.cut_range, t.cut, t.stride, t.slots, A.nnz, A.vec_ok ? 1 : 0, s.alpha, s.beta};
+    if (!t.cut_range) return A.bf16 ? launch_gather_t<BF16, false>(a, t.num_chunks, t.lds, st, done) : launch_gather_t<F32, false>(a, t.num_chunks, t.lds, st, done);
+    hipEvent_t const last = t.cut.carry_row ? nullptr : done;
+    const hipError_t e = A.bf16 ? launch_gather_t<BF16, true>(a, t.num_chunks, t.lds, st, last) : launch_gather_t<F32, true>(a, t.num_chunks, t.lds, st, last);
+    return e == hipSuccess && t.cut.carry_row ? launch_cut_rows(t.cut, t.num_chunks, y, s.alpha, st, done) : e;
+}
+
+const char* gather_kernel_name() { return "spmv_gather_kernel"; }
+
+}  // namespace spmv

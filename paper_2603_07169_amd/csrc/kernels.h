@@ -202,6 +202,25 @@ hipError_t launch_column_block_scatter(const MatrixView& A, int shift, int C, co
 // cb_vals[k] = vals[cb_src[k]] for the nnz regrouped entries (the caller's values may have changed).
 hipError_t launch_column_block_values(const MatrixView& A, const int32_t* cb_src, void* cb_vals, hipStream_t st);
 
+// The row-wise product with x gathered in column order, of a MERGE or ADAPTIVE handle (device arrays owned by the handle).
+constexpr size_t kGatherMaxLds = 160 * 1024 - 8192;  // LDS of a chunk; the rest is the kernel's own
+constexpr int32_t kGatherMaxSlots = (1 << 15) - 8;   // a place in a chunk takes 15 bits, one more is the padding's
+struct GatherTiles {
+    int32_t* chunk_desc;  // [2*(num_chunks+1)] pairs (first row, first entry)
+    uint32_t* words;      // [num_chunks * stride * 256] a chunk's entries by column: place in the chunk, column less the group's first
+    int32_t* base;        // [num_chunks * stride] first column of each group of 256
+    int32_t* cut_range;   // [2*(num_chunks+1)] (see finish_cut); null: no chunk cuts a row (ADAPTIVE)
+    CutScratch cut;
+    int32_t num_chunks, stride, slots;
+    size_t lds;
+};
+// LDS slots of the largest chunk (desc: HOST array), and the LDS bytes of a workgroup for them and at most `rows` rows.
+int32_t gather_slots(bool bf16, const int32_t* desc, int64_t P);
+size_t gather_lds(bool bf16, int32_t slots, int32_t rows);
+// Analysis time: fills words and base; *flag is set where they cannot express the matrix.
+hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_t* flag, hipStream_t st);
+hipError_t launch_gather(const GatherTiles& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done);
+
 // The two-pass plan (device arrays owned by the handle).
 struct TwoPhase {
     int32_t shift;              // column blocks of 2^shift columns (of 2^shift groups' columns when group == 8)
@@ -269,6 +288,7 @@ hipError_t launch_reduce_selftest(const float* in, float* out, hipStream_t st);
 
 const char* scalar_kernel_name();
 const char* vector_kernel_name();
+const char* gather_kernel_name();
 const char* tile_kernel_name();  // kernel of the adaptive and merge plans
 const char* windowed_kernel_name(WindowKernel k);
 const char* spmm_kernel_name();

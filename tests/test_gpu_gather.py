@@ -1,0 +1,151 @@
+"""GPU: the row-wise product with x gathered in column order (spmv_gather_kernel) - one chunk to a compute unit and four, chunks of
+several rounds of words, cut rows, unaligned arrays, and the matrices that stay with the tile kernel - against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_07169_amd as s
+import workloads as w
+from gpu_util import DeviceProblem, assert_close, reference
+
+pytestmark = pytest.mark.gpu
+
+GATHER, TILE = "spmv_gather_kernel", "spmv_tile_kernel"
+
+
+def problem(lens, n, dtype, seed=0, beta=0.5, width=None):
+    """Integer-valued, so that every order of summation gives the same binary32 number: |sum| < 40000 * 32 < 2^24."""
+    rng = np.random.default_rng(seed)
+    lens = np.asarray(lens, dtype=np.int64)
+    m = lens.size
+    rowptr = np.concatenate(([0], np.cumsum(lens))).astype(np.int32)
+    rows = np.repeat(np.arange(m, dtype=np.int64), lens)
+    cols = rng.integers(0, n, rows.size) if width is None else np.clip(rows * n // m + rng.integers(0, width, rows.size), 0, n - 1)
+    vals, x = rng.integers(-4, 5, rows.size).astype(np.float32), rng.integers(-8, 9, n).astype(np.float32)
+    if dtype == "bf16":
+        vals, x = ((a.view(np.uint32) >> 16).astype(np.uint16) for a in (vals, x))
+    return w.CsrProblem(name="gather", dtype=dtype, m=m, n=n, rowptr=rowptr, colidx=cols.astype(np.int32), vals=vals, x=x,
+                        alpha=1.0, beta=beta, y0=rng.integers(-8, 9, m).astype(np.float32))
+
+
+def check(p, kernel, offset=0, params=None, runs=2):
+    d = DeviceProblem(p, offset)
+    A = d.matrix(params)
+    assert s.spmv_csr_main_kernel_name(A.handle) == kernel
+    y_ref, _ = reference(p)
+    for _ in range(runs):  # the counters of cut rows are back at zero after a run
+        assert np.array_equal(d.run(A), y_ref.astype(np.float32))
+    return d, A
+
+
+UNIFORM = {  # ADAPTIVE: rows x length, columns
+    "rows_of_16": ([16] * 30000, 30000),                       # several lanes a row in binary32
+    "odd": (np.random.default_rng(1).integers(0, 40, 40001), 9973),
+    "least": ([8] * 49152, 50000),                             # the fewest entries the rule takes
+    "long_rows": ([700] * 3000, 70000),                        # a wavefront a row
+    "four_words_a_lane": ([16] * 220000, 100000),
+    "four_chunks": ([16] * 300000, 100000),                    # binary32: four chunks to a compute unit; bf16: words in two rounds
+    "banded": ([24] * 30000, 400000),
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("name", list(UNIFORM))
+def test_uncut_rows(name, dtype):
+    lens, n = UNIFORM[name]
+    p = problem(lens, n, dtype, beta=0.5, width=20000 if name == "banded" else None)
+    d, A = check(p, GATHER, runs=1)
+    assert A.info.plan == s.SPMV_PLAN_ADAPTIVE
+    y_ref, _ = reference(p, 1.0, 0.0)  # an old y that is not to be read
+    y = d.run(A, beta=0.0, y_init=torch.full((p.m,), float("nan"), device="cuda"))
+    assert np.array_equal(y, y_ref.astype(np.float32))
+
+
+def lengths_with(long_rows, short=60000, seed=3):
+    lens = np.random.default_rng(seed).integers(0, 9, short)
+    for at, length in long_rows:
+        lens[at] = length
+    return lens
+
+
+CUT = {
+    "first_and_last": lengths_with([(0, 3000), (59999, 5000)]),
+    "neighbours": lengths_with([(i, 1700) for i in range(100, 130)]),      # both ends of a chunk inside rows
+    "over_many_chunks": lengths_with([(7, 30000), (8, 513), (9, 40000)]),  # chunks without a row's end
+    "all_long": [2900] * 150,
+    "snapped": lengths_with([(i, 512) for i in range(0, 60000, 50)] + [(77, 2000)]),
+    "least": lengths_with([(5, 1100)], short=16100),                        # about the fewest entries the rule takes
+    "empty_ends": np.concatenate(([0] * 5000, lengths_with([(100, 2000)]), [0] * 7000)),
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("name", list(CUT))
+def test_cut_rows(name, dtype):
+    p = problem(CUT[name], 50000, dtype)
+    kernel = GATHER if p.nnz >= 1 << 16 else TILE
+    _, A = check(p, kernel)
+    assert A.info.plan == s.SPMV_PLAN_MERGE
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("plan", ["adaptive", "merge"])
+def test_unaligned_arrays(plan, dtype):
+    lens = UNIFORM["odd"][0] if plan == "adaptive" else CUT["neighbours"]
+    check(problem(lens, 9973, dtype), GATHER, offset=1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_real_values(dtype):
+    p = problem(CUT["neighbours"], 30000, dtype)
+    rng = np.random.default_rng(5)
+    vals, x = rng.standard_normal(p.nnz).astype(np.float32), rng.standard_normal(p.n).astype(np.float32)
+    p.vals, p.x = (a if dtype == "f32" else (a.view(np.uint32) >> 16).astype(np.uint16) for a in (vals, x))
+    d = DeviceProblem(p)
+    A = d.matrix()
+    y_ref, S_ref = reference(p)
+    assert_close(p, d.run(A), y_ref, S_ref, p.alpha, p.beta)
+
+
+def test_values_changed_in_place_and_non_finite_x():
+    p = problem(UNIFORM["odd"][0], 9973, "f32", beta=0.0)
+    d, A = check(p, GATHER)
+    p.vals = -p.vals
+    d.vals.neg_()
+    assert np.array_equal(d.run(A), reference(p)[0].astype(np.float32))
+    used = int(p.colidx[7])
+    d.x[used] = float("inf")
+    y = d.run(A)
+    rows = np.unique(np.repeat(np.arange(p.m), np.diff(p.rowptr))[p.colidx == used])
+    assert not np.isfinite(y[rows]).all() and np.isfinite(np.delete(y, rows)).all()
+
+
+def test_matrices_of_the_tile_kernel():
+    check(problem([8] * 40000, 50000, "f32"), TILE)                                      # too few entries
+    check(problem([40000] * 3, 100000, "f32"), TILE)                                     # rows over too many chunks
+    check(problem([16] * 30000, 30000, "f32"), TILE, params=dict(plan=s.SPMV_PLAN_ADAPTIVE))
+    check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(plan=s.SPMV_PLAN_MERGE))
+    check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(items_per_chunk=512))
+    check(problem([8] * 50000, 200_000_000, "bf16"), TILE)                               # neighbours too far apart for a word
+
+
+def test_graph_replays_and_streams():
+    p = problem(UNIFORM["odd"][0], 9973, "f32")
+    d, A = check(p, GATHER)
+    y_ref = reference(p)[0].astype(np.float32)
+    y = torch.zeros(p.m, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        A.run(d.x, y, 1.0, p.beta, torch.cuda.current_stream().cuda_stream)
+    for _ in range(3):
+        y.copy_(d.y0)
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy(), y_ref)
+        assert np.array_equal(d.run(A), y_ref)
+    streams, ys = [torch.cuda.Stream() for _ in range(2)], [d.y0.clone() for _ in range(2)]
+    torch.cuda.synchronize()
+    for st, out in zip(streams, ys):  # an adaptive handle keeps no scratch: its runs may overlap
+        A.run(d.x, out, 1.0, p.beta, st.cuda_stream)
+    torch.cuda.synchronize()
+    assert all(np.array_equal(out.cpu().numpy(), y_ref) for out in ys)

@@ -52,6 +52,8 @@ int sheets_pay(int elem, int64_t m, int64_t nnz, int64_t nb, int block_nnz, int 
 int stream_lanes(int elem, int64_t m, int64_t nnz, int rows_max, int places, int common) {
     return spmv::stream_lanes(elem, m, nnz, rows_max, places, common);
 }
+int gather_choice(int64_t m, int64_t nnz, int plan, int64_t max_len, int cus, int k) { return spmv::gather_choice(m, nnz, plan, max_len, cus, k); }
+int64_t gather_snap(int plan, int64_t max_len, int64_t items) { return spmv::gather_snap(plan, max_len, items); }
 int common_len(int64_t m, const int32_t* rp) { return spmv::common_row_length(m, rp); }
 }
 """
@@ -286,3 +288,20 @@ def test_common_row_length_of_a_sample(rules, line):
         for length in (5, 27, 64):
             assert rules.common_len(i64(m), P(rowptr_of(np.where((at == 0) | (at == line - 1), length - 3, length)))) == length
     assert rules.common_len(i64(9000), P(rowptr_of([7, 8, 9] * 3000))) == 0
+
+
+def test_gather_rule(rules):
+    import paper_2603_07169_amd as s
+    choice = lambda m, nnz, plan, longest, k=1: rules.gather_choice(i64(m), i64(nnz), plan, i64(longest), 256, k)
+    rules.gather_snap.restype = C.c_int64
+    A, M = s.SPMV_PLAN_ADAPTIVE, s.SPMV_PLAN_MERGE
+    assert choice(30000, 3 << 17, A, 20) and not choice(30000, (3 << 17) - 1, A, 20)
+    items = -(-(30000 + 480000) // 256)
+    assert choice(30000, 480000, A, items // 2) and not choice(30000, 480000, A, items // 2 + 1)  # half a chunk is the longest uncut row
+    assert not choice(30000, 480000, A, items // 2, 4)                                             # chunks of a quarter the steps
+    assert choice(10000, 1 << 16, M, 2000) and not choice(10000, (1 << 16) - 1, M, 2000)
+    assert choice(10000, 1 << 16, M, 32 * 512) and not choice(10000, 1 << 16, M, 32 * 512 + 1)     # chunks of 512 steps at least
+    for plan in (s.SPMV_PLAN_SCALAR, s.SPMV_PLAN_VECTOR, s.SPMV_PLAN_BINNED, s.SPMV_PLAN_WINDOWED, s.SPMV_PLAN_TWOPHASE, s.SPMV_PLAN_COLBLOCK, s.SPMV_PLAN_SELL):
+        assert not choice(30000, 1 << 20, plan, 20)
+    assert rules.gather_snap(A, i64(300), i64(2000)) == 300
+    assert rules.gather_snap(M, i64(9000), i64(2000)) == 512 and rules.gather_snap(M, i64(9000), i64(512)) == 511
