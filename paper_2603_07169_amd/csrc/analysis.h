@@ -79,7 +79,9 @@ bool two_phase_choice(int64_t m, int64_t n, int64_t nnz, spmv_dtype_t dtype, int
 // us, tile kernel / in column order:
 //   - ADAPTIVE, rows of 16, FP32 and bf16: 160 k entries 3.7 / 4.4 and 3.8 / 4.3, 320 k 4.1 / 4.2 and 4.0 / 4.3, rows of 8, 320 k 4.3 / 5.0 and
 //     4.3 / 4.3, 400 k 4.5 / 4.5 and 4.3 / 4.0; rows of 16, 800 k 5.9 / 5.2 and 5.1 / 4.0, 1.6 M 10.7 / 7.9 and 9.0 / 5.4, 3.2 M 19.5 / 14.5 and 16.9 / 8.8.
-//     Rows are not cut there, so the longest may take half a chunk.
+//     Rows are not cut there, so the longest may take half a chunk.  Out of a graph, with an x that the compute units' own caches hold: 2048
+//     columns 490 k and 670 k entries 4.0 / 3.9 and 3.7 / 3.6 FP32, 3.9 / 3.7 and 4.2 / 3.9 bf16;
+//     5000 columns, 800 k 4.6 / 4.3 and 4.1 / 3.6.
 //   - MERGE, power-law rows: 92 k entries 8.6 / 5.7 and 8.4 / 5.5, 626 k 10.6 / 7.4 and 10.1 / 6.8, 2.6 M 20.2 / 16.6 and 18.6 / 13.3; 20 000 rows
 //     of 3 and one of 1500, 61 k entries, 4.8 / 5.7 and 4.5 / 5.2.  A row that many small chunks cut is put together by one lane of the last:
 //     3 rows of 40 000 in chunks of 512 8.4 / 14.0; 300 000 rows of 5 and one of 200 000, 26 chunks, 21.8 / 13.2.

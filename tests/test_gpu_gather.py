@@ -125,6 +125,7 @@ def test_matrices_of_the_tile_kernel():
     check(problem([40000] * 3, 100000, "f32"), TILE)                                     # rows over too many chunks
     check(problem([16] * 30000, 30000, "f32"), TILE, params=dict(plan=s.SPMV_PLAN_ADAPTIVE))
     check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(plan=s.SPMV_PLAN_MERGE))
+    check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(prepare_spmm=1))   # a handle for products with matrices
     check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(items_per_chunk=512))
     check(problem([8] * 50000, 200_000_000, "bf16"), TILE)                               # neighbours too far apart for a word
 
