@@ -93,7 +93,7 @@ hipError_t launch_column_block_count(const MatrixView& A, int shift, int C, int3
     const int ntiles = column_block_tiles(A.nnz);
     if (ntiles <= 0) return hipSuccess;
     if (C > kMaxColBlocks) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(cb_tile_kernel<false>, dim3(ntiles), dim3(64), 0, st, A.rowptr, A.colidx, A.vals, A.bf16 ? 2 : 4, A.m,
+    launch_kernel(cb_tile_kernel<false>, dim3(ntiles), dim3(64), 0, st, A.rowptr, A.colidx, A.vals, A.bf16 ? 2 : 4, A.m,
                        A.nnz, shift, C, ntiles, tile_counts, nullptr, nullptr, nullptr, nullptr, nullptr);
     return hipGetLastError();
 }
@@ -103,7 +103,7 @@ hipError_t launch_column_block_scatter(const MatrixView& A, int shift, int C, co
     const int ntiles = column_block_tiles(A.nnz);
     if (ntiles <= 0) return hipSuccess;
     if (C > kMaxColBlocks) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(cb_tile_kernel<true>, dim3(ntiles), dim3(64), 0, st, A.rowptr, A.colidx, A.vals, A.bf16 ? 2 : 4, A.m,
+    launch_kernel(cb_tile_kernel<true>, dim3(ntiles), dim3(64), 0, st, A.rowptr, A.colidx, A.vals, A.bf16 ? 2 : 4, A.m,
                        A.nnz, shift, C, ntiles, nullptr, tile_base, cb_row, cb_col, cb_src, cb_vals);
     return hipGetLastError();
 }
@@ -113,10 +113,10 @@ hipError_t launch_column_block_values(const MatrixView& A, const int32_t* cb_src
     int grid = ceil_div(A.nnz, kWG);
     if (grid > 8192) grid = 8192;
     if (A.bf16)
-        hipLaunchKernelGGL(cb_values_kernel<uint16_t>, dim3(grid), dim3(kWG), 0, st, static_cast<const uint16_t*>(A.vals), cb_src,
+        launch_kernel(cb_values_kernel<uint16_t>, dim3(grid), dim3(kWG), 0, st, static_cast<const uint16_t*>(A.vals), cb_src,
                            static_cast<uint16_t*>(cb_vals), A.nnz);
     else
-        hipLaunchKernelGGL(cb_values_kernel<float>, dim3(grid), dim3(kWG), 0, st, static_cast<const float*>(A.vals), cb_src,
+        launch_kernel(cb_values_kernel<float>, dim3(grid), dim3(kWG), 0, st, static_cast<const float*>(A.vals), cb_src,
                            static_cast<float*>(cb_vals), A.nnz);
     return hipGetLastError();
 }

@@ -327,7 +327,7 @@ hipError_t launch_coo_t(int32_t m, int32_t nnz, const int32_t* row, const int32_
                         float* y, Scalars s, hipStream_t st) {
     using E = typename T::elem;
     int grid = ceil_div(m, kWG);
-    hipLaunchKernelGGL(scale_y_kernel, dim3(grid > 2048 ? 2048 : grid), dim3(kWG), 0, st, y, m, s.beta);
+    launch_kernel(scale_y_kernel, dim3(grid > 2048 ? 2048 : grid), dim3(kWG), 0, st, y, m, s.beta);
     if (nnz > 0) {
         // the caller's arrays start where they start: whole-vector loads only if all three are aligned as they are
         const bool vec = reinterpret_cast<uintptr_t>(row) % 16 == 0 && reinterpret_cast<uintptr_t>(col) % 16 == 0 &&
@@ -338,7 +338,7 @@ hipError_t launch_coo_t(int32_t m, int32_t nnz, const int32_t* row, const int32_
         // 187 -> 167 at 64 (bf16 146 -> 136).
         const int stretches = ceil_div(nnz, 4 * kWG);
         grid = stretches <= 8192 ? stretches : (stretches <= 16384 ? 8192 : (stretches + 1) / 2);
-        hipLaunchKernelGGL((spmv_coo_kernel<T>), dim3(grid), dim3(kWG), 0, st, row, col,
+        launch_kernel((spmv_coo_kernel<T>), dim3(grid), dim3(kWG), 0, st, row, col,
                            static_cast<const E*>(vals), static_cast<const E*>(x), y, nnz, 0, vec ? 1 : 0, s.alpha);
     }
     return hipGetLastError();
@@ -349,7 +349,7 @@ hipError_t launch_csc_tg(int32_t m, int32_t n, int32_t nnz, const int32_t* col_o
                          const void* x, float* y, Scalars s, hipStream_t st) {
     using E = typename T::elem;
     const int grid = ceil_div(m, kWG);
-    hipLaunchKernelGGL(scale_y_kernel, dim3(grid > 2048 ? 2048 : grid), dim3(kWG), 0, st, y, m, s.beta);
+    launch_kernel(scale_y_kernel, dim3(grid > 2048 ? 2048 : grid), dim3(kWG), 0, st, y, m, s.beta);
     if (n <= 0) return hipGetLastError();
     const int blocks = ceil_div(static_cast<int64_t>(n) * G, kWG);
     if (m <= kCscLdsRows) {
@@ -364,10 +364,10 @@ hipError_t launch_csc_tg(int32_t m, int32_t n, int32_t nnz, const int32_t* col_o
         const int lds_blocks = ceil_div(static_cast<int64_t>(n) * G, kCscLdsWG);
         const int col_blocks = lds_blocks > kCscLdsBlocks ? kCscLdsBlocks : lds_blocks;
         const int parts = (nnz <= (1 << 20) && nnz >= 8 * static_cast<int64_t>(n) && m >= 2) ? 2 : 1;
-        hipLaunchKernelGGL((spmv_csc_lds_kernel<T, G>), dim3(col_blocks, parts), dim3(kCscLdsWG), sizeof(float) * (m / parts + 1), st,
+        launch_kernel((spmv_csc_lds_kernel<T, G>), dim3(col_blocks, parts), dim3(kCscLdsWG), sizeof(float) * (m / parts + 1), st,
                            col_offsets, row, static_cast<const E*>(vals), static_cast<const E*>(x), y, m, n, s.alpha);
     } else {
-        hipLaunchKernelGGL((spmv_csc_kernel<T, G>), dim3(blocks), dim3(kWG), 0, st, col_offsets, row,
+        launch_kernel((spmv_csc_kernel<T, G>), dim3(blocks), dim3(kWG), 0, st, col_offsets, row,
                            static_cast<const E*>(vals), static_cast<const E*>(x), y, n, s.alpha);
     }
     return hipGetLastError();
@@ -377,9 +377,8 @@ template <typename T, int G>
 hipError_t launch_ell_tg(int32_t m, int32_t width, const int32_t* col_ids, const void* vals, const void* x, float* y,
                          Scalars s, hipStream_t st) {
     using E = typename T::elem;
-    hipLaunchKernelGGL((spmv_ell_kernel<T, G>), dim3(ceil_div(static_cast<int64_t>(m) * G, kWG)), dim3(kWG), 0, st,
+    return launch_kernel((spmv_ell_kernel<T, G>), dim3(ceil_div(static_cast<int64_t>(m) * G, kWG)), dim3(kWG), 0, st,
                        col_ids, static_cast<const E*>(vals), static_cast<const E*>(x), y, m, width, s.alpha, s.beta);
-    return hipGetLastError();
 }
 
 }  // namespace
@@ -387,8 +386,7 @@ hipError_t launch_ell_tg(int32_t m, int32_t width, const int32_t* col_ids, const
 hipError_t launch_scale_y(float* y, int32_t m, float beta, hipStream_t st) {
     if (m <= 0) return hipSuccess;
     const int grid = ceil_div(m, kWG);
-    hipLaunchKernelGGL(scale_y_kernel, dim3(grid > 2048 ? 2048 : grid), dim3(kWG), 0, st, y, m, beta);
-    return hipGetLastError();
+    return launch_kernel(scale_y_kernel, dim3(grid > 2048 ? 2048 : grid), dim3(kWG), 0, st, y, m, beta);
 }
 
 hipError_t launch_coo_accumulate(bool bf16, int32_t nnz, const int32_t* row, const int32_t* col, const void* vals,
@@ -405,10 +403,10 @@ hipError_t launch_coo_accumulate(bool bf16, int32_t nnz, const int32_t* row, con
     int grid = ceil_div(static_cast<int64_t>(nnz) + shift, 4 * kWG);
     if (grid > 8192) grid = 8192;
     if (bf16)
-        hipLaunchKernelGGL((spmv_coo_kernel<BF16>), dim3(grid), dim3(kWG), 0, st, row, col, static_cast<const uint16_t*>(vals),
+        launch_kernel((spmv_coo_kernel<BF16>), dim3(grid), dim3(kWG), 0, st, row, col, static_cast<const uint16_t*>(vals),
                            static_cast<const uint16_t*>(x), y, nnz, vec ? shift : 0, vec ? 1 : 0, alpha);
     else
-        hipLaunchKernelGGL((spmv_coo_kernel<F32>), dim3(grid), dim3(kWG), 0, st, row, col, static_cast<const float*>(vals),
+        launch_kernel((spmv_coo_kernel<F32>), dim3(grid), dim3(kWG), 0, st, row, col, static_cast<const float*>(vals),
                            static_cast<const float*>(x), y, nnz, vec ? shift : 0, vec ? 1 : 0, alpha);
     return hipGetLastError();
 }
@@ -456,10 +454,9 @@ hipError_t launch_ell_tile(int32_t m, int32_t width, const int32_t* col_ids, con
     const int pad = width % 32 == 0 ? 1 : 0;
     const size_t lds = sizeof(int) * static_cast<size_t>(rows * (width + 4 * pad) + T::VEC) + sizeof(E) * static_cast<size_t>(rows * (width + T::VEC * pad) + T::VEC) +
                        64 * sizeof(E) + 16 + sizeof(float) * static_cast<size_t>(rows);
-    hipLaunchKernelGGL((spmv_ell_tile_kernel<T>), dim3(ceil_div(m, rows)), dim3(kWG), lds, st, col_ids,
+    return launch_kernel((spmv_ell_tile_kernel<T>), dim3(ceil_div(m, rows)), dim3(kWG), lds, st, col_ids,
                        static_cast<const E*>(vals), static_cast<const E*>(x), y, m, width, rows, s.alpha, s.beta,
                        vec_ok ? 1 : 0);
-    return hipGetLastError();
 }
 
 }  // namespace

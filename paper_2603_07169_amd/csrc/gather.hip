@@ -297,9 +297,8 @@ hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_
     static thread_local size_t allowed = 0;
     const hipError_t e = allow_lds(gather_build_kernel, lds, &allowed);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(gather_build_kernel, dim3(t.num_chunks), dim3(kGatherWG), lds, st, A.colidx, t.chunk_desc, A.n, shift,
+    return launch_kernel(gather_build_kernel, dim3(t.num_chunks), dim3(kGatherWG), lds, st, A.colidx, t.chunk_desc, A.n, shift,
                        A.bf16 ? BF16::VEC : F32::VEC, t.stride, t.slots, t.words, t.base, flag);
-    return hipGetLastError();
 }
 
 hipError_t launch_gather(const GatherTiles& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done) {

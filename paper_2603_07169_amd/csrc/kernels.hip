@@ -1531,9 +1531,8 @@ template <typename T>
 hipError_t launch_scalar_t(const MatrixView& A, const int32_t* rows, int32_t count, const void* x, float* y, Scalars s,
                            hipStream_t st) {
     using E = typename T::elem;
-    hipLaunchKernelGGL((spmv_scalar_kernel<T>), dim3(ceil_div(count, kWG)), dim3(kWG), 0, st, A.rowptr, A.colidx,
+    return launch_kernel((spmv_scalar_kernel<T>), dim3(ceil_div(count, kWG)), dim3(kWG), 0, st, A.rowptr, A.colidx,
                        static_cast<const E*>(A.vals), static_cast<const E*>(x), y, rows, count, s.alpha, s.beta);
-    return hipGetLastError();
 }
 
 template <typename T, int G>
@@ -1541,10 +1540,9 @@ hipError_t launch_vector_tg(const MatrixView& A, const int32_t* rows, int32_t co
                             Scalars s, hipStream_t st) {
     using E = typename T::elem;
     const int grid = ceil_div(static_cast<int64_t>(count) * G, kWG);
-    hipLaunchKernelGGL((spmv_vector_kernel<T, G>), dim3(grid), dim3(kWG), 0, st, A.rowptr, A.colidx,
+    return launch_kernel((spmv_vector_kernel<T, G>), dim3(grid), dim3(kWG), 0, st, A.rowptr, A.colidx,
                        static_cast<const E*>(A.vals), static_cast<const E*>(x), y, rows, count, s.alpha, s.beta,
                        A.vec_ok ? 1 : 0, A.n, reinterpret_cast<uintptr_t>(x) % 16 == 0 ? 1 : 0);
-    return hipGetLastError();
 }
 
 template <typename T>
@@ -1642,8 +1640,7 @@ hipError_t launch_window_g(const TileArgs& a, size_t lds, hipStream_t st) {
             allowed = lds;
         }
     }
-    hipLaunchKernelGGL(kernel, dim3(a.nparts), dim3(256), lds, st, a);
-    return hipGetLastError();
+    return launch_kernel(kernel, dim3(a.nparts), dim3(256), lds, st, a);
 }
 
 template <typename T, int XPL, int NG>
@@ -1658,8 +1655,7 @@ hipError_t launch_pattern_g(const TileArgs& a, size_t lds, hipStream_t st) {
             allowed = lds;
         }
     }
-    hipLaunchKernelGGL(kernel, dim3(a.nparts), dim3(256), lds, st, a);
-    return hipGetLastError();
+    return launch_kernel(kernel, dim3(a.nparts), dim3(256), lds, st, a);
 }
 
 // Workgroups of the stream kernel that a compute unit holds at once, by their LDS: 160 KB, handed out in pieces of 1280 bytes (a
@@ -1669,9 +1665,8 @@ int stream_places(size_t buf_bytes) { return static_cast<int>(160 * 1024 / ((2 *
 // One workgroup per place on the device, or per block, if there are fewer.
 template <typename T, int P, int XPL>
 hipError_t launch_stream_x(const TileArgs& a, int64_t places, hipStream_t st) {
-    hipLaunchKernelGGL((spmv_pattern_kernel<T, XPL, P>), dim3(static_cast<unsigned>(a.nparts < places ? a.nparts : places)),
+    return launch_kernel((spmv_pattern_kernel<T, XPL, P>), dim3(static_cast<unsigned>(a.nparts < places ? a.nparts : places)),
                        dim3(kStreamRows * P), 2 * static_cast<size_t>(a.buf_bytes), st, a);
-    return hipGetLastError();
 }
 template <typename T, int P>
 hipError_t launch_stream_p(const TileArgs& a, int places, int cus, hipStream_t st) {
@@ -1766,9 +1761,8 @@ hipError_t launch_window_build(const MatrixView& A, const int32_t* block_nz, int
                                uint16_t* lidx, hipStream_t st) {
     if (nb <= 0) return hipSuccess;
     const int shift = A.bf16 ? 3 : 2;
-    hipLaunchKernelGGL(window_build_kernel, dim3(nb), dim3(256), 0, st, block_nz, A.colidx, block_nnz, shift,
+    return launch_kernel(window_build_kernel, dim3(nb), dim3(256), 0, st, block_nz, A.colidx, block_nnz, shift,
                        fill ? 1 : 0, nv, xv_ptr, xv_start, xv_pad, x_cap, lidx);
-    return hipGetLastError();
 }
 
 hipError_t launch_pattern_build(const int32_t* block_desc, int32_t nb, const int32_t* rowptr, const uint16_t* lidx, int32_t block_nnz,
@@ -1776,11 +1770,11 @@ hipError_t launch_pattern_build(const int32_t* block_desc, int32_t nb, const int
                                 int32_t pt_cap, const SheetPlan* sheets, hipStream_t st) {
     if (nb <= 0) return hipSuccess;
     const SheetPlan p = sheets ? *sheets : SheetPlan{};
-    hipLaunchKernelGGL(pattern_build_kernel, dim3(nb), dim3(256), 0, st, block_desc, rowptr, lidx, block_nnz, fill ? 1 : 0, run_desc,
+    launch_kernel(pattern_build_kernel, dim3(nb), dim3(256), 0, st, block_desc, rowptr, lidx, block_nnz, fill ? 1 : 0, run_desc,
                        pat_pad, pt_cap, p.map_bytes, p.need, p.first);
     if (!fill) {
         const int grid = nb < 256 * 64 ? (nb + 255) / 256 : 64;
-        hipLaunchKernelGGL(pattern_totals_kernel, dim3(grid), dim3(256), 0, st, block_desc, static_cast<const int32_t*>(run_desc), nb,
+        launch_kernel(pattern_totals_kernel, dim3(grid), dim3(256), 0, st, block_desc, static_cast<const int32_t*>(run_desc), nb,
                            static_cast<const int32_t*>(p.need), max_table, p.largest, covered);
     }
     return hipGetLastError();
@@ -1789,9 +1783,8 @@ hipError_t launch_pattern_build(const int32_t* block_desc, int32_t nb, const int
 hipError_t launch_sheet_fill(const int32_t* block_desc, int32_t nb, const int32_t* rowptr, const uint16_t* lidx, const SheetPlan& p,
                              int32_t stride, unsigned char* sheets, hipStream_t st) {
     if (nb <= 0) return hipSuccess;
-    hipLaunchKernelGGL(sheet_fill_kernel, dim3(nb), dim3(64), 0, st, block_desc, rowptr, lidx, p.elem_bytes, p.map_bytes, stride,
+    return launch_kernel(sheet_fill_kernel, dim3(nb), dim3(64), 0, st, block_desc, rowptr, lidx, p.elem_bytes, p.map_bytes, stride,
                        static_cast<const uint16_t*>(p.first), sheets);
-    return hipGetLastError();
 }
 
 hipError_t launch_merge(const MatrixView& A, const int32_t* chunk_desc, int32_t P, int32_t items_per_chunk, const CutScratch& cut,
@@ -1821,21 +1814,18 @@ hipError_t launch_cut_rows(const CutScratch& cut, int32_t P, float* y, float alp
 hipError_t launch_lidx_groups(const uint16_t* lidx, int32_t groups, uint16_t* lidx8, int32_t* flag, hipStream_t st) {
     if (groups <= 0) return hipSuccess;
     const int grid = ceil_div(groups, kWG);
-    hipLaunchKernelGGL(lidx_groups_kernel, dim3(grid > 8192 ? 8192 : grid), dim3(kWG), 0, st, lidx, groups, lidx8, flag);
-    return hipGetLastError();
+    return launch_kernel(lidx_groups_kernel, dim3(grid > 8192 ? 8192 : grid), dim3(kWG), 0, st, lidx, groups, lidx8, flag);
 }
 
 hipError_t launch_validate_columns(const MatrixView& A, int32_t* flag, hipStream_t st) {
     if (A.nnz <= 0) return hipSuccess;
     int grid = ceil_div(A.nnz, kWG);
     if (grid > 4096) grid = 4096;
-    hipLaunchKernelGGL(validate_columns_kernel, dim3(grid), dim3(kWG), 0, st, A.colidx, A.nnz, A.n, flag);
-    return hipGetLastError();
+    return launch_kernel(validate_columns_kernel, dim3(grid), dim3(kWG), 0, st, A.colidx, A.nnz, A.n, flag);
 }
 
 hipError_t launch_reduce_selftest(const float* in, float* out, hipStream_t st) {
-    hipLaunchKernelGGL(reduce_selftest_kernel, dim3(1), dim3(64), 0, st, in, out);
-    return hipGetLastError();
+    return launch_kernel(reduce_selftest_kernel, dim3(1), dim3(64), 0, st, in, out);
 }
 
 const char* scalar_kernel_name() { return "spmv_scalar_kernel"; }

@@ -95,10 +95,10 @@ hipError_t launch_sell_fill(const MatrixView& A, const int32_t* slice_ptr, int32
     if (ns <= 0) return hipSuccess;
     const dim3 grid(ceil_div(ns, kWG / 64));
     if (A.bf16)
-        hipLaunchKernelGGL(sell_fill_kernel<uint16_t>, grid, dim3(kWG), 0, st, A.rowptr, A.colidx, static_cast<const uint16_t*>(A.vals),
+        launch_kernel(sell_fill_kernel<uint16_t>, grid, dim3(kWG), 0, st, A.rowptr, A.colidx, static_cast<const uint16_t*>(A.vals),
                            slice_ptr, A.m, ns, sell_col, sell_src, static_cast<uint16_t*>(sell_val));
     else
-        hipLaunchKernelGGL(sell_fill_kernel<float>, grid, dim3(kWG), 0, st, A.rowptr, A.colidx, static_cast<const float*>(A.vals),
+        launch_kernel(sell_fill_kernel<float>, grid, dim3(kWG), 0, st, A.rowptr, A.colidx, static_cast<const float*>(A.vals),
                            slice_ptr, A.m, ns, sell_col, sell_src, static_cast<float*>(sell_val));
     return hipGetLastError();
 }
@@ -108,10 +108,10 @@ hipError_t launch_sell_values(const MatrixView& A, const int32_t* sell_src, void
     int64_t g = (slots + kWG - 1) / kWG;
     const dim3 grid(static_cast<unsigned>(g > 8192 ? 8192 : g));
     if (A.bf16)
-        hipLaunchKernelGGL(sell_values_kernel<uint16_t>, grid, dim3(kWG), 0, st, static_cast<const uint16_t*>(A.vals), sell_src,
+        launch_kernel(sell_values_kernel<uint16_t>, grid, dim3(kWG), 0, st, static_cast<const uint16_t*>(A.vals), sell_src,
                            static_cast<uint16_t*>(sell_val), slots, A.nnz);
     else
-        hipLaunchKernelGGL(sell_values_kernel<float>, grid, dim3(kWG), 0, st, static_cast<const float*>(A.vals), sell_src,
+        launch_kernel(sell_values_kernel<float>, grid, dim3(kWG), 0, st, static_cast<const float*>(A.vals), sell_src,
                            static_cast<float*>(sell_val), slots, A.nnz);
     return hipGetLastError();
 }
@@ -121,10 +121,10 @@ hipError_t launch_sell(const MatrixView& A, const int32_t* slice_ptr, int32_t ns
     if (ns <= 0) return hipSuccess;
     const dim3 grid(ceil_div(ns, kWG / 64));
     if (A.bf16)
-        hipLaunchKernelGGL(spmv_sell_kernel<BF16>, grid, dim3(kWG), 0, st, slice_ptr, sell_col, static_cast<const uint16_t*>(sell_val),
+        launch_kernel(spmv_sell_kernel<BF16>, grid, dim3(kWG), 0, st, slice_ptr, sell_col, static_cast<const uint16_t*>(sell_val),
                            static_cast<const uint16_t*>(x), y, A.m, ns, s.alpha, s.beta);
     else
-        hipLaunchKernelGGL(spmv_sell_kernel<F32>, grid, dim3(kWG), 0, st, slice_ptr, sell_col, static_cast<const float*>(sell_val),
+        launch_kernel(spmv_sell_kernel<F32>, grid, dim3(kWG), 0, st, slice_ptr, sell_col, static_cast<const float*>(sell_val),
                            static_cast<const float*>(x), y, A.m, ns, s.alpha, s.beta);
     return hipGetLastError();
 }

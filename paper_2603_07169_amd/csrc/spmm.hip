@@ -994,11 +994,11 @@ hipError_t launch_spmm_t(const SpmmArgs& a, bool single, bool sorted, dim3 grid,
     }
     const dim3 block(kSpmmWG);
     if (sorted) {
-        if (single) hipLaunchKernelGGL((spmm_csr_kernel<T, true, true>), grid, block, lds, st, a);
-        else hipLaunchKernelGGL((spmm_csr_kernel<T, false, true>), grid, block, lds, st, a);
+        if (single) launch_kernel((spmm_csr_kernel<T, true, true>), grid, block, lds, st, a);
+        else launch_kernel((spmm_csr_kernel<T, false, true>), grid, block, lds, st, a);
     } else {
-        if (single) hipLaunchKernelGGL((spmm_csr_kernel<T, true, false>), grid, block, lds, st, a);
-        else hipLaunchKernelGGL((spmm_csr_kernel<T, false, false>), grid, block, lds, st, a);
+        if (single) launch_kernel((spmm_csr_kernel<T, true, false>), grid, block, lds, st, a);
+        else launch_kernel((spmm_csr_kernel<T, false, false>), grid, block, lds, st, a);
     }
     return hipGetLastError();
 }
@@ -1015,10 +1015,10 @@ hipError_t launch_spmm_packed_t(const SpmmPackedArgs& a, bool col16, bool single
     }
     const dim3 block(kSpmmWG);
     if (col16) {
-        if (single) hipLaunchKernelGGL((spmm_packed_kernel<T, true, uint16_t>), grid, block, lds, st, a);
-        else hipLaunchKernelGGL((spmm_packed_kernel<T, false, uint16_t>), grid, block, lds, st, a);
+        if (single) launch_kernel((spmm_packed_kernel<T, true, uint16_t>), grid, block, lds, st, a);
+        else launch_kernel((spmm_packed_kernel<T, false, uint16_t>), grid, block, lds, st, a);
     } else {
-        hipLaunchKernelGGL((spmm_packed_kernel<T, false, int32_t>), grid, block, lds, st, a);
+        launch_kernel((spmm_packed_kernel<T, false, int32_t>), grid, block, lds, st, a);
     }
     return hipGetLastError();
 }
@@ -1027,10 +1027,10 @@ template <typename CT>
 hipError_t launch_spmm_pack_t(const MatrixView& A, const int32_t* rows, const int32_t* desc, int32_t num_groups, CT* pcol, float* pval,
                               int32_t* psrc, hipStream_t st) {
     if (A.bf16)
-        hipLaunchKernelGGL((spmm_pack_kernel<CT, uint16_t>), dim3(num_groups), dim3(64), 0, st, A.rowptr, A.colidx,
+        launch_kernel((spmm_pack_kernel<CT, uint16_t>), dim3(num_groups), dim3(64), 0, st, A.rowptr, A.colidx,
                            static_cast<const uint16_t*>(A.vals), rows, desc, A.m, A.n, pcol, pval, psrc);
     else
-        hipLaunchKernelGGL((spmm_pack_kernel<CT, float>), dim3(num_groups), dim3(64), 0, st, A.rowptr, A.colidx,
+        launch_kernel((spmm_pack_kernel<CT, float>), dim3(num_groups), dim3(64), 0, st, A.rowptr, A.colidx,
                            static_cast<const float*>(A.vals), rows, desc, A.m, A.n, pcol, pval, psrc);
     return hipGetLastError();
 }
@@ -1114,8 +1114,7 @@ hipError_t launch_spmm_pair_k(const SpmmPairArgs& a, dim3 grid, hipStream_t st) 
         if (e != hipSuccess) return e;
         allowed = true;
     }
-    hipLaunchKernelGGL((spmm_pair_kernel<T, READ_C, C32>), grid, dim3(kSpmmWG), kPairLdsBytes, st, a);
-    return hipGetLastError();
+    return launch_kernel((spmm_pair_kernel<T, READ_C, C32>), grid, dim3(kSpmmWG), kPairLdsBytes, st, a);
 }
 
 template <typename T>
@@ -1138,7 +1137,7 @@ hipError_t launch_spmm_pair_pack(const MatrixView& A, const PairRows& P, hipStre
     const int64_t stretches = (2 * static_cast<int64_t>(P.longest_steps) + kPairSegment - 1) / kPairSegment;
     const int64_t most = 16384 / P.num_groups;
     const int per_row = static_cast<int>(stretches < most ? stretches : (most > 1 ? most : 1));
-    hipLaunchKernelGGL(spmm_pair_pack_kernel, dim3(4 * P.num_groups, per_row), dim3(64), 0, st, A.rowptr, A.colidx, P.rows, P.desc, A.m, P.ent, P.src);
+    launch_kernel(spmm_pair_pack_kernel, dim3(4 * P.num_groups, per_row), dim3(64), 0, st, A.rowptr, A.colidx, P.rows, P.desc, A.m, P.ent, P.src);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? launch_spmm_pair_values(A, P, st) : e;
 }
@@ -1149,10 +1148,10 @@ template <bool PAIRS>
 hipError_t launch_spmm_values(const MatrixView& A, const int32_t* src, uint32_t* out, int64_t slots, hipStream_t st) {
     if (slots <= 0) return hipSuccess;
     if (A.bf16)
-        hipLaunchKernelGGL((spmm_values_kernel<uint16_t, PAIRS>), dim3(capped_grid(slots)), dim3(kWG), 0, st,
+        launch_kernel((spmm_values_kernel<uint16_t, PAIRS>), dim3(capped_grid(slots)), dim3(kWG), 0, st,
                            static_cast<const uint16_t*>(A.vals), src, out, slots);
     else
-        hipLaunchKernelGGL((spmm_values_kernel<float, PAIRS>), dim3(capped_grid(slots)), dim3(kWG), 0, st,
+        launch_kernel((spmm_values_kernel<float, PAIRS>), dim3(capped_grid(slots)), dim3(kWG), 0, st,
                            static_cast<const float*>(A.vals), src, out, slots);
     return hipGetLastError();
 }

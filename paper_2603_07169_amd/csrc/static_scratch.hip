@@ -106,7 +106,7 @@ extern "C" spmv_status_t spmv_csr_run_static(int64_t m, int64_t n, int64_t nnz, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int ipc = spmv::kDefaultItemsPerChunk;
     const int P = static_cast<int>((m + nnz + ipc - 1) / ipc);  // >= 1 and <= kStaticMaxChunks
-    hipLaunchKernelGGL(static_splits_kernel, dim3((P + 1 + 255) / 256), dim3(256), 0, st, rowptr, A.m, A.nnz, ipc, P, desc, arrivals);
+    spmv::launch_kernel(static_splits_kernel, dim3((P + 1 + 255) / 256), dim3(256), 0, st, rowptr, A.m, A.nnz, ipc, P, desc, arrivals);
     if (spmv::note_hip_error(hipGetLastError())) return SPMV_ERR_HIP;
     // How many chunks cut a row is known on the device only.  A kernel for them costs 1 to 4 us (24 M entries in rows of 16: 124 ->
     // 126; 12 M in power-law rows 106 -> 110), none up to 77 (24 M entries in rows of 300 196 -> 119, two fifths of them in such

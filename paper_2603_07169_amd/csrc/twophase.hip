@@ -660,14 +660,14 @@ hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* 
             auto k = tp_multiply_group_kernel<BF16>;
             static thread_local size_t allowed = 0;
             if ((e = allow_lds(k, lds1, &allowed)) != hipSuccess) return e;
-            hipLaunchKernelGGL(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
+            launch_kernel(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
                                static_cast<const uint16_t*>(t.tp_val), static_cast<const uint16_t*>(x), A.n, t.shift,
                                t.prod);
         } else {
             auto k = tp_multiply_group_kernel<F32>;
             static thread_local size_t allowed = 0;
             if ((e = allow_lds(k, lds1, &allowed)) != hipSuccess) return e;
-            hipLaunchKernelGGL(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
+            launch_kernel(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
                                static_cast<const float*>(t.tp_val), static_cast<const float*>(x), A.n, t.shift, t.prod);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -677,14 +677,14 @@ hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* 
             auto k = tp_multiply_kernel<BF16, kTpMulGroups>;
             static thread_local size_t allowed = 0;
             if ((e = allow_lds(k, lds1, &allowed)) != hipSuccess) return e;
-            hipLaunchKernelGGL(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
+            launch_kernel(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
                                static_cast<const uint16_t*>(t.tp_val), static_cast<const uint16_t*>(x), A.n, t.shift,
                                t.prod);
         } else {
             auto k = tp_multiply_kernel<F32, kTpMulGroups>;
             static thread_local size_t allowed = 0;
             if ((e = allow_lds(k, lds1, &allowed)) != hipSuccess) return e;
-            hipLaunchKernelGGL(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
+            launch_kernel(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
                                static_cast<const float*>(t.tp_val), static_cast<const float*>(x), A.n, t.shift, t.prod);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -700,7 +700,7 @@ hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* 
 
 hipError_t launch_two_phase_groups(const int32_t* colidx, int32_t ngroups, int32_t* gcol, int32_t* flag, hipStream_t st) {
     if (ngroups <= 0) return hipSuccess;
-    hipLaunchKernelGGL(tp_groups_kernel, dim3(capped_grid(ngroups)), dim3(kWG), 0, st, colidx, ngroups, gcol, flag);
+    launch_kernel(tp_groups_kernel, dim3(capped_grid(ngroups)), dim3(kWG), 0, st, colidx, ngroups, gcol, flag);
     return hipGetLastError();
 }
 
@@ -711,9 +711,9 @@ namespace {
 hipError_t exclusive_scan(const int32_t* in, int64_t count, int32_t* sums, int32_t* out, hipStream_t st) {
     if (count <= 0) return hipSuccess;
     const int nblocks = static_cast<int>(two_phase_scan_blocks(count));
-    hipLaunchKernelGGL(tp_scan_sums_kernel, dim3(nblocks), dim3(kWG), 0, st, in, count, sums);
-    hipLaunchKernelGGL(tp_scan_top_kernel, dim3(1), dim3(kWG), 0, st, sums, nblocks);
-    hipLaunchKernelGGL(tp_scan_apply_kernel, dim3(nblocks), dim3(kWG), 0, st, in, count, static_cast<const int32_t*>(sums), out);
+    launch_kernel(tp_scan_sums_kernel, dim3(nblocks), dim3(kWG), 0, st, in, count, sums);
+    launch_kernel(tp_scan_top_kernel, dim3(1), dim3(kWG), 0, st, sums, nblocks);
+    launch_kernel(tp_scan_apply_kernel, dim3(nblocks), dim3(kWG), 0, st, in, count, static_cast<const int32_t*>(sums), out);
     return hipGetLastError();
 }
 }  // namespace
@@ -722,12 +722,12 @@ hipError_t launch_two_phase_tables(const MatrixView& A, int shift, int32_t C, in
                                    const TwoPhaseTables& w, int32_t* chunk_g, hipStream_t st) {
     const int64_t T = static_cast<int64_t>(C) * P;
     hipError_t e;
-    hipLaunchKernelGGL(tp_count_kernel, dim3(P), dim3(kWG), 0, st, A.colidx, chunk_desc, shift, C, P, w.padded);
+    launch_kernel(tp_count_kernel, dim3(P), dim3(kWG), 0, st, A.colidx, chunk_desc, shift, C, P, w.padded);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = exclusive_scan(w.padded, T, w.scan_sums, w.base1, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(tp_chunk_columns_kernel, dim3(ceil_div(P + 1, kWG)), dim3(kWG), 0, st, w.padded, C, P, w.within, w.in_chunk);
+    launch_kernel(tp_chunk_columns_kernel, dim3(ceil_div(P + 1, kWG)), dim3(kWG), 0, st, w.padded, C, P, w.within, w.in_chunk);
     if ((e = exclusive_scan(w.in_chunk, static_cast<int64_t>(P) + 1, w.scan_sums, w.chunk_first, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(tp_starts_kernel, dim3(ceil_div((C > P ? C : P) + 1, kWG)), dim3(kWG), 0, st, w.base1, w.padded, C, P,
+    launch_kernel(tp_starts_kernel, dim3(ceil_div((C > P ? C : P) + 1, kWG)), dim3(kWG), 0, st, w.base1, w.padded, C, P,
                        w.chunk_first, w.block_first, chunk_g);
     return hipGetLastError();
 }
@@ -736,9 +736,9 @@ hipError_t launch_two_phase_place(const MatrixView& A, int shift, int32_t C, int
                                   const int32_t* chunk_desc, int64_t slots, int group, uint16_t* tp_col, void* tp_val,
                                   int32_t* tp_src, int32_t* tp_from, uint16_t* tp_pos, hipStream_t st) {
     // padding first: column = the zero slot after the x block, value 0, no source, position "dropped"
-    hipLaunchKernelGGL(tp_fill16_kernel, dim3(capped_grid(slots)), dim3(kWG), 0, st, tp_col, slots,
+    launch_kernel(tp_fill16_kernel, dim3(capped_grid(slots)), dim3(kWG), 0, st, tp_col, slots,
                        static_cast<uint16_t>(1u << shift));
-    hipLaunchKernelGGL(tp_fill16_kernel, dim3(capped_grid(slots)), dim3(kWG), 0, st, tp_pos, slots, static_cast<uint16_t>(0xFFFF));
+    launch_kernel(tp_fill16_kernel, dim3(capped_grid(slots)), dim3(kWG), 0, st, tp_pos, slots, static_cast<uint16_t>(0xFFFF));
     hipError_t e = hipMemsetAsync(tp_val, 0, static_cast<size_t>(slots) * group * (A.bf16 ? 2 : 4), st);
     if (e != hipSuccess) return e;
     if ((e = hipMemsetAsync(tp_src, 0xFF, static_cast<size_t>(slots) * 4, st)) != hipSuccess) return e;
@@ -751,7 +751,7 @@ hipError_t launch_two_phase_place(const MatrixView& A, int shift, int32_t C, int
                        static_cast<size_t>(kTwoPhaseItems) * (sizeof(uint32_t) + 3 * sizeof(uint16_t));
     static thread_local size_t allowed = 0;
     if ((e = allow_lds(tp_place_kernel, lds, &allowed)) != hipSuccess) return e;
-    hipLaunchKernelGGL(tp_place_kernel, dim3(P), dim3(kWG), lds, st, a);
+    launch_kernel(tp_place_kernel, dim3(P), dim3(kWG), lds, st, a);
     return hipGetLastError();
 }
 
@@ -761,18 +761,18 @@ hipError_t launch_two_phase_values(const MatrixView& A, const int32_t* tp_src, v
     if (group == 8) {
         const int ngroups = A.nnz / 8;
         if (A.bf16)
-            hipLaunchKernelGGL(tp_group_values_kernel<uint16_t>, dim3(capped_grid(8 * slots)), dim3(kWG), 0, st,
+            launch_kernel(tp_group_values_kernel<uint16_t>, dim3(capped_grid(8 * slots)), dim3(kWG), 0, st,
                                static_cast<const uint16_t*>(A.vals), tp_src, static_cast<uint16_t*>(tp_val), slots, ngroups);
         else
-            hipLaunchKernelGGL(tp_group_values_kernel<float>, dim3(capped_grid(8 * slots)), dim3(kWG), 0, st,
+            launch_kernel(tp_group_values_kernel<float>, dim3(capped_grid(8 * slots)), dim3(kWG), 0, st,
                                static_cast<const float*>(A.vals), tp_src, static_cast<float*>(tp_val), slots, ngroups);
         return hipGetLastError();
     }
     if (A.bf16)
-        hipLaunchKernelGGL(tp_values_kernel<uint16_t>, dim3(capped_grid(slots)), dim3(kWG), 0, st,
+        launch_kernel(tp_values_kernel<uint16_t>, dim3(capped_grid(slots)), dim3(kWG), 0, st,
                            static_cast<const uint16_t*>(A.vals), tp_src, static_cast<uint16_t*>(tp_val), static_cast<int>(slots));
     else
-        hipLaunchKernelGGL(tp_values_kernel<float>, dim3(capped_grid(slots)), dim3(kWG), 0, st, static_cast<const float*>(A.vals),
+        launch_kernel(tp_values_kernel<float>, dim3(capped_grid(slots)), dim3(kWG), 0, st, static_cast<const float*>(A.vals),
                            tp_src, static_cast<float*>(tp_val), static_cast<int>(slots));
     return hipGetLastError();
 }
