@@ -83,7 +83,7 @@ struct spmv_csr_s {
     spmv::CutScratch tp_cut{};
     size_t tp_reduce_lds = 0;
     std::vector<int32_t> tp_row, tp_nz;  // host copies for the read-back
-    spmv::GatherTiles gather{};  // MERGE and ADAPTIVE plans: x gathered in column order (words: null where the tile kernel runs)
+    spmv::GatherTiles gather{};  // MERGE, ADAPTIVE and WINDOWED plans: x gathered in column order (words: null where it is not)
     // The MERGE and TWOPHASE plans keep scratch in the handle (carries, products): a run on another stream while one is
     // still in flight would share it.  An event recorded behind every such run tells.
     hipEvent_t scratch_free = nullptr;
@@ -706,32 +706,62 @@ spmv_status_t build_sell(spmv_csr_s* h, const HostRowptr& rowptr_host, spmv::Ana
     return SPMV_ERR_ALLOC;
 }
 
-// The entries in column order chunk by chunk, for a MERGE or ADAPTIVE handle where gathering x in that order is the faster way.
-// Without room for them, or where 15 + 17 bits an entry cannot express them, the tile kernel runs.
+// The entries in column order chunk by chunk, for a MERGE or ADAPTIVE handle where gathering x in that order is the faster way, or the groups of
+// eight of a WINDOWED one (next to its windows, which serve an x that does not allow 16-byte reads).
+// Without room for them, or where 15 + 17 bits an entry cannot express them, the plan's other kernel runs.
 spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const spmv::Analysis& a) try {
     const int32_t plan = a.info.plan;
     const bool bf16 = h->dtype == SPMV_BF16, cuts_rows = plan == SPMV_PLAN_MERGE;
+    const bool on_groups = plan == SPMV_PLAN_WINDOWED && a.info.lidx_grouped && bf16 && h->vec_ok && h->nnz >= spmv::kGatherGroupEntries;
+    if (!on_groups && plan != SPMV_PLAN_MERGE && plan != SPMV_PLAN_ADAPTIVE) return SPMV_OK;
     int dev = 0, cus = 0;
     if (hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev))) return SPMV_ERR_HIP;
-    std::vector<int32_t> rows, entries, desc, cuts;
+    std::vector<int32_t> rows, entries, desc, cuts, rowptr_groups;
     spmv::GatherTiles& t = h->gather;
-    int64_t P = 0;
-    // One chunk to a compute unit, or, where its LDS does not hold that, four, two at a time (FP32, 300 000 rows of 16: two chunks, one at a
-    // time, 22.3 us, three, two at a time, 22.4, four 22.1, the tile kernel 26.5; power law, 5.4 M entries: 33.5, 36.6, 31.3, 34.2).
-    for (int k = 1;; k += 3) {
-        if (k > 4) return SPMV_OK;
-        const int64_t places = static_cast<int64_t>(cus) * k, items = std::max((h->m + h->nnz + places - 1) / places, spmv::kGatherMinItems);
-        const int64_t snap = spmv::gather_snap(plan, a.info.max_len, items);
-        if (items + snap > spmv::kGatherMaxSlots) continue;
-        if (!spmv::gather_choice(h->m, h->nnz, plan, a.info.max_len, cus, k)) return SPMV_OK;
-        spmv::merge_path_splits(h->m, h->nnz, rowptr_host.data(), items, &rows, &entries);
-        spmv::merge_chunk_desc(h->m, rowptr_host.data(), rows, entries, snap, &desc);
+    int64_t P = 0, nent = h->nnz, longest = a.info.max_len;
+    const int32_t* rowptr = rowptr_host.data();
+    t.group = 1;
+    if (on_groups) {
+        rowptr_groups.resize(rowptr_host.size());
+        for (size_t i = 0; i < rowptr_host.size(); ++i) rowptr_groups[i] = rowptr_host[i] / spmv::kTpGroup;
+        rowptr = rowptr_groups.data();
+        nent /= spmv::kTpGroup;
+        longest /= spmv::kTpGroup;
+        t.group = spmv::kTpGroup;
+    }
+    auto cut = [&](int64_t items, int64_t snap, int32_t* most_rows) {
+        spmv::merge_path_splits(h->m, nent, rowptr, items, &rows, &entries);
+        spmv::merge_chunk_desc(h->m, rowptr, rows, entries, snap, &desc);
         P = static_cast<int64_t>(rows.size()) - 1;
-        int32_t most_rows = 0;
-        for (int64_t p = 0; p < P; ++p) most_rows = std::max(most_rows, rows[static_cast<size_t>(p) + 1] - rows[static_cast<size_t>(p)]);
-        t.slots = spmv::gather_slots(bf16, desc.data(), P);
-        t.lds = spmv::gather_lds(bf16, t.slots, most_rows);
-        if (t.lds <= (k == 1 ? spmv::kGatherMaxLds : spmv::kGatherMaxLds / 2) && t.slots <= spmv::kGatherMaxSlots) break;
+        *most_rows = 0;
+        for (int64_t p = 0; p < P; ++p) *most_rows = std::max(*most_rows, rows[static_cast<size_t>(p) + 1] - rows[static_cast<size_t>(p)]);
+    };
+    int32_t most_rows = 0;
+    // On groups: whole rounds of two chunks to a compute unit, as few as the LDS allows.  Else one chunk to a compute unit, or, where its LDS
+    // does not hold that, four, two at a time (FP32, 300 000 rows of 16: two chunks, one at a time, 22.3 us, three, two at a time, 22.4, four 22.1,
+    // the tile kernel 26.5; power law, 5.4 M entries: 33.5, 36.6, 31.3, 34.2).
+    for (int64_t k = on_groups ? 2 : 1;; k += on_groups ? 2 : 3) {
+        const int64_t places = cus * k;
+        int64_t items = (h->m + nent + places - 1) / places;
+        if (on_groups) {
+            if (2 * longest > items) return SPMV_OK;
+            if (16 * items > static_cast<int64_t>(spmv::kGatherGroupLds) * 2) continue;  // no room even if half of the steps were rows' ends
+            cut(items, longest, &most_rows);
+            t.slots = 1;
+            for (size_t p = 0; p < static_cast<size_t>(P); ++p) t.slots = std::max(t.slots, desc[2 * p + 3] - desc[2 * p + 1]);
+            t.lds = spmv::gather_group_lds(t.slots, most_rows);
+            if (t.lds <= spmv::kGatherGroupLds && t.slots <= spmv::kGatherGroupSlots) break;
+        } else {
+            if (k > 4) return SPMV_OK;
+            items = std::max(items, spmv::kGatherMinItems);
+            const int64_t snap = spmv::gather_snap(plan, longest);
+            if (items + snap > spmv::kGatherMaxSlots) continue;
+            if (!spmv::gather_choice(h->m, h->nnz, plan, longest, cus, static_cast<int>(k))) return SPMV_OK;
+            cut(items, snap, &most_rows);
+            t.slots = spmv::gather_slots(bf16, desc.data(), P);
+            t.lds = spmv::gather_lds(bf16, t.slots, most_rows);
+            if (t.lds <= (k == 1 ? spmv::kGatherMaxLds : spmv::kGatherMaxLds / 2) && t.slots <= spmv::kGatherMaxSlots) break;
+        }
     }
     t.num_chunks = static_cast<int32_t>(P);
     t.stride = 1;
@@ -1070,6 +1100,10 @@ spmv_status_t spmv_csr_run(spmv_handle_t h, const void* x, float* y, float alpha
                                       h->info.block_nnz, h->info.rows_max, x, y, s, st);
             break;
         case SPMV_PLAN_WINDOWED:
+            if (h->gather.words && reinterpret_cast<uintptr_t>(x) % 16 == 0) {
+                e = spmv::launch_gather(h->gather, A, x, y, s, st, nullptr);
+                break;
+            }
             e = spmv::launch_windowed(A, h->d_block_desc, static_cast<int32_t>(h->info.num_row_blocks), h->info.block_nnz,
                                       h->max_block_entries, h->info.rows_max, windows_of(h), x, y, s, st);
             break;
@@ -1407,6 +1441,7 @@ const char* spmv_csr_kernel_name(spmv_handle_t h, const void* x, float beta) {
         case SPMV_PLAN_ADAPTIVE:
         case SPMV_PLAN_MERGE: return h->gather.words ? spmv::gather_kernel_name() : spmv::tile_kernel_name();
         case SPMV_PLAN_WINDOWED:
+            if (h->gather.words && reinterpret_cast<uintptr_t>(x) % 16 == 0) return spmv::gather_group_kernel_name();
             return spmv::windowed_kernel_name(
                 spmv::windowed_kernel(view_of(h), h->max_block_entries, h->info.rows_max, windows_of(h), x, beta));
         case SPMV_PLAN_COLBLOCK: return "spmv_coo_kernel";

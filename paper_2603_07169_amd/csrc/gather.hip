@@ -14,6 +14,7 @@ constexpr int kGatherWG = 1024;        // lanes of a workgroup
 constexpr int kGatherWords = 256;      // words of a group: a wavefront's load of 16 bytes a lane
 constexpr int kGatherPosBits = 15;     // low bits of a word: the entry's place in its chunk; above them its column less the group's first
 constexpr int kGatherDeferred = 512;   // rows far longer than the mean that a chunk can set aside (a chunk holds less than 2^15 entries)
+constexpr int kGatherGroupWG = 512;    // lanes of a workgroup on groups of eight
 constexpr int kGatherBuckets = 16384;  // column intervals the entries of a chunk are sorted by, at most
 
 struct GatherArgs {
@@ -178,11 +179,113 @@ __global__ __launch_bounds__(kGatherWG) void spmv_gather_kernel(const GatherArgs
     tile_rows<false, WG>(static_cast<const AtSlot*>(nullptr), vals_l, x_l, seg + done, nr - done, r0 + done, seg[nr] - seg[done], o, deferred, &n_deferred, tid);
 }
 
+// The same for a group-aligned matrix in bf16 (every row a whole number of groups of eight entries, every group an aligned run of eight
+// columns; a WINDOWED handle), with groups in the place of entries: x is gathered, and kept in LDS, in runs of eight; a lane multiplies a group by
+// its run with one 16-byte read of either, its values asked for before x is; the row phase adds up the groups' sums.
+// Bound: the window kernel copies about every run of x anew for each block of 32 rows, in no order (address units 80 % busy).  Two
+// chunks of half the LDS to a compute unit, so that one gathers while the other multiplies.  Windows / this, us out of a graph: 100 000 rows of
+// 10 runs 10.4 / 7.9, 200 000 of 8 15.4 / 11.8, 200 000 of 16 25.9 / 19.2, 400 000 of 10 34.7 / 26.3, 500 000 of 16 57.9 / 46.2, 1 M of 5 42.9 / 37.0.  With
+// 1024 lanes and all of the LDS 7.3, 10.9, 21.0, 29.7, 57.6, 41.3.  FP32, whose runs take twice the LDS: 200 000 of 16 42.4 / 41.6, 1 M of 5
+// 65.8 / 80.3; it stays with the windows.
+__global__ __launch_bounds__(kGatherGroupWG) void spmv_gather_group_kernel(const GatherArgs a) {
+    constexpr int WG = kGatherGroupWG, WAVES = WG / 64, U = 2, PER_LANE = kGatherGroupSlots / WG;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ int deferred[kMaxDeferred];
+    __shared__ int n_deferred;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int part = xcd_remap(blockIdx.x, gridDim.x);
+    const u32x4* const x = static_cast<const u32x4*>(a.x);
+    const u32x4* const words = reinterpret_cast<const u32x4*>(a.words) + static_cast<size_t>(part) * a.stride * 64;
+    const int32_t* const base = a.base + static_cast<size_t>(part) * a.stride;
+
+    u32x4 w[U];
+    int first[U];
+    auto ask = [&](int g0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int g = g0 + wave + u * WAVES;
+            const int held = g < a.stride ? g : a.stride - 1;
+            w[u] = __builtin_nontemporal_load(words + held * 64 + lane);
+            first[u] = base[held];
+        }
+    };
+    ask(0);
+    const int r0 = a.chunk_desc[2 * part];
+    const int k0 = a.chunk_desc[2 * part + 1];
+    const int nr = a.chunk_desc[2 * part + 2] - r0;
+    const int groups = a.chunk_desc[2 * part + 3] - k0;
+    u32x4* const x_l = reinterpret_cast<u32x4*>(smem_raw);            // [cap + 1]
+    float* const sums = reinterpret_cast<float*>(x_l + a.cap + 1);    // [cap]
+    int* const seg = reinterpret_cast<int*>(sums + a.cap);            // [nr + 1]
+    float* const y0_l = reinterpret_cast<float*>(seg + nr + 1);
+
+    u32x4 v[PER_LANE];
+#pragma unroll
+    for (int u = 0; u < PER_LANE; ++u) {
+        const int i = tid + u * WG;
+        if (i < groups) v[u] = __builtin_nontemporal_load(static_cast<const u32x4*>(a.vals) + static_cast<size_t>(k0) + i);
+    }
+    for (int i = tid; i <= nr; i += WG) seg[i] = (a.rowptr[r0 + i] >> 3) - k0;
+    if (tid == 0) n_deferred = 0;
+    if (a.beta != 0.f)
+        for (int i = tid; i < nr; i += WG) y0_l[i] = a.y[r0 + i];
+
+    for (int g0 = 0;;) {
+        u32x4 xv[U][4];
+        unsigned at[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                xv[u][i] = x[static_cast<unsigned>(first[u]) + (w[u][i] >> kGatherPosBits)];
+                at[u][i] = w[u][i] & ((1u << kGatherPosBits) - 1);
+            }
+        const int here = g0;
+        g0 += U * WAVES;
+        const bool more = g0 < a.stride;
+        if (more) ask(g0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (here + wave + u * WAVES < a.stride) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x_l[at[u][i]] = xv[u][i];
+            }
+        if (!more) break;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER_LANE; ++u) {
+        const int i = tid + u * WG;
+        if (i < groups) {
+            const u32x4 xs = x_l[i];
+            // Two chains of four products, exact in binary32 as they are: 2.1 roundings at the sum's full size for the eight, against 4.4 in one chain
+            // and 3 in a tree of pairs.  With the row phase adding groups in 64 bits (GroupSums) rows of 4 / 6 / 10 / 16 groups are 2.4, 3.2, 3.6 and
+            // 4.4e-8 off the 64-bit result, with the windows 2.7, 3.3, 4.0 and 4.6, with these chains and binary32 2.7, 3.4, 4.1, 4.6.
+            float four[2];
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                float acc = 0.f;
+#pragma unroll
+                for (int t = 2 * half; t < 2 * half + 2; ++t) {
+                    acc = __builtin_fmaf(__uint_as_float(v[u][t] << 16), __uint_as_float(xs[t] << 16), acc);
+                    acc = __builtin_fmaf(__uint_as_float(v[u][t] & 0xFFFF0000u), __uint_as_float(xs[t] & 0xFFFF0000u), acc);
+                }
+                four[half] = acc;
+            }
+            sums[i] = four[0] + four[1];
+        }
+    }
+    __syncthreads();
+    const RowOut o{a.y, y0_l, a.alpha, a.beta, nullptr, false};
+    tile_rows<false, WG>(static_cast<const GroupSums*>(nullptr), sums, static_cast<const float*>(nullptr), seg, nr, r0, groups, o, deferred, &n_deferred, tid);
+}
+
 // Analysis: one workgroup per chunk sorts its entries by column interval (counts, prefix sums, places handed out with a counter per
 // interval, all in LDS) and writes the chunk's words.  Inside an interval - at least a line of x - the order does not matter, to
 // the gathers no more than to the result.  *flag is set where a column is out of range or too far from its group's first.
 __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* __restrict__ colidx, const int32_t* __restrict__ chunk_desc,
-                                                                 int n, int shift, int vec, int stride, int cap,
+                                                                 int n, int shift, int gs, int vec, int stride, int cap,
                                                                  uint32_t* __restrict__ words, int32_t* __restrict__ base, int32_t* flag) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int WG = kGatherWG;
@@ -196,6 +299,7 @@ __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* 
     const int k0a = k0 & ~(vec - 1);
     const int entries = k1 - k0;
     bool bad = false;
+    auto column = [&](int k) { return colidx[static_cast<size_t>(k) << gs] >> gs; };  // gs: 3 where the entries are groups of eight, else 0
     auto bucket_of = [&](int c) {
         if (c < 0 || c >= n) {
             bad = true;
@@ -205,7 +309,7 @@ __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* 
     };
     for (int i = tid; i < buckets; i += WG) place[i] = 0;
     __syncthreads();
-    for (int k = k0 + tid; k < k1; k += WG) atomicAdd(place + bucket_of(colidx[k]), 1);
+    for (int k = k0 + tid; k < k1; k += WG) atomicAdd(place + bucket_of(column(k)), 1);
     __syncthreads();
     // exclusive prefix sums: a lane takes a run of buckets
     const int run = (buckets + WG - 1) / WG, b0 = tid * run, b1 = b0 + run < buckets ? b0 + run : buckets;
@@ -234,7 +338,7 @@ __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* 
     auto put = [&](int i, uint32_t word) { out[(i & ~(kGatherWords - 1)) + 4 * (i & 63) + ((i >> 6) & 3)] = word; };
     for (int i = entries + tid; i < stride * kGatherWords; i += WG) put(i, static_cast<uint32_t>(cap));
     for (int k = k0 + tid; k < k1; k += WG) {
-        const int c = colidx[k];
+        const int c = column(k);
         const int i = atomicAdd(place + bucket_of(c), 1);
         const uint32_t off = static_cast<uint32_t>(c - group_first[i / kGatherWords]);
         if (off >= 1u << (32 - kGatherPosBits)) bad = true;
@@ -274,6 +378,10 @@ hipError_t launch_gather_t(const GatherArgs& a, int32_t P, size_t lds, hipStream
 
 }  // namespace
 
+size_t gather_group_lds(int32_t groups, int32_t rows) {
+    return 16 * (static_cast<size_t>(groups) + 1) + 4 * static_cast<size_t>(groups) + 4 * (2 * static_cast<size_t>(rows) + 1);
+}
+
 int32_t gather_slots(bool bf16, const int32_t* chunk_desc, int64_t P) {
     const int vec = bf16 ? BF16::VEC : F32::VEC;
     int32_t most = vec;
@@ -290,25 +398,32 @@ size_t gather_lds(bool bf16, int32_t slots, int32_t rows) {
 }
 
 hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_t* flag, hipStream_t st) {
-    const int line = A.bf16 ? 6 : 5;  // columns of a line of x
-    int shift = line;
-    while (((A.n - 1) >> shift) + 1 > kGatherBuckets) ++shift;
-    const size_t lds = sizeof(int) * static_cast<size_t>(((A.n - 1) >> shift) + 1);
+    const int gs = t.group == 8 ? 3 : 0;
+    const int n = t.group == 8 ? (A.n + 7) / 8 : A.n;
+    int shift = (A.bf16 ? 6 : 5) - gs;  // log2 of the columns (runs of columns) of a line of x
+    while (((n - 1) >> shift) + 1 > kGatherBuckets) ++shift;
+    const size_t lds = sizeof(int) * static_cast<size_t>(((n - 1) >> shift) + 1);
     static thread_local size_t allowed = 0;
     const hipError_t e = allow_lds(gather_build_kernel, lds, &allowed);
     if (e != hipSuccess) return e;
-    return launch_kernel(gather_build_kernel, dim3(t.num_chunks), dim3(kGatherWG), lds, st, A.colidx, t.chunk_desc, A.n, shift,
-                       A.bf16 ? BF16::VEC : F32::VEC, t.stride, t.slots, t.words, t.base, flag);
+    return launch_kernel(gather_build_kernel, dim3(t.num_chunks), dim3(kGatherWG), lds, st, A.colidx, t.chunk_desc, n, shift, gs,
+                         t.group == 8 ? 1 : (A.bf16 ? BF16::VEC : F32::VEC), t.stride, t.slots, t.words, t.base, flag);
 }
 
 hipError_t launch_gather(const GatherTiles& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done) {
     const GatherArgs a{t.chunk_desc, t.words, t.base, A.rowptr, A.vals, x, y, t.cut_range, t.cut, t.stride, t.slots, A.nnz, A.vec_ok ? 1 : 0, s.alpha, s.beta};
+    if (t.group == 8) {
+        static thread_local size_t allowed = 0;
+        const hipError_t e = allow_lds(spmv_gather_group_kernel, t.lds, &allowed);
+        return e == hipSuccess ? launch_kernel(spmv_gather_group_kernel, dim3(t.num_chunks), dim3(kGatherGroupWG), t.lds, st, a) : e;
+    }
     if (!t.cut_range) return A.bf16 ? launch_gather_t<BF16, false>(a, t.num_chunks, t.lds, st, done) : launch_gather_t<F32, false>(a, t.num_chunks, t.lds, st, done);
     hipEvent_t const last = t.cut.carry_row ? nullptr : done;
     const hipError_t e = A.bf16 ? launch_gather_t<BF16, true>(a, t.num_chunks, t.lds, st, last) : launch_gather_t<F32, true>(a, t.num_chunks, t.lds, st, last);
     return e == hipSuccess && t.cut.carry_row ? launch_cut_rows(t.cut, t.num_chunks, y, s.alpha, st, done) : e;
 }
 
+const char* gather_group_kernel_name() { return "spmv_gather_group_kernel"; }
 const char* gather_kernel_name() { return "spmv_gather_kernel"; }
 
 }  // namespace spmv

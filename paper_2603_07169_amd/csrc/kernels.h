@@ -212,8 +212,15 @@ struct GatherTiles {
     int32_t* cut_range;   // [2*(num_chunks+1)] (see finish_cut); null: no chunk cuts a row (ADAPTIVE)
     CutScratch cut;
     int32_t num_chunks, stride, slots;
+    int32_t group;  // 1, or 8: entries, places and columns above are groups of eight (a WINDOWED handle of a group-aligned bf16 matrix)
     size_t lds;
 };
+constexpr int32_t kGatherGroupSlots = 4096;              // most groups of a chunk
+constexpr size_t kGatherGroupLds = kGatherMaxLds / 2;    // two workgroups to a compute unit
+// Fewest entries.  Windows / gathered, us call by call: 3.2 M in rows of 8 groups 6.1 / 5.5, 3.8 M of 6 6.2 / 6.4, 5.1 M of 16 7.6 / 6.5, of 4 10.0 / 8.0,
+// 5.8 M of 6 and of 12 8.5 / 7.4 and 8.4 / 7.1, 8 M of 10 10.7 / 8.2.
+constexpr int64_t kGatherGroupEntries = 1 << 22;
+size_t gather_group_lds(int32_t groups, int32_t rows);
 // LDS slots of the largest chunk (desc: HOST array), and the LDS bytes of a workgroup for them and at most `rows` rows.
 int32_t gather_slots(bool bf16, const int32_t* desc, int64_t P);
 size_t gather_lds(bool bf16, int32_t slots, int32_t rows);
@@ -289,6 +296,7 @@ hipError_t launch_reduce_selftest(const float* in, float* out, hipStream_t st);
 const char* scalar_kernel_name();
 const char* vector_kernel_name();
 const char* gather_kernel_name();
+const char* gather_group_kernel_name();
 const char* tile_kernel_name();  // kernel of the adaptive and merge plans
 const char* windowed_kernel_name(WindowKernel k);
 const char* spmm_kernel_name();

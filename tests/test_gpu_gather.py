@@ -73,7 +73,8 @@ CUT = {
     "neighbours": lengths_with([(i, 1700) for i in range(100, 130)]),      # both ends of a chunk inside rows
     "over_many_chunks": lengths_with([(7, 30000), (8, 513), (9, 40000)]),  # chunks without a row's end
     "all_long": [2900] * 150,
-    "snapped": lengths_with([(i, 512) for i in range(0, 60000, 50)] + [(77, 2000)]),
+    "snapped": lengths_with([(i, 2048) for i in range(0, 60000, 400)] + [(77, 2049)]),
+    "rows_over_empty_chunks": lengths_with([(i, 2048) for i in range(0, 60, 2)], short=9000),  # chunks of 512 steps: most are left empty
     "least": lengths_with([(5, 1100)], short=16100),                        # about the fewest entries the rule takes
     "empty_ends": np.concatenate(([0] * 5000, lengths_with([(100, 2000)]), [0] * 7000)),
 }
@@ -128,6 +129,37 @@ def test_matrices_of_the_tile_kernel():
     check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(prepare_spmm=1))   # a handle for products with matrices
     check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(items_per_chunk=512))
     check(problem([8] * 50000, 200_000_000, "bf16"), TILE)                               # neighbours too far apart for a word
+
+
+GROUPS = {  # runs of eight a row, runs in x
+    "blocks": ([8] * 70000, 5000),
+    "odd": (np.random.default_rng(2).integers(0, 19, 60003), 4001),
+    "long_rows": ([70] * 8000, 12500),
+    "several_rounds": ([10] * 400000, 50000),
+}
+
+
+@pytest.mark.parametrize("name", list(GROUPS))
+def test_groups_of_eight(name):
+    runs, width = GROUPS[name]
+    p = problem(runs, width, "bf16", seed=4)
+    first = 8 * p.colidx.astype(np.int64)
+    rng = np.random.default_rng(6)
+    q = w.CsrProblem(name="groups", dtype="bf16", m=p.m, n=8 * width + 3, rowptr=8 * p.rowptr,
+                     colidx=(first[:, None] + np.arange(8)).reshape(-1).astype(np.int32), vals=np.resize(p.vals, 8 * p.nnz),
+                     x=(rng.integers(-8, 9, 8 * width + 3).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16), alpha=1.0, beta=0.5, y0=p.y0)
+    d, A = check(q, "spmv_gather_group_kernel")
+    assert A.info.plan == s.SPMV_PLAN_WINDOWED
+    y_ref, _ = reference(q, 1.0, 0.0)
+    assert np.array_equal(d.run(A, beta=0.0, y_init=torch.full((q.m,), float("nan"), device="cuda")), y_ref.astype(np.float32))
+    moved = torch.empty(q.n + 1, dtype=torch.int16, device="cuda")[1:]  # an x that 16-byte reads do not fit: the windows
+    moved.copy_(d.x)
+    d.x = moved
+    assert s.spmv_csr_kernel_name(A.handle, d.x.data_ptr(), q.beta) == "spmv_window_kernel"
+    assert np.array_equal(d.run(A), reference(q)[0].astype(np.float32))
+    if name == "blocks":
+        check(q, "spmv_window_kernel", offset=1)                          # values that they do not fit
+        check(q, "spmv_window_kernel", params=dict(prepare_spmm=1))
 
 
 def test_graph_replays_and_streams():
