@@ -167,8 +167,8 @@ void merge_path_splits_snapped(int64_t m, int64_t nnz, const int32_t* rowptr, in
     }
 }
 
-int64_t gather_snap(int32_t plan, int64_t max_len) {
-    return plan == SPMV_PLAN_ADAPTIVE ? max_len : kGatherSnap;
+int64_t gather_snap(int32_t plan, int64_t max_len, int64_t items) {
+    return plan == SPMV_PLAN_ADAPTIVE ? max_len : (items <= kGatherSnap ? kGatherSnap : kTwoPhaseSnap);
 }
 
 bool gather_choice(int64_t m, int64_t nnz, int32_t plan, int64_t max_len, int32_t cus, int k) {

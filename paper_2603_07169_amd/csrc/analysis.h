@@ -87,10 +87,11 @@ bool two_phase_choice(int64_t m, int64_t n, int64_t nnz, spmv_dtype_t dtype, int
 //     3 rows of 40 000 in chunks of 512 8.4 / 14.0; 300 000 rows of 5 and one of 200 000, 26 chunks, 21.8 / 13.2.
 bool gather_choice(int64_t m, int64_t nnz, int32_t plan, int64_t max_len, int32_t cus, int k);
 constexpr int64_t kGatherMinItems = 512;  // fewest steps of a chunk: a wavefront's worth or two of every load
-// Rows of at most this many entries are not cut by chunks.  512 / 2048 / 4096 entries on power-law rows, FP32: 20 000 rows 5.85 / 5.11 / 4.78 us,
-// 50 000 6.74 / 6.30 / 6.34, 333 333 16.8 / 16.7 / 16.9, 450 000 22.8 / 22.7 / 23.4.  A chunk of fewer steps may be left empty by it.
+// Rows of at most this many entries are not cut by chunks of `items` steps.  A cut costs a chunk 1 to 2 us that show where it is short, a row
+// kept whole makes its chunk the longest.  512 / 2048 entries, power-law rows, FP32: 20 000 rows (chunks of 700 steps) 5.85 / 5.11 us, 50 000 6.74 / 6.30,
+// 100 000 (3500 steps) 7.89 / 8.22, 333 333 (11 700) 16.8 / 16.7 and, with other rows, 16.9 / 18.0.  A chunk of fewer steps may be left empty by it.
 constexpr int64_t kGatherSnap = 2048;
-int64_t gather_snap(int32_t plan, int64_t max_len);
+int64_t gather_snap(int32_t plan, int64_t max_len, int64_t items);
 // The pieces of the multiply pass from where the column blocks start in the multiply order (block_first[C+1], in slots,
 // the last entry = all slots): every block's groups cut evenly into the fewest pieces of at most piece_groups.
 // The two-pass plan on groups of eight entries (a group-aligned matrix: every row starts at a multiple of eight entries and

@@ -754,7 +754,7 @@ spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const s
         } else {
             if (k > 4) return SPMV_OK;
             items = std::max(items, spmv::kGatherMinItems);
-            const int64_t snap = spmv::gather_snap(plan, longest);
+            const int64_t snap = spmv::gather_snap(plan, longest, items);
             if (items + snap > spmv::kGatherMaxSlots) continue;
             if (!spmv::gather_choice(h->m, h->nnz, plan, longest, cus, static_cast<int>(k))) return SPMV_OK;
             cut(items, snap, &most_rows);

@@ -159,15 +159,17 @@ __global__ __launch_bounds__(kGatherWG) void spmv_gather_kernel(const GatherArgs
             __syncthreads();
             const RowOut o{a.y, y0_l, a.alpha, a.beta, nullptr, head_cut};
             const CutOut c{a.cut.carry_val, a.cut.arrivals, a.cut_range, nullptr, 0, a.cut.carry_row};
+            auto sum_of = [&](int v0) {
+                double s = 0;
+                for (int v = v0; v < v0 + WAVES / 2; ++v) s += part_sums[v];
+                return static_cast<float>(s);
+            };
             // the last two wavefronts, which have no rows to spare for a last sweep
             if (tid == WG - 128 && head_cut) {
-                float s = 0.f;
-                for (int v = 0; v < WAVES / 2; ++v) s += part_sums[v];
-                finish_cut(o, c, r0, part, true, epilogue(s, a.alpha, a.beta, y0_l, 0));
+                finish_cut(o, c, r0, part, true, epilogue(sum_of(0), a.alpha, a.beta, y0_l, 0));
             }
             if (tid == WG - 64 && tail_cut) {
-                float s = 0.f;
-                for (int v = WAVES / 2; v < WAVES; ++v) s += part_sums[v];
+                const float s = sum_of(WAVES / 2);
                 if (a.cut.carry_row) a.cut.carry_val[part] = s;
                 else finish_cut(o, c, r0 + nr, part, false, s);
             }

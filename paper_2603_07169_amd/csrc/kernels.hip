@@ -1467,7 +1467,7 @@ __global__ __launch_bounds__(kWG) void cut_rows_kernel(const CutRowsArgs a) {
     if (p >= a.P) return;
     const int r = a.carry_row[p];
     if (r < 0 || (p > 0 && a.carry_row[p - 1] == r)) return;
-    float s = 0.f;
+    double s = 0;  // as in finish_cut
     bool more = true;  // eight at a time: a row over a hundred chunks is a hundred round trips to memory otherwise
     for (int q = p; more; q += 8) {
         int row[8];
@@ -1484,7 +1484,7 @@ __global__ __launch_bounds__(kWG) void cut_rows_kernel(const CutRowsArgs a) {
             if (more) s += val[u];
         }
     }
-    a.y[r] += a.alpha * s;
+    a.y[r] = static_cast<float>(a.y[r] + a.alpha * s);
 }
 
 // lidx8[g] = lidx[8g] for every whole aligned group of eight entries; *flag = 1 if some group's positions are not

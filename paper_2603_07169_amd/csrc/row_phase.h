@@ -83,7 +83,8 @@ __device__ __forceinline__ float gather_batch(const AtSlot*, const E* vals, cons
 // into a handful of cache lines.  The lane's entries are taken in batches of 8, then 4, 2, 1.
 template <int G, typename I, typename E>
 __device__ __forceinline__ float segment_dot(const I* cols, const E* vals, const E* x, int b, int e, int tl) {
-    float acc = 0.f;
+    // chunks of gathered x hold rows several times as long as a tile's: their batches are added in 64 bits
+    std::conditional_t<std::is_same_v<I, AtSlot>, double, float> acc = 0;
     int j = b + tl;
     int cnt = (e - j + G - 1) / G;  // entries this lane takes (<= 0 when the segment is shorter than the team)
     for (; cnt >= 8; cnt -= 8, j += 8 * G) acc += gather_batch<8, G>(cols, vals, x, j);
@@ -98,7 +99,7 @@ __device__ __forceinline__ float segment_dot(const I* cols, const E* vals, const
         cnt -= 2;
     }
     if (cnt >= 1) acc += gather_batch<1, G>(cols, vals, x, j);
-    return acc;
+    return static_cast<float>(acc);
 }
 
 // Where the row phase of a tile sends its results.
@@ -143,7 +144,7 @@ __device__ __forceinline__ void finish_cut(const RowOut& o, const CutOut& c, int
     const unsigned last = static_cast<unsigned>(p1 - p0);
     if (atomicInc(c.arrivals + p0, last) != last) return;
     asm volatile("" ::: "memory");
-    float s = 0.f;
+    double s = 0;  // a row's parts in 64 bits: one that is cut many times would else be rounded at its full size as often
     for (int q = p0; q < p1; q += 8) {
         float part_sum[8];
 #pragma unroll
@@ -153,7 +154,7 @@ __device__ __forceinline__ void finish_cut(const RowOut& o, const CutOut& c, int
         for (int u = 0; u < 8; ++u)
             if (q + u < p1) s += part_sum[u];
     }
-    const float y = __hip_atomic_load(o.y + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + o.alpha * s;
+    const float y = static_cast<float>(__hip_atomic_load(o.y + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + o.alpha * s);
     __hip_atomic_store(o.y + r, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 

@@ -53,7 +53,7 @@ int stream_lanes(int elem, int64_t m, int64_t nnz, int rows_max, int places, int
     return spmv::stream_lanes(elem, m, nnz, rows_max, places, common);
 }
 int gather_choice(int64_t m, int64_t nnz, int plan, int64_t max_len, int cus, int k) { return spmv::gather_choice(m, nnz, plan, max_len, cus, k); }
-int64_t gather_snap(int plan, int64_t max_len) { return spmv::gather_snap(plan, max_len); }
+int64_t gather_snap(int plan, int64_t max_len, int64_t items) { return spmv::gather_snap(plan, max_len, items); }
 int common_len(int64_t m, const int32_t* rp) { return spmv::common_row_length(m, rp); }
 }
 """
@@ -303,4 +303,5 @@ def test_gather_rule(rules):
     assert choice(10000, 1 << 16, M, 32 * 512) and not choice(10000, 1 << 16, M, 32 * 512 + 1)     # chunks of 512 steps at least
     for plan in (s.SPMV_PLAN_SCALAR, s.SPMV_PLAN_VECTOR, s.SPMV_PLAN_BINNED, s.SPMV_PLAN_WINDOWED, s.SPMV_PLAN_TWOPHASE, s.SPMV_PLAN_COLBLOCK, s.SPMV_PLAN_SELL):
         assert not choice(30000, 1 << 20, plan, 20)
-    assert rules.gather_snap(A, i64(300)) == 300 and rules.gather_snap(M, i64(9000)) == 2048
+    assert rules.gather_snap(A, i64(300), i64(2000)) == 300
+    assert rules.gather_snap(M, i64(9000), i64(2048)) == 2048 and rules.gather_snap(M, i64(9000), i64(2049)) == 512
