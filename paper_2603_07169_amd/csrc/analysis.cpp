@@ -178,6 +178,12 @@ bool gather_choice(int64_t m, int64_t nnz, int32_t plan, int64_t max_len, int32_
     return nnz >= 1 << 16 && max_len <= 32 * std::max(items, kGatherMinItems);
 }
 
+bool rows_of_groups(int64_t m, const int32_t* rowptr) {
+    for (int64_t i = 0; i <= m; ++i)
+        if (rowptr[i] % kTpGroup != 0) return false;
+    return true;
+}
+
 void merge_chunk_desc(int64_t m, const int32_t* rowptr, const std::vector<int32_t>& mp_row, const std::vector<int32_t>& mp_nz,
                       int64_t snap, std::vector<int32_t>* desc) {
     desc->resize(2 * mp_row.size());

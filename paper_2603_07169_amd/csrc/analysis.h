@@ -92,6 +92,9 @@ constexpr int64_t kGatherMinItems = 512;  // fewest steps of a chunk: a wavefron
 // 100 000 (3500 steps) 7.89 / 8.22, 333 333 (11 700) 16.8 / 16.7 and, with other rows, 16.9 / 18.0.  A chunk of fewer steps may be left empty by it.
 constexpr int64_t kGatherSnap = 2048;
 int64_t gather_snap(int32_t plan, int64_t max_len, int64_t items);
+// Whether every row is a whole number of groups of eight entries, as a plan that is laid out over the groups needs it.  Grouped window positions
+// do not say so: they ask it of the row blocks only, and of the entries of a group only that their positions follow one another.
+bool rows_of_groups(int64_t m, const int32_t* rowptr);
 // The pieces of the multiply pass from where the column blocks start in the multiply order (block_first[C+1], in slots,
 // the last entry = all slots): every block's groups cut evenly into the fewest pieces of at most piece_groups.
 // The two-pass plan on groups of eight entries (a group-aligned matrix: every row starts at a multiple of eight entries and

@@ -514,9 +514,7 @@ spmv_status_t build_column_blocks(spmv_csr_s* h, spmv::Analysis* a) {
 spmv_status_t check_groups(spmv_csr_s* h, const HostRowptr& rowptr_host, bool* aligned, int32_t** d_gcol) {
     *aligned = false;
     *d_gcol = nullptr;
-    if (h->nnz == 0 || h->nnz % spmv::kTpGroup != 0) return SPMV_OK;
-    for (int32_t r : rowptr_host)
-        if (r % spmv::kTpGroup != 0) return SPMV_OK;
+    if (h->nnz == 0 || !spmv::rows_of_groups(h->m, rowptr_host.data())) return SPMV_OK;
     const int32_t ngroups = static_cast<int32_t>(h->nnz / spmv::kTpGroup);
     int32_t* d_flag = nullptr;
     int32_t flag = 0;
@@ -708,11 +706,13 @@ spmv_status_t build_sell(spmv_csr_s* h, const HostRowptr& rowptr_host, spmv::Ana
 
 // The entries in column order chunk by chunk, for a MERGE or ADAPTIVE handle where gathering x in that order is the faster way, or the groups of
 // eight of a WINDOWED one (next to its windows, which serve an x that does not allow 16-byte reads).
-// Without room for them, or where 15 + 17 bits an entry cannot express them, the plan's other kernel runs.
+// Without room for them, where 15 + 17 bits an entry cannot express them, or where a group is no aligned run of columns, the plan's other kernel runs.
 spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const spmv::Analysis& a) try {
     const int32_t plan = a.info.plan;
     const bool bf16 = h->dtype == SPMV_BF16, cuts_rows = plan == SPMV_PLAN_MERGE;
-    const bool on_groups = plan == SPMV_PLAN_WINDOWED && a.info.lidx_grouped && bf16 && h->vec_ok && h->nnz >= spmv::kGatherGroupEntries;
+    // (grouped positions come first because they are known: a group-aligned matrix has them, not every matrix that has them is group-aligned)
+    const bool on_groups = plan == SPMV_PLAN_WINDOWED && a.info.lidx_grouped && bf16 && h->vec_ok && h->nnz >= spmv::kGatherGroupEntries &&
+                           h->n >= spmv::kTpGroup && spmv::rows_of_groups(h->m, rowptr_host.data());
     if (!on_groups && plan != SPMV_PLAN_MERGE && plan != SPMV_PLAN_ADAPTIVE) return SPMV_OK;
     int dev = 0, cus = 0;
     if (hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev))) return SPMV_ERR_HIP;

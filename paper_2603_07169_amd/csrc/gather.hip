@@ -285,7 +285,8 @@ __global__ __launch_bounds__(kGatherGroupWG) void spmv_gather_group_kernel(const
 
 // Analysis: one workgroup per chunk sorts its entries by column interval (counts, prefix sums, places handed out with a counter per
 // interval, all in LDS) and writes the chunk's words.  Inside an interval - at least a line of x - the order does not matter, to
-// the gathers no more than to the result.  *flag is set where a column is out of range or too far from its group's first.
+// the gathers no more than to the result.  *flag is set where a column is out of range or too far from its group's first, or where eight
+// entries that are to be one are not an aligned run of eight columns (colidx is 16-byte aligned then).
 __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* __restrict__ colidx, const int32_t* __restrict__ chunk_desc,
                                                                  int n, int shift, int gs, int vec, int stride, int cap,
                                                                  uint32_t* __restrict__ words, int32_t* __restrict__ base, int32_t* flag) {
@@ -312,6 +313,15 @@ __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* 
     for (int i = tid; i < buckets; i += WG) place[i] = 0;
     __syncthreads();
     for (int k = k0 + tid; k < k1; k += WG) atomicAdd(place + bucket_of(column(k)), 1);
+    if (gs != 0)
+        for (int k = k0 + tid; k < k1; k += WG) {
+            const i32x4* const eight = reinterpret_cast<const i32x4*>(colidx) + 2 * static_cast<size_t>(k);
+            const i32x4 lo = eight[0], hi = eight[1];
+            bool run = (lo[0] & 7) == 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) run = run && lo[i] == lo[0] + i && hi[i] == lo[0] + 4 + i;
+            bad = bad || !run;
+        }
     __syncthreads();
     // exclusive prefix sums: a lane takes a run of buckets
     const int run = (buckets + WG - 1) / WG, b0 = tid * run, b1 = b0 + run < buckets ? b0 + run : buckets;
@@ -401,7 +411,7 @@ size_t gather_lds(bool bf16, int32_t slots, int32_t rows) {
 
 hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_t* flag, hipStream_t st) {
     const int gs = t.group == 8 ? 3 : 0;
-    const int n = t.group == 8 ? (A.n + 7) / 8 : A.n;
+    const int n = t.group == 8 ? A.n / 8 : A.n;  // whole runs of eight: the kernel reads all of a run
     int shift = (A.bf16 ? 6 : 5) - gs;  // log2 of the columns (runs of columns) of a line of x
     while (((n - 1) >> shift) + 1 > kGatherBuckets) ++shift;
     const size_t lds = sizeof(int) * static_cast<size_t>(((n - 1) >> shift) + 1);

@@ -162,6 +162,39 @@ def test_groups_of_eight(name):
         check(q, "spmv_window_kernel", params=dict(prepare_spmm=1))
 
 
+def consecutive(lens, first, n):
+    """A bf16 problem whose rows' columns follow one another."""
+    lens = np.asarray(lens, dtype=np.int64)
+    rowptr = np.concatenate(([0], np.cumsum(lens)))
+    cols = np.repeat(np.asarray(first), lens) + np.arange(rowptr[-1]) - np.repeat(rowptr[:-1], lens)
+    assert rowptr[-1] >= 1 << 22 and cols.max() < n
+    rng = np.random.default_rng(8)
+    short = lambda size: (rng.integers(-8, 9, size).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    return w.CsrProblem(name="consecutive", dtype="bf16", m=lens.size, n=n, rowptr=rowptr.astype(np.int32), colidx=cols.astype(np.int32),
+                        vals=short(cols.size), x=short(n), alpha=1.0, beta=0.5, y0=rng.integers(-8, 9, lens.size).astype(np.float32))
+
+
+def ends(lens):
+    return np.concatenate(([0], np.cumsum(lens)[:-1]))
+
+
+NOT_GROUPS = {  # grouped positions, but rows that begin or end inside a group, or groups at columns that are no multiple of eight
+    "diagonal": lambda: consecutive([1] * ((1 << 22) + 5), np.arange((1 << 22) + 5), (1 << 22) + 5),
+    "rows_of_4": lambda: consecutive([4] * (1 << 20), 4 * np.arange(1 << 20), 1 << 22),
+    "rows_of_12": lambda: consecutive([12] * 400000, 12 * np.arange(400000), 4800000),
+    "rows_of_4_and_12": lambda: consecutive([4, 12] * 300000, ends([4, 12] * 300000), 4800000),
+    "short_last_row": lambda: consecutive([8] * 599999 + [5], 8 * np.arange(600000), 4800000),
+    "band": lambda: consecutive([16] * 300000, np.arange(300000), 300015),
+}
+
+
+@pytest.mark.parametrize("name", list(NOT_GROUPS))
+def test_grouped_positions_that_are_no_groups_stay_with_the_windows(name):
+    p = NOT_GROUPS[name]()
+    _, A = check(p, "spmv_window_kernel")
+    assert A.info.plan == s.SPMV_PLAN_WINDOWED and A.info.lidx_grouped == 1
+
+
 def test_graph_replays_and_streams():
     p = problem(UNIFORM["odd"][0], 9973, "f32")
     d, A = check(p, GATHER)

@@ -53,6 +53,7 @@ int stream_lanes(int elem, int64_t m, int64_t nnz, int rows_max, int places, int
     return spmv::stream_lanes(elem, m, nnz, rows_max, places, common);
 }
 int gather_choice(int64_t m, int64_t nnz, int plan, int64_t max_len, int cus, int k) { return spmv::gather_choice(m, nnz, plan, max_len, cus, k); }
+int rows_of_groups(int64_t m, const int32_t* rp) { return spmv::rows_of_groups(m, rp); }
 int64_t gather_snap(int plan, int64_t max_len, int64_t items) { return spmv::gather_snap(plan, max_len, items); }
 int common_len(int64_t m, const int32_t* rp) { return spmv::common_row_length(m, rp); }
 }
@@ -305,3 +306,32 @@ def test_gather_rule(rules):
         assert not choice(30000, 1 << 20, plan, 20)
     assert rules.gather_snap(A, i64(300), i64(2000)) == 300
     assert rules.gather_snap(M, i64(9000), i64(2048)) == 2048 and rules.gather_snap(M, i64(9000), i64(2049)) == 512
+
+
+NOT_GROUPS = {  # row lengths, first column of every row: each row's columns follow one another
+    "diagonal": ([1] * 512, np.arange(512)),
+    "rows_of_4": ([4] * 512, 4 * np.arange(512)),
+    "rows_of_12": ([12] * 512, 12 * np.arange(512)),
+    "rows_of_4_and_12": ([4, 12] * 256, np.arange(512) // 2 * 16 + np.arange(512) % 2 * 4),
+    "short_last_row": ([8] * 511 + [5], 8 * np.arange(512)),
+    "band": ([16] * 512, np.arange(512)),  # whole groups, at columns that are no multiple of eight
+}
+
+
+@pytest.mark.parametrize("name", list(NOT_GROUPS))
+def test_grouped_positions_do_not_make_a_matrix_of_groups(rules, name):
+    """What the product on groups of eight asks of the rows (the columns are asked of the device); the positions of all these are grouped."""
+    lens, first = NOT_GROUPS[name]
+    rp = rowptr_of(lens)
+    cols = (np.repeat(first, lens) + np.arange(rp[-1]) - np.repeat(rp[:-1], lens)).astype(np.int32)
+    blocks = oracle.row_blocks(rp, 1024, 64)
+    _, _, _, lidx = oracle.x_windows(rp, cols, blocks, 1024, 8)
+    assert oracle.lidx_grouped(rp, blocks, lidx) and not oracle.csr_groups(len(lens), rp, cols)
+    assert rules.rows_of_groups(i64(len(lens)), P(rp)) == (name == "band")
+
+
+def test_rows_of_groups(rules):
+    for lens in ([], [0, 0], [8], [0, 16, 8, 0, 24]):
+        assert rules.rows_of_groups(i64(len(lens)), P(rowptr_of(lens)))
+    for lens in ([7], [8, 1], [4, 4], [8, 12, 4, 8], [0, 9]):
+        assert not rules.rows_of_groups(i64(len(lens)), P(rowptr_of(lens)))
