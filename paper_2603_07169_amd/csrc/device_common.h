@@ -6,6 +6,8 @@
 
 #include <cstdint>
 
+#include "lds_grant.h"
+
 namespace spmv {
 namespace {
 
@@ -117,6 +119,13 @@ hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds
         void* args[] = {const_cast<void*>(static_cast<const void*>(&p))...};
         return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, args, lds, st);
     }(values...);
+}
+
+// Lets KERNEL be launched with `lds` bytes of dynamic LDS on the current device.
+template <auto KERNEL>
+hipError_t allow_lds(size_t lds) {
+    static LdsGrant grant;
+    return grant(reinterpret_cast<const void*>(KERNEL), lds);
 }
 
 // Launches a kernel; done, if not null, is recorded at its end by the dispatch itself.  An event recorded behind the kernel is a

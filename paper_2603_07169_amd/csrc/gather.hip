@@ -359,20 +359,10 @@ __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* 
     if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) *flag = 1;  // plain store: every writer writes 1
 }
 
-template <typename K>
-hipError_t allow_lds(K kernel, size_t lds, size_t* allowed) {
-    if (lds <= 64 * 1024 || lds <= *allowed) return hipSuccess;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    if (e == hipSuccess) *allowed = lds;
-    return e;
-}
-
 template <typename T, bool MERGE, int U>
 hipError_t launch_gather_u(const GatherArgs& a, int32_t P, size_t lds, hipStream_t st, hipEvent_t done) {
-    auto k = spmv_gather_kernel<T, MERGE, U>;
-    static thread_local size_t allowed = 0;
-    const hipError_t e = allow_lds(k, lds, &allowed);
-    return e == hipSuccess ? launch_with_event(k, dim3(P), dim3(kGatherWG), lds, st, done, a) : e;
+    const hipError_t e = allow_lds<spmv_gather_kernel<T, MERGE, U>>(lds);
+    return e == hipSuccess ? launch_with_event(spmv_gather_kernel<T, MERGE, U>, dim3(P), dim3(kGatherWG), lds, st, done, a) : e;
 }
 
 template <typename T, bool MERGE>
@@ -415,8 +405,7 @@ hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_
     int shift = (A.bf16 ? 6 : 5) - gs;  // log2 of the columns (runs of columns) of a line of x
     while (((n - 1) >> shift) + 1 > kGatherBuckets) ++shift;
     const size_t lds = sizeof(int) * static_cast<size_t>(((n - 1) >> shift) + 1);
-    static thread_local size_t allowed = 0;
-    const hipError_t e = allow_lds(gather_build_kernel, lds, &allowed);
+    const hipError_t e = allow_lds<gather_build_kernel>(lds);
     if (e != hipSuccess) return e;
     return launch_kernel(gather_build_kernel, dim3(t.num_chunks), dim3(kGatherWG), lds, st, A.colidx, t.chunk_desc, n, shift, gs,
                          t.group == 8 ? 1 : (A.bf16 ? BF16::VEC : F32::VEC), t.stride, t.slots, t.words, t.base, flag);
@@ -425,8 +414,7 @@ hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_
 hipError_t launch_gather(const GatherTiles& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done) {
     const GatherArgs a{t.chunk_desc, t.words, t.base, A.rowptr, A.vals, x, y, t.cut_range, t.cut, t.stride, t.slots, A.nnz, A.vec_ok ? 1 : 0, s.alpha, s.beta};
     if (t.group == 8) {
-        static thread_local size_t allowed = 0;
-        const hipError_t e = allow_lds(spmv_gather_group_kernel, t.lds, &allowed);
+        const hipError_t e = allow_lds<spmv_gather_group_kernel>(t.lds);
         return e == hipSuccess ? launch_kernel(spmv_gather_group_kernel, dim3(t.num_chunks), dim3(kGatherGroupWG), t.lds, st, a) : e;
     }
     if (!t.cut_range) return A.bf16 ? launch_gather_t<BF16, false>(a, t.num_chunks, t.lds, st, done) : launch_gather_t<F32, false>(a, t.num_chunks, t.lds, st, done);

@@ -1610,16 +1610,8 @@ size_t merge_lds_bytes(int items) {
 template <typename T, bool MERGE, int WG>
 hipError_t launch_tiles_wg(const TileArgs& a, size_t lds, hipStream_t st, hipEvent_t done) {
     auto kernel = spmv_tile_kernel<T, MERGE, WG>;
-    if (lds > 64 * 1024) {
-        // beyond the default limit the kernel has to be told once (per process) how much it may get
-        static thread_local size_t allowed = 0;
-        if (lds > allowed) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-            if (e != hipSuccess) return e;
-            allowed = lds;
-        }
-    }
+    const hipError_t e = allow_lds<spmv_tile_kernel<T, MERGE, WG>>(lds);
+    if (e != hipSuccess) return e;
     return launch_with_event(kernel, dim3(a.nparts), dim3(WG), lds, st, done, a);
 }
 
@@ -1631,30 +1623,16 @@ hipError_t launch_tiles(const TileArgs& a, size_t lds, hipStream_t st, hipEvent_
 template <typename T, int XPL, int NG, bool GROUPED>
 hipError_t launch_window_g(const TileArgs& a, size_t lds, hipStream_t st) {
     auto kernel = spmv_window_kernel<T, 256, XPL, NG, GROUPED>;
-    if (lds > 64 * 1024) {
-        static thread_local size_t allowed = 0;
-        if (lds > allowed) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-            if (e != hipSuccess) return e;
-            allowed = lds;
-        }
-    }
+    const hipError_t e = allow_lds<spmv_window_kernel<T, 256, XPL, NG, GROUPED>>(lds);
+    if (e != hipSuccess) return e;
     return launch_kernel(kernel, dim3(a.nparts), dim3(256), lds, st, a);
 }
 
 template <typename T, int XPL, int NG>
 hipError_t launch_pattern_g(const TileArgs& a, size_t lds, hipStream_t st) {
     auto kernel = spmv_pattern_block_kernel<T, 256, XPL, NG>;
-    if (lds > 64 * 1024) {
-        static thread_local size_t allowed = 0;
-        if (lds > allowed) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-            if (e != hipSuccess) return e;
-            allowed = lds;
-        }
-    }
+    const hipError_t e = allow_lds<spmv_pattern_block_kernel<T, 256, XPL, NG>>(lds);
+    if (e != hipSuccess) return e;
     return launch_kernel(kernel, dim3(a.nparts), dim3(256), lds, st, a);
 }
 

@@ -976,51 +976,25 @@ bool spmm_vec_ok(bool bf16, const void* B, int64_t ldb, const float* C, int64_t 
 
 namespace {
 
-template <typename K>
-hipError_t allow_lds(K kernel, size_t lds) {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+template <auto KERNEL, typename Args>
+hipError_t launch_spmm_k(dim3 grid, dim3 block, size_t lds, hipStream_t st, const Args& a) {
+    const hipError_t e = allow_lds<KERNEL>(lds);
+    return e == hipSuccess ? launch_kernel(KERNEL, grid, block, lds, st, a) : e;
 }
 
 template <typename T>
 hipError_t launch_spmm_t(const SpmmArgs& a, bool single, bool sorted, dim3 grid, size_t lds, hipStream_t st) {
-    static thread_local bool allowed = false;
-    if (!allowed) {
-        hipError_t e = allow_lds(spmm_csr_kernel<T, true, true>, lds);
-        if (e == hipSuccess) e = allow_lds(spmm_csr_kernel<T, true, false>, lds);
-        if (e == hipSuccess) e = allow_lds(spmm_csr_kernel<T, false, true>, lds);
-        if (e == hipSuccess) e = allow_lds(spmm_csr_kernel<T, false, false>, lds);
-        if (e != hipSuccess) return e;
-        allowed = true;
-    }
     const dim3 block(kSpmmWG);
-    if (sorted) {
-        if (single) launch_kernel((spmm_csr_kernel<T, true, true>), grid, block, lds, st, a);
-        else launch_kernel((spmm_csr_kernel<T, false, true>), grid, block, lds, st, a);
-    } else {
-        if (single) launch_kernel((spmm_csr_kernel<T, true, false>), grid, block, lds, st, a);
-        else launch_kernel((spmm_csr_kernel<T, false, false>), grid, block, lds, st, a);
-    }
-    return hipGetLastError();
+    if (sorted) return single ? launch_spmm_k<spmm_csr_kernel<T, true, true>>(grid, block, lds, st, a) : launch_spmm_k<spmm_csr_kernel<T, false, true>>(grid, block, lds, st, a);
+    return single ? launch_spmm_k<spmm_csr_kernel<T, true, false>>(grid, block, lds, st, a) : launch_spmm_k<spmm_csr_kernel<T, false, false>>(grid, block, lds, st, a);
 }
 
 template <typename T>
 hipError_t launch_spmm_packed_t(const SpmmPackedArgs& a, bool col16, bool single, dim3 grid, size_t lds, hipStream_t st) {
-    static thread_local bool allowed = false;
-    if (!allowed) {
-        hipError_t e = allow_lds(spmm_packed_kernel<T, true, uint16_t>, lds);
-        if (e == hipSuccess) e = allow_lds(spmm_packed_kernel<T, false, uint16_t>, lds);
-        if (e == hipSuccess) e = allow_lds(spmm_packed_kernel<T, false, int32_t>, lds);
-        if (e != hipSuccess) return e;
-        allowed = true;
-    }
     const dim3 block(kSpmmWG);
-    if (col16) {
-        if (single) launch_kernel((spmm_packed_kernel<T, true, uint16_t>), grid, block, lds, st, a);
-        else launch_kernel((spmm_packed_kernel<T, false, uint16_t>), grid, block, lds, st, a);
-    } else {
-        launch_kernel((spmm_packed_kernel<T, false, int32_t>), grid, block, lds, st, a);
-    }
-    return hipGetLastError();
+    if (!col16) return launch_spmm_k<spmm_packed_kernel<T, false, int32_t>>(grid, block, lds, st, a);
+    return single ? launch_spmm_k<spmm_packed_kernel<T, true, uint16_t>>(grid, block, lds, st, a)
+                  : launch_spmm_k<spmm_packed_kernel<T, false, uint16_t>>(grid, block, lds, st, a);
 }
 
 template <typename CT>
@@ -1108,13 +1082,7 @@ namespace {
 
 template <typename T, bool READ_C, bool C32>
 hipError_t launch_spmm_pair_k(const SpmmPairArgs& a, dim3 grid, hipStream_t st) {
-    static thread_local bool allowed = false;
-    if (!allowed) {
-        const hipError_t e = allow_lds(spmm_pair_kernel<T, READ_C, C32>, kPairLdsBytes);
-        if (e != hipSuccess) return e;
-        allowed = true;
-    }
-    return launch_kernel((spmm_pair_kernel<T, READ_C, C32>), grid, dim3(kSpmmWG), kPairLdsBytes, st, a);
+    return launch_spmm_k<spmm_pair_kernel<T, READ_C, C32>>(grid, dim3(kSpmmWG), kPairLdsBytes, st, a);
 }
 
 template <typename T>

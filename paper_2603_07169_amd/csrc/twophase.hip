@@ -636,15 +636,6 @@ int capped_grid(int64_t items) {
     return static_cast<int>(g > 8192 ? 8192 : (g < 1 ? 1 : g));
 }
 
-template <typename K>
-hipError_t allow_lds(K kernel, size_t lds, size_t* allowed) {
-    if (lds <= 64 * 1024 || lds <= *allowed) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       static_cast<int>(lds));
-    if (e == hipSuccess) *allowed = lds;
-    return e;
-}
-
 }  // namespace
 
 size_t two_phase_reduce_lds(int32_t entries, int32_t rows) {
@@ -657,16 +648,14 @@ hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* 
         // a slot is a group of eight entries: the block of x as 2^shift aligned runs of eight, and one run of zeros
         const size_t lds1 = (A.bf16 ? 16 : 32) * ((size_t{1} << t.shift) + 1);
         if (A.bf16) {
-            auto k = tp_multiply_group_kernel<BF16>;
-            static thread_local size_t allowed = 0;
-            if ((e = allow_lds(k, lds1, &allowed)) != hipSuccess) return e;
+            constexpr auto k = tp_multiply_group_kernel<BF16>;
+            if ((e = allow_lds<k>(lds1)) != hipSuccess) return e;
             launch_kernel(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
                                static_cast<const uint16_t*>(t.tp_val), static_cast<const uint16_t*>(x), A.n, t.shift,
                                t.prod);
         } else {
-            auto k = tp_multiply_group_kernel<F32>;
-            static thread_local size_t allowed = 0;
-            if ((e = allow_lds(k, lds1, &allowed)) != hipSuccess) return e;
+            constexpr auto k = tp_multiply_group_kernel<F32>;
+            if ((e = allow_lds<k>(lds1)) != hipSuccess) return e;
             launch_kernel(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
                                static_cast<const float*>(t.tp_val), static_cast<const float*>(x), A.n, t.shift, t.prod);
         }
@@ -674,16 +663,14 @@ hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* 
     } else if (t.num_pieces > 0) {
         const size_t lds1 = sizeof(float) * ((size_t{1} << t.shift) + 4);
         if (A.bf16) {
-            auto k = tp_multiply_kernel<BF16, kTpMulGroups>;
-            static thread_local size_t allowed = 0;
-            if ((e = allow_lds(k, lds1, &allowed)) != hipSuccess) return e;
+            constexpr auto k = tp_multiply_kernel<BF16, kTpMulGroups>;
+            if ((e = allow_lds<k>(lds1)) != hipSuccess) return e;
             launch_kernel(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
                                static_cast<const uint16_t*>(t.tp_val), static_cast<const uint16_t*>(x), A.n, t.shift,
                                t.prod);
         } else {
-            auto k = tp_multiply_kernel<F32, kTpMulGroups>;
-            static thread_local size_t allowed = 0;
-            if ((e = allow_lds(k, lds1, &allowed)) != hipSuccess) return e;
+            constexpr auto k = tp_multiply_kernel<F32, kTpMulGroups>;
+            if ((e = allow_lds<k>(lds1)) != hipSuccess) return e;
             launch_kernel(k, dim3(t.num_pieces), dim3(kTpMulWG), lds1, st, t.piece_c, t.piece_g, t.tp_col,
                                static_cast<const float*>(t.tp_val), static_cast<const float*>(x), A.n, t.shift, t.prod);
         }
@@ -691,9 +678,8 @@ hipError_t launch_two_phase(const TwoPhase& t, const MatrixView& A, const void* 
     }
     const TpReduceArgs a{t.chunk_desc, t.chunk_g, t.tp_from, t.tp_pos, t.prod, A.rowptr, y, t.cut_range, t.cut, t.num_chunks,
                          t.group == 8 ? 3 : 0, s.alpha, s.beta};
-    auto k = tp_reduce_kernel<kTpRedWG, kTpRedGroups>;
-    static thread_local size_t allowed = 0;
-    if ((e = allow_lds(k, t.reduce_lds, &allowed)) != hipSuccess) return e;
+    constexpr auto k = tp_reduce_kernel<kTpRedWG, kTpRedGroups>;
+    if ((e = allow_lds<k>(t.reduce_lds)) != hipSuccess) return e;
     e = launch_with_event(k, dim3(t.num_chunks), dim3(kTpRedWG), t.reduce_lds, st, t.cut.carry_row ? nullptr : done, a);
     return e == hipSuccess && t.cut.carry_row ? launch_cut_rows(t.cut, t.num_chunks, y, s.alpha, st, done) : e;
 }
@@ -749,8 +735,7 @@ hipError_t launch_two_phase_place(const MatrixView& A, int shift, int32_t C, int
                         group > 1 ? 0 : (A.bf16 ? 2 : 4), span_cap, tp_col, tp_val, tp_src, tp_from, tp_pos};
     const size_t lds = sizeof(int) * (static_cast<size_t>(kWG / 64 + 2) * span_cap + ((span_cap + 4) & ~3)) +
                        static_cast<size_t>(kTwoPhaseItems) * (sizeof(uint32_t) + 3 * sizeof(uint16_t));
-    static thread_local size_t allowed = 0;
-    if ((e = allow_lds(tp_place_kernel, lds, &allowed)) != hipSuccess) return e;
+    if ((e = allow_lds<tp_place_kernel>(lds)) != hipSuccess) return e;
     launch_kernel(tp_place_kernel, dim3(P), dim3(kWG), lds, st, a);
     return hipGetLastError();
 }
