@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2603_07169_amd as s
 import workloads as w
 from gpu_util import DeviceProblem, assert_close, reference
@@ -68,24 +69,88 @@ def lengths_with(long_rows, short=60000, seed=3):
     return lens
 
 
-CUT = {
+CUT = {  # chunks that begin inside a row
     "first_and_last": lengths_with([(0, 3000), (59999, 5000)]),
-    "neighbours": lengths_with([(i, 1700) for i in range(100, 130)]),      # both ends of a chunk inside rows
+    "neighbours": lengths_with([(i, 2500) for i in range(100, 130)]),      # both ends of a chunk inside rows
     "over_many_chunks": lengths_with([(7, 30000), (8, 513), (9, 40000)]),  # chunks without a row's end
     "all_long": [2900] * 150,
-    "snapped": lengths_with([(i, 2048) for i in range(0, 60000, 400)] + [(77, 2049)]),
-    "rows_over_empty_chunks": lengths_with([(i, 2048) for i in range(0, 60, 2)], short=9000),  # chunks of 512 steps: most are left empty
-    "least": lengths_with([(5, 1100)], short=16100),                        # about the fewest entries the rule takes
+    "snapped": lengths_with([(i, 2048) for i in range(0, 60000, 800)] + [(77, 2049)]),     # the one row that chunks of up to 2048 steps cut
+    "long_chunks": lengths_with([(i, 2048) for i in range(0, 60000, 400)] + [(77, 2049)]),  # beyond that, rows of more than 512 entries
+    "next_to_empty_chunks": lengths_with([(i + j, 2048 if j == 1 else 2100) for i in range(0, 60, 6) for j in range(3)], short=9000),
+    "empty_ends": np.concatenate(([0] * 5000, lengths_with([(100, 2500)]), [0] * 7000)),
+}
+UNCUT = {  # the same plan, no chunk begins inside a row
+    "least": lengths_with([(5, 1100)], short=16200),                        # 65570 entries: the rule takes 65536
+    "neighbours": lengths_with([(i, 1700) for i in range(100, 130)]),
+    "over_empty_chunks": lengths_with([(i, 2048) for i in range(0, 60, 2)], short=9000),  # chunks of 512 steps: most are left empty
     "empty_ends": np.concatenate(([0] * 5000, lengths_with([(100, 2000)]), [0] * 7000)),
 }
+FULL = {  # storage, chunks to a compute unit, whether the pieces of cut rows are left to the second kernel
+    "many_cuts_f32": ([9000] * 900, "f32", 4, True),
+    "many_cuts_bf16": ([9000] * 1200, "bf16", 4, True),
+    "few_cuts": (lengths_with([(7, 30000), (99, 20000), (50000, 9000)], short=1200000), "f32", 4, False),
+    "words_in_rounds": (lengths_with([(7, 30000), (99, 20000), (50000, 9000)], short=1200000), "bf16", 1, False),
+}
+
+
+def chunks_of(p, to_a_unit):
+    """Steps of a chunk, and per chunk its first row, first entry and whether it begins inside a row: the oracle's merge path, with the cuts
+    inside rows that a chunk does not cut moved back."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count * to_a_unit
+    items = max(-(-(p.m + p.nnz) // units), 512)
+    rows, entries = oracle.merge_path(p.rowptr, items)
+    lens = np.append(np.diff(p.rowptr), 0)
+    inside = p.rowptr[rows] < entries
+    cut = inside & (lens[rows] > (2048 if items <= 2048 else 512))
+    return items, rows, np.where(inside & ~cut, p.rowptr[rows], entries), cut
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("name", list(CUT))
 def test_cut_rows(name, dtype):
     p = problem(CUT[name], 50000, dtype)
-    kernel = GATHER if p.nnz >= 1 << 16 else TILE
-    _, A = check(p, kernel)
+    items, _, entries, cut = chunks_of(p, 1)
+    assert cut.any()
+    if name == "neighbours":
+        assert (cut[:-1] & cut[1:]).any()
+    if name in ("snapped", "long_chunks"):
+        longest = np.diff(p.rowptr)[oracle.merge_path(p.rowptr, items)[0][:-1][cut[:-1]]]
+        assert set(longest) == {2049} if name == "snapped" else items > 2048
+    if name == "next_to_empty_chunks":
+        empty = np.diff(entries) == 0
+        assert (cut[:-2] & empty[1:]).any() and (empty[:-1] & cut[2:]).any()  # an empty chunk behind a row's last piece, and one before its first
+    _, A = check(p, GATHER)
+    assert A.info.plan == s.SPMV_PLAN_MERGE
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("name", list(UNCUT))
+def test_merge_plan_without_cut_rows(name, dtype):
+    p = problem(UNCUT[name], 50000, dtype)
+    _, _, entries, cut = chunks_of(p, 1)
+    assert not cut.any()
+    if name == "least":
+        assert 1 << 16 <= p.nnz < (1 << 16) + 100
+    if name == "over_empty_chunks":
+        assert (np.diff(entries) == 0).sum() > 64
+    _, A = check(p, GATHER)
+    assert A.info.plan == s.SPMV_PLAN_MERGE
+
+
+@pytest.mark.parametrize("name", list(FULL))
+def test_cut_rows_of_full_chunks(name):
+    lens, dtype, to_a_unit, second_kernel = FULL[name]
+    p = problem(lens, 50000, dtype)
+    for k in (1, 4):  # the fewest chunks whose values and x fit the LDS
+        items, rows, entries, cut = chunks_of(p, k)
+        slots = np.diff(entries).max()
+        fits = items + 512 <= 32760 and (2 if dtype == "bf16" else 4) * 2 * slots + 8 * np.diff(rows).max() + 64 <= (160 - 8) * 1024 // min(k, 2)
+        assert fits == (k == to_a_unit)
+        if fits:
+            break
+    assert cut.any() and (12 * (cut.sum() - 600) > cut.size - 1) == second_kernel
+    assert name != "words_in_rounds" or slots > 64 * 256  # 16 wavefronts, four words of a lane at a time
+    _, A = check(p, GATHER)
     assert A.info.plan == s.SPMV_PLAN_MERGE
 
 
@@ -123,6 +188,7 @@ def test_values_changed_in_place_and_non_finite_x():
 
 def test_matrices_of_the_tile_kernel():
     check(problem([8] * 40000, 50000, "f32"), TILE)                                      # too few entries
+    check(problem(lengths_with([(5, 1100)], short=16100), 50000, "f32"), TILE)            # too few entries, one row over the length of a block
     check(problem([40000] * 3, 100000, "f32"), TILE)                                     # rows over too many chunks
     check(problem([16] * 30000, 30000, "f32"), TILE, params=dict(plan=s.SPMV_PLAN_ADAPTIVE))
     check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(plan=s.SPMV_PLAN_MERGE))
