@@ -178,6 +178,15 @@ bool gather_choice(int64_t m, int64_t nnz, int32_t plan, int64_t max_len, int32_
     return nnz >= 1 << 16 && max_len <= 32 * std::max(items, kGatherMinItems);
 }
 
+bool gather_pays(int64_t m, int64_t nnz, int32_t plan, bool bf16, int32_t cus, int64_t chunks, int64_t most_lines, int64_t lines, int64_t stretch_lines) {
+    if (nnz + 4 * m <= kGatherAlways * cus) return true;
+    const int64_t saved = (stretch_lines - lines) / cus - (most_lines - lines / chunks);
+    if (plan == SPMV_PLAN_MERGE) return saved >= (bf16 ? -1250 : -2000);
+    return 16 * saved * cus >= (bf16 ? 11 : 4) * m;
+}
+
+bool gather_groups_choice(int64_t m, int64_t groups, int32_t cus) { return groups >= (m <= int64_t{3072} * cus ? 2 : 3) * m; }
+
 bool rows_of_groups(int64_t m, const int32_t* rowptr) {
     for (int64_t i = 0; i <= m; ++i)
         if (rowptr[i] % kTpGroup != 0) return false;

@@ -86,6 +86,27 @@ bool two_phase_choice(int64_t m, int64_t n, int64_t nnz, spmv_dtype_t dtype, int
 //     of 3 and one of 1500, 61 k entries, 4.8 / 5.7 and 4.5 / 5.2.  A row that many small chunks cut is put together by one lane of the last:
 //     3 rows of 40 000 in chunks of 512 8.4 / 14.0; 300 000 rows of 5 and one of 200 000, 26 chunks, 21.8 / 13.2.
 bool gather_choice(int64_t m, int64_t nnz, int32_t plan, int64_t max_len, int32_t cus, int k);
+// Whether that stays so once the lines of x are known (kGatherFound).  A compute unit takes a line from the L2s in about 1 ns.  The tile kernel asks for
+// about the lines that stretches of 1024 entries touch; a unit with a chunk of the gathered product for those that its chunk touches, and all
+// wait for the chunk with the most.  So lines are saved where neighbouring rows share few, and lost where they share most (a stencil, a narrow
+// band) and a few long or scattered rows fall into one chunk.  Over 229 matrices of 0.15 to 9 M entries what the gathered product gains goes with the lines
+// saved to a compute unit, 0.7 to 0.8 ns each; the plan on cut rows gains 2 us by itself, the other one loses 0.2 us (FP32) or 0.6 us (bf16) for 1000 rows.
+// us, tile kernel / in column order, lines saved:
+//   - MERGE, one row of 9000 in a 27-point stencil: 64 000 rows 7.9 / 7.4, -1030, 125 000 9.4 / 10.5, -3300, 216 000 bf16 10.9 / 13.2, -2900; 640 000 rows of 5
+//     and one of 9000 11.8 / 17.3, -7000; a band of 150 000 x 16 and a row of 2500 in every 5000 12.3 / 10.2, -1450, of 300 000, bf16, 15.1 / 14.0, -1220;
+//     of 100 000 x 40 and one row, bf16, 9.5 / 10.2, -1290.
+//   - ADAPTIVE, 2-D grid with 64 scattered rows: 360 000 rows 6.3 / 7.2, -2150, 640 000 8.6 / 13.1, -2180; with a row of 300 in every 300: 360 000 8.6 / 10.0, 40,
+//     bf16 7.0 / 8.8, 80, 640 000 bf16 11.2 / 13.2, 180; bands of 300 000 x 5, FP32, 4000 wide 5.8 / 5.7, 580, bf16, 10 000 wide 5.2 / 5.6, 720, 40 000 wide
+//     6.4 / 5.7, 2150; 490 000 rows of 5 in no order 13.3 / 12.3, 790, bf16 12.7 / 11.6, 1400.
+//   - Short calls are bound by other things: 200 000 rows of 5 and 64 scattered 5.6 / 5.1, -2040, a 27-point stencil of 64 000 and 64 scattered rows 8.0 / 6.6,
+//     -1370, bf16 7.1 / 5.7; 200 000 rows of 5 and a row of 300 in every 300 (4700 entries and 790 rows to a unit) 6.0 / 6.1.
+// Given up for it: 640 000 rows of 5 and a row of 300 in every 300, FP32, 13.7 us instead of 14.3; 100 000 x 40 with a row of 2500 in every 5000, bf16, 9.7 instead of 10.1.
+bool gather_pays(int64_t m, int64_t nnz, int32_t plan, bool bf16, int32_t cus, int64_t chunks, int64_t most_lines, int64_t lines, int64_t stretch_lines);
+constexpr int64_t kGatherAlways = 7680;  // entries and four times rows to a compute unit up to which the lines are not looked at
+// Whether the groups of eight of a WINDOWED matrix of m rows and `groups` groups are gathered by cus compute units.  Windows / gathered, us: rows of one group,
+// 600 000 6.7 to 8.6 / 6.2 to 9.0, 1.5 M 12.5 / 13.5, 16.0 / 18.9 (scattered); of two, 600 000 9.2 / 8.0, 12.9 / 11.7, 1.5 M 17.2 / 18.1, 24.4 / 24.5, 21.5 / 18.7; of three,
+// 600 000 12.8 / 11.8, 17.9 / 18.3; of four, 400 000 19.4 / 9.3, 20.7 / 13.5.
+bool gather_groups_choice(int64_t m, int64_t groups, int32_t cus);
 constexpr int64_t kGatherMinItems = 512;  // fewest steps of a chunk: a wavefront's worth or two of every load
 // Rows of at most this many entries are not cut by chunks of `items` steps.  A cut costs a chunk 1 to 2 us that show where it is short, a row
 // kept whole makes its chunk the longest.  512 / 2048 entries, power-law rows, FP32: 20 000 rows (chunks of 700 steps) 5.85 / 5.11 us, 50 000 6.74 / 6.30,

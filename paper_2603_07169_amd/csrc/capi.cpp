@@ -706,7 +706,8 @@ spmv_status_t build_sell(spmv_csr_s* h, const HostRowptr& rowptr_host, spmv::Ana
 
 // The entries in column order chunk by chunk, for a MERGE or ADAPTIVE handle where gathering x in that order is the faster way, or the groups of
 // eight of a WINDOWED one (next to its windows, which serve an x that does not allow 16-byte reads).
-// Without room for them, where 15 + 17 bits an entry cannot express them, or where a group is no aligned run of columns, the plan's other kernel runs.
+// Without room for them, where 15 + 17 bits an entry cannot express them, where a group is no aligned run of columns, or where the lines of x that the
+// build has counted speak against it, the plan's other kernel runs.
 spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const spmv::Analysis& a) try {
     const int32_t plan = a.info.plan;
     const bool bf16 = h->dtype == SPMV_BF16, cuts_rows = plan == SPMV_PLAN_MERGE;
@@ -716,6 +717,7 @@ spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const s
     if (!on_groups && plan != SPMV_PLAN_MERGE && plan != SPMV_PLAN_ADAPTIVE) return SPMV_OK;
     int dev = 0, cus = 0;
     if (hip_failed(hipGetDevice(&dev)) || hip_failed(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev))) return SPMV_ERR_HIP;
+    if (on_groups && !spmv::gather_groups_choice(h->m, h->nnz / spmv::kTpGroup, cus)) return SPMV_OK;
     std::vector<int32_t> rows, entries, desc, cuts, rowptr_groups;
     spmv::GatherTiles& t = h->gather;
     int64_t P = 0, nent = h->nnz, longest = a.info.max_len;
@@ -774,16 +776,16 @@ spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const s
         spmv::cut_ranges(h->m, rowptr_host.data(), rows, entries, &cuts);
         for (size_t q = 0; 2 * q < cuts.size(); ++q) num_cuts += cuts[2 * q] >= 0;
     }
-    // One allocation and one upload: what the host has made, a zero that the build may set and the zeroes of the arrivals; behind them what
+    // One allocation and one upload: what the host has made, zeroes for what the build finds and for the arrivals; behind them what
     // the device makes (a call for each: 10 to 120 us more for every analysis).
     const size_t groups = static_cast<size_t>(P) * static_cast<size_t>(t.stride), chunks = static_cast<size_t>(P);
     const bool cut_kernel = cuts_rows && spmv::use_cut_rows_kernel(num_cuts, P);
     std::vector<int32_t> head(desc);
     head.insert(head.end(), cuts.begin(), cuts.end());
-    const size_t flag_at = head.size();
-    head.resize((flag_at + 1 + (cuts_rows ? chunks : 0) + 3) & ~size_t{3}, 0);
+    const size_t found_at = head.size(), arrivals_at = found_at + spmv::kGatherFound;
+    head.resize((arrivals_at + (cuts_rows ? chunks : 0) + 3) & ~size_t{3}, 0);
     int32_t* pool = nullptr;
-    int32_t flag = 0;
+    int32_t found[spmv::kGatherFound] = {};
     if (hip_failed(hipMalloc(reinterpret_cast<void**>(&pool), 4 * (head.size() + 257 * groups + chunks)))) {
         (void)hipGetLastError();
         t = spmv::GatherTiles{};
@@ -791,17 +793,19 @@ spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const s
     }
     t.chunk_desc = pool;
     t.cut_range = cuts_rows ? pool + desc.size() : nullptr;
-    if (cuts_rows && cut_kernel) t.cut.carry_row = pool + flag_at + 1;
-    if (cuts_rows && !cut_kernel) t.cut.arrivals = reinterpret_cast<unsigned*>(pool + flag_at + 1);
+    if (cuts_rows && cut_kernel) t.cut.carry_row = pool + arrivals_at;
+    if (cuts_rows && !cut_kernel) t.cut.arrivals = reinterpret_cast<unsigned*>(pool + arrivals_at);
     t.words = reinterpret_cast<uint32_t*>(pool + head.size());
     t.base = pool + head.size() + 256 * groups;
     t.cut.carry_val = reinterpret_cast<float*>(t.base + groups);
     spmv_status_t st = SPMV_OK;
     if (hip_failed(hipMemcpy(pool, head.data(), 4 * head.size(), hipMemcpyHostToDevice)) ||
-        hip_failed(spmv::launch_gather_build(view_of(h), t, pool + flag_at, nullptr)) ||
-        hip_failed(hipMemcpy(&flag, pool + flag_at, sizeof flag, hipMemcpyDeviceToHost)))
+        hip_failed(spmv::launch_gather_build(view_of(h), t, pool + found_at, nullptr)) ||
+        hip_failed(hipMemcpy(found, pool + found_at, sizeof found, hipMemcpyDeviceToHost)))
         st = SPMV_ERR_HIP;
-    if (st != SPMV_OK || flag != 0) free_gather(h);
+    if (st != SPMV_OK || found[spmv::kGatherBad] != 0 ||
+        (!on_groups && !spmv::gather_pays(h->m, h->nnz, plan, bf16, cus, P, found[spmv::kGatherMostLines], found[spmv::kGatherLines], found[spmv::kGatherStretchLines])))
+        free_gather(h);
     return st;
 } catch (const std::bad_alloc&) {
     free_gather(h);

@@ -2,6 +2,8 @@
 // and x too large for a compute unit's cache.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "analysis.h"
 #include "device_common.h"
 #include "kernels.h"
@@ -285,11 +287,12 @@ __global__ __launch_bounds__(kGatherGroupWG) void spmv_gather_group_kernel(const
 
 // Analysis: one workgroup per chunk sorts its entries by column interval (counts, prefix sums, places handed out with a counter per
 // interval, all in LDS) and writes the chunk's words.  Inside an interval - at least a line of x - the order does not matter, to
-// the gathers no more than to the result.  *flag is set where a column is out of range or too far from its group's first, or where eight
-// entries that are to be one are not an aligned run of eight columns (colidx is 16-byte aligned then).
+// the gathers no more than to the result.  found[kGatherBad] is set where a column is out of range or too far from its group's first, or where
+// eight entries that are to be one are not an aligned run of eight columns (colidx is 16-byte aligned then).  The rest of found is what
+// gather_pays looks at: the intervals that chunks touch and, unless the entries are groups, those that stretches of 1024 entries touch.
 __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* __restrict__ colidx, const int32_t* __restrict__ chunk_desc,
                                                                  int n, int shift, int gs, int vec, int stride, int cap,
-                                                                 uint32_t* __restrict__ words, int32_t* __restrict__ base, int32_t* flag) {
+                                                                 uint32_t* __restrict__ words, int32_t* __restrict__ base, int32_t* found) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int WG = kGatherWG;
     int* const place = reinterpret_cast<int*>(smem_raw);  // [buckets]
@@ -312,6 +315,16 @@ __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* 
     };
     for (int i = tid; i < buckets; i += WG) place[i] = 0;
     __syncthreads();
+    int stretch_lines = 0, lines = 0;
+    if (gs == 0) {
+        for (int s = 0; s * WG < entries; ++s) {
+            const int k = k0 + s * WG + tid;
+            if (k < k1 && atomicMax(place + bucket_of(column(k)), s + 1) <= s) ++stretch_lines;
+            __syncthreads();
+        }
+        for (int i = tid; i < buckets; i += WG) place[i] = 0;
+        __syncthreads();
+    }
     for (int k = k0 + tid; k < k1; k += WG) atomicAdd(place + bucket_of(column(k)), 1);
     if (gs != 0)
         for (int k = k0 + tid; k < k1; k += WG) {
@@ -326,7 +339,10 @@ __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* 
     // exclusive prefix sums: a lane takes a run of buckets
     const int run = (buckets + WG - 1) / WG, b0 = tid * run, b1 = b0 + run < buckets ? b0 + run : buckets;
     int mine = 0;
-    for (int b = b0; b < b1; ++b) mine += place[b];
+    for (int b = b0; b < b1; ++b) {
+        mine += place[b];
+        lines += place[b] != 0;
+    }
     int before = mine;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -356,7 +372,26 @@ __global__ __launch_bounds__(kGatherWG) void gather_build_kernel(const int32_t* 
         if (off >= 1u << (32 - kGatherPosBits)) bad = true;
         put(i, off << kGatherPosBits | static_cast<uint32_t>(k - k0a));
     }
-    if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) *flag = 1;  // plain store: every writer writes 1
+    if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) found[kGatherBad] = 1;  // plain store: every writer writes 1
+    // place is no longer needed
+    __syncthreads();
+    if (tid < 2) place[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        lines += __shfl_xor(lines, d);
+        stretch_lines += __shfl_xor(stretch_lines, d);
+    }
+    if (lane == 0) {
+        atomicAdd(place, lines);
+        atomicAdd(place + 1, stretch_lines);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        atomicMax(found + kGatherMostLines, place[0]);
+        atomicAdd(found + kGatherLines, place[0]);
+        atomicAdd(found + kGatherStretchLines, place[1]);
+    }
 }
 
 template <typename T, bool MERGE, int U>
@@ -399,16 +434,16 @@ size_t gather_lds(bool bf16, int32_t slots, int32_t rows) {
     return e * (2 * static_cast<size_t>(slots) + vec) + 4 * (2 * static_cast<size_t>(rows) + 2);
 }
 
-hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_t* flag, hipStream_t st) {
+hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_t* found, hipStream_t st) {
     const int gs = t.group == 8 ? 3 : 0;
     const int n = t.group == 8 ? A.n / 8 : A.n;  // whole runs of eight: the kernel reads all of a run
     int shift = (A.bf16 ? 6 : 5) - gs;  // log2 of the columns (runs of columns) of a line of x
     while (((n - 1) >> shift) + 1 > kGatherBuckets) ++shift;
-    const size_t lds = sizeof(int) * static_cast<size_t>(((n - 1) >> shift) + 1);
+    const size_t lds = sizeof(int) * std::max<size_t>(((n - 1) >> shift) + 1, 2);
     const hipError_t e = allow_lds<gather_build_kernel>(lds);
     if (e != hipSuccess) return e;
     return launch_kernel(gather_build_kernel, dim3(t.num_chunks), dim3(kGatherWG), lds, st, A.colidx, t.chunk_desc, n, shift, gs,
-                         t.group == 8 ? 1 : (A.bf16 ? BF16::VEC : F32::VEC), t.stride, t.slots, t.words, t.base, flag);
+                         t.group == 8 ? 1 : (A.bf16 ? BF16::VEC : F32::VEC), t.stride, t.slots, t.words, t.base, found);
 }
 
 hipError_t launch_gather(const GatherTiles& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done) {

@@ -224,8 +224,11 @@ size_t gather_group_lds(int32_t groups, int32_t rows);
 // LDS slots of the largest chunk (desc: HOST array), and the LDS bytes of a workgroup for them and at most `rows` rows.
 int32_t gather_slots(bool bf16, const int32_t* desc, int64_t P);
 size_t gather_lds(bool bf16, int32_t slots, int32_t rows);
-// Analysis time: fills words and base; *flag is set where they cannot express the matrix.
-hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_t* flag, hipStream_t st);
+// Analysis time: fills words and base, and found (device, zeroes before): whether they cannot express the matrix, and the 128-byte lines of x that
+// the chunk with the most of them touches, that all chunks touch, and that all stretches of 1024 consecutive entries of a chunk touch (an x of more than
+// 16384 lines: intervals of several lines, so that there are at most as many).
+enum { kGatherBad, kGatherMostLines, kGatherLines, kGatherStretchLines, kGatherFound };
+hipError_t launch_gather_build(const MatrixView& A, const GatherTiles& t, int32_t* found, hipStream_t st);
 hipError_t launch_gather(const GatherTiles& t, const MatrixView& A, const void* x, float* y, Scalars s, hipStream_t st, hipEvent_t done);
 
 // The two-pass plan (device arrays owned by the handle).

@@ -197,6 +197,68 @@ def test_matrices_of_the_tile_kernel():
     check(problem([8] * 50000, 200_000_000, "bf16"), TILE)                               # neighbours too far apart for a word
 
 
+def near(side, at, length, scattered):
+    """A 2-D grid's five neighbours, and `scattered` columns anywhere in some rows: row lengths and columns."""
+    m = side * side
+    near_cols = np.arange(m)[:, None] + np.array([-side, -1, 0, 1, side])
+    lens = np.full(m, 5)
+    lens[at] = length
+    cols = np.random.default_rng(7).integers(0, m, lens.sum())
+    starts = np.concatenate(([0], np.cumsum(lens)[:-1]))
+    for j in range(5):
+        cols[starts + j] = np.clip(near_cols[:, j], 0, m - 1)
+    if not scattered:
+        cols = np.random.default_rng(8).permutation(m)[cols]
+    return lens, cols, m
+
+
+NEAR = {  # columns of neighbouring rows near each other, but for some rows; the same in no order
+    "few_long_rows": lambda: near(800, [99, 300000], 4000, True),
+    "block_of_scattered_rows": lambda: near(800, np.arange(999, 1063), 45, True),
+    "long_rows_everywhere": lambda: near(600, np.arange(7, 360000, 300), 305, True),
+    "short_call": lambda: near(440, np.arange(999, 1063), 45, True),
+    "no_order": lambda: near(800, np.arange(999, 1063), 45, False),
+    "no_order_cut": lambda: near(800, [99, 300000], 4000, False),
+}
+
+
+def lines_of(p, chunk_of_entry, chunks):
+    """The 128-byte lines of x that the chunk with the most of them, all chunks, and all stretches of 1024 entries of a chunk touch."""
+    line = p.colidx.astype(np.int64) // (64 if p.dtype == "bf16" else 32)
+    per_chunk = np.bincount(np.unique(chunk_of_entry << 32 | line) >> 32, minlength=chunks)
+    first = np.searchsorted(chunk_of_entry, np.arange(chunks))
+    by_column = np.sort(chunk_of_entry << 32 | p.colidx) & 0xFFFFFFFF
+    group = chunk_of_entry << 12 | (np.arange(p.nnz) - first[chunk_of_entry]) // 256
+    starts = np.flatnonzero(np.append(True, group[1:] != group[:-1]))
+    assert (np.maximum.reduceat(by_column, starts) - by_column[starts]).max() < (1 << 17) - 64  # nothing else speaks against the words
+    stretch = chunk_of_entry << 12 | (np.arange(p.nnz) - first[chunk_of_entry]) // 1024
+    return per_chunk.max(), per_chunk.sum(), np.unique(stretch << 32 | line).size
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("name", list(NEAR))
+def test_the_lines_of_x_decide(name, dtype):
+    """The kernel is the one that the rule gives for the lines as they are counted here."""
+    lens, cols, n = NEAR[name]()
+    p = problem(lens, n, dtype)
+    p.colidx = cols.astype(np.int32)
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    _, _, entries, cut = chunks_of(p, 1)
+    merge = name in ("few_long_rows", "no_order_cut")
+    if not merge:  # no row is cut
+        _, rows, _, _ = chunks_of(p, 1)
+        entries = np.where(p.rowptr[rows] < entries, p.rowptr[rows], entries)
+    chunk = np.repeat(np.arange(entries.size - 1), np.diff(entries))
+    most, total, stretches = lines_of(p, chunk, entries.size - 1)
+    saved = (stretches - total) / units - (most - total / (entries.size - 1))
+    least = (-1250 if dtype == "bf16" else -2000) if merge else p.m / units * (11 if dtype == "bf16" else 4) / 16
+    short = p.nnz + 4 * p.m <= 7680 * units
+    assert short == (name == "short_call") and abs(saved - least) > 10  # the rule divides in whole numbers
+    _, A = check(p, GATHER if short or saved >= least else TILE)
+    assert A.info.plan == (s.SPMV_PLAN_MERGE if merge else s.SPMV_PLAN_ADAPTIVE)
+    assert (saved >= least) == name.startswith("no_order")
+
+
 GROUPS = {  # runs of eight a row, runs in x
     "blocks": ([8] * 70000, 5000),
     "odd": (np.random.default_rng(2).integers(0, 19, 60003), 4001),

@@ -53,6 +53,10 @@ int stream_lanes(int elem, int64_t m, int64_t nnz, int rows_max, int places, int
     return spmv::stream_lanes(elem, m, nnz, rows_max, places, common);
 }
 int gather_choice(int64_t m, int64_t nnz, int plan, int64_t max_len, int cus, int k) { return spmv::gather_choice(m, nnz, plan, max_len, cus, k); }
+int gather_pays(int64_t m, int64_t nnz, int plan, int bf16, int cus, int64_t chunks, int64_t most, int64_t lines, int64_t stretch_lines) {
+    return spmv::gather_pays(m, nnz, plan, bf16 != 0, cus, chunks, most, lines, stretch_lines);
+}
+int gather_groups_choice(int64_t m, int64_t groups, int cus) { return spmv::gather_groups_choice(m, groups, cus); }
 int rows_of_groups(int64_t m, const int32_t* rp) { return spmv::rows_of_groups(m, rp); }
 int64_t gather_snap(int plan, int64_t max_len, int64_t items) { return spmv::gather_snap(plan, max_len, items); }
 int common_len(int64_t m, const int32_t* rp) { return spmv::common_row_length(m, rp); }
@@ -306,6 +310,31 @@ def test_gather_rule(rules):
         assert not choice(30000, 1 << 20, plan, 20)
     assert rules.gather_snap(A, i64(300), i64(2000)) == 300
     assert rules.gather_snap(M, i64(9000), i64(2048)) == 2048 and rules.gather_snap(M, i64(9000), i64(2049)) == 512
+
+
+def test_gather_rule_of_the_lines(rules):
+    """Lines saved to a compute unit: what stretches of entries touch beyond their chunks, less what the worst chunk is above the mean."""
+    import paper_2603_07169_amd as s
+    A, M = s.SPMV_PLAN_ADAPTIVE, s.SPMV_PLAN_MERGE
+
+    def pays(m, nnz, plan, bf16, saved, excess=0, mean=100, chunks=256):
+        return rules.gather_pays(i64(m), i64(nnz), plan, bf16, 256, i64(chunks), i64(mean + excess), i64(mean * chunks), i64(mean * chunks + 256 * (saved + excess)))
+
+    for excess, chunks in ((0, 256), (700, 256), (700, 1024)):
+        at = lambda *case: pays(*case, excess=excess, chunks=chunks)
+        assert at(10000, 4 << 20, M, 0, -2000) and not at(10000, 4 << 20, M, 0, -2001)
+        assert at(10000, 4 << 20, M, 1, -1250) and not at(10000, 4 << 20, M, 1, -1251)
+        assert at(256 * 1600, 4 << 20, A, 0, 400) and not at(256 * 1600, 4 << 20, A, 0, 399)       # a quarter of the rows to a unit
+        assert at(256 * 1600, 4 << 20, A, 1, 1100) and not at(256 * 1600, 4 << 20, A, 1, 1099)     # eleven sixteenths
+    for plan in (A, M):  # short calls, whatever the lines are
+        assert pays(256 * 500, 256 * 5680, plan, 1, -9000) and not pays(256 * 500, 256 * 5680 + 1, plan, 1, -9000)
+
+
+def test_rule_of_gathered_groups(rules):
+    takes = lambda m, groups: rules.gather_groups_choice(i64(m), i64(groups), 256)
+    few, many = 3072 * 256, 3072 * 256 + 1
+    assert takes(few, 2 * few) and not takes(few, 2 * few - 1)
+    assert takes(many, 3 * many) and not takes(many, 3 * many - 1)
 
 
 NOT_GROUPS = {  # row lengths, first column of every row: each row's columns follow one another
