@@ -171,10 +171,10 @@ int64_t gather_snap(int32_t plan, int64_t max_len, int64_t items) {
     return plan == SPMV_PLAN_ADAPTIVE ? max_len : (items <= kGatherSnap ? kGatherSnap : kTwoPhaseSnap);
 }
 
-bool gather_choice(int64_t m, int64_t nnz, int32_t plan, int64_t max_len, int32_t cus, int k) {
+bool gather_choice(int64_t m, int64_t nnz, int32_t plan, bool bf16, int64_t max_len, int32_t cus, int k) {
     if (plan != SPMV_PLAN_MERGE && plan != SPMV_PLAN_ADAPTIVE) return false;
     const int64_t items = (m + nnz + static_cast<int64_t>(cus) * k - 1) / (static_cast<int64_t>(cus) * k);
-    if (plan == SPMV_PLAN_ADAPTIVE) return nnz >= 3 << 17 && 2 * max_len <= items;
+    if (plan == SPMV_PLAN_ADAPTIVE) return nnz >= (bf16 ? 3 << 17 : 3 << 18) && 2 * max_len <= items;
     return nnz >= 1 << 16 && max_len <= 32 * std::max(items, kGatherMinItems);
 }
 

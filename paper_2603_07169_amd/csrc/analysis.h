@@ -77,15 +77,16 @@ bool two_phase_choice(int64_t m, int64_t n, int64_t nnz, spmv_dtype_t dtype, int
                       int64_t entries_counted);
 // Whether x is gathered in column order (spmv_gather_kernel) by k chunks to a compute unit, where AUTO has arrived at a row-wise plan.
 // us, tile kernel / in column order:
-//   - ADAPTIVE, rows of 16, FP32 and bf16: 160 k entries 3.7 / 4.4 and 3.8 / 4.3, 320 k 4.1 / 4.2 and 4.0 / 4.3, rows of 8, 320 k 4.3 / 5.0 and
-//     4.3 / 4.3, 400 k 4.5 / 4.5 and 4.3 / 4.0; rows of 16, 800 k 5.9 / 5.2 and 5.1 / 4.0, 1.6 M 10.7 / 7.9 and 9.0 / 5.4, 3.2 M 19.5 / 14.5 and 16.9 / 8.8.
-//     Rows are not cut there, so the longest may take half a chunk.  Out of a graph, with an x that the compute units' own caches hold: 2048
-//     columns 490 k and 670 k entries 4.0 / 3.9 and 3.7 / 3.6 FP32, 3.9 / 3.7 and 4.2 / 3.9 bf16;
-//     5000 columns, 800 k 4.6 / 4.3 and 4.1 / 3.6.
+//   - ADAPTIVE, FP32, call by call and out of a graph: rows of 8, 393 k entries 4.1 / 4.8 and 3.9 / 4.9, 480 k 4.75 / 4.75 and 4.7 / 4.8, 640 k 5.3 / 5.5 and
+//     5.5 / 5.6, 800 k 6.0 / 5.9 and 6.1 / 6.1; of 16, 480 k 4.4 / 4.5 and 4.3 / 4.5, 640 k 5.0 / 4.8 and 5.05 / 5.0, 800 k 5.7 / 5.1 and 5.9 / 5.4; of 30, 600 k
+//     4.5 / 4.2 and 4.5 / 4.3; of 5, 800 k 7.4 / 5.8; an x of 2048 columns, 480 k 3.9 / 4.0 and 3.75 / 4.0, 655 k 4.2 / 4.2 and 4.0 / 4.2; rows of 16, 1.6 M 10.7 / 7.9, 3.2 M
+//     19.5 / 14.5.  bf16: rows of 8, 320 k 4.3 / 4.3, 393 k 4.15 / 4.05 and 3.9 / 4.0, 480 k 4.6 / 3.95; of 16, 320 k 4.0 / 4.3, 416 k 4.05 / 3.85 and 3.9 / 3.7,
+//     800 k 5.1 / 4.05, 1.6 M 9.0 / 5.4, 3.2 M 16.9 / 8.8; 2048 columns, 480 k 3.95 / 3.75 and 3.9 / 3.75, 655 k 4.15 / 3.9 and 4.0 / 3.9.
+//     Rows are not cut there, so the longest may take half a chunk.
 //   - MERGE, power-law rows: 92 k entries 8.6 / 5.7 and 8.4 / 5.5, 626 k 10.6 / 7.4 and 10.1 / 6.8, 2.6 M 20.2 / 16.6 and 18.6 / 13.3; 20 000 rows
 //     of 3 and one of 1500, 61 k entries, 4.8 / 5.7 and 4.5 / 5.2.  A row that many small chunks cut is put together by one lane of the last:
 //     3 rows of 40 000 in chunks of 512 8.4 / 14.0; 300 000 rows of 5 and one of 200 000, 26 chunks, 21.8 / 13.2.
-bool gather_choice(int64_t m, int64_t nnz, int32_t plan, int64_t max_len, int32_t cus, int k);
+bool gather_choice(int64_t m, int64_t nnz, int32_t plan, bool bf16, int64_t max_len, int32_t cus, int k);
 // Whether that stays so once the lines of x are known (kGatherFound).  A compute unit takes a line from the L2s in about 1 ns.  The tile kernel asks for
 // about the lines that stretches of 1024 entries touch; a unit with a chunk of the gathered product for those that its chunk touches, and all
 // wait for the chunk with the most.  So lines are saved where neighbouring rows share few, and lost where they share most (a stencil, a narrow

@@ -758,7 +758,7 @@ spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const s
             items = std::max(items, spmv::kGatherMinItems);
             const int64_t snap = spmv::gather_snap(plan, longest, items);
             if (items + snap > spmv::kGatherMaxSlots) continue;
-            if (!spmv::gather_choice(h->m, h->nnz, plan, longest, cus, static_cast<int>(k))) return SPMV_OK;
+            if (!spmv::gather_choice(h->m, h->nnz, plan, bf16, longest, cus, static_cast<int>(k))) return SPMV_OK;
             cut(items, snap, &most_rows);
             t.slots = spmv::gather_slots(bf16, desc.data(), P);
             t.lds = spmv::gather_lds(bf16, t.slots, most_rows);

@@ -40,20 +40,20 @@ def check(p, kernel, offset=0, params=None, runs=2):
 
 
 UNIFORM = {  # ADAPTIVE: rows x length, columns
-    "rows_of_16": ([16] * 30000, 30000),                       # several lanes a row in binary32
-    "odd": (np.random.default_rng(1).integers(0, 40, 40001), 9973),
-    "least": ([8] * 49152, 50000),                             # the fewest entries the rule takes
+    "rows_of_16": ([16] * 50000, 50000),                       # several lanes a row in binary32
+    "odd": (np.random.default_rng(1).integers(0, 40, 50001), 9973),
+    "least": {"f32": ([8] * 98304, 50000), "bf16": ([8] * 49152, 50000)},  # the fewest entries the rule takes
     "long_rows": ([700] * 3000, 70000),                        # a wavefront a row
     "four_words_a_lane": ([16] * 220000, 100000),
     "four_chunks": ([16] * 300000, 100000),                    # binary32: four chunks to a compute unit; bf16: words in two rounds
-    "banded": ([24] * 30000, 400000),
+    "banded": ([24] * 40000, 400000),
 }
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("name", list(UNIFORM))
 def test_uncut_rows(name, dtype):
-    lens, n = UNIFORM[name]
+    lens, n = UNIFORM[name][dtype] if name == "least" else UNIFORM[name]
     p = problem(lens, n, dtype, beta=0.5, width=20000 if name == "banded" else None)
     d, A = check(p, GATHER, runs=1)
     assert A.info.plan == s.SPMV_PLAN_ADAPTIVE
@@ -187,10 +187,11 @@ def test_values_changed_in_place_and_non_finite_x():
 
 
 def test_matrices_of_the_tile_kernel():
-    check(problem([8] * 40000, 50000, "f32"), TILE)                                      # too few entries
+    check(problem([8] * 98303, 50000, "f32"), TILE)                                      # too few entries
+    check(problem([8] * 49151, 50000, "bf16"), TILE)
     check(problem(lengths_with([(5, 1100)], short=16100), 50000, "f32"), TILE)            # too few entries, one row over the length of a block
     check(problem([40000] * 3, 100000, "f32"), TILE)                                     # rows over too many chunks
-    check(problem([16] * 30000, 30000, "f32"), TILE, params=dict(plan=s.SPMV_PLAN_ADAPTIVE))
+    check(problem([16] * 50000, 50000, "f32"), TILE, params=dict(plan=s.SPMV_PLAN_ADAPTIVE))
     check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(plan=s.SPMV_PLAN_MERGE))
     check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(prepare_spmm=1))   # a handle for products with matrices
     check(problem(CUT["neighbours"], 50000, "f32"), TILE, params=dict(items_per_chunk=512))

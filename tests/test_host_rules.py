@@ -52,7 +52,7 @@ int sheets_pay(int elem, int64_t m, int64_t nnz, int64_t nb, int block_nnz, int 
 int stream_lanes(int elem, int64_t m, int64_t nnz, int rows_max, int places, int common) {
     return spmv::stream_lanes(elem, m, nnz, rows_max, places, common);
 }
-int gather_choice(int64_t m, int64_t nnz, int plan, int64_t max_len, int cus, int k) { return spmv::gather_choice(m, nnz, plan, max_len, cus, k); }
+int gather_choice(int64_t m, int64_t nnz, int plan, int bf16, int64_t max_len, int cus, int k) { return spmv::gather_choice(m, nnz, plan, bf16 != 0, max_len, cus, k); }
 int gather_pays(int64_t m, int64_t nnz, int plan, int bf16, int cus, int64_t chunks, int64_t most, int64_t lines, int64_t stretch_lines) {
     return spmv::gather_pays(m, nnz, plan, bf16 != 0, cus, chunks, most, lines, stretch_lines);
 }
@@ -297,15 +297,16 @@ def test_common_row_length_of_a_sample(rules, line):
 
 def test_gather_rule(rules):
     import paper_2603_07169_amd as s
-    choice = lambda m, nnz, plan, longest, k=1: rules.gather_choice(i64(m), i64(nnz), plan, i64(longest), 256, k)
     rules.gather_snap.restype = C.c_int64
     A, M = s.SPMV_PLAN_ADAPTIVE, s.SPMV_PLAN_MERGE
-    assert choice(30000, 3 << 17, A, 20) and not choice(30000, (3 << 17) - 1, A, 20)
-    items = -(-(30000 + 480000) // 256)
-    assert choice(30000, 480000, A, items // 2) and not choice(30000, 480000, A, items // 2 + 1)  # half a chunk is the longest uncut row
-    assert not choice(30000, 480000, A, items // 2, 4)                                             # chunks of a quarter the steps
-    assert choice(10000, 1 << 16, M, 2000) and not choice(10000, (1 << 16) - 1, M, 2000)
-    assert choice(10000, 1 << 16, M, 32 * 512) and not choice(10000, 1 << 16, M, 32 * 512 + 1)     # chunks of 512 steps at least
+    for bf16, least in ((0, 3 << 18), (1, 3 << 17)):
+        choice = lambda m, nnz, plan, longest, k=1: rules.gather_choice(i64(m), i64(nnz), plan, bf16, i64(longest), 256, k)
+        assert choice(30000, least, A, 20) and not choice(30000, least - 1, A, 20)
+        items = -(-(30000 + least) // 256)
+        assert choice(30000, least, A, items // 2) and not choice(30000, least, A, items // 2 + 1)  # half a chunk is the longest uncut row
+        assert not choice(30000, least, A, items // 2, 4)                                           # chunks of a quarter the steps
+        assert choice(10000, 1 << 16, M, 2000) and not choice(10000, (1 << 16) - 1, M, 2000)
+        assert choice(10000, 1 << 16, M, 32 * 512) and not choice(10000, 1 << 16, M, 32 * 512 + 1)  # chunks of 512 steps at least
     for plan in (s.SPMV_PLAN_SCALAR, s.SPMV_PLAN_VECTOR, s.SPMV_PLAN_BINNED, s.SPMV_PLAN_WINDOWED, s.SPMV_PLAN_TWOPHASE, s.SPMV_PLAN_COLBLOCK, s.SPMV_PLAN_SELL):
         assert not choice(30000, 1 << 20, plan, 20)
     assert rules.gather_snap(A, i64(300), i64(2000)) == 300
