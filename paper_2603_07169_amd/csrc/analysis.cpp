@@ -171,11 +171,12 @@ int64_t gather_snap(int32_t plan, int64_t max_len, int64_t items) {
     return plan == SPMV_PLAN_ADAPTIVE ? max_len : (items <= kGatherSnap ? kGatherSnap : kTwoPhaseSnap);
 }
 
-bool gather_choice(int64_t m, int64_t nnz, int32_t plan, bool bf16, int64_t max_len, int32_t cus, int k) {
+bool gather_choice(int64_t m, int64_t n, int64_t nnz, int32_t plan, bool bf16, int64_t max_len, int32_t cus, int k) {
     if (plan != SPMV_PLAN_MERGE && plan != SPMV_PLAN_ADAPTIVE) return false;
     const int64_t items = (m + nnz + static_cast<int64_t>(cus) * k - 1) / (static_cast<int64_t>(cus) * k);
-    if (plan == SPMV_PLAN_ADAPTIVE) return nnz >= (bf16 ? 3 << 17 : 3 << 18) && 2 * max_len <= items;
-    return nnz >= 1 << 16 && max_len <= 32 * std::max(items, kGatherMinItems);
+    if (plan == SPMV_PLAN_MERGE) return nnz >= 1 << 16 && max_len <= 32 * (items - 192);
+    if (bf16 && 2 * n <= kGatherSmallX && nnz >= 768 * m) return false;
+    return nnz >= (bf16 ? 3 << 17 : 3 << 18) && 2 * max_len <= items;
 }
 
 bool gather_pays(int64_t m, int64_t nnz, int32_t plan, bool bf16, int32_t cus, int64_t chunks, int64_t most_lines, int64_t lines, int64_t stretch_lines) {

@@ -82,11 +82,15 @@ bool two_phase_choice(int64_t m, int64_t n, int64_t nnz, spmv_dtype_t dtype, int
 //     4.5 / 4.2 and 4.5 / 4.3; of 5, 800 k 7.4 / 5.8; an x of 2048 columns, 480 k 3.9 / 4.0 and 3.75 / 4.0, 655 k 4.2 / 4.2 and 4.0 / 4.2; rows of 16, 1.6 M 10.7 / 7.9, 3.2 M
 //     19.5 / 14.5.  bf16: rows of 8, 320 k 4.3 / 4.3, 393 k 4.15 / 4.05 and 3.9 / 4.0, 480 k 4.6 / 3.95; of 16, 320 k 4.0 / 4.3, 416 k 4.05 / 3.85 and 3.9 / 3.7,
 //     800 k 5.1 / 4.05, 1.6 M 9.0 / 5.4, 3.2 M 16.9 / 8.8; 2048 columns, 480 k 3.95 / 3.75 and 3.9 / 3.75, 655 k 4.15 / 3.9 and 4.0 / 3.9.
-//     Rows are not cut there, so the longest may take half a chunk.
+//     Rows are not cut there, so the longest may take half a chunk.  Long rows in bf16 whose x a unit's own cache holds (12 000 columns): 3000 rows of 1000 7.5 / 7.9,
+//     of 1500 9.5 / 10.5, 2000 of 2400 10.6 / 11.1, 5000 of 1000 10.6 / 11.1; 9000 of 500 11.4 / 10.6, 12 000 of 300 9.75 / 8.65; 3000 of 1000 in 50 000 columns 9.9 / 8.0.
 //   - MERGE, power-law rows: 92 k entries 8.6 / 5.7 and 8.4 / 5.5, 626 k 10.6 / 7.4 and 10.1 / 6.8, 2.6 M 20.2 / 16.6 and 18.6 / 13.3; 20 000 rows
 //     of 3 and one of 1500, 61 k entries, 4.8 / 5.7 and 4.5 / 5.2.  A row that many small chunks cut is put together by one lane of the last:
-//     3 rows of 40 000 in chunks of 512 8.4 / 14.0; 300 000 rows of 5 and one of 200 000, 26 chunks, 21.8 / 13.2.
-bool gather_choice(int64_t m, int64_t nnz, int32_t plan, bool bf16, int64_t max_len, int32_t cus, int k);
+//     3 rows of 40 000 in chunks of 512 8.4 / 14.0; 5 of 16 000 7.1 / 7.8; 13 000 rows of 5 and one of 16 000 6.3 / 7.3, one of 9000 6.0 / 6.3, one of 4000 6.6 / 5.1; 25 600 and
+//     one of 16 000 (chunks of 660 steps) 6.6 / 7.2, 50 000 of 3 and one of 16 000 (840) 7.35 / 6.7; 300 000 rows of 5 and one of 200 000, 26 chunks, 21.8 / 13.2.
+//     Where the pieces are so many that they go to cut_rows_kernel: 900 rows of 9000 21.7 / 23.3, scattered 23.6 / 26.1; bf16, 1200 of 9000 23.4 / 24.9, 600 of 16 000
+//     24.4 / 25.5; rows over several chunks, 60 of 100 000 22.8 / 20.5, bf16, 120 of 100 000 29.9 / 25.1 (gather_leaves_pieces).
+bool gather_choice(int64_t m, int64_t n, int64_t nnz, int32_t plan, bool bf16, int64_t max_len, int32_t cus, int k);
 // Whether that stays so once the lines of x are known (kGatherFound).  A compute unit takes a line from the L2s in about 1 ns.  The tile kernel asks for
 // about the lines that stretches of 1024 entries touch; a unit with a chunk of the gathered product for those that its chunk touches, and all
 // wait for the chunk with the most.  So lines are saved where neighbouring rows share few, and lost where they share most (a stencil, a narrow
@@ -108,6 +112,8 @@ constexpr int64_t kGatherAlways = 7680;  // entries and four times rows to a com
 // 600 000 6.7 to 8.6 / 6.2 to 9.0, 1.5 M 12.5 / 13.5, 16.0 / 18.9 (scattered); of two, 600 000 9.2 / 8.0, 12.9 / 11.7, 1.5 M 17.2 / 18.1, 24.4 / 24.5, 21.5 / 18.7; of three,
 // 600 000 12.8 / 11.8, 17.9 / 18.3; of four, 400 000 19.4 / 9.3, 20.7 / 13.5.
 bool gather_groups_choice(int64_t m, int64_t groups, int32_t cus);
+inline bool gather_leaves_pieces(int64_t m, int64_t chunks) { return 8 * m <= chunks; }
+constexpr int64_t kGatherSmallX = 32 * 1024;  // bytes of x that a compute unit's own cache holds
 constexpr int64_t kGatherMinItems = 512;  // fewest steps of a chunk: a wavefront's worth or two of every load
 // Rows of at most this many entries are not cut by chunks of `items` steps.  A cut costs a chunk 1 to 2 us that show where it is short, a row
 // kept whole makes its chunk the longest.  512 / 2048 entries, power-law rows, FP32: 20 000 rows (chunks of 700 steps) 5.85 / 5.11 us, 50 000 6.74 / 6.30,

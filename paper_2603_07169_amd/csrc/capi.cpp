@@ -758,7 +758,7 @@ spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const s
             items = std::max(items, spmv::kGatherMinItems);
             const int64_t snap = spmv::gather_snap(plan, longest, items);
             if (items + snap > spmv::kGatherMaxSlots) continue;
-            if (!spmv::gather_choice(h->m, h->nnz, plan, bf16, longest, cus, static_cast<int>(k))) return SPMV_OK;
+            if (!spmv::gather_choice(h->m, h->n, h->nnz, plan, bf16, longest, cus, static_cast<int>(k))) return SPMV_OK;
             cut(items, snap, &most_rows);
             t.slots = spmv::gather_slots(bf16, desc.data(), P);
             t.lds = spmv::gather_lds(bf16, t.slots, most_rows);
@@ -780,6 +780,7 @@ spmv_status_t build_gather(spmv_csr_s* h, const HostRowptr& rowptr_host, const s
     // the device makes (a call for each: 10 to 120 us more for every analysis).
     const size_t groups = static_cast<size_t>(P) * static_cast<size_t>(t.stride), chunks = static_cast<size_t>(P);
     const bool cut_kernel = cuts_rows && spmv::use_cut_rows_kernel(num_cuts, P);
+    if (cut_kernel && !spmv::gather_leaves_pieces(h->m, P)) return SPMV_OK;
     std::vector<int32_t> head(desc);
     head.insert(head.end(), cuts.begin(), cuts.end());
     const size_t found_at = head.size(), arrivals_at = found_at + spmv::kGatherFound;

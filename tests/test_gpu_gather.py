@@ -15,7 +15,7 @@ GATHER, TILE = "spmv_gather_kernel", "spmv_tile_kernel"
 
 
 def problem(lens, n, dtype, seed=0, beta=0.5, width=None):
-    """Integer-valued, so that every order of summation gives the same binary32 number: |sum| < 40000 * 32 < 2^24."""
+    """Integer-valued, so that every order of summation gives the same binary32 number: |sum| < 100000 * 32 < 2^24."""
     rng = np.random.default_rng(seed)
     lens = np.asarray(lens, dtype=np.int64)
     m = lens.size
@@ -86,8 +86,8 @@ UNCUT = {  # the same plan, no chunk begins inside a row
     "empty_ends": np.concatenate(([0] * 5000, lengths_with([(100, 2000)]), [0] * 7000)),
 }
 FULL = {  # storage, chunks to a compute unit, whether the pieces of cut rows are left to the second kernel
-    "many_cuts_f32": ([9000] * 900, "f32", 4, True),
-    "many_cuts_bf16": ([9000] * 1200, "bf16", 4, True),
+    "many_cuts_f32": ([100000] * 60, "f32", 4, True),
+    "many_cuts_bf16": ([100000] * 110, "bf16", 4, True),
     "few_cuts": (lengths_with([(7, 30000), (99, 20000), (50000, 9000)], short=1200000), "f32", 4, False),
     "words_in_rounds": (lengths_with([(7, 30000), (99, 20000), (50000, 9000)], short=1200000), "bf16", 1, False),
 }
@@ -189,6 +189,8 @@ def test_values_changed_in_place_and_non_finite_x():
 def test_matrices_of_the_tile_kernel():
     check(problem([8] * 98303, 50000, "f32"), TILE)                                      # too few entries
     check(problem([8] * 49151, 50000, "bf16"), TILE)
+    check(problem([1000] * 2000, 12000, "bf16"), TILE)                                   # long rows, an x that a unit's cache holds
+    check(problem([9000] * 900, 50000, "f32"), TILE)                                     # pieces of cut rows in nearly every chunk
     check(problem(lengths_with([(5, 1100)], short=16100), 50000, "f32"), TILE)            # too few entries, one row over the length of a block
     check(problem([40000] * 3, 100000, "f32"), TILE)                                     # rows over too many chunks
     check(problem([16] * 50000, 50000, "f32"), TILE, params=dict(plan=s.SPMV_PLAN_ADAPTIVE))

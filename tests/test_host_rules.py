@@ -52,7 +52,9 @@ int sheets_pay(int elem, int64_t m, int64_t nnz, int64_t nb, int block_nnz, int 
 int stream_lanes(int elem, int64_t m, int64_t nnz, int rows_max, int places, int common) {
     return spmv::stream_lanes(elem, m, nnz, rows_max, places, common);
 }
-int gather_choice(int64_t m, int64_t nnz, int plan, int bf16, int64_t max_len, int cus, int k) { return spmv::gather_choice(m, nnz, plan, bf16 != 0, max_len, cus, k); }
+int gather_choice(int64_t m, int64_t n, int64_t nnz, int plan, int bf16, int64_t max_len, int cus, int k) {
+    return spmv::gather_choice(m, n, nnz, plan, bf16 != 0, max_len, cus, k);
+}
 int gather_pays(int64_t m, int64_t nnz, int plan, int bf16, int cus, int64_t chunks, int64_t most, int64_t lines, int64_t stretch_lines) {
     return spmv::gather_pays(m, nnz, plan, bf16 != 0, cus, chunks, most, lines, stretch_lines);
 }
@@ -300,13 +302,16 @@ def test_gather_rule(rules):
     rules.gather_snap.restype = C.c_int64
     A, M = s.SPMV_PLAN_ADAPTIVE, s.SPMV_PLAN_MERGE
     for bf16, least in ((0, 3 << 18), (1, 3 << 17)):
-        choice = lambda m, nnz, plan, longest, k=1: rules.gather_choice(i64(m), i64(nnz), plan, bf16, i64(longest), 256, k)
+        choice = lambda m, nnz, plan, longest, k=1, n=50000: rules.gather_choice(i64(m), i64(n), i64(nnz), plan, bf16, i64(longest), 256, k)
         assert choice(30000, least, A, 20) and not choice(30000, least - 1, A, 20)
         items = -(-(30000 + least) // 256)
         assert choice(30000, least, A, items // 2) and not choice(30000, least, A, items // 2 + 1)  # half a chunk is the longest uncut row
         assert not choice(30000, least, A, items // 2, 4)                                           # chunks of a quarter the steps
         assert choice(10000, 1 << 16, M, 2000) and not choice(10000, (1 << 16) - 1, M, 2000)
-        assert choice(10000, 1 << 16, M, 32 * 512) and not choice(10000, 1 << 16, M, 32 * 512 + 1)  # chunks of 512 steps at least
+        steps = -(-(10000 + (1 << 16)) // 256)
+        assert choice(10000, 1 << 16, M, 32 * (steps - 192)) and not choice(10000, 1 << 16, M, 32 * (steps - 192) + 1)
+        assert choice(1000, 768000, A, 800, n=16384) == (not bf16 and 768000 >= least)              # long rows, an x that a unit's cache holds
+        assert not bf16 or (choice(1000, 767999, A, 800, n=16384) and choice(1000, 768000, A, 800, n=16385))
     for plan in (s.SPMV_PLAN_SCALAR, s.SPMV_PLAN_VECTOR, s.SPMV_PLAN_BINNED, s.SPMV_PLAN_WINDOWED, s.SPMV_PLAN_TWOPHASE, s.SPMV_PLAN_COLBLOCK, s.SPMV_PLAN_SELL):
         assert not choice(30000, 1 << 20, plan, 20)
     assert rules.gather_snap(A, i64(300), i64(2000)) == 300
