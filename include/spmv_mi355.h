@@ -8,7 +8,8 @@
  * the BLAS form of it,
  *     y <- alpha * A * x + beta * y,
  * with A and x stored either as IEEE binary32 or as bf16 (upper half of a binary32), products
- * and sums always taken in binary32, y always binary32.  The paper classes this operation
+ * taken in binary32, sums in binary32 or (the parts of long and of cut rows) in binary64, y always
+ * binary32.  The paper classes this operation
  * as bound by memory bandwidth (App. A, bottleneck distribution), so every kernel behind
  * this interface is organised around streaming values/col_indices once with wide loads.
  *
@@ -98,7 +99,8 @@ typedef struct {
     int32_t vector_lanes;     /* VECTOR plan: lanes per row, power of two 2..64; default: chosen from nnz/m */
     int32_t skip_validation;  /* nonzero: do not scan colidx for out-of-range columns in analyze */
     int32_t prepare_spmm;     /* 1: also build spmm_rows, the row order spmm_csr_run() then works in
-                                 (and, where it pays, a packed copy of A); 0: spmm_csr_run() takes the rows as they come */
+                                 (and, where it pays, a packed copy of A); 0: spmm_csr_run() takes the rows as they come.
+                                 With 1 x is not gathered in column order (see analyze): spmv_csr_run() may be slower */
     int32_t reserved;         /* must be zero */
 } spmv_analyze_params_t;
 
@@ -228,8 +230,9 @@ spmv_status_t spmv_csr_create(spmv_handle_t* out, int64_t m, int64_t n, int64_t 
  *     UNSUPPORTED when V is larger.  The library then holds 2 bytes per
  *     stored entry of its own (lidx) and run() no longer reads colidx.  The positions are
  *     grouped (lidx_grouped = 1) when every row block starts at a multiple of eight entries and
- *     every aligned group of eight entries 8g .. 8g+7 (8g+8 <= nnz) has lidx[8g+i] = lidx[8g] + i:
- *     rows made of aligned runs of columns.  run() then reads one position per group (a copy of
+ *     every aligned group of eight entries 8g .. 8g+7 (8g+8 <= nnz) has lidx[8g+i] = lidx[8g] + i,
+ *     as rows made of aligned runs of eight columns have (and others: a diagonal, a band).  The window
+ *     kernel then reads one position per group (a copy of
  *     lidx[8g], 2 bytes per eight entries) and counts the other seven up from it.
  *     Row patterns (looked for when the positions are not grouped).  Row i of a block has base_i = lidx of its first
  *     entry (0 for an empty row) and rel_i[j] = lidx of its j-th entry minus base_i.  The rows of a block are cut
@@ -247,6 +250,20 @@ spmv_status_t spmv_csr_create(spmv_handle_t* out, int64_t m, int64_t n, int64_t 
  *     Where every block has at most 16 such runs (and meets the other conditions), whether lidx_patterned is 1 or 0, and the
  *     rows' length and number do not speak against it, the library also keeps the runs and lists in one piece per block, and
  *     run() reads those; they are not read back.
+ *   - x gathered in column order (plan AUTO that ends at ADAPTIVE, MERGE or WINDOWED, with block_nnz, rows_max, items_per_chunk
+ *     and prepare_spmm left 0).  The entry list is cut into chunks of its own, one or four to a compute unit, and the entries
+ *     of every chunk are listed by column: 4 bytes an entry, built on the device from colidx, and a few per cent of padding.  run() then
+ *     gathers x in that order; it reads vals and rowptr where the caller keeps them (no copy, nothing to refresh) and colidx no more.
+ *     info.plan, the sizes and the lists read back stay those of the plan (row_blocks, mp_row / mp_nz and the numbers of them describe
+ *     what the plan's own kernel would take; they are not what runs), and so does the rule for runs in flight (ADAPTIVE runs may overlap,
+ *     MERGE runs may not); spmv_csr_kernel_name() tells.  Results are reproducible bit for bit.  Used where
+ *       ADAPTIVE: nnz >= 3 * 2^18 (bf16: 3 * 2^17), the longest row is at most half a chunk, and in bf16 not for rows of 768 entries on average with n <= 16384;
+ *       MERGE: nnz >= 2^16, no row longer than 32 chunks of 192 steps less, and pieces of cut rows not in nearly every chunk;
+ *       both, unless the matrix is small: the 128-byte lines of x that stretches of 1024 entries touch outnumber those that chunks touch by enough
+ *         (columns that neighbouring rows share already gain nothing);
+ *       WINDOWED, bf16: rows and columns made of whole groups of eight (as for the two-pass plan on groups below), nnz >= 2^22, two groups a row on average
+ *         or more (three from 3072 rows to a compute unit on), colidx, vals and the x of the run 16-byte aligned; 4 bytes a group, next to the windows;
+ *     and the memory could be had.
  *   - column blocks (plan AUTO that arrived at ADAPTIVE or MERGE, or plan COLBLOCK; built on the
  *     device).  Columns are cut into blocks of W = 4 MiB / element size columns; the entries are
  *     regrouped block after block, keeping their row-major order inside a block, each with its
@@ -444,7 +461,8 @@ spmv_status_t spmv_csr_get_analysis_info(spmv_handle_t h, spmv_analysis_info_t* 
  * patterns, column blocks, the two-pass layout, the sparse-times-dense orders, packed copy and pairs form), from the handle's
  * own host memory what was derived from rowptr on the host and is read by the kernels only through the interleaved descriptors
  * (bin_rows unless the plan is BINNED, row_blocks, mp_row, mp_nz; the descriptors hold the merge-path splits that fall inside
- * a row of at most min(256, items_per_chunk - 1) entries moved back to the row's first entry). */
+ * a row of at most min(256, items_per_chunk - 1) entries moved back to the row's first entry; where x is gathered in column
+ * order no kernel reads them). */
 spmv_status_t spmv_csr_get_analysis(spmv_handle_t h, const spmv_analysis_host_t* out);
 
 /* The analysis of spmv_csr_analyze() on a HOST copy of rowptr, with HOST outputs and no device

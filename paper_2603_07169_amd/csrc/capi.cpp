@@ -1028,7 +1028,7 @@ spmv_status_t spmv_csr_analyze(spmv_handle_t h, const spmv_analyze_params_t* par
     if (st == SPMV_OK && p.prepare_spmm) st = build_spmm_order(h, rowptr_host, &a);
     // chunks and blocks that the caller shapes are the tile kernel's
     const bool own_shape = params && (params->items_per_chunk != 0 || params->block_nnz != 0 || params->rows_max != 0);
-    // (and a handle prepared for the sparse-times-dense product is spared the 0.1 to 0.6 ms: products with a vector run as they did)
+    // (and a handle prepared for the sparse-times-dense product is spared the 0.05 to 0.4 ms: products with a vector run as they did)
     if (st == SPMV_OK && p.plan == SPMV_PLAN_AUTO && !own_shape && !p.prepare_spmm && h->nnz > 0) st = build_gather(h, rowptr_host, a);
     // the only plan whose run writes this
     if (st == SPMV_OK && a.info.plan == SPMV_PLAN_MERGE && !h->gather.words && hip_failed(alloc_cut_scratch(&h->cut, merge_cuts, a.info.num_chunks)))

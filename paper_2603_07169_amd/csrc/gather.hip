@@ -1,5 +1,5 @@
-// gfx950 kernels for the row-wise product with x gathered in column order: the MERGE and ADAPTIVE plans where the chip is full
-// and x too large for a compute unit's cache.
+// gfx950 kernels for the row-wise product with x gathered in column order: MERGE and ADAPTIVE handles and, on groups of eight, WINDOWED ones, where
+// analysis.h's gather_choice, gather_pays and gather_groups_choice say so from the entries, the row lengths and the lines of x that are touched.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
