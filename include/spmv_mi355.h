@@ -257,7 +257,7 @@ spmv_status_t spmv_csr_create(spmv_handle_t* out, int64_t m, int64_t n, int64_t 
  *     info.plan, the sizes and the lists read back stay those of the plan (row_blocks, mp_row / mp_nz and the numbers of them describe
  *     what the plan's own kernel would take; they are not what runs), and so does the rule for runs in flight (ADAPTIVE runs may overlap,
  *     MERGE runs may not); spmv_csr_kernel_name() tells.  Results are reproducible bit for bit.  Used where
- *       ADAPTIVE: nnz >= 3 * 2^18 (bf16: 3 * 2^17), the longest row is at most half a chunk, and in bf16 not for rows of 768 entries on average with n <= 16384;
+ *       ADAPTIVE: nnz >= 7 * 2^16 (3 * 2^17 in bf16 and with more than 2^17 rows), the longest row is at most half a chunk, and in bf16 not for rows of 768 entries on average with n <= 16384;
  *       MERGE: nnz >= 2^16, no row longer than 32 chunks of 192 steps less, and pieces of cut rows not in nearly every chunk;
  *       both, unless the matrix is small: the 128-byte lines of x that stretches of 1024 entries touch outnumber those that chunks touch by enough
  *         (columns that neighbouring rows share already gain nothing);

@@ -176,7 +176,7 @@ bool gather_choice(int64_t m, int64_t n, int64_t nnz, int32_t plan, bool bf16, i
     const int64_t items = (m + nnz + static_cast<int64_t>(cus) * k - 1) / (static_cast<int64_t>(cus) * k);
     if (plan == SPMV_PLAN_MERGE) return nnz >= 1 << 16 && max_len <= 32 * (items - 192);
     if (bf16 && 2 * n <= kGatherSmallX && nnz >= 768 * m) return false;
-    return nnz >= (bf16 ? 3 << 17 : 3 << 18) && 2 * max_len <= items;
+    return nnz >= (bf16 || m > 1 << 17 ? 3 << 17 : 7 << 16) && 2 * max_len <= items;
 }
 
 bool gather_pays(int64_t m, int64_t nnz, int32_t plan, bool bf16, int32_t cus, int64_t chunks, int64_t most_lines, int64_t lines, int64_t stretch_lines) {

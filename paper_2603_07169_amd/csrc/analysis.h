@@ -78,10 +78,12 @@ bool two_phase_choice(int64_t m, int64_t n, int64_t nnz, spmv_dtype_t dtype, int
 // Whether x is gathered in column order (spmv_gather_kernel) by k chunks to a compute unit, where AUTO has arrived at a row-wise plan.
 // us, tile kernel / in column order:
 //   - ADAPTIVE, FP32, call by call and out of a graph: rows of 8, 393 k entries 4.1 / 4.8 and 3.9 / 4.9, 480 k 4.75 / 4.75 and 4.7 / 4.8, 640 k 5.3 / 5.5 and
-//     5.5 / 5.6, 800 k 6.0 / 5.9 and 6.1 / 6.1; of 16, 480 k 4.4 / 4.5 and 4.3 / 4.5, 640 k 5.0 / 4.8 and 5.05 / 5.0, 800 k 5.7 / 5.1 and 5.9 / 5.4; of 30, 600 k
-//     4.5 / 4.2 and 4.5 / 4.3; of 5, 800 k 7.4 / 5.8; an x of 2048 columns, 480 k 3.9 / 4.0 and 3.75 / 4.0, 655 k 4.2 / 4.2 and 4.0 / 4.2; rows of 16, 1.6 M 10.7 / 7.9, 3.2 M
-//     19.5 / 14.5.  bf16: rows of 8, 320 k 4.3 / 4.3, 393 k 4.15 / 4.05 and 3.9 / 4.0, 480 k 4.6 / 3.95; of 16, 320 k 4.0 / 4.3, 416 k 4.05 / 3.85 and 3.9 / 3.7,
-//     800 k 5.1 / 4.05, 1.6 M 9.0 / 5.4, 3.2 M 16.9 / 8.8; 2048 columns, 480 k 3.95 / 3.75 and 3.9 / 3.75, 655 k 4.15 / 3.9 and 4.0 / 3.9.
+//     5.5 / 5.6, 800 k 6.0 / 5.9 and 6.1 / 6.1; of 9, 400 k 4.45 / 4.2 and 4.3 / 4.3, 600 k 5.2 / 4.7; of 16, 400 k 4.15 / 4.15 and 4.0 / 4.3, 460 k 4.35 / 4.3 and 4.25 / 4.45,
+//     600 k 4.9 / 4.7 and 4.9 / 4.9, 780 k 5.5 / 5.2, 1.6 M 10.7 / 7.9, 3.2 M 19.5 / 14.5; of 24, 400 k 4.05 / 4.05 and 4.0 / 4.1, 600 k 4.65 / 4.35; of 40, 460 k 4.05 / 3.95 and 4.1 / 4.05;
+//     of 5, 500 k 4.7 / 4.75, 600 k 5.25 / 5.0, 20 000 columns 4.3 / 4.0 and 4.6 / 4.0.  From 131 072 rows on the tile kernel takes more than eight tiles to a compute unit: 131 000 of 4
+//     5.05 / 5.4, 131 200 of 4 5.3 / 4.9, 140 000 of 3 5.6 / 4.8, of 5 6.9 / 5.6, 250 000 of 2 6.4 / 5.6.  An x of 2048 or 4000 columns: 480 k 3.9 / 3.95 and 3.75 / 4.0, 600 k rows of 16
+//     4.6 / 4.2 and 4.5 / 4.3, 655 k 4.2 / 4.2 and 4.0 / 4.2.  bf16: rows of 8, 320 k 4.3 / 4.3, 393 k 4.15 / 4.05 and 3.9 / 4.0, 480 k 4.6 / 3.95; of 16, 320 k 4.0 / 4.3, 416 k 4.05 / 3.85
+//     and 3.9 / 3.7, 800 k 5.1 / 4.05, 1.6 M 9.0 / 5.4, 3.2 M 16.9 / 8.8; 2048 columns, 480 k 3.95 / 3.75 and 3.9 / 3.75, 655 k 4.15 / 3.9 and 4.0 / 3.9.
 //     Rows are not cut there, so the longest may take half a chunk.  Long rows in bf16 whose x a unit's own cache holds (12 000 columns): 3000 rows of 1000 7.5 / 7.9,
 //     of 1500 9.5 / 10.5, 2000 of 2400 10.6 / 11.1, 5000 of 1000 10.6 / 11.1; 9000 of 500 11.4 / 10.6, 12 000 of 300 9.75 / 8.65; 3000 of 1000 in 50 000 columns 9.9 / 8.0.
 //   - MERGE, power-law rows: 92 k entries 8.6 / 5.7 and 8.4 / 5.5, 626 k 10.6 / 7.4 and 10.1 / 6.8, 2.6 M 20.2 / 16.6 and 18.6 / 13.3; 20 000 rows

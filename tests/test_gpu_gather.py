@@ -42,7 +42,8 @@ def check(p, kernel, offset=0, params=None, runs=2):
 UNIFORM = {  # ADAPTIVE: rows x length, columns
     "rows_of_16": ([16] * 50000, 50000),                       # several lanes a row in binary32
     "odd": (np.random.default_rng(1).integers(0, 40, 50001), 9973),
-    "least": {"f32": ([8] * 98304, 50000), "bf16": ([8] * 49152, 50000)},  # the fewest entries the rule takes
+    "least": {"f32": ([8] * 57344, 50000), "bf16": ([8] * 49152, 50000)},  # the fewest entries the rule takes
+    "many_rows": ([3] * 131073, 50000),
     "long_rows": ([700] * 3000, 70000),                        # a wavefront a row
     "four_words_a_lane": ([16] * 220000, 100000),
     "four_chunks": ([16] * 300000, 100000),                    # binary32: four chunks to a compute unit; bf16: words in two rounds
@@ -187,7 +188,7 @@ def test_values_changed_in_place_and_non_finite_x():
 
 
 def test_matrices_of_the_tile_kernel():
-    check(problem([8] * 98303, 50000, "f32"), TILE)                                      # too few entries
+    check(problem([8] * 57343, 50000, "f32"), TILE)                                      # too few entries
     check(problem([8] * 49151, 50000, "bf16"), TILE)
     check(problem([1000] * 2000, 12000, "bf16"), TILE)                                   # long rows, an x that a unit's cache holds
     check(problem([9000] * 900, 50000, "f32"), TILE)                                     # pieces of cut rows in nearly every chunk

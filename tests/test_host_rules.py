@@ -301,16 +301,17 @@ def test_gather_rule(rules):
     import paper_2603_07169_amd as s
     rules.gather_snap.restype = C.c_int64
     A, M = s.SPMV_PLAN_ADAPTIVE, s.SPMV_PLAN_MERGE
-    for bf16, least in ((0, 3 << 18), (1, 3 << 17)):
+    for bf16, least in ((0, 7 << 16), (1, 3 << 17)):
         choice = lambda m, nnz, plan, longest, k=1, n=50000: rules.gather_choice(i64(m), i64(n), i64(nnz), plan, bf16, i64(longest), 256, k)
         assert choice(30000, least, A, 20) and not choice(30000, least - 1, A, 20)
+        assert choice((1 << 17) + 1, 3 << 17, A, 20) and choice(1 << 17, 3 << 17, A, 20) == bool(bf16)
         items = -(-(30000 + least) // 256)
         assert choice(30000, least, A, items // 2) and not choice(30000, least, A, items // 2 + 1)  # half a chunk is the longest uncut row
         assert not choice(30000, least, A, items // 2, 4)                                           # chunks of a quarter the steps
         assert choice(10000, 1 << 16, M, 2000) and not choice(10000, (1 << 16) - 1, M, 2000)
         steps = -(-(10000 + (1 << 16)) // 256)
         assert choice(10000, 1 << 16, M, 32 * (steps - 192)) and not choice(10000, 1 << 16, M, 32 * (steps - 192) + 1)
-        assert choice(1000, 768000, A, 800, n=16384) == (not bf16 and 768000 >= least)              # long rows, an x that a unit's cache holds
+        assert choice(1000, 768000, A, 800, n=16384) == (not bf16)                                  # long rows, an x that a unit's cache holds
         assert not bf16 or (choice(1000, 767999, A, 800, n=16384) and choice(1000, 768000, A, 800, n=16385))
     for plan in (s.SPMV_PLAN_SCALAR, s.SPMV_PLAN_VECTOR, s.SPMV_PLAN_BINNED, s.SPMV_PLAN_WINDOWED, s.SPMV_PLAN_TWOPHASE, s.SPMV_PLAN_COLBLOCK, s.SPMV_PLAN_SELL):
         assert not choice(30000, 1 << 20, plan, 20)
